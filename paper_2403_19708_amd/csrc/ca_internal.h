@@ -25,20 +25,21 @@ struct MoveArgs {
 };
 
 // Second contiguous destination of a launch that writes what it reads twice (the new turn's K/V go into the pool AND
-// to the tier in one pass): token (contig_tok0 + i) of the source also lands at token (dst2_tok0 + i) of dst2.
+// to the tier in one pass): new token i of the entry also lands at row i of dst.
 struct MoveArgs2 {
-    uint8_t *dst2_k[kMaxSeqsPerLaunch];
-    uint8_t *dst2_v[kMaxSeqsPerLaunch];
-    int64_t dst2_tok0[kMaxSeqsPerLaunch];
+    uint8_t *dst_k[kMaxSeqsPerLaunch];
+    uint8_t *dst_v[kMaxSeqsPerLaunch];
 };
 
 constexpr int kMoveUnroll = 2;   // 16-byte loads in flight per lane of the move kernel (one pass = kMoveUnroll*256 vectors)
 
 struct MoveShape {
     const int32_t *block_table;  // device [n_seqs][max_pages]
+    const int32_t *n_keep;       // device [n_seqs]    } where the new turn of a conversation lies on either side
+    const int32_t *cu_q;         // device [n_seqs+1]  } (append launches)
     int32_t max_pages;
     int32_t n_kv_heads;
-    int32_t vecs_per_row;        // head_dim * esize / 16
+    int32_t vec_shift;           // log2 of the 16-byte vectors per head and token (3 or 4)
     int32_t heads_per_wg;        // heads one workgroup moves (grid.x slices the heads, and K/V)
     int32_t n_in_launch;
     int32_t max_pages_touched;   // largest number of pages a range of this launch touches
@@ -49,24 +50,26 @@ struct MoveShape {
 // to_pool = true: contiguous -> pages (unpack / append); false: pages -> contiguous (pack).
 hipError_t launch_move(bool to_pool, const MoveArgs &args, const MoveShape &shape, uint8_t *k_pool,
                        uint8_t *v_pool, hipStream_t stream);
-// contiguous -> pages as launch_move(true, ...), and every vector is also stored to the second destination
-hipError_t launch_move_dual(const MoveArgs &args, const MoveArgs2 &second, const MoveShape &shape, uint8_t *k_pool,
-                            uint8_t *v_pool, hipStream_t stream);
+// the new turn of conversations [0, shape.n_in_launch): rows cu_q[c].. of new_k / new_v -> context tokens n_keep[c]..
+hipError_t launch_append(const MoveShape &shape, const uint8_t *new_k, const uint8_t *new_v, uint8_t *k_pool, uint8_t *v_pool,
+                         hipStream_t stream);
+// the same for conversations [first, first + shape.n_in_launch), and every vector is also stored to the second destination
+hipError_t launch_append_save(const MoveShape &shape, int first, const MoveArgs2 &second, const uint8_t *new_k, const uint8_t *new_v,
+                              uint8_t *k_pool, uint8_t *v_pool, hipStream_t stream);
 
 // ---------------------------------------------------------------------------------------
 // Section 3.4: per-token metadata of the rebased plan
 // ---------------------------------------------------------------------------------------
 struct RebaseArgs {
+    const uint8_t *image;        // the plan's arrays in pinned host memory, as the GPU addresses it
+    uint8_t *meta;               // where they go in device memory
+    int64_t image_vecs;          // 16-byte vectors to copy
+    int64_t off_table, off_n_keep, off_cu_q, off_cu_k;   // byte offsets in the image: [n_seqs][max_pages], [n_seqs], [n_seqs+1] x 2
     int32_t n_seqs;
     int32_t max_pages;
-    const int32_t *block_table;  // device
-    const int32_t *n_keep;       // device [n_seqs]
-    const int32_t *cu_q;         // device [n_seqs+1]
-    const int32_t *cu_k;         // device [n_seqs+1]
     int32_t *q_pos;              // device [sum new]
     int32_t *q_seq;              // device [sum new]
     int32_t *slot_map;           // device [sum context]
-    int32_t total_q, total_k;
 };
 hipError_t launch_rebase(const RebaseArgs &args, hipStream_t stream);
 

@@ -12,6 +12,7 @@
 #include <cstdio>
 #include <cstring>
 #include <functional>
+#include <mutex>
 #include <new>
 #include <string>
 #include <vector>
@@ -27,9 +28,38 @@ static __device__ __align__(256) uint8_t scratch[kStaticScratchBytes];
 constexpr int kMaxDevices = 64;
 static void *static_scratch_ptr[kMaxDevices] = {nullptr};   // [device ordinal], filled by ca_create with that device current
 
+// The internal streams (copy-in, unpack, save) of a GPU, shared by every context of the process on it.  A process has
+// four hardware queues here, and streams that share one wait for each other's unfinished work: with three streams per
+// context the append of one context's turn sat behind another context's loads as soon as a second context existed
+// (three contexts in turn, 236 MB of pinned history each: 6.4 ms a turn, 4.6 ms with one context's three streams).  One
+// set plus the caller's stream is four.  Contexts on different threads may use the set at once: enqueueing is thread-safe,
+// and every wait is on an event recorded right behind the work it stands for, so another context's work only ever queues
+// in front or behind.  Created for the first context of a GPU, destroyed with its last.
+struct StreamSet {
+    hipStream_t copy = nullptr, unpack = nullptr, save = nullptr;
+    int users = 0;
+};
+static std::mutex stream_sets_mutex;
+static StreamSet stream_sets[kMaxDevices];   // [device ordinal]
+
 struct ca_ctx {
     ca_config cfg{};
-    hipStream_t s_copy = nullptr, s_unpack = nullptr, s_save = nullptr;
+    hipStream_t s_copy = nullptr, s_unpack = nullptr, s_save = nullptr;   // of the device's set
+    bool holds_streams = false;
+    // What the streams still owe this context.  An event costs the stream it is recorded on about 3 us and a wait across
+    // streams about 11 us of host time and 20 us from one stream's kernel to the other's, so none is made that nothing needs.
+    bool copy_waits_plan = false, unpack_waits_plan = false, save_waits_plan = false;   // the stream has not yet been told to wait for ev_plan
+    hipEvent_t load_done = nullptr;    // event behind the newest load on the unpack stream (one of ev_ready), null: none outstanding
+    bool save_pending = false;         // ev_saved stands behind work on the save stream that may be unfinished
+    bool joined_null = false;          // the default stream already waits for all of it
+    // short moves run on a stream of the caller's instead (see runs_inline): the newest one, and the event behind it (null on
+    // the default stream, which outlives the context and can be asked or recorded on when it matters)
+    bool inline_pending = false;
+    hipStream_t inline_stream = nullptr;
+    hipEvent_t inline_done = nullptr, ev_inline = nullptr;
+    hipStream_t plan_stream = nullptr; // the stream ca_rope_rebase was given
+    std::vector<uint8_t> ready_inline; // per layer: loaded on the plan's stream
+    hipEvent_t ev_saved = nullptr;
     // staging ring: `depth` slots for loads, `depth` for saves; slot = [K tokens | V tokens]
     uint8_t *load_slots = nullptr, *save_slots = nullptr;
     size_t slot_bytes = 0, half_slot_bytes = 0;
@@ -38,14 +68,14 @@ struct ca_ctx {
     int64_t load_count = 0, save_count = 0;
     float2 *rope = nullptr;
     // plan metadata: one pinned host image, one device image
-    uint8_t *h_meta = nullptr, *d_meta = nullptr;
+    uint8_t *h_meta = nullptr, *h_meta_dev = nullptr, *d_meta = nullptr;   // (h_meta_dev: h_meta as the GPU addresses it)
     size_t meta_bytes = 0;
-    hipEvent_t ev_meta_copied = nullptr, ev_plan = nullptr, ev_after = nullptr;
-    hipEvent_t ev_join[3] = {nullptr, nullptr, nullptr};
+    hipEvent_t ev_plan = nullptr, ev_after = nullptr;
     bool meta_in_flight = false;
-    // offsets (bytes) inside the metadata image
+    // offsets (bytes) inside the metadata image; those of the uploaded part change from plan to plan (its arrays lie back
+    // to back, so that only what the plan uses crosses the host link)
     size_t off_table = 0, off_n_keep = 0, off_cu_q = 0, off_cu_k = 0, off_items = 0, off_combine = 0, off_q_pos = 0,
-           off_q_seq = 0, off_slot_map = 0, upload_bytes = 0;
+           off_q_seq = 0, off_slot_map = 0, upload_capacity = 0;
     size_t items_capacity = 0;         // work items the image has room for
     float *partial = nullptr;          // shares of row tiles whose keys were split over workgroups
     uint16_t *k_rot = nullptr;         // keys of the batch context rotated once per layer (dense pages)
@@ -109,6 +139,7 @@ ca_status fail(ca_ctx *ctx, ca_status st, const char *fmt, ...) {
         }                                                                                        \
     } while (0)
 
+constexpr size_t kMetaAlign = 64;            // alignment of the arrays of the metadata image
 constexpr int kHostStoreWorkgroups = 128;   // workgroups of a pack kernel whose destination is pinned host memory
 
 // How a save reaches a pinned tier when the configuration leaves the choice to the library (save_mode 0).  Measured on
@@ -174,19 +205,111 @@ MemKind mem_kind(const void *p) {
     return MemKind::kUnknown;
 }
 
-// true if [p, p+bytes) lies inside one device allocation
-bool device_range_ok(const void *p, size_t bytes) {
-    if (!p) return false;
-    if (mem_kind(p) != MemKind::kDevice) return false;
-    hipDeviceptr_t base = nullptr;
-    size_t size = 0;
-    hipError_t e = hipMemGetAddressRange(&base, &size, (hipDeviceptr_t)p);
-    if (e != hipSuccess) {
-        (void)hipGetLastError();
-        return true;  // kind was device; range query unsupported for this allocation
+// Kind and extent of the allocations a call's pointers lie in.  One API call asks about up to two pointers per
+// conversation and they mostly come out of one or two allocations: the last answer is kept for the length of the call
+// (never longer, an allocation may be gone by the next one).
+class MemMap {
+public:
+    // kind of p; *inside = [p, p + bytes) does not leave its allocation (true where the runtime cannot tell)
+    MemKind look(const void *p, size_t bytes, bool *inside) {
+        const uint8_t *q = (const uint8_t *)p;
+        if (base_ && q >= base_ && q < base_ + size_) {
+            *inside = bytes <= (size_t)(base_ + size_ - q);
+            return kind_;
+        }
+        const MemKind k = mem_kind(p);
+        *inside = true;
+        if (k == MemKind::kUnknown) return k;
+        hipDeviceptr_t base = nullptr;
+        size_t size = 0;
+        if (hipMemGetAddressRange(&base, &size, (hipDeviceptr_t)p) != hipSuccess) {
+            (void)hipGetLastError();
+            return k;
+        }
+        const uint8_t *b = (const uint8_t *)base;
+        if (q < b || q >= b + size) { *inside = false; return k; }
+        base_ = b; size_ = size; kind_ = k;
+        *inside = bytes <= (size_t)(b + size - q);
+        return k;
     }
-    const uint8_t *b = (const uint8_t *)base, *q = (const uint8_t *)p;
-    return q >= b && q + bytes <= b + size;
+    // true if [p, p+bytes) lies inside one device allocation
+    bool device_range_ok(const void *p, size_t bytes) {
+        bool inside = false;
+        return p && look(p, bytes, &inside) == MemKind::kDevice && inside;
+    }
+
+private:
+    const uint8_t *base_ = nullptr;
+    size_t size_ = 0;
+    MemKind kind_ = MemKind::kUnknown;
+};
+
+// ---- which stream a move runs on, and what waits for it ---------------------------------------------------------
+// A move between the tier and the pool has an internal stream so that it overlaps with the caller's kernels.  Getting
+// there and back costs about 20 us on the GPU and as much on the host (measured: a kernel, event, wait, kernel, event, wait
+// loop over two streams 27 us, the two kernels on one stream 7.5 us), so a move that is shorter than that runs on the
+// caller's stream: one to or from device memory of at most 16 MB (about 8 us), one across the host link of at most 256 KB
+// for a save (6 us; stores) and 512 KB for a load (12 us; reads).
+constexpr int64_t kInlineDeviceBytes = (int64_t)16 << 20;
+constexpr int64_t kInlineHostSaveBytes = (int64_t)256 << 10;
+constexpr int64_t kInlineHostLoadBytes = (int64_t)512 << 10;
+
+// the caller may have destroyed the stream it made the plan on
+bool stream_alive(hipStream_t stream) {
+    if (stream == nullptr) return true;
+    const hipError_t e = hipStreamQuery(stream);
+    if (e == hipSuccess) return true;
+    (void)hipGetLastError();
+    return e == hipErrorNotReady;
+}
+
+// May the next short move run on `stream`?  Only one stream's inline moves are kept track of at a time.
+bool inline_free(ca_ctx *ctx, hipStream_t stream) {
+    if (!ctx->inline_pending || ctx->inline_stream == stream) return true;
+    if (ctx->inline_stream != nullptr ? hipEventQuery(ctx->inline_done) == hipSuccess : hipStreamQuery(nullptr) == hipSuccess) {
+        ctx->inline_pending = false;
+        return true;
+    }
+    (void)hipGetLastError();
+    return false;
+}
+
+// a short move has been queued on `stream`; `done`: the event recorded behind it (may be null on the default stream only)
+void note_inline(ca_ctx *ctx, hipStream_t stream, hipEvent_t done) {
+    ctx->inline_pending = true;
+    ctx->inline_stream = stream;
+    ctx->inline_done = done;
+}
+
+hipError_t note_inline(ca_ctx *ctx, hipStream_t stream) {
+    if (stream != nullptr) {
+        const hipError_t e = hipEventRecord(ctx->ev_inline, stream);
+        if (e != hipSuccess) return e;
+    }
+    note_inline(ctx, stream, stream != nullptr ? ctx->ev_inline : nullptr);
+    return hipSuccess;
+}
+
+// first use of an internal stream under a plan: it waits for the plan's metadata
+hipError_t after_plan(ca_ctx *ctx, hipStream_t stream, bool *waits) {
+    if (!*waits) return hipSuccess;
+    *waits = false;
+    return hipStreamWaitEvent(stream, ctx->ev_plan, 0);
+}
+
+// a stream of the caller's waits for the plan's metadata (nothing to do for HIP on the stream the plan was made on)
+hipError_t caller_after_plan(ca_ctx *ctx, hipStream_t stream) {
+    return stream == nullptr && ctx->plan_stream == nullptr ? hipSuccess : hipStreamWaitEvent(stream, ctx->ev_plan, 0);
+}
+
+// `stream` waits for the load of `layer`
+hipError_t after_load(ca_ctx *ctx, int32_t layer, hipStream_t stream) {
+    if (ctx->ready_inline[layer] && ctx->plan_stream == nullptr) {
+        if (stream == nullptr) return hipSuccess;      // same stream
+        const hipError_t e = hipEventRecord(ctx->ev_ready[layer], nullptr);
+        if (e != hipSuccess) return e;
+    }
+    return hipStreamWaitEvent(stream, ctx->ev_ready[layer], 0);   // (nothing to do for HIP on the stream it was recorded on)
 }
 
 }  // namespace
@@ -505,17 +628,15 @@ const char *ca_last_error(const ca_ctx *ctx) { return ctx ? ctx->err.c_str() : "
 void ca_destroy(ca_ctx *ctx) {
     if (!ctx) return;
     (void)hipSetDevice(ctx->cfg.device);
-    if (ctx->s_copy) (void)hipStreamSynchronize(ctx->s_copy);
-    if (ctx->s_unpack) (void)hipStreamSynchronize(ctx->s_unpack);
-    if (ctx->s_save) (void)hipStreamSynchronize(ctx->s_save);
+    (void)ca_sync(ctx);
     for (auto e : ctx->ev_slot_copied) if (e) (void)hipEventDestroy(e);
     for (auto e : ctx->ev_slot_copied2) if (e) (void)hipEventDestroy(e);
     for (auto e : ctx->ev_slot_free) if (e) (void)hipEventDestroy(e);
     for (auto e : ctx->ev_ready) if (e) (void)hipEventDestroy(e);
-    if (ctx->ev_meta_copied) (void)hipEventDestroy(ctx->ev_meta_copied);
+    if (ctx->ev_saved) (void)hipEventDestroy(ctx->ev_saved);
+    if (ctx->ev_inline) (void)hipEventDestroy(ctx->ev_inline);
     if (ctx->ev_plan) (void)hipEventDestroy(ctx->ev_plan);
     if (ctx->ev_after) (void)hipEventDestroy(ctx->ev_after);
-    for (auto e : ctx->ev_join) if (e) (void)hipEventDestroy(e);
     for (auto &iv : ctx->intervals) { (void)hipEventDestroy(iv.start); (void)hipEventDestroy(iv.stop); }
     for (auto e : ctx->spare_events) (void)hipEventDestroy(e);
     if (ctx->load_slots) (void)hipFree(ctx->load_slots);
@@ -526,9 +647,16 @@ void ca_destroy(ca_ctx *ctx) {
     if (ctx->v_t) (void)hipFree(ctx->v_t);
     if (ctx->d_meta) (void)hipFree(ctx->d_meta);
     if (ctx->h_meta) (void)hipHostFree(ctx->h_meta);
-    if (ctx->s_copy) (void)hipStreamDestroy(ctx->s_copy);
-    if (ctx->s_unpack) (void)hipStreamDestroy(ctx->s_unpack);
-    if (ctx->s_save) (void)hipStreamDestroy(ctx->s_save);
+    if (ctx->holds_streams) {
+        std::lock_guard<std::mutex> hold(stream_sets_mutex);
+        StreamSet &set = stream_sets[ctx->cfg.device];
+        if (--set.users == 0) {
+            (void)hipStreamDestroy(set.copy);
+            (void)hipStreamDestroy(set.unpack);
+            (void)hipStreamDestroy(set.save);
+            set = StreamSet{};
+        }
+    }
     delete ctx;
 }
 
@@ -542,9 +670,26 @@ static ca_status create_impl(ca_ctx *ctx) {
     CA_HIP(ctx, hipGetDeviceCount(&n_dev));
     if (c.device >= n_dev) return fail(ctx, CA_ERR_OUT_OF_RANGE, "device %d of %d", c.device, n_dev);
     CA_HIP(ctx, hipSetDevice(c.device));
-    CA_HIP(ctx, hipStreamCreateWithFlags(&ctx->s_copy, hipStreamNonBlocking));
-    CA_HIP(ctx, hipStreamCreateWithFlags(&ctx->s_unpack, hipStreamNonBlocking));
-    CA_HIP(ctx, hipStreamCreateWithFlags(&ctx->s_save, hipStreamNonBlocking));
+    if (c.device >= kMaxDevices) return fail(ctx, CA_ERR_OUT_OF_RANGE, "device %d: at most %d are served", c.device, kMaxDevices);
+    {
+        std::lock_guard<std::mutex> hold(stream_sets_mutex);
+        StreamSet &set = stream_sets[c.device];
+        if (set.users == 0) {
+            hipError_t e = hipSuccess;
+            for (hipStream_t *s : {&set.copy, &set.unpack, &set.save})
+                if (e == hipSuccess && (e = hipStreamCreateWithFlags(s, hipStreamNonBlocking)) != hipSuccess) *s = nullptr;
+            if (e != hipSuccess) {
+                for (hipStream_t s : {set.copy, set.unpack, set.save}) if (s) (void)hipStreamDestroy(s);
+                set = StreamSet{};
+                CA_HIP(ctx, e);
+            }
+        }
+        ++set.users;
+        ctx->holds_streams = true;
+        ctx->s_copy = set.copy;
+        ctx->s_unpack = set.unpack;
+        ctx->s_save = set.save;
+    }
     const int depth = c.pipeline_depth;
     ctx->half_slot_bytes = align_up((size_t)c.max_batch_kv_tokens * (size_t)row_bytes(c), 256);
     ctx->slot_bytes = 2 * ctx->half_slot_bytes;
@@ -561,12 +706,13 @@ static ca_status create_impl(ca_ctx *ctx) {
     }
     ctx->ev_ready.assign(c.n_layers, nullptr);
     ctx->loaded.assign(c.n_layers, 0);
+    ctx->ready_inline.assign(c.n_layers, 0);
     for (int i = 0; i < c.n_layers; ++i)
         CA_HIP(ctx, hipEventCreateWithFlags(&ctx->ev_ready[i], hipEventDisableTiming));
-    CA_HIP(ctx, hipEventCreateWithFlags(&ctx->ev_meta_copied, hipEventDisableTiming));
+    CA_HIP(ctx, hipEventCreateWithFlags(&ctx->ev_saved, hipEventDisableTiming));
+    CA_HIP(ctx, hipEventCreateWithFlags(&ctx->ev_inline, hipEventDisableTiming));
     CA_HIP(ctx, hipEventCreateWithFlags(&ctx->ev_plan, hipEventDisableTiming));
     CA_HIP(ctx, hipEventCreateWithFlags(&ctx->ev_after, hipEventDisableTiming));
-    for (auto &e : ctx->ev_join) CA_HIP(ctx, hipEventCreateWithFlags(&e, hipEventDisableTiming));
 
     // Rotary table (Section 3.4): cos/sin of pos * base^(-2i/D), evaluated in fp64, stored fp32.
     {
@@ -585,8 +731,8 @@ static ca_status create_impl(ca_ctx *ctx) {
         CA_HIP(ctx, hipMemcpy(ctx->rope, tab.data(), tab.size() * sizeof(float2), hipMemcpyHostToDevice));
     }
 
-    // Metadata image layout.  Uploaded part first (block table rows are packed to the batch's
-    // max_pages, bounded by ceil(max_positions/page)+1 columns), device-computed arrays after it.
+    // Capacity of the metadata image: the uploaded part (its layout is a plan's own, see ca_rope_rebase; block table rows
+    // have at most ceil(max_positions/page)+1 columns), then the device-computed arrays.
     {
         const size_t max_cols = (size_t)(c.max_positions + c.page_size - 1) / c.page_size + 1;
         const size_t units = (size_t)c.max_seqs * c.n_kv_heads;
@@ -596,25 +742,22 @@ static ca_status create_impl(ca_ctx *ctx) {
         const size_t max_items = (size_t)c.max_batch_q_tokens * g * c.n_kv_heads / kAttnTileRowsMin + units + kAttnMaxParts;
         const size_t max_items_padded = (max_items + 1) * kXcds;  // worst case: every tile on one die
         ctx->items_capacity = max_items_padded;
-        size_t off = 0;
-        ctx->off_table = off;   off = align_up(off + (size_t)c.max_seqs * max_cols * 4, 256);
-        ctx->off_n_keep = off;  off = align_up(off + (size_t)c.max_seqs * 4, 256);
-        ctx->off_cu_q = off;    off = align_up(off + ((size_t)c.max_seqs + 1) * 4, 256);
-        ctx->off_cu_k = off;    off = align_up(off + ((size_t)c.max_seqs + 1) * 4, 256);
         ctx->k_rot_pages = (size_t)c.max_batch_kv_tokens / c.page_size + (size_t)c.max_seqs;
-        ctx->off_dense0 = off;  off = align_up(off + (size_t)c.max_seqs * 4, 256);
-        ctx->off_rot_src = off; off = align_up(off + ctx->k_rot_pages * 4, 256);
-        ctx->off_rot_pos = off; off = align_up(off + ctx->k_rot_pages * 4, 256);
-        ctx->off_rot_nvalid = off; off = align_up(off + ctx->k_rot_pages * 4, 256);
-        ctx->off_combine = off; off = align_up(off + (size_t)kAttnMaxParts * sizeof(CombineItem), 256);
-        ctx->off_items = off;   off = align_up(off + max_items_padded * sizeof(WorkItem), 256);
-        ctx->upload_bytes = off;
+        size_t off = 0;
+        const auto add = [&off](size_t bytes) { const size_t at = off; off = align_up(off + bytes, kMetaAlign); return at; };
+        add((size_t)c.max_seqs * max_cols * 4);                       // block table
+        for (int i = 0; i < 4; ++i) add(((size_t)c.max_seqs + 1) * 4); // n_keep, cu_q, cu_k, dense0
+        for (int i = 0; i < 3; ++i) add(ctx->k_rot_pages * 4);        // rot_src, rot_pos, rot_nvalid
+        add((size_t)kAttnMaxParts * sizeof(CombineItem));
+        add(max_items_padded * sizeof(WorkItem));
+        ctx->upload_capacity = off = align_up(off, 256);
         ctx->off_q_pos = off;   off = align_up(off + (size_t)c.max_batch_q_tokens * 4, 256);
         ctx->off_q_seq = off;   off = align_up(off + (size_t)c.max_batch_q_tokens * 4, 256);
         ctx->off_slot_map = off; off = align_up(off + (size_t)c.max_batch_kv_tokens * 4, 256);
         ctx->meta_bytes = off;
         CA_HIP(ctx, hipMalloc((void **)&ctx->d_meta, ctx->meta_bytes));
-        CA_HIP(ctx, hipHostMalloc((void **)&ctx->h_meta, ctx->upload_bytes, hipHostMallocDefault));
+        CA_HIP(ctx, hipHostMalloc((void **)&ctx->h_meta, ctx->upload_capacity, hipHostMallocMapped));
+        CA_HIP(ctx, hipHostGetDevicePointer((void **)&ctx->h_meta_dev, ctx->h_meta, 0));
     }
     // Partial results of row tiles whose keys are split over workgroups (only the LDS-direct kernel splits).
     const bool may_split = c.attn_split == 0 && direct_variant(c);
@@ -667,19 +810,30 @@ ca_status ca_create(const ca_config *cfg, ca_ctx **out) {
 
 ca_status ca_sync(ca_ctx *ctx) {
     if (!ctx) return CA_ERR_INVALID_ARG;
-    CA_HIP(ctx, hipStreamSynchronize(ctx->s_copy));
-    CA_HIP(ctx, hipStreamSynchronize(ctx->s_unpack));
-    CA_HIP(ctx, hipStreamSynchronize(ctx->s_save));
+    if (ctx->load_done) CA_HIP(ctx, hipEventSynchronize(ctx->load_done));
+    ctx->load_done = nullptr;
+    if (ctx->save_pending) CA_HIP(ctx, hipEventSynchronize(ctx->ev_saved));
+    ctx->save_pending = false;
+    if (ctx->inline_pending) {
+        if (ctx->inline_done) CA_HIP(ctx, hipEventSynchronize(ctx->inline_done));
+        else CA_HIP(ctx, hipStreamSynchronize(nullptr));
+    }
+    ctx->inline_pending = false;
     return CA_OK;
 }
 
 ca_status ca_join(ca_ctx *ctx, void *stream) {
     if (!ctx) return CA_ERR_INVALID_ARG;
     hipStream_t s = (hipStream_t)stream;
-    hipStream_t internal[3] = {ctx->s_copy, ctx->s_unpack, ctx->s_save};
-    for (int i = 0; i < 3; ++i) {
-        CA_HIP(ctx, hipEventRecord(ctx->ev_join[i], internal[i]));
-        CA_HIP(ctx, hipStreamWaitEvent(s, ctx->ev_join[i], 0));
+    // (the copies of a staged load are in front of its unpack kernel, which waits for both halves)
+    if ((ctx->load_done || ctx->save_pending) && !(s == nullptr && ctx->joined_null)) {
+        if (ctx->load_done) CA_HIP(ctx, hipStreamWaitEvent(s, ctx->load_done, 0));
+        if (ctx->save_pending) CA_HIP(ctx, hipStreamWaitEvent(s, ctx->ev_saved, 0));
+        if (s == nullptr) ctx->joined_null = true;
+    }
+    if (ctx->inline_pending && !(s == nullptr && ctx->inline_stream == nullptr)) {
+        if (!ctx->inline_done) CA_HIP(ctx, hipEventRecord(ctx->ev_inline, nullptr));
+        CA_HIP(ctx, hipStreamWaitEvent(s, ctx->inline_done ? ctx->inline_done : ctx->ev_inline, 0));
     }
     return CA_OK;
 }
@@ -697,12 +851,10 @@ ca_status ca_rope_rebase(ca_ctx *ctx, const ca_batch *b, void *stream_) {
     CA_HIP(ctx, hipSetDevice(c.device));
 
     const int B = b->n_seqs;
-    const size_t max_cols = (size_t)(c.max_positions + c.page_size - 1) / c.page_size + 1;
-    const int cols = (int)std::min<size_t>((size_t)b->max_pages, max_cols);
 
     // the pinned image may still be the source of the previous plan's upload
     if (ctx->meta_in_flight) {
-        CA_HIP(ctx, hipEventSynchronize(ctx->ev_meta_copied));
+        CA_HIP(ctx, hipEventSynchronize(ctx->ev_plan));
         ctx->meta_in_flight = false;
     }
 
@@ -734,6 +886,8 @@ ca_status ca_rope_rebase(ca_ctx *ctx, const ca_batch *b, void *stream_) {
         ctx->cu_k[i + 1] = ctx->cu_k[i] + ctx->n_keep[i] + b->new_len[i];
         ctx->cu_n[i + 1] = ctx->cu_n[i] + ctx->n_keep[i];
     }
+    int cols = 1;   // block table columns in use
+    for (int i = 0; i < B; ++i) cols = std::max(cols, (ctx->n_keep[i] + b->new_len[i] + c.page_size - 1) / c.page_size);
     ctx->n_seqs = B;
     ctx->max_pages = cols;
     ctx->num_pages = b->num_pages;
@@ -742,12 +896,19 @@ ca_status ca_rope_rebase(ca_ctx *ctx, const ca_batch *b, void *stream_) {
     ctx->total_n = ctx->cu_n[B];
 
     // ---- host image -------------------------------------------------------------------------
+    // The arrays of the plan lie back to back.  Each is no longer than what ca_create made room for.
+    size_t up = 0;
+    const auto put = [&up](size_t bytes) { const size_t at = up; up = align_up(up + bytes, kMetaAlign); return at; };
+    ctx->off_n_keep = put((size_t)B * 4);
+    ctx->off_cu_q = put((size_t)(B + 1) * 4);
+    ctx->off_cu_k = put((size_t)(B + 1) * 4);
+    ctx->off_table = put((size_t)B * cols * 4);
     int32_t *h_table = (int32_t *)(ctx->h_meta + ctx->off_table);
     for (int i = 0; i < B; ++i) {
-        const int64_t ctx_len = (int64_t)ctx->n_keep[i] + b->new_len[i];
-        const int pages = (int)((ctx_len + c.page_size - 1) / c.page_size);
-        for (int p = 0; p < cols; ++p)  // unused columns point at the row's first page: always a valid page
-            h_table[(size_t)i * cols + p] = b->block_table[(int64_t)i * b->max_pages + (p < pages ? p : 0)];
+        const int pages = (ctx->n_keep[i] + b->new_len[i] + c.page_size - 1) / c.page_size;
+        const int32_t *from = b->block_table + (int64_t)i * b->max_pages;
+        std::memcpy(h_table + (size_t)i * cols, from, (size_t)pages * 4);
+        std::fill(h_table + (size_t)i * cols + pages, h_table + (size_t)(i + 1) * cols, from[0]);  // always a valid page
     }
     std::memcpy(ctx->h_meta + ctx->off_n_keep, ctx->n_keep.data(), (size_t)B * 4);
     std::memcpy(ctx->h_meta + ctx->off_cu_q, ctx->cu_q.data(), (size_t)(B + 1) * 4);
@@ -774,6 +935,14 @@ ca_status ca_rope_rebase(ca_ctx *ctx, const ca_batch *b, void *stream_) {
                              (c.attn_prerotate == 2 || (c.attn_prerotate == 0 && tiles256 >= (int64_t)3 * B));
             if (ctx->prerotate && c.attn_tile_rows == 0) tile = 256;
             ctx->pipelined = ctx->prerotate && ctx->v_t && tile == 256 && c.attn_variant != 3 && c.attn_variant != 1;
+            size_t dense_pages = 0;
+            if (ctx->prerotate)
+                for (int i = 0; i < B; ++i) dense_pages += (size_t)((ctx->n_keep[i] + b->new_len[i] + c.page_size - 1) / c.page_size);
+            if (dense_pages > ctx->k_rot_pages) return fail(ctx, CA_ERR_OUT_OF_RANGE, "ca_rope_rebase: internal: %zu dense pages exceed %zu", dense_pages, ctx->k_rot_pages);
+            ctx->off_dense0 = put((size_t)B * 4);
+            ctx->off_rot_src = put(dense_pages * 4);
+            ctx->off_rot_pos = put(dense_pages * 4);
+            ctx->off_rot_nvalid = put(dense_pages * 4);
             int32_t *dense0 = (int32_t *)(ctx->h_meta + ctx->off_dense0);
             int32_t *rot_src = (int32_t *)(ctx->h_meta + ctx->off_rot_src), *rot_pos = (int32_t *)(ctx->h_meta + ctx->off_rot_pos);
             int32_t *rot_nvalid = (int32_t *)(ctx->h_meta + ctx->off_rot_nvalid);
@@ -788,7 +957,6 @@ ca_status ca_rope_rebase(ca_ctx *ctx, const ca_batch *b, void *stream_) {
                     rot_nvalid[at] = std::min(c.page_size, ctx->n_keep[i] + b->new_len[i] - p * c.page_size);
                 }
             }
-            if ((size_t)at > ctx->k_rot_pages) return fail(ctx, CA_ERR_OUT_OF_RANGE, "ca_rope_rebase: internal: %d dense pages exceed %zu", at, ctx->k_rot_pages);
             ctx->n_dense_pages = at;
         }
         ctx->tile_rows = tile;
@@ -894,6 +1062,7 @@ ca_status ca_rope_rebase(ca_ctx *ctx, const ca_batch *b, void *stream_) {
             }
         }
         // number the shares of split row tiles consecutively and list the tiles for the merge
+        ctx->off_combine = put((size_t)n_split_parts * sizeof(CombineItem));    // (a tile has at least two shares)
         CombineItem *combine = (CombineItem *)(ctx->h_meta + ctx->off_combine);
         int32_t n_combine = 0;
         {
@@ -919,6 +1088,7 @@ ca_status ca_rope_rebase(ca_ctx *ctx, const ca_batch *b, void *stream_) {
         for (auto &v : per_die) longest = std::max(longest, v.size());
         const size_t n_items = longest * kXcds;
         if (n_items > ctx->items_capacity) return fail(ctx, CA_ERR_OUT_OF_RANGE, "ca_rope_rebase: %zu work items exceed capacity %zu", n_items, ctx->items_capacity);
+        ctx->off_items = put(n_items * sizeof(WorkItem));
         WorkItem *items = (WorkItem *)(ctx->h_meta + ctx->off_items);
         for (size_t s = 0; s < longest; ++s)
             for (int d = 0; d < kXcds; ++d)
@@ -926,34 +1096,32 @@ ca_status ca_rope_rebase(ca_ctx *ctx, const ca_batch *b, void *stream_) {
         ctx->n_items = (int32_t)n_items;
     }
 
-    // ---- order against everything still using the previous plan, then upload + per-token kernel --
+    // ---- order against everything still using the previous plan, then upload + per-token arrays in one kernel --
+    if (up > ctx->upload_capacity) return fail(ctx, CA_ERR_OUT_OF_RANGE, "ca_rope_rebase: internal: image of %zu bytes exceeds %zu", up, ctx->upload_capacity);
     st = ca_join(ctx, stream_);
     if (st != CA_OK) return st;
-    const size_t up = ctx->off_items + (size_t)ctx->n_items * sizeof(WorkItem);
-    CA_HIP(ctx, hipMemcpyAsync(ctx->d_meta, ctx->h_meta, up, hipMemcpyHostToDevice, stream));
-    CA_HIP(ctx, hipEventRecord(ctx->ev_meta_copied, stream));
-    ctx->meta_in_flight = true;
-
     RebaseArgs ra{};
     ra.n_seqs = B;
     ra.max_pages = cols;
-    ra.block_table = (const int32_t *)(ctx->d_meta + ctx->off_table);
-    ra.n_keep = (const int32_t *)(ctx->d_meta + ctx->off_n_keep);
-    ra.cu_q = (const int32_t *)(ctx->d_meta + ctx->off_cu_q);
-    ra.cu_k = (const int32_t *)(ctx->d_meta + ctx->off_cu_k);
+    ra.image = ctx->h_meta_dev;
+    ra.meta = ctx->d_meta;
+    ra.image_vecs = (int64_t)(up / 16);
+    ra.off_table = (int64_t)ctx->off_table;
+    ra.off_n_keep = (int64_t)ctx->off_n_keep;
+    ra.off_cu_q = (int64_t)ctx->off_cu_q;
+    ra.off_cu_k = (int64_t)ctx->off_cu_k;
     ra.q_pos = (int32_t *)(ctx->d_meta + ctx->off_q_pos);
     ra.q_seq = (int32_t *)(ctx->d_meta + ctx->off_q_seq);
     ra.slot_map = (int32_t *)(ctx->d_meta + ctx->off_slot_map);
-    ra.total_q = (int32_t)ctx->total_q;
-    ra.total_k = (int32_t)ctx->total_k;
     CA_HIP(ctx, launch_rebase(ra, stream));
 
-    // internal streams start work of this plan only after the metadata exists
+    // internal streams start work of this plan only after the metadata exists (each waits when it is first used)
     CA_HIP(ctx, hipEventRecord(ctx->ev_plan, stream));
-    CA_HIP(ctx, hipStreamWaitEvent(ctx->s_copy, ctx->ev_plan, 0));
-    CA_HIP(ctx, hipStreamWaitEvent(ctx->s_unpack, ctx->ev_plan, 0));
-    CA_HIP(ctx, hipStreamWaitEvent(ctx->s_save, ctx->ev_plan, 0));
+    ctx->meta_in_flight = true;
+    ctx->copy_waits_plan = ctx->unpack_waits_plan = ctx->save_waits_plan = true;
+    ctx->plan_stream = stream;
     std::fill(ctx->loaded.begin(), ctx->loaded.end(), 0);
+    std::fill(ctx->ready_inline.begin(), ctx->ready_inline.end(), 0);
     ctx->has_plan = true;
     return CA_OK;
 }
@@ -992,22 +1160,28 @@ struct Segment {  // one conversation's share of a move
     int32_t ctx_tok0, count, seq;
 };
 
-// narrow_workgroups > 0: launch about that many workgroups at most (each then walks several pages)
-ca_status run_move(ca_ctx *ctx, bool to_pool, const std::vector<Segment> &segs, void *k_pool, void *v_pool,
-                   hipStream_t stream, int narrow_workgroups = 0) {
+MoveShape move_shape(const ca_ctx *ctx, int max_tokens) {
     const ca_config &c = ctx->cfg;
     MoveShape shape{};
     shape.block_table = (const int32_t *)(ctx->d_meta + ctx->off_table);
+    shape.n_keep = (const int32_t *)(ctx->d_meta + ctx->off_n_keep);
+    shape.cu_q = (const int32_t *)(ctx->d_meta + ctx->off_cu_q);
     shape.max_pages = ctx->max_pages;
     shape.n_kv_heads = c.n_kv_heads;
-    shape.vecs_per_row = c.head_dim * 2 / 16;
-    // one 256-lane pass of kMoveUnroll x 16 bytes per lane covers 16 tokens of this many heads
-    shape.heads_per_wg = std::max(1, std::min(c.n_kv_heads, kMoveUnroll * 256 / (16 * shape.vecs_per_row)));
+    shape.vec_shift = c.head_dim == 128 ? 4 : 3;      // 16-byte vectors per head and token: 16 or 8
+    // one 256-lane pass of kMoveUnroll x 16 bytes per lane covers the tokens of a page (of a decode step: one) of this many heads
+    const int tokens = std::max(1, std::min(kPageSize, max_tokens));
+    shape.heads_per_wg = std::max(1, std::min(c.n_kv_heads, (kMoveUnroll * 256 / tokens) >> shape.vec_shift));
+    return shape;
+}
+
+// narrow_workgroups > 0: launch about that many workgroups at most (each then walks several pages)
+ca_status run_move(ca_ctx *ctx, bool to_pool, const std::vector<Segment> &segs, void *k_pool, void *v_pool,
+                   hipStream_t stream, int narrow_workgroups = 0) {
     for (size_t at = 0; at < segs.size(); at += kMaxSeqsPerLaunch) {
         MoveArgs args;
-        std::memset(&args, 0, sizeof args);
         const int n = (int)std::min<size_t>(kMaxSeqsPerLaunch, segs.size() - at);
-        int max_touched = 0;
+        int max_touched = 0, max_tokens = 0;
         for (int i = 0; i < n; ++i) {
             const Segment &s = segs[at + i];
             args.contig_k[i] = s.k;
@@ -1016,13 +1190,15 @@ ca_status run_move(ca_ctx *ctx, bool to_pool, const std::vector<Segment> &segs, 
             args.ctx_tok0[i] = s.ctx_tok0;
             args.count[i] = s.count;
             args.seq[i] = s.seq;
+            max_tokens = std::max(max_tokens, s.count);
             if (s.count > 0)
                 max_touched = std::max(max_touched, (s.ctx_tok0 + s.count - 1) / kPageSize - s.ctx_tok0 / kPageSize + 1);
         }
+        MoveShape shape = move_shape(ctx, max_tokens);
         shape.n_in_launch = n;
         shape.max_pages_touched = max_touched;
         if (narrow_workgroups > 0) {
-            const int slices = (c.n_kv_heads + shape.heads_per_wg - 1) / shape.heads_per_wg;
+            const int slices = (shape.n_kv_heads + shape.heads_per_wg - 1) / shape.heads_per_wg;
             shape.max_grid_y = std::max(1, narrow_workgroups / (2 * slices * n));
         }
         CA_HIP(ctx, launch_move(to_pool, args, shape, (uint8_t *)k_pool, (uint8_t *)v_pool, stream));
@@ -1030,13 +1206,56 @@ ca_status run_move(ca_ctx *ctx, bool to_pool, const std::vector<Segment> &segs, 
     return CA_OK;
 }
 
-ca_status check_pools(ca_ctx *ctx, const char *who, const void *k_pool, const void *v_pool) {
+// shape of a launch that moves the new turn of conversations [first, first + n)
+MoveShape new_turn_shape(const ca_ctx *ctx, int first, int n) {
+    int max_touched = 0, max_tokens = 0;
+    for (int q = first; q < first + n; ++q) {
+        max_tokens = std::max(max_tokens, ctx->new_len[q]);
+        max_touched = std::max(max_touched, (ctx->n_keep[q] + ctx->new_len[q] - 1) / kPageSize - ctx->n_keep[q] / kPageSize + 1);
+    }
+    MoveShape shape = move_shape(ctx, max_tokens);
+    shape.n_in_launch = n;
+    shape.max_pages_touched = max_touched;
+    return shape;
+}
+
+// the new turn's K/V -> pool, on `stream`
+ca_status run_append(ca_ctx *ctx, const void *new_k, const void *new_v, void *k_pool, void *v_pool, hipStream_t stream) {
+    int iv;
+    CA_HIP(ctx, prof_begin(ctx, kProfAppend, stream, &iv));
+    CA_HIP(ctx, launch_append(new_turn_shape(ctx, 0, ctx->n_seqs), (const uint8_t *)new_k, (const uint8_t *)new_v, (uint8_t *)k_pool,
+                              (uint8_t *)v_pool, stream));
+    CA_HIP(ctx, prof_end(ctx, iv, stream));
+    return CA_OK;
+}
+
+ca_status check_pools(ca_ctx *ctx, const char *who, const void *k_pool, const void *v_pool, MemMap &map) {
     if (!k_pool || !v_pool) return fail(ctx, CA_ERR_INVALID_ARG, "%s: pool pointer is NULL", who);
     const size_t bytes = (size_t)ctx->num_pages * ctx->cfg.page_size * (size_t)row_bytes(ctx->cfg);
-    if (!device_range_ok(k_pool, bytes) || !device_range_ok(v_pool, bytes))
+    if (!map.device_range_ok(k_pool, bytes) || !map.device_range_ok(v_pool, bytes))
         return fail(ctx, CA_ERR_INVALID_ARG, "%s: a pool is not device memory holding num_pages=%d pages (%zu bytes)", who,
                     ctx->num_pages, bytes);
     return CA_OK;
+}
+
+// Is a save of `bytes` so short that it runs on the caller's stream?  (save_mode 1 keeps what it asks for, the staging slot.)
+bool save_is_short(const ca_ctx *ctx, bool to_host, int64_t bytes) {
+    return ctx->cfg.save_mode != 1 && bytes <= (to_host ? kInlineHostSaveBytes : kInlineDeviceBytes);
+}
+
+// the save stream continues behind the plan and the work queued so far on `after`
+ca_status save_follows(ca_ctx *ctx, hipStream_t after) {
+    if (after != nullptr || ctx->plan_stream != nullptr) CA_HIP(ctx, after_plan(ctx, ctx->s_save, &ctx->save_waits_plan));
+    ctx->save_waits_plan = false;          // (behind the default stream: the plan is in front there)
+    CA_HIP(ctx, hipEventRecord(ctx->ev_after, after));
+    CA_HIP(ctx, hipStreamWaitEvent(ctx->s_save, ctx->ev_after, 0));
+    return CA_OK;
+}
+
+hipError_t note_save(ca_ctx *ctx) {
+    ctx->save_pending = true;
+    ctx->joined_null = false;
+    return hipEventRecord(ctx->ev_saved, ctx->s_save);
 }
 
 ca_status check_layer_plan(ca_ctx *ctx, const char *who, int32_t layer) {
@@ -1057,26 +1276,36 @@ ca_status ca_kv_load_layer(ca_ctx *ctx, int32_t layer, const void *const *src_k,
     if (ctx->loaded[layer]) return fail(ctx, CA_ERR_NOT_READY, "ca_kv_load_layer: layer %d already loaded under this plan", layer);
     const ca_config &c = ctx->cfg;
     CA_HIP(ctx, hipSetDevice(c.device));
-    st = check_pools(ctx, "ca_kv_load_layer", k_pool, v_pool);
+    MemMap map;
+    st = check_pools(ctx, "ca_kv_load_layer", k_pool, v_pool, map);
     if (st != CA_OK) return st;
 
     const int B = ctx->n_seqs;
     const int64_t rb = row_bytes(c);
     bool any_host = false, any_unknown = false;
+    MemMap map_k;          // (keys and values may be in an allocation each)
     for (int i = 0; i < B; ++i) {
         if (ctx->n_keep[i] == 0) continue;
         if (!src_k[i] || !src_v[i]) return fail(ctx, CA_ERR_INVALID_ARG, "ca_kv_load_layer: source of conversation %d is NULL", i);
-        const MemKind kk = mem_kind(src_k[i]), kv = mem_kind(src_v[i]);
+        const size_t need = (size_t)ctx->hist_len[i] * rb;
+        bool k_in, v_in;
+        const MemKind kk = map_k.look(src_k[i], need, &k_in), kv = map.look(src_v[i], need, &v_in);
         if (kk == MemKind::kUnknown || kv == MemKind::kUnknown) any_unknown = true;
         if (kk == MemKind::kPinnedHost || kv == MemKind::kPinnedHost) any_host = true;
-        if (kk == MemKind::kDevice && !device_range_ok(src_k[i], (size_t)ctx->hist_len[i] * rb))
+        if (kk == MemKind::kDevice && !k_in)
             return fail(ctx, CA_ERR_INVALID_ARG, "ca_kv_load_layer: K source of conversation %d is smaller than hist_len tokens", i);
-        if (kv == MemKind::kDevice && !device_range_ok(src_v[i], (size_t)ctx->hist_len[i] * rb))
+        if (kv == MemKind::kDevice && !v_in)
             return fail(ctx, CA_ERR_INVALID_ARG, "ca_kv_load_layer: V source of conversation %d is smaller than hist_len tokens", i);
     }
     if (any_unknown)
         return fail(ctx, CA_ERR_INVALID_ARG, "ca_kv_load_layer: a source is neither pinned host nor device memory");
-    const bool staged = c.load_mode == 1 || (c.load_mode == 0 && any_host);
+    const int64_t move_bytes = 2 * ctx->total_n * rb;
+    const bool small = move_bytes <= (any_host ? kInlineHostLoadBytes : kInlineDeviceBytes);
+    const bool staged = c.load_mode == 1 || (c.load_mode == 0 && any_host && !small);
+    const bool on_caller = small && !staged && stream_alive(ctx->plan_stream) && inline_free(ctx, ctx->plan_stream);
+    hipStream_t mover = on_caller ? ctx->plan_stream : ctx->s_unpack;
+    if (on_caller) CA_HIP(ctx, caller_after_plan(ctx, mover));
+    else CA_HIP(ctx, after_plan(ctx, ctx->s_unpack, &ctx->unpack_waits_plan));
 
     std::vector<Segment> segs;
     segs.reserve(B);
@@ -1088,6 +1317,7 @@ ca_status ca_kv_load_layer(ca_ctx *ctx, int32_t layer, const void *const *src_k,
         // both: two copy queues keep the host link busier than one (each fills the gaps between the other's
         // per-conversation copies), and a stream of its own for the second queue would be one more than the hardware
         // queues a process has, which makes unrelated streams wait for each other.
+        CA_HIP(ctx, after_plan(ctx, ctx->s_copy, &ctx->copy_waits_plan));
         // the slot is free again once the unpack that last read it has finished (the unpack stream is behind it anyway)
         if (ctx->slot_used[slot]) CA_HIP(ctx, hipStreamWaitEvent(ctx->s_copy, ctx->ev_slot_free[slot], 0));
         int iv_copy;
@@ -1134,12 +1364,19 @@ ca_status ca_kv_load_layer(ca_ctx *ctx, int32_t layer, const void *const *src_k,
             }
         }
         int iv_unpack;
-        CA_HIP(ctx, prof_begin(ctx, kProfUnpack, ctx->s_unpack, &iv_unpack));
-        st = run_move(ctx, true, segs, k_pool, v_pool, ctx->s_unpack);
+        CA_HIP(ctx, prof_begin(ctx, kProfUnpack, mover, &iv_unpack));
+        st = run_move(ctx, true, segs, k_pool, v_pool, mover);
         if (st != CA_OK) return st;
-        CA_HIP(ctx, prof_end(ctx, iv_unpack, ctx->s_unpack));
+        CA_HIP(ctx, prof_end(ctx, iv_unpack, mover));
     }
-    CA_HIP(ctx, hipEventRecord(ctx->ev_ready[layer], ctx->s_unpack));
+    if (!on_caller || mover != nullptr) CA_HIP(ctx, hipEventRecord(ctx->ev_ready[layer], mover));
+    if (on_caller) {
+        note_inline(ctx, mover, mover != nullptr ? ctx->ev_ready[layer] : nullptr);
+    } else {
+        ctx->load_done = ctx->ev_ready[layer];
+        ctx->joined_null = false;
+    }
+    ctx->ready_inline[layer] = on_caller ? 1 : 0;
     ctx->loaded[layer] = 1;
     return CA_OK;
 }
@@ -1151,20 +1388,13 @@ ca_status ca_kv_append_layer(ca_ctx *ctx, int32_t layer, const void *new_k, cons
     if (st != CA_OK) return st;
     const ca_config &c = ctx->cfg;
     CA_HIP(ctx, hipSetDevice(c.device));
-    st = check_pools(ctx, "ca_kv_append_layer", k_pool, v_pool);
+    MemMap map;
+    st = check_pools(ctx, "ca_kv_append_layer", k_pool, v_pool, map);
     if (st != CA_OK) return st;
     const size_t bytes = (size_t)ctx->total_q * (size_t)row_bytes(c);
-    if (!device_range_ok(new_k, bytes) || !device_range_ok(new_v, bytes))
+    if (!map.device_range_ok(new_k, bytes) || !map.device_range_ok(new_v, bytes))
         return fail(ctx, CA_ERR_INVALID_ARG, "ca_kv_append_layer: new_k/new_v must be device memory of %zu bytes", bytes);
-    std::vector<Segment> segs;
-    for (int i = 0; i < ctx->n_seqs; ++i)
-        segs.push_back({(uint8_t *)new_k, (uint8_t *)new_v, ctx->cu_q[i], ctx->n_keep[i], ctx->new_len[i], i});
-    int iv;
-    CA_HIP(ctx, prof_begin(ctx, kProfAppend, (hipStream_t)stream, &iv));
-    st = run_move(ctx, true, segs, k_pool, v_pool, (hipStream_t)stream);
-    if (st != CA_OK) return st;
-    CA_HIP(ctx, prof_end(ctx, iv, (hipStream_t)stream));
-    return CA_OK;
+    return run_append(ctx, new_k, new_v, k_pool, v_pool, (hipStream_t)stream);
 }
 
 ca_status ca_kv_save_layer(ca_ctx *ctx, int32_t layer, const int32_t *tok_begin, const int32_t *tok_end,
@@ -1178,7 +1408,8 @@ ca_status ca_kv_save_layer(ca_ctx *ctx, int32_t layer, const int32_t *tok_begin,
         return fail(ctx, CA_ERR_INVALID_ARG, "ca_kv_save_layer: tok_begin and tok_end must both be given or both NULL");
     const ca_config &c = ctx->cfg;
     CA_HIP(ctx, hipSetDevice(c.device));
-    st = check_pools(ctx, "ca_kv_save_layer", k_pool, v_pool);
+    MemMap map, map_k;
+    st = check_pools(ctx, "ca_kv_save_layer", k_pool, v_pool, map);
     if (st != CA_OK) return st;
 
     const int B = ctx->n_seqs;
@@ -1198,24 +1429,32 @@ ca_status ca_kv_save_layer(ca_ctx *ctx, int32_t layer, const int32_t *tok_begin,
         if (r[i].off < 0) return fail(ctx, CA_ERR_OUT_OF_RANGE, "ca_kv_save_layer: conversation %d: negative destination offset", i);
         if (r[i].e == r[i].b) continue;
         if (!dst_k[i] || !dst_v[i]) return fail(ctx, CA_ERR_INVALID_ARG, "ca_kv_save_layer: destination of conversation %d is NULL", i);
-        const MemKind kk = mem_kind(dst_k[i]), kv = mem_kind(dst_v[i]);
+        const size_t need = (size_t)(r[i].off + (r[i].e - r[i].b)) * rb;
+        bool k_in, v_in;
+        const MemKind kk = map_k.look(dst_k[i], need, &k_in), kv = map.look(dst_v[i], need, &v_in);
         if (kk == MemKind::kUnknown || kv == MemKind::kUnknown)
             return fail(ctx, CA_ERR_INVALID_ARG, "ca_kv_save_layer: destination of conversation %d is neither pinned host nor device memory", i);
         if (kk == MemKind::kPinnedHost || kv == MemKind::kPinnedHost) any_host = true;
-        const size_t need = (size_t)(r[i].off + (r[i].e - r[i].b)) * rb;
-        if ((kk == MemKind::kDevice && !device_range_ok(dst_k[i], need)) || (kv == MemKind::kDevice && !device_range_ok(dst_v[i], need)))
+        if ((kk == MemKind::kDevice && !k_in) || (kv == MemKind::kDevice && !v_in))
             return fail(ctx, CA_ERR_INVALID_ARG, "ca_kv_save_layer: destination of conversation %d is smaller than offset + count tokens", i);
         total += r[i].e - r[i].b;
     }
     if (total > c.max_batch_kv_tokens) return fail(ctx, CA_ERR_OUT_OF_RANGE, "ca_kv_save_layer: %lld tokens exceed a staging slot", (long long)total);
-    const bool staged = any_host ? !host_save_in_place(ctx, total) : c.save_mode == 1;
+    hipStream_t after = (hipStream_t)after_stream;
+    const bool on_caller = save_is_short(ctx, any_host, 2 * total * rb) && inline_free(ctx, after);
+    const bool staged = !on_caller && (any_host ? !host_save_in_place(ctx, total) : c.save_mode == 1);
 
     // saving starts after the producer of this layer's K/V: the work queued on `after_stream`, and the load of
     // this layer if one was issued (its unpack runs on an internal stream and may still be writing the pages a
     // range of kept-history tokens reads)
-    CA_HIP(ctx, hipEventRecord(ctx->ev_after, (hipStream_t)after_stream));
-    CA_HIP(ctx, hipStreamWaitEvent(ctx->s_save, ctx->ev_after, 0));
-    if (ctx->loaded[layer]) CA_HIP(ctx, hipStreamWaitEvent(ctx->s_save, ctx->ev_ready[layer], 0));
+    hipStream_t saver = on_caller ? after : ctx->s_save;
+    if (on_caller) {
+        CA_HIP(ctx, caller_after_plan(ctx, after));
+    } else {
+        st = save_follows(ctx, after);
+        if (st != CA_OK) return st;
+    }
+    if (ctx->loaded[layer]) CA_HIP(ctx, after_load(ctx, layer, saver));
 
     std::vector<Segment> segs;
     segs.reserve(B);
@@ -1256,18 +1495,21 @@ ca_status ca_kv_save_layer(ca_ctx *ctx, int32_t layer, const int32_t *tok_begin,
             segs.push_back({(uint8_t *)dst_k[i], (uint8_t *)dst_v[i], r[i].off, r[i].b, cnt, i});
         }
         int iv_pack;
-        CA_HIP(ctx, prof_begin(ctx, kProfPack, ctx->s_save, &iv_pack));
+        CA_HIP(ctx, prof_begin(ctx, kProfPack, saver, &iv_pack));
         // stores that cross the host link are bound by the link: a few workgroups saturate it, and a grid that filled the
         // GPU with waiting wavefronts would take the compute units from the attention kernel running beside it
-        st = run_move(ctx, false, segs, (void *)k_pool, (void *)v_pool, ctx->s_save, any_host ? kHostStoreWorkgroups : 0);
+        st = run_move(ctx, false, segs, (void *)k_pool, (void *)v_pool, saver, any_host ? kHostStoreWorkgroups : 0);
         if (st != CA_OK) return st;
-        CA_HIP(ctx, prof_end(ctx, iv_pack, ctx->s_save));
+        CA_HIP(ctx, prof_end(ctx, iv_pack, saver));
     }
+    if (on_caller) CA_HIP(ctx, note_inline(ctx, saver));
+    else CA_HIP(ctx, note_save(ctx));
     return CA_OK;
 }
 
 // Appending and saving the new turn in one call: the saved bytes ARE the appended bytes (keys without positions,
-// Section 3.4), so the pool need not be read back.  Device destinations (and pinned ones under save_mode 2): one kernel
+// Section 3.4), so the pool need not be read back.  Device destinations (and pinned ones under save_mode 2, or when the
+// turn is short): one kernel
 // reads new_k/new_v once and stores every vector twice (pool and tier).  Pinned destinations by default: append kernel,
 // then the pack kernel writes the tier in place from the save stream.  Pinned destinations with staged saving: the
 // copy-out on the save stream reads new_k/new_v directly; no pack kernel, no staging slot.
@@ -1279,107 +1521,78 @@ ca_status ca_kv_append_save_layer(ca_ctx *ctx, int32_t layer, const void *new_k,
     if (!dst_k || !dst_v) return fail(ctx, CA_ERR_INVALID_ARG, "ca_kv_append_save_layer: destination pointer array is NULL");
     const ca_config &c = ctx->cfg;
     CA_HIP(ctx, hipSetDevice(c.device));
-    st = check_pools(ctx, "ca_kv_append_save_layer", k_pool, v_pool);
+    MemMap map, map_k;
+    st = check_pools(ctx, "ca_kv_append_save_layer", k_pool, v_pool, map);
     if (st != CA_OK) return st;
     const int64_t rb = row_bytes(c);
     const size_t bytes = (size_t)ctx->total_q * (size_t)rb;
-    if (!device_range_ok(new_k, bytes) || !device_range_ok(new_v, bytes))
+    if (!map.device_range_ok(new_k, bytes) || !map.device_range_ok(new_v, bytes))
         return fail(ctx, CA_ERR_INVALID_ARG, "ca_kv_append_save_layer: new_k/new_v must be device memory of %zu bytes", bytes);
     const int B = ctx->n_seqs;
     bool any_host = false;
     for (int i = 0; i < B; ++i) {
         if (!dst_k[i] || !dst_v[i]) return fail(ctx, CA_ERR_INVALID_ARG, "ca_kv_append_save_layer: destination of conversation %d is NULL", i);
-        const MemKind kk = mem_kind(dst_k[i]), kv = mem_kind(dst_v[i]);
+        const size_t need = (size_t)(ctx->hist_len[i] + ctx->new_len[i]) * rb;
+        bool k_in, v_in;
+        const MemKind kk = map_k.look(dst_k[i], need, &k_in), kv = map.look(dst_v[i], need, &v_in);
         if (kk == MemKind::kUnknown || kv == MemKind::kUnknown)
             return fail(ctx, CA_ERR_INVALID_ARG, "ca_kv_append_save_layer: destination of conversation %d is neither pinned host nor device memory", i);
         if (kk == MemKind::kPinnedHost || kv == MemKind::kPinnedHost) any_host = true;
-        const size_t need = (size_t)(ctx->hist_len[i] + ctx->new_len[i]) * rb;
-        if ((kk == MemKind::kDevice && !device_range_ok(dst_k[i], need)) || (kv == MemKind::kDevice && !device_range_ok(dst_v[i], need)))
+        if ((kk == MemKind::kDevice && !k_in) || (kv == MemKind::kDevice && !v_in))
             return fail(ctx, CA_ERR_INVALID_ARG, "ca_kv_append_save_layer: destination of conversation %d is smaller than hist_len + new_len tokens", i);
     }
-    const bool staged = any_host ? !host_save_in_place(ctx, ctx->total_q) : c.save_mode == 1;
     hipStream_t stream = (hipStream_t)stream_;
-    if (!staged && any_host && c.save_mode == 0) {
-        // a pinned tier: the append kernel on the caller's stream, then the pack kernel on the save stream writes the
-        // new tokens to the tier in place (the caller's stream must not wait for stores that cross the host link)
-        std::vector<Segment> segs;
-        for (int i = 0; i < B; ++i)
-            segs.push_back({(uint8_t *)new_k, (uint8_t *)new_v, ctx->cu_q[i], ctx->n_keep[i], ctx->new_len[i], i});
+    const bool in_place = !any_host || host_save_in_place(ctx, ctx->total_q);
+    const bool one_kernel = any_host ? c.save_mode == 2 || (save_is_short(ctx, any_host, 2 * (int64_t)bytes) && inline_free(ctx, stream))
+                                     : c.save_mode != 1;
+    if (!one_kernel) {
+        // the append kernel on the caller's stream (which must not wait for stores that cross the host link); the write-back
+        // follows it on the save stream
+        st = run_append(ctx, new_k, new_v, k_pool, v_pool, stream);
+        if (st == CA_OK) st = save_follows(ctx, stream);
+        if (st != CA_OK) return st;
         int iv;
-        CA_HIP(ctx, prof_begin(ctx, kProfAppend, stream, &iv));
-        st = run_move(ctx, true, segs, k_pool, v_pool, stream);
-        if (st != CA_OK) return st;
-        CA_HIP(ctx, prof_end(ctx, iv, stream));
-        CA_HIP(ctx, hipEventRecord(ctx->ev_after, stream));
-        CA_HIP(ctx, hipStreamWaitEvent(ctx->s_save, ctx->ev_after, 0));
-        if (ctx->loaded[layer]) CA_HIP(ctx, hipStreamWaitEvent(ctx->s_save, ctx->ev_ready[layer], 0));
-        segs.clear();
-        for (int i = 0; i < B; ++i)
-            if (ctx->new_len[i] > 0)
-                segs.push_back({(uint8_t *)dst_k[i], (uint8_t *)dst_v[i], ctx->hist_len[i], ctx->n_keep[i], ctx->new_len[i], i});
-        int iv_pack;
-        CA_HIP(ctx, prof_begin(ctx, kProfPack, ctx->s_save, &iv_pack));
-        st = run_move(ctx, false, segs, k_pool, v_pool, ctx->s_save, kHostStoreWorkgroups);
-        if (st != CA_OK) return st;
-        CA_HIP(ctx, prof_end(ctx, iv_pack, ctx->s_save));
-        return CA_OK;
-    }
-    if (staged) {
-        // append on the caller's stream; the copy-out follows it on the save stream, straight from new_k / new_v
-        std::vector<Segment> segs;
-        for (int i = 0; i < B; ++i)
-            segs.push_back({(uint8_t *)new_k, (uint8_t *)new_v, ctx->cu_q[i], ctx->n_keep[i], ctx->new_len[i], i});
-        int iv;
-        CA_HIP(ctx, prof_begin(ctx, kProfAppend, stream, &iv));
-        st = run_move(ctx, true, segs, k_pool, v_pool, stream);
-        if (st != CA_OK) return st;
-        CA_HIP(ctx, prof_end(ctx, iv, stream));
-        CA_HIP(ctx, hipEventRecord(ctx->ev_after, stream));
-        CA_HIP(ctx, hipStreamWaitEvent(ctx->s_save, ctx->ev_after, 0));
-        int iv_out;
-        CA_HIP(ctx, prof_begin(ctx, kProfCopyOut, ctx->s_save, &iv_out));
-        for (int i = 0; i < B; ++i) {
-            const size_t n = (size_t)ctx->new_len[i] * rb, src_off = (size_t)ctx->cu_q[i] * rb, dst_off = (size_t)ctx->hist_len[i] * rb;
-            CA_HIP(ctx, hipMemcpyAsync((uint8_t *)dst_k[i] + dst_off, (const uint8_t *)new_k + src_off, n, hipMemcpyDefault, ctx->s_save));
-            CA_HIP(ctx, hipMemcpyAsync((uint8_t *)dst_v[i] + dst_off, (const uint8_t *)new_v + src_off, n, hipMemcpyDefault, ctx->s_save));
+        if (any_host && in_place) {
+            // the pack kernel writes the new tokens to the tier in place
+            std::vector<Segment> segs;
+            for (int i = 0; i < B; ++i)
+                if (ctx->new_len[i] > 0)
+                    segs.push_back({(uint8_t *)dst_k[i], (uint8_t *)dst_v[i], ctx->hist_len[i], ctx->n_keep[i], ctx->new_len[i], i});
+            if (ctx->loaded[layer]) CA_HIP(ctx, after_load(ctx, layer, ctx->s_save));
+            CA_HIP(ctx, prof_begin(ctx, kProfPack, ctx->s_save, &iv));
+            st = run_move(ctx, false, segs, k_pool, v_pool, ctx->s_save, kHostStoreWorkgroups);
+            if (st != CA_OK) return st;
+        } else {
+            // one copy per conversation, straight from new_k / new_v
+            CA_HIP(ctx, prof_begin(ctx, kProfCopyOut, ctx->s_save, &iv));
+            for (int i = 0; i < B; ++i) {
+                const size_t n = (size_t)ctx->new_len[i] * rb, src_off = (size_t)ctx->cu_q[i] * rb, dst_off = (size_t)ctx->hist_len[i] * rb;
+                CA_HIP(ctx, hipMemcpyAsync((uint8_t *)dst_k[i] + dst_off, (const uint8_t *)new_k + src_off, n, hipMemcpyDefault, ctx->s_save));
+                CA_HIP(ctx, hipMemcpyAsync((uint8_t *)dst_v[i] + dst_off, (const uint8_t *)new_v + src_off, n, hipMemcpyDefault, ctx->s_save));
+            }
         }
-        CA_HIP(ctx, prof_end(ctx, iv_out, ctx->s_save));
+        CA_HIP(ctx, prof_end(ctx, iv, ctx->s_save));
+        CA_HIP(ctx, note_save(ctx));
         return CA_OK;
     }
-    // one pass: every vector of the new turn goes to its page and to its row of the tier
-    MoveShape shape{};
-    shape.block_table = (const int32_t *)(ctx->d_meta + ctx->off_table);
-    shape.max_pages = ctx->max_pages;
-    shape.n_kv_heads = c.n_kv_heads;
-    shape.vecs_per_row = c.head_dim * 2 / 16;
-    shape.heads_per_wg = std::max(1, std::min(c.n_kv_heads, kMoveUnroll * 256 / (16 * shape.vecs_per_row)));
-    int iv;
+    // one pass: every vector of the new turn goes to its page and to its row of the tier.  A short turn written across the
+    // host link this way also counts as the write-back it replaces.
+    int iv, iv_back = -1;
     CA_HIP(ctx, prof_begin(ctx, kProfAppend, stream, &iv));
+    if (any_host && c.save_mode != 2) CA_HIP(ctx, prof_begin(ctx, in_place ? kProfPack : kProfCopyOut, stream, &iv_back));
     for (int at = 0; at < B; at += kMaxSeqsPerLaunch) {
-        MoveArgs args;
         MoveArgs2 second;
-        std::memset(&args, 0, sizeof args);
-        std::memset(&second, 0, sizeof second);
         const int n = std::min(kMaxSeqsPerLaunch, B - at);
-        int max_touched = 0;
-        for (int i = 0; i < n; ++i) {
-            const int q = at + i;
-            args.contig_k[i] = (uint8_t *)new_k;
-            args.contig_v[i] = (uint8_t *)new_v;
-            args.contig_tok0[i] = ctx->cu_q[q];
-            args.ctx_tok0[i] = ctx->n_keep[q];
-            args.count[i] = ctx->new_len[q];
-            args.seq[i] = q;
-            second.dst2_k[i] = (uint8_t *)dst_k[q];
-            second.dst2_v[i] = (uint8_t *)dst_v[q];
-            second.dst2_tok0[i] = ctx->hist_len[q];       // new token j is saved behind the history, at token hist_len + j
-            max_touched = std::max(max_touched, (ctx->n_keep[q] + ctx->new_len[q] - 1) / kPageSize - ctx->n_keep[q] / kPageSize + 1);
+        for (int i = 0; i < n; ++i) {       // new token j is saved behind the history, at token hist_len + j
+            second.dst_k[i] = (uint8_t *)dst_k[at + i] + (size_t)ctx->hist_len[at + i] * rb;
+            second.dst_v[i] = (uint8_t *)dst_v[at + i] + (size_t)ctx->hist_len[at + i] * rb;
         }
-        shape.n_in_launch = n;
-        shape.max_pages_touched = max_touched;
-        CA_HIP(ctx, launch_move_dual(args, second, shape, (uint8_t *)k_pool, (uint8_t *)v_pool, stream));
+        CA_HIP(ctx, launch_append_save(new_turn_shape(ctx, at, n), at, second, (const uint8_t *)new_k, (const uint8_t *)new_v,
+                                       (uint8_t *)k_pool, (uint8_t *)v_pool, stream));
     }
+    CA_HIP(ctx, prof_end(ctx, iv_back, stream));
     CA_HIP(ctx, prof_end(ctx, iv, stream));
+    if (any_host && c.save_mode != 2) CA_HIP(ctx, note_inline(ctx, stream));    // ca_sync and ca_join cover it, as they would the save stream
     return CA_OK;
 }
 
@@ -1394,16 +1607,17 @@ static ca_status attn_impl(ca_ctx *ctx, int32_t layer, const void *q, const void
     if (st != CA_OK) return st;
     const ca_config &c = ctx->cfg;
     CA_HIP(ctx, hipSetDevice(c.device));
-    st = check_pools(ctx, "ca_cached_prefill_attn", k_pool, v_pool);
+    MemMap map;
+    st = check_pools(ctx, "ca_cached_prefill_attn", k_pool, v_pool, map);
     if (st != CA_OK) return st;
     if (!(softmax_scale > 0.f) || !std::isfinite(softmax_scale))
         return fail(ctx, CA_ERR_INVALID_ARG, "ca_cached_prefill_attn: softmax_scale must be finite and > 0");
     const size_t q_bytes = (size_t)ctx->total_q * c.n_q_heads * c.head_dim * 2;
-    if (!device_range_ok(q, q_bytes) || !device_range_ok(out, q_bytes))
+    if (!map.device_range_ok(q, q_bytes) || !map.device_range_ok(out, q_bytes))
         return fail(ctx, CA_ERR_INVALID_ARG, "ca_cached_prefill_attn: q/out must be device memory of %zu bytes", q_bytes);
     hipStream_t stream = (hipStream_t)stream_;
     if (ctx->loaded[layer]) {
-        CA_HIP(ctx, hipStreamWaitEvent(stream, ctx->ev_ready[layer], 0));
+        CA_HIP(ctx, after_load(ctx, layer, stream));
     } else if (c.require_load && ctx->total_n > 0) {
         return fail(ctx, CA_ERR_NOT_READY, "ca_cached_prefill_attn: layer %d has kept history but was not loaded under this plan", layer);
     }

@@ -20,6 +20,14 @@ constexpr int kMoveThreads = 256;
 constexpr int kUnroll = kMoveUnroll;
 constexpr int kMoveMaxGridY = 32768;
 
+// One contiguous range of context tokens of one conversation, for keys or for values, and where it lies outside the pool.
+struct Piece {
+    uint8_t *contig;        // token contig_tok0 + i <-> context token ctx_tok0 + i, i < count
+    int64_t contig_tok0;
+    int ctx_tok0, count, seq;
+    uint8_t *second;        // kDual: row i receives token i too
+};
+
 // grid: x = (slice of heads, K or V), y = page of the conversation's context (counted from the first
 // page the range touches), z = conversation entry of this launch.  A workgroup moves, for one of the
 // two arrays, the tokens of its page that lie inside the range for heads_per_wg heads, kUnroll loads
@@ -31,13 +39,11 @@ constexpr int kMoveMaxGridY = 32768;
 // kDual (with kToPool): every vector read from the contiguous side is stored twice, into the pool and into a second
 // contiguous destination (the tier): the new turn's K/V are appended and saved in one pass over them.
 template <bool kToPool, bool kNT, bool kDual>
-__device__ inline void move_body(const MoveArgs &a, const MoveShape &s, uint8_t *__restrict__ k_pool,
-                                 uint8_t *__restrict__ v_pool, const MoveArgs2 &b) {
+__device__ inline void move_piece(const Piece &p, const MoveShape &s, uint8_t *__restrict__ side) {
     static_assert(!kDual || kToPool, "the second destination goes with contiguous -> pages");
-    const int e = blockIdx.z;  // entry of this launch
-    const bool values = blockIdx.x & 1;
-    const int ctx_begin = a.ctx_tok0[e];
-    const int ctx_end = ctx_begin + a.count[e];
+    const int ctx_begin = p.ctx_tok0;
+    const int ctx_end = ctx_begin + p.count;
+    const int vs = s.vec_shift;
     // grid.y is capped below the launch limit; longer ranges take more than one trip
     for (int col = blockIdx.y; col < s.max_pages_touched; col += gridDim.y) {
         const int page_col = ctx_begin / kPageSize + col;
@@ -46,22 +52,20 @@ __device__ inline void move_body(const MoveArgs &a, const MoveShape &s, uint8_t 
         if (t_first >= t_last) break;   // past the last page of this range
         const int slot0 = t_first - page_col * kPageSize;
         const int n_tok = t_last - t_first;
-        const int vpr = s.vecs_per_row;
         const int H = s.n_kv_heads;
         const int h_first = (blockIdx.x >> 1) * s.heads_per_wg;
         const int h_count = min(s.heads_per_wg, H - h_first);
-        const int page = s.block_table[(int64_t)a.seq[e] * s.max_pages + page_col];
-        const int64_t row_vecs = (int64_t)H * vpr;  // 16-byte vectors per token on the contiguous side
-        const int64_t contig_first = a.contig_tok0[e] + (t_first - ctx_begin);
-        vec16 *contig = reinterpret_cast<vec16 *>(values ? a.contig_v[e] : a.contig_k[e]) + contig_first * row_vecs + (int64_t)h_first * vpr;
-        vec16 *pool = reinterpret_cast<vec16 *>(values ? v_pool : k_pool) + (((int64_t)page * H + h_first) * kPageSize + slot0) * vpr;
+        const int page = s.block_table[(int64_t)p.seq * s.max_pages + page_col];
+        const int64_t row_vecs = (int64_t)H << vs;  // 16-byte vectors per token on the contiguous side
+        const int64_t contig_first = p.contig_tok0 + (t_first - ctx_begin);
+        vec16 *contig = reinterpret_cast<vec16 *>(p.contig) + contig_first * row_vecs + ((int64_t)h_first << vs);
+        vec16 *pool = reinterpret_cast<vec16 *>(side) + ((((int64_t)page * H + h_first) * kPageSize + slot0) << vs);
         vec16 *second = nullptr;
-        if (kDual) second = reinterpret_cast<vec16 *>(values ? b.dst2_v[e] : b.dst2_k[e]) + (b.dst2_tok0[e] + (t_first - ctx_begin)) * row_vecs + (int64_t)h_first * vpr;
+        if (kDual) second = reinterpret_cast<vec16 *>(p.second) + (t_first - ctx_begin) * row_vecs + ((int64_t)h_first << vs);
 
         // vector id v -> (head, token, 16-byte piece), piece fastest
-        const int per_head = n_tok * vpr;
+        const int per_head = n_tok << vs;
         const int total = h_count * per_head;
-        const int head_stride_pool = kPageSize * vpr;
         for (int v0 = threadIdx.x; v0 < total; v0 += kMoveThreads * kUnroll) {
             vec16 r[kUnroll];
             int pool_idx[kUnroll];
@@ -70,13 +74,13 @@ __device__ inline void move_body(const MoveArgs &a, const MoveShape &s, uint8_t 
 #pragma unroll
             for (int u = 0; u < kUnroll; ++u) {
                 const int v = v0 + u * kMoveThreads;
-                const int hl = v / per_head;
+                const int hl = n_tok == kPageSize ? v / kPageSize >> vs : v / per_head;
                 const int rem = v - hl * per_head;
-                const int ti = rem / vpr;
-                const int piece = rem - ti * vpr;
+                const int ti = rem >> vs;
+                const int piece = rem - (ti << vs);
                 live[u] = v < total;
-                pool_idx[u] = hl * head_stride_pool + ti * vpr + piece;
-                contig_idx[u] = (int64_t)ti * row_vecs + hl * vpr + piece;
+                pool_idx[u] = (((hl * kPageSize) + ti) << vs) + piece;
+                contig_idx[u] = (int64_t)ti * row_vecs + (hl << vs) + piece;
                 if (live[u]) {
                     const vec16 *src = kToPool ? contig + contig_idx[u] : pool + pool_idx[u];
                     r[u] = kNT ? __builtin_nontemporal_load(src) : *src;
@@ -97,33 +101,59 @@ __device__ inline void move_body(const MoveArgs &a, const MoveShape &s, uint8_t 
 template <bool kToPool, bool kNT>
 __global__ __launch_bounds__(kMoveThreads) void move_kernel(MoveArgs a, MoveShape s, uint8_t *__restrict__ k_pool,
                                                             uint8_t *__restrict__ v_pool) {
-    move_body<kToPool, kNT, false>(a, s, k_pool, v_pool, MoveArgs2{});
+    const int e = blockIdx.z;  // entry of this launch
+    const bool values = blockIdx.x & 1;
+    const Piece p{values ? a.contig_v[e] : a.contig_k[e], a.contig_tok0[e], a.ctx_tok0[e], a.count[e], a.seq[e], nullptr};
+    move_piece<kToPool, kNT, false>(p, s, values ? v_pool : k_pool);
 }
 
-__global__ __launch_bounds__(kMoveThreads) void move_dual_kernel(MoveArgs a, MoveArgs2 b, MoveShape s, uint8_t *__restrict__ k_pool,
-                                                                 uint8_t *__restrict__ v_pool) {
-    move_body<true, true, true>(a, s, k_pool, v_pool, b);
+// The new turn of conversation `seq`: everything but the pointers is in the plan's metadata, so the arguments are a few
+// words whatever the batch (a launch with 2.6 KB of per-conversation arguments costs the host 0.4 to 1.3 us more).
+__device__ inline Piece new_turn(const MoveShape &s, int seq, const uint8_t *from, uint8_t *second) {
+    const int q = s.cu_q[seq];
+    return Piece{const_cast<uint8_t *>(from), q, s.n_keep[seq], s.cu_q[seq + 1] - q, seq, second};
 }
 
-// One thread per context token: which conversation it belongs to (binary search in the prefix
-// sums), where it lives in the pool, and for new tokens their rebased position.
-__global__ __launch_bounds__(256) void rebase_kernel(RebaseArgs a) {
-    const int i = blockIdx.x * blockDim.x + threadIdx.x;
-    if (i >= a.total_k) return;
-    int lo = 0, hi = a.n_seqs;  // largest c with cu_k[c] <= i
-    while (hi - lo > 1) {
-        const int mid = (lo + hi) >> 1;
-        if (a.cu_k[mid] <= i) lo = mid; else hi = mid;
+__global__ __launch_bounds__(kMoveThreads) void append_kernel(MoveShape s, const uint8_t *__restrict__ new_k, const uint8_t *__restrict__ new_v,
+                                                              uint8_t *__restrict__ k_pool, uint8_t *__restrict__ v_pool) {
+    const bool values = blockIdx.x & 1;
+    move_piece<true, true, false>(new_turn(s, blockIdx.z, values ? new_v : new_k, nullptr), s, values ? v_pool : k_pool);
+}
+
+__global__ __launch_bounds__(kMoveThreads) void append_save_kernel(MoveArgs2 b, MoveShape s, int first, const uint8_t *__restrict__ new_k,
+                                                                   const uint8_t *__restrict__ new_v, uint8_t *__restrict__ k_pool,
+                                                                   uint8_t *__restrict__ v_pool) {
+    const bool values = blockIdx.x & 1;
+    move_piece<true, true, true>(new_turn(s, first + blockIdx.z, values ? new_v : new_k, values ? b.dst_v[blockIdx.z] : b.dst_k[blockIdx.z]), s,
+                                 values ? v_pool : k_pool);
+}
+
+// Brings a plan's metadata to the device and forms its per-token arrays, in one launch and without a copy engine: the
+// image is read from pinned host memory by the kernel (20 KB: 3 us, where hipMemcpyAsync in front of a kernel took 15 to
+// 35 us).  The first copy_wgs workgroups copy; the others own 256 context tokens of one conversation at a time: where a token
+// lives in the pool, and for new tokens their rebased position.  They read what they need of the image from the host as
+// well, two dependent reads, so nothing waits for the copy inside the launch.
+constexpr int kRebaseThreads = 256;
+__global__ __launch_bounds__(kRebaseThreads) void rebase_kernel(RebaseArgs a, int copy_wgs, int chunks) {
+    if ((int)blockIdx.x < copy_wgs) {
+        const vec16 *src = reinterpret_cast<const vec16 *>(a.image);
+        vec16 *dst = reinterpret_cast<vec16 *>(a.meta);
+        for (int64_t i = (int64_t)blockIdx.x * kRebaseThreads + threadIdx.x; i < a.image_vecs; i += (int64_t)copy_wgs * kRebaseThreads) dst[i] = src[i];
+        return;
     }
-    const int c = lo;
-    const int t = i - a.cu_k[c];
-    const int page = a.block_table[(int64_t)c * a.max_pages + t / kPageSize];
-    a.slot_map[i] = page * kPageSize + t % kPageSize;
-    const int n = a.n_keep[c];
-    if (t >= n) {
-        const int j = t - n;
-        a.q_pos[a.cu_q[c] + j] = t;  // new token j sits at position n + j of the truncated context
-        a.q_seq[a.cu_q[c] + j] = c;
+    const int at = blockIdx.x - copy_wgs;
+    const int c = at / chunks;
+    const int32_t *cu_k = reinterpret_cast<const int32_t *>(a.image + a.off_cu_k);
+    const int k0 = cu_k[c], len = cu_k[c + 1] - k0;
+    const int n = reinterpret_cast<const int32_t *>(a.image + a.off_n_keep)[c];
+    const int q0 = reinterpret_cast<const int32_t *>(a.image + a.off_cu_q)[c];
+    for (int t = (at - c * chunks) * kRebaseThreads + threadIdx.x; t < len; t += chunks * kRebaseThreads) {
+        const int page = reinterpret_cast<const int32_t *>(a.image + a.off_table)[(int64_t)c * a.max_pages + t / kPageSize];
+        a.slot_map[k0 + t] = page * kPageSize + t % kPageSize;
+        if (t >= n) {
+            a.q_pos[q0 + t - n] = t;  // new token j sits at position n + j of the truncated context
+            a.q_seq[q0 + t - n] = c;
+        }
     }
 }
 
@@ -144,19 +174,29 @@ hipError_t launch_move(bool to_pool, const MoveArgs &args, const MoveShape &shap
     return hipGetLastError();
 }
 
-hipError_t launch_move_dual(const MoveArgs &args, const MoveArgs2 &second, const MoveShape &shape, uint8_t *k_pool,
-                            uint8_t *v_pool, hipStream_t stream) {
+hipError_t launch_append(const MoveShape &shape, const uint8_t *new_k, const uint8_t *new_v, uint8_t *k_pool, uint8_t *v_pool,
+                         hipStream_t stream) {
     if (shape.n_in_launch <= 0 || shape.max_pages_touched <= 0) return hipSuccess;
     const int slices = (shape.n_kv_heads + shape.heads_per_wg - 1) / shape.heads_per_wg;
     dim3 grid(2 * slices, std::min(shape.max_pages_touched, kMoveMaxGridY), shape.n_in_launch);
-    hipLaunchKernelGGL(move_dual_kernel, grid, dim3(kMoveThreads), 0, stream, args, second, shape, k_pool, v_pool);
+    hipLaunchKernelGGL(append_kernel, grid, dim3(kMoveThreads), 0, stream, shape, new_k, new_v, k_pool, v_pool);
+    return hipGetLastError();
+}
+
+hipError_t launch_append_save(const MoveShape &shape, int first, const MoveArgs2 &second, const uint8_t *new_k, const uint8_t *new_v,
+                              uint8_t *k_pool, uint8_t *v_pool, hipStream_t stream) {
+    if (shape.n_in_launch <= 0 || shape.max_pages_touched <= 0) return hipSuccess;
+    const int slices = (shape.n_kv_heads + shape.heads_per_wg - 1) / shape.heads_per_wg;
+    dim3 grid(2 * slices, std::min(shape.max_pages_touched, kMoveMaxGridY), shape.n_in_launch);
+    hipLaunchKernelGGL(append_save_kernel, grid, dim3(kMoveThreads), 0, stream, second, shape, first, new_k, new_v, k_pool, v_pool);
     return hipGetLastError();
 }
 
 hipError_t launch_rebase(const RebaseArgs &args, hipStream_t stream) {
-    if (args.total_k <= 0) return hipSuccess;
-    dim3 grid((args.total_k + 255) / 256);
-    hipLaunchKernelGGL(rebase_kernel, grid, dim3(256), 0, stream, args);
+    if (args.n_seqs <= 0) return hipSuccess;
+    const int chunks = std::min((args.max_pages * kPageSize + kRebaseThreads - 1) / kRebaseThreads, std::max(1, (1 << 20) / args.n_seqs));
+    const int copy_wgs = (int)std::max<int64_t>(1, std::min<int64_t>(256, (args.image_vecs + kRebaseThreads - 1) / kRebaseThreads));
+    hipLaunchKernelGGL(rebase_kernel, dim3(copy_wgs + chunks * args.n_seqs), dim3(kRebaseThreads), 0, stream, args, copy_wgs, chunks);
     return hipGetLastError();
 }
 

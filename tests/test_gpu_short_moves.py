@@ -1,0 +1,99 @@
+"""Short loads and saves run on the caller's streams instead of the internal ones: turns just below and above the sizes
+at which that changes, on the default stream and on others (the attention on a stream of its own, the next turn's plan on
+yet another), one context or two in turn.  ca_sync and ca_join must cover such moves like any other; every output is checked
+against the oracle, pool and tier bit for bit."""
+import numpy as np
+import pytest
+import torch
+
+from harness import Case, GpuRun, torch_to_bits
+
+pytestmark = pytest.mark.gpu
+
+
+def check(run):
+    case = run.case
+    for l in range(case.n_layers):
+        for which, pool, host in (("k", run.k_pool[l], run.host_k[l]), ("v", run.v_pool[l], run.host_v[l])):
+            assert np.array_equal(torch_to_bits(pool), case.oracle_pool(l, which)), (l, which)
+            for c in range(case.B):
+                got = torch_to_bits(host[c])
+                assert np.array_equal(got[:case.hist_len[c]], case.tensor(l, f"{which}_hist", c)), (l, which, c)
+                assert np.array_equal(got[case.hist_len[c]:], case.tensor(l, f"{which}_new", c)), (l, which, c)
+        for c in range(case.B):
+            err = np.abs(run.out_f64(l, c) - case.oracle_out(l, c))
+            assert err.max() <= 2e-2 and err.mean() <= 2e-3, (l, c)
+
+
+# kept tokens x 1 KiB (two KV heads of 128, keys and values): 512 and 513 KiB to load; new tokens: 256 and 257 KiB to save
+SIZES = {"shortest": ([1], [1]), "at-the-line": ([500, 12], [250, 6]), "past-it": ([500, 13], [250, 7])}
+
+
+@pytest.mark.parametrize("tier", ["pinned", "device"])
+@pytest.mark.parametrize("streams", ["default", "own", "three"])
+@pytest.mark.parametrize("size", list(SIZES))
+def test_turn(size, streams, tier):
+    hist, new = SIZES[size]
+    case = Case(hist, new, [0] * len(hist), 4, 2, 128, seed=81, n_layers=3, window=1024)
+    run = GpuRun(case, tier=tier)
+    try:
+        s = {"default": [None] * 3, "own": [torch.cuda.Stream()] * 3, "three": [torch.cuda.Stream() for _ in range(3)]}[streams]
+        for turn in range(2):                     # the second turn repeats the first: its plan must wait for the first one's moves
+            run.rebase(s[turn])
+            if streams == "three":
+                for other in s:                   # appending on another stream than the plan's is the caller's to order
+                    other.wait_stream(s[turn])
+            for l in range(case.n_layers):
+                run.load(l)
+            for l in range(case.n_layers):
+                if l == 1:
+                    run.append(l, s[1]); run.attn(l, s[1]); run.save(l, after_stream=s[1])
+                else:
+                    run.ctx.kv_append_save_layer(l, run.k_new[l], run.v_new[l], run.k_pool[l], run.v_pool[l], run.host_k[l],
+                                                 run.host_v[l], s[l])
+                    run.attn(l, s[l])
+            run.ctx.join(s[2])
+            if streams == "three":
+                s[1].wait_stream(s[0]); s[1].wait_stream(s[2])
+        run.finish()
+        check(run)
+    finally:
+        run.close()
+
+
+def test_sync_alone_covers_a_short_save():
+    case = Case([40, 3], [2, 30], [0, 0], 4, 4, 64, seed=82, window=256)
+    for stream in (None, torch.cuda.Stream()):
+        run = GpuRun(case, tier="pinned")
+        try:
+            run.rebase(stream)
+            run.load(0)
+            run.append(0, stream)
+            run.save(0, after_stream=stream)
+            run.ctx.sync()
+            for which, host in (("k", run.host_k[0]), ("v", run.host_v[0])):
+                for c in range(case.B):
+                    assert np.array_equal(torch_to_bits(host[c])[case.hist_len[c]:], case.tensor(0, f"{which}_new", c)), (which, c)
+        finally:
+            run.close()
+
+
+def test_two_contexts_in_turn_share_the_internal_streams():
+    cases = [Case([700, 90], [70, 200], [0, 30], 4, 2, 128, seed=83, n_layers=3, window=1024),
+             Case([20, 800], [300, 9], [0, 0], 4, 2, 128, seed=84, n_layers=3, window=1024)]
+    runs = [GpuRun(c, tier="pinned") for c in cases]
+    try:
+        for run in runs * 2:
+            run.rebase()
+            for l in range(run.case.n_layers):
+                run.load(l)
+            for l in range(run.case.n_layers):
+                run.append(l); run.attn(l); run.save(l)
+        runs[0].finish()
+        check(runs[0])
+        runs[0].close()                           # the other context keeps the streams
+        runs[1].finish()
+        check(runs[1])
+    finally:
+        for run in runs:
+            run.close()
