@@ -352,6 +352,8 @@ class Job:
         for k, nbytes in (("unpack", self.unpack_bytes), ("append", app), ("pack", self.pack_bytes)):
             ms, n = prof[k]
             us = ms / n * 1e3 if n else None
+            if us is not None and us < 2.0:      # a load across the host link scatters as it copies: its unpack intervals are empty
+                us = None
             out[k] = {"avg_launch_us": us, "gbs": nbytes / (us * 1e-6) / 1e9 if us else None,
                       "frac_hbm_peak": nbytes / (us * 1e-6) / 1e9 / HBM_PEAK_GBS if us else None}
         return out

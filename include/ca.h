@@ -19,9 +19,9 @@
  *     ordinary host memory unless "pinned" is stated (then hipHostMalloc'd / torch
  *     pin_memory).  Streams are hipStream_t passed as void*; NULL is the default stream.
  *   - The caller owns every tensor (pools, Q, output, host tier).  The library owns its
- *     context: three internal streams (copy-in, unpack, save), events, a ring of staging
- *     slots in HBM, a rotary table and small per-batch metadata.  It never frees or
- *     reallocates caller memory.
+ *     context: events, a ring of staging slots in HBM, a rotary table and small per-batch
+ *     metadata.  Three internal streams (copy-in, unpack, save) are shared by the contexts
+ *     on a GPU.  It never frees or reallocates caller memory.
  *   - Every call validates its arguments on the host BEFORE anything is launched and
  *     returns a ca_status; nothing throws or aborts.  ca_last_error() gives the text of
  *     the last failure on that context.  A context is not thread-safe.
@@ -75,20 +75,16 @@ typedef struct {
     int64_t max_batch_kv_tokens; /* largest sum over the batch of context tokens; sizes one   */
                                  /* staging slot and the metadata                             */
     int64_t max_batch_q_tokens;  /* largest sum over the batch of new tokens                  */
-    int32_t load_mode;       /* 0: choose per source pointer; 1: copy into a staging slot,    */
-                             /* then unpack; 2: the unpack kernel reads the source in place   */
-                             /* (source must be device-accessible)                            */
-    int32_t save_mode;       /* for ca_kv_save_layer / ca_kv_append_save_layer.  Device memory is  */
-                             /* written in place by the pack kernel unless 1.  Pinned host memory: */
-                             /* 1 pack into a staging slot, then one copy per conversation on a    */
-                             /* copy engine (about 8 GB/s for turns of a few hundred tokens, and   */
-                             /* disturbs no kernel); 2 the pack kernel stores over the host link   */
-                             /* from the internal save stream (about 40 GB/s, but kernels running  */
-                             /* beside it are held up for about as long as it runs; with 2         */
-                             /* ca_kv_append_save_layer stores from the one kernel on the caller's */
-                             /* stream); 0 chooses per call: staged while the tokens to save are   */
-                             /* fewer than a fifth of the kept history loaded per layer (the       */
-                             /* copies then hide under the load), else in place                    */
+    int32_t load_mode;       /* 0, 2: one kernel reads the source in place and scatters it into   */
+                             /* the pages (pinned sources by a few workgroups, which keep the host */
+                             /* link full and the GPU free); 1: copy into a staging slot, then     */
+                             /* unpack.  Sources must be device memory or pinned host memory       */
+    int32_t save_mode;       /* for ca_kv_save_layer / ca_kv_append_save_layer.  0: device memory and */
+                             /* pinned host memory are written in place, pinned memory by a few     */
+                             /* workgroups on the save stream; 1: pack into a staging slot, then    */
+                             /* one copy per conversation on a copy engine; 2: as 0, but            */
+                             /* ca_kv_append_save_layer writes a pinned tier from the one kernel    */
+                             /* on the caller's stream whatever the size                            */
     int32_t attn_variant;    /* 0: choose (the streaming kernel for a batch of decode steps, else the    */
                              /* matrix-core kernel); 1: scalar fp32 kernel (slow, for checking); 2: the  */
                              /* matrix-core kernel, K/V loaded straight into LDS, whatever the batch;    */
@@ -219,13 +215,13 @@ ca_status ca_rebase_read(ca_ctx *ctx, int32_t which, int32_t *out, int64_t capac
  * [keep_start[c], hist_len[c]) of src_k[c] / src_v[c] (contiguous layout, pointer to saved
  * token 0 of this layer; host array of n_seqs pointers) -- or, with a discarding list, the
  * tokens of its kept ranges in order -- become context tokens [0, n_keep[c]).
- * Truncation and discarding are just source offsets.  Runs on the internal copy-in and unpack streams and
- * marks the layer ready; ca_cached_prefill_attn(layer) waits for that mark on its own stream.
- * Sources: pinned host memory (staged hipMemcpyAsync into a ring slot + unpack kernel -- the K
- * half is copied on the copy-in stream and the V half on the unpack stream, two copy queues
- * keeping the host link busier than one -- or read in place by the unpack kernel, see load_mode)
- * or device memory (read in place).  A layer can be loaded once per plan (CA_ERR_NOT_READY
- * otherwise).                                                                                  */
+ * Truncation and discarding are just source offsets.  Runs on the internal unpack stream -- a load
+ * of at most 512 KB from pinned or 16 MB from device memory on the stream of ca_rope_rebase, which
+ * is shorter than the way to another stream and back -- and marks the layer ready;
+ * ca_cached_prefill_attn(layer) waits for that mark on its own stream.
+ * Sources: pinned host memory or device memory, read in place (staged with load_mode 1: the K half
+ * is copied on the copy-in stream and the V half on the unpack stream in front of the unpack kernel).
+ * A layer can be loaded once per plan (CA_ERR_NOT_READY otherwise).                             */
 ca_status ca_kv_load_layer(ca_ctx *ctx, int32_t layer, const void *const *src_k,
                            const void *const *src_v, void *k_pool, void *v_pool);
 
@@ -263,9 +259,9 @@ ca_status ca_cached_prefill_attn_static(ca_ctx *ctx, int32_t layer, const void *
  * (contiguous layout, pointer to saved token 0) starting at token dst_tok_offset[c] (host int64
  * array; NULL means hist_len[c], i.e. append behind the saved history).  Keys leave without
  * positional encoding, exactly as stored.  Runs on the internal save stream after the work
- * queued so far on `after_stream`.  Destinations: device memory (written in place by the pack
- * kernel) or pinned host memory (pack kernel into a ring slot + hipMemcpyAsync, or written in place:
- * see save_mode).                                                                                  */
+ * queued so far on `after_stream`, a save of at most 128 KB to pinned or 16 MB to device memory on
+ * `after_stream` itself; ca_sync and ca_join cover it either way.  Destinations: device memory or
+ * pinned host memory, written in place by the pack kernel unless save_mode is 1.                   */
 ca_status ca_kv_save_layer(ca_ctx *ctx, int32_t layer, const int32_t *tok_begin,
                            const int32_t *tok_end, const void *k_pool, const void *v_pool,
                            void *const *dst_k, void *const *dst_v, const int64_t *dst_tok_offset,
@@ -274,20 +270,20 @@ ca_status ca_kv_save_layer(ca_ctx *ctx, int32_t layer, const int32_t *tok_begin,
 /* ca_kv_append_layer and ca_kv_save_layer (default range and offset: the new tokens go behind the
  * saved history of every conversation) in one call that reads new_k / new_v once: what is saved IS
  * what is appended, keys without positional encoding (Sections 3.2.2, 3.4), so the pool is not read
- * back.  Device destinations (and pinned ones under save_mode 2): one kernel on `stream` stores every
- * vector twice, to its page and to its row of the tier.  Pinned destinations otherwise: the append
- * kernel runs on `stream`; then either one copy per conversation follows on the internal save stream
- * straight from new_k / new_v (no pack kernel, no staging slot; new_k / new_v must then stay unchanged
- * until ca_sync or ca_join), or the pack kernel follows there and writes the tier in place (see
- * save_mode for which).  Same arguments, checks and statuses as the two calls it replaces.          */
+ * back.  Device destinations, and pinned ones of at most 128 KB or under save_mode 2: one kernel on
+ * `stream` stores every vector twice, to its page and to its row of the tier.  Pinned destinations
+ * otherwise: the append kernel runs on `stream`; then the pack kernel follows on the internal save
+ * stream and writes the tier in place, or with save_mode 1 one copy per conversation straight from
+ * new_k / new_v (no pack kernel, no staging slot; new_k / new_v must then stay unchanged until
+ * ca_sync or ca_join).  Same arguments, checks and statuses as the two calls it replaces.          */
 ca_status ca_kv_append_save_layer(ca_ctx *ctx, int32_t layer, const void *new_k, const void *new_v,
                                   void *k_pool, void *v_pool, void *const *dst_k, void *const *dst_v,
                                   void *stream);
 
-/* Blocks the host until the internal streams are idle. */
+/* Blocks the host until every load and save queued so far is done. */
 ca_status ca_sync(ca_ctx *ctx);
 
-/* Makes `stream` wait (device side) for everything queued so far on the internal streams. */
+/* Makes `stream` wait (device side) for every load and save queued so far. */
 ca_status ca_join(ca_ctx *ctx, void *stream);
 
 /* ---- timing of the library's own GPU work ------------------------------------------------ */
@@ -297,6 +293,8 @@ ca_status ca_join(ca_ctx *ctx, void *stream);
  * intervals of one kind recorded since the last read of that kind, and forgets them.
  * kind: 0 load copy-in (one interval per layer), 1 unpack kernel(s), 2 append kernel(s),
  *       3 attention kernel, 4 pack kernel(s), 5 save copy-out (one interval per layer).
+ * A load that one kernel brings across the host link counts as copy-in, with an empty unpack
+ * interval behind it; a short write-back by the append kernel also as copy-out.
  * on: 0 off; 1 every kind; any other value 2 * mask times only the kinds k with bit k of mask
  *     set (events cost a few per cent of a step of short kernels; a caller that needs one
  *     kernel's duration inside a timed region can restrict them to that kind).                 */

@@ -43,13 +43,14 @@ struct MoveShape {
     int32_t heads_per_wg;        // heads one workgroup moves (grid.x slices the heads, and K/V)
     int32_t n_in_launch;
     int32_t max_pages_touched;   // largest number of pages a range of this launch touches
-    int32_t max_grid_y;          // 0: one workgroup row per page; > 0: at most this many rows, each walking several pages
-                                 // (a kernel that stores over the host link is bound by the link and should hold few compute units)
 };
 
 // to_pool = true: contiguous -> pages (unpack / append); false: pages -> contiguous (pack).
 hipError_t launch_move(bool to_pool, const MoveArgs &args, const MoveShape &shape, uint8_t *k_pool,
                        uint8_t *v_pool, hipStream_t stream);
+// the same between the pool and pinned host memory, with at most `workgroups` workgroups
+hipError_t launch_link(bool to_pool, const MoveArgs &args, const MoveShape &shape, int workgroups, uint8_t *k_pool, uint8_t *v_pool,
+                       hipStream_t stream);
 // the new turn of conversations [0, shape.n_in_launch): rows cu_q[c].. of new_k / new_v -> context tokens n_keep[c]..
 hipError_t launch_append(const MoveShape &shape, const uint8_t *new_k, const uint8_t *new_v, uint8_t *k_pool, uint8_t *v_pool,
                          hipStream_t stream);

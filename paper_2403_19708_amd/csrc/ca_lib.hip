@@ -140,19 +140,14 @@ ca_status fail(ca_ctx *ctx, ca_status st, const char *fmt, ...) {
     } while (0)
 
 constexpr size_t kMetaAlign = 64;            // alignment of the arrays of the metadata image
-constexpr int kHostStoreWorkgroups = 128;   // workgroups of a pack kernel whose destination is pinned host memory
-
-// How a save reaches a pinned tier when the configuration leaves the choice to the library (save_mode 0).  Measured on
-// MI355X with 64 conversations per layer: the per-conversation copies out of a staging slot (a few hundred KB each)
-// move about 8 GB/s, run on a copy engine and disturb nothing; a pack kernel that stores over the host link moves about
-// 40 GB/s, but while it runs an attention kernel beside it takes about that much longer (the slow stores hold up the
-// queues its own stores go through).  The copies are the better choice as long as they hide under the layer's load
-// (about 50 GB/s): fewer than a fifth as many tokens to save as kept history to load.  Beyond that the save stream
-// would bound the step, and the kernel's bounded cost is the smaller one.
-bool host_save_in_place(const ca_ctx *ctx, int64_t tokens_to_save) {
-    if (ctx->cfg.save_mode != 0) return ctx->cfg.save_mode == 2;
-    return tokens_to_save * 5 > ctx->total_n;
-}
+// Workgroups of a kernel that moves between the pool and pinned host memory (32 KB in flight each), measured on MI355X with
+// 16 conversations of a grouped-query layer (169 MB to load, 18 MB to save), the attention of another layer beside it:
+//   loads   4: 46 GB/s   8: 57, attention 7 % slower   10: 57, 20 %    16: 56, 1.7 x   32: 57, 3.8 x
+//   saves   2: 34 GB/s   4: 44, attention undisturbed   8: 53, 1.2 x   16: 54
+// Past what the link holds the requests queue up in the memory system in front of everyone else's.  Whole turns (two layers
+// of 64 such conversations, us): 27648 with 6 load workgroups, 27006 with 8, 26780 with 10, 26706 with 12.
+constexpr int kLinkLoadWorkgroups = 10;
+constexpr int kLinkSaveWorkgroups = 4;
 
 enum ProfileKind { kProfCopyIn = 0, kProfUnpack = 1, kProfAppend = 2, kProfAttn = 3, kProfPack = 4, kProfCopyOut = 5, kProfKinds = 6 };
 
@@ -248,10 +243,10 @@ private:
 // A move between the tier and the pool has an internal stream so that it overlaps with the caller's kernels.  Getting
 // there and back costs about 20 us on the GPU and as much on the host (measured: a kernel, event, wait, kernel, event, wait
 // loop over two streams 27 us, the two kernels on one stream 7.5 us), so a move that is shorter than that runs on the
-// caller's stream: one to or from device memory of at most 16 MB (about 8 us), one across the host link of at most 256 KB
-// for a save (6 us; stores) and 512 KB for a load (12 us; reads).
+// caller's stream: one to or from device memory of at most 16 MB (about 8 us), one across the host link of at most 128 KB
+// for a save (4 us; stores) and 512 KB for a load (12 us; reads).
 constexpr int64_t kInlineDeviceBytes = (int64_t)16 << 20;
-constexpr int64_t kInlineHostSaveBytes = (int64_t)256 << 10;
+constexpr int64_t kInlineHostSaveBytes = (int64_t)128 << 10;
 constexpr int64_t kInlineHostLoadBytes = (int64_t)512 << 10;
 
 // the caller may have destroyed the stream it made the plan on
@@ -1175,9 +1170,9 @@ MoveShape move_shape(const ca_ctx *ctx, int max_tokens) {
     return shape;
 }
 
-// narrow_workgroups > 0: launch about that many workgroups at most (each then walks several pages)
+// link_workgroups > 0: the contiguous side is pinned host memory; a kernel of that many workgroups moves it
 ca_status run_move(ca_ctx *ctx, bool to_pool, const std::vector<Segment> &segs, void *k_pool, void *v_pool,
-                   hipStream_t stream, int narrow_workgroups = 0) {
+                   hipStream_t stream, int link_workgroups = 0) {
     for (size_t at = 0; at < segs.size(); at += kMaxSeqsPerLaunch) {
         MoveArgs args;
         const int n = (int)std::min<size_t>(kMaxSeqsPerLaunch, segs.size() - at);
@@ -1197,9 +1192,9 @@ ca_status run_move(ca_ctx *ctx, bool to_pool, const std::vector<Segment> &segs, 
         MoveShape shape = move_shape(ctx, max_tokens);
         shape.n_in_launch = n;
         shape.max_pages_touched = max_touched;
-        if (narrow_workgroups > 0) {
-            const int slices = (shape.n_kv_heads + shape.heads_per_wg - 1) / shape.heads_per_wg;
-            shape.max_grid_y = std::max(1, narrow_workgroups / (2 * slices * n));
+        if (link_workgroups > 0) {
+            CA_HIP(ctx, launch_link(to_pool, args, shape, link_workgroups, (uint8_t *)k_pool, (uint8_t *)v_pool, stream));
+            continue;
         }
         CA_HIP(ctx, launch_move(to_pool, args, shape, (uint8_t *)k_pool, (uint8_t *)v_pool, stream));
     }
@@ -1301,7 +1296,7 @@ ca_status ca_kv_load_layer(ca_ctx *ctx, int32_t layer, const void *const *src_k,
         return fail(ctx, CA_ERR_INVALID_ARG, "ca_kv_load_layer: a source is neither pinned host nor device memory");
     const int64_t move_bytes = 2 * ctx->total_n * rb;
     const bool small = move_bytes <= (any_host ? kInlineHostLoadBytes : kInlineDeviceBytes);
-    const bool staged = c.load_mode == 1 || (c.load_mode == 0 && any_host && !small);
+    const bool staged = c.load_mode == 1;
     const bool on_caller = small && !staged && stream_alive(ctx->plan_stream) && inline_free(ctx, ctx->plan_stream);
     hipStream_t mover = on_caller ? ctx->plan_stream : ctx->s_unpack;
     if (on_caller) CA_HIP(ctx, caller_after_plan(ctx, mover));
@@ -1363,10 +1358,16 @@ ca_status ca_kv_load_layer(ca_ctx *ctx, int32_t layer, const void *const *src_k,
                 at += len;
             }
         }
-        int iv_unpack;
-        CA_HIP(ctx, prof_begin(ctx, kProfUnpack, mover, &iv_unpack));
-        st = run_move(ctx, true, segs, k_pool, v_pool, mover);
+        // Across the host link one kernel reads the tier in place and scatters it into the pages.  It counts as the layer's
+        // copy-in; the unpacking, which is part of it, as an empty interval behind it.
+        const bool link = any_host && !on_caller;
+        int iv_in = -1, iv_unpack;
+        if (link) CA_HIP(ctx, prof_begin(ctx, kProfCopyIn, mover, &iv_in));
+        else CA_HIP(ctx, prof_begin(ctx, kProfUnpack, mover, &iv_unpack));
+        st = run_move(ctx, true, segs, k_pool, v_pool, mover, link ? kLinkLoadWorkgroups : 0);
         if (st != CA_OK) return st;
+        CA_HIP(ctx, prof_end(ctx, iv_in, mover));
+        if (link) CA_HIP(ctx, prof_begin(ctx, kProfUnpack, mover, &iv_unpack));
         CA_HIP(ctx, prof_end(ctx, iv_unpack, mover));
     }
     if (!on_caller || mover != nullptr) CA_HIP(ctx, hipEventRecord(ctx->ev_ready[layer], mover));
@@ -1442,7 +1443,7 @@ ca_status ca_kv_save_layer(ca_ctx *ctx, int32_t layer, const int32_t *tok_begin,
     if (total > c.max_batch_kv_tokens) return fail(ctx, CA_ERR_OUT_OF_RANGE, "ca_kv_save_layer: %lld tokens exceed a staging slot", (long long)total);
     hipStream_t after = (hipStream_t)after_stream;
     const bool on_caller = save_is_short(ctx, any_host, 2 * total * rb) && inline_free(ctx, after);
-    const bool staged = !on_caller && (any_host ? !host_save_in_place(ctx, total) : c.save_mode == 1);
+    const bool staged = c.save_mode == 1;
 
     // saving starts after the producer of this layer's K/V: the work queued on `after_stream`, and the load of
     // this layer if one was issued (its unpack runs on an internal stream and may still be writing the pages a
@@ -1496,9 +1497,7 @@ ca_status ca_kv_save_layer(ca_ctx *ctx, int32_t layer, const int32_t *tok_begin,
         }
         int iv_pack;
         CA_HIP(ctx, prof_begin(ctx, kProfPack, saver, &iv_pack));
-        // stores that cross the host link are bound by the link: a few workgroups saturate it, and a grid that filled the
-        // GPU with waiting wavefronts would take the compute units from the attention kernel running beside it
-        st = run_move(ctx, false, segs, (void *)k_pool, (void *)v_pool, saver, any_host ? kHostStoreWorkgroups : 0);
+        st = run_move(ctx, false, segs, (void *)k_pool, (void *)v_pool, saver, any_host && !on_caller ? kLinkSaveWorkgroups : 0);
         if (st != CA_OK) return st;
         CA_HIP(ctx, prof_end(ctx, iv_pack, saver));
     }
@@ -1542,7 +1541,6 @@ ca_status ca_kv_append_save_layer(ca_ctx *ctx, int32_t layer, const void *new_k,
             return fail(ctx, CA_ERR_INVALID_ARG, "ca_kv_append_save_layer: destination of conversation %d is smaller than hist_len + new_len tokens", i);
     }
     hipStream_t stream = (hipStream_t)stream_;
-    const bool in_place = !any_host || host_save_in_place(ctx, ctx->total_q);
     const bool one_kernel = any_host ? c.save_mode == 2 || (save_is_short(ctx, any_host, 2 * (int64_t)bytes) && inline_free(ctx, stream))
                                      : c.save_mode != 1;
     if (!one_kernel) {
@@ -1552,7 +1550,7 @@ ca_status ca_kv_append_save_layer(ca_ctx *ctx, int32_t layer, const void *new_k,
         if (st == CA_OK) st = save_follows(ctx, stream);
         if (st != CA_OK) return st;
         int iv;
-        if (any_host && in_place) {
+        if (c.save_mode == 0) {
             // the pack kernel writes the new tokens to the tier in place
             std::vector<Segment> segs;
             for (int i = 0; i < B; ++i)
@@ -1560,7 +1558,7 @@ ca_status ca_kv_append_save_layer(ca_ctx *ctx, int32_t layer, const void *new_k,
                     segs.push_back({(uint8_t *)dst_k[i], (uint8_t *)dst_v[i], ctx->hist_len[i], ctx->n_keep[i], ctx->new_len[i], i});
             if (ctx->loaded[layer]) CA_HIP(ctx, after_load(ctx, layer, ctx->s_save));
             CA_HIP(ctx, prof_begin(ctx, kProfPack, ctx->s_save, &iv));
-            st = run_move(ctx, false, segs, k_pool, v_pool, ctx->s_save, kHostStoreWorkgroups);
+            st = run_move(ctx, false, segs, k_pool, v_pool, ctx->s_save, kLinkSaveWorkgroups);
             if (st != CA_OK) return st;
         } else {
             // one copy per conversation, straight from new_k / new_v
@@ -1579,7 +1577,7 @@ ca_status ca_kv_append_save_layer(ca_ctx *ctx, int32_t layer, const void *new_k,
     // host link this way also counts as the write-back it replaces.
     int iv, iv_back = -1;
     CA_HIP(ctx, prof_begin(ctx, kProfAppend, stream, &iv));
-    if (any_host && c.save_mode != 2) CA_HIP(ctx, prof_begin(ctx, in_place ? kProfPack : kProfCopyOut, stream, &iv_back));
+    if (any_host && c.save_mode != 2) CA_HIP(ctx, prof_begin(ctx, kProfCopyOut, stream, &iv_back));
     for (int at = 0; at < B; at += kMaxSeqsPerLaunch) {
         MoveArgs2 second;
         const int n = std::min(kMaxSeqsPerLaunch, B - at);

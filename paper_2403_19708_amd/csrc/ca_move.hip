@@ -17,6 +17,12 @@ namespace {
 typedef __attribute__((ext_vector_type(4))) unsigned int vec16;  // one 16-byte piece
 
 constexpr int kMoveThreads = 256;
+
+// *p through the scalar cache: p is uniform and nothing writes *p while the kernel runs
+__device__ inline int32_t load_uniform(const int32_t *p) {
+    return *reinterpret_cast<const __attribute__((address_space(4))) int32_t *>(reinterpret_cast<uintptr_t>(p));
+}
+
 constexpr int kUnroll = kMoveUnroll;
 constexpr int kMoveMaxGridY = 32768;
 
@@ -55,7 +61,7 @@ __device__ inline void move_piece(const Piece &p, const MoveShape &s, uint8_t *_
         const int H = s.n_kv_heads;
         const int h_first = (blockIdx.x >> 1) * s.heads_per_wg;
         const int h_count = min(s.heads_per_wg, H - h_first);
-        const int page = s.block_table[(int64_t)p.seq * s.max_pages + page_col];
+        const int page = load_uniform(s.block_table + (int64_t)p.seq * s.max_pages + page_col);
         const int64_t row_vecs = (int64_t)H << vs;  // 16-byte vectors per token on the contiguous side
         const int64_t contig_first = p.contig_tok0 + (t_first - ctx_begin);
         vec16 *contig = reinterpret_cast<vec16 *>(p.contig) + contig_first * row_vecs + ((int64_t)h_first << vs);
@@ -107,11 +113,72 @@ __global__ __launch_bounds__(kMoveThreads) void move_kernel(MoveArgs a, MoveShap
     move_piece<kToPool, kNT, false>(p, s, values ? v_pool : k_pool);
 }
 
+// Moves between the pool and pinned host memory: bound by the host link, which a few workgroups keep full (a round trip
+// takes about 2 us and a workgroup has 32 KB in flight; 8 to 10 of them read at 57 GB/s, which is what one large copy by a
+// copy engine reaches).  A grid that filled the GPU with waiting wavefronts holds up the kernels running beside it; so do
+// loads issued ahead of the stores (with 8 workgroups the attention beside a load 1.25 x instead of 1.07 x, the load no
+// faster).  A workgroup's unit is a group of consecutive pages of one conversation, keys or values: whole token rows,
+// contiguous on the host side, about 32 KB (one page of 8 heads of 128 or more).  first[e] = groups of the entries before e.
+struct LinkUnits {
+    int32_t first[kMaxSeqsPerLaunch + 1];
+    int32_t pages;        // pages per group
+};
+
+template <bool kToPool, bool kOnePage>      // kOnePage: units.pages == 1, the page is uniform over the workgroup
+__global__ __launch_bounds__(kMoveThreads) void link_kernel(MoveArgs a, LinkUnits units, MoveShape s, uint8_t *__restrict__ k_pool,
+                                                            uint8_t *__restrict__ v_pool) {
+    constexpr int kLinkUnroll = 8;
+    const int vs = s.vec_shift;
+    const int H = s.n_kv_heads;
+    const int row_vecs = H << vs;
+    const bool values = blockIdx.x & 1;
+    vec16 *const side = reinterpret_cast<vec16 *>(values ? v_pool : k_pool);
+    const int n_units = units.first[s.n_in_launch];
+    int e = 0;
+    for (int unit = blockIdx.x >> 1; unit < n_units; unit += gridDim.x >> 1) {
+        while (unit >= units.first[e + 1]) ++e;
+        const int begin = a.ctx_tok0[e], end = begin + a.count[e];
+        const int page_col = begin / kPageSize + (unit - units.first[e]) * units.pages;
+        const int t_first = max(begin, page_col * kPageSize), t_last = min(end, (page_col + units.pages) * kPageSize);
+        const int total = (t_last - t_first) * row_vecs;
+        const int32_t *table = s.block_table + (int64_t)a.seq[e] * s.max_pages + page_col;
+        vec16 *contig = reinterpret_cast<vec16 *>(values ? a.contig_v[e] : a.contig_k[e]) + (a.contig_tok0[e] + (t_first - begin)) * row_vecs;
+        // page ids of the unit: one (by a scalar load, which no store is waited for with), or page i in lane i of every wavefront
+        const int pages = kOnePage ? load_uniform(table) : table[min((int)threadIdx.x & 63, (t_last - 1) / kPageSize - page_col)];
+        for (int v0 = threadIdx.x; v0 - (int)threadIdx.x < total; v0 += kMoveThreads * kLinkUnroll) {
+            // where vector v of the unit lies in the pool
+            const auto in_pool = [&](int v) __attribute__((always_inline)) {
+                const int row = v / row_vecs;
+                const int rem = v - row * row_vecs;       // (head, piece)
+                const int slot = t_first + row - page_col * kPageSize;
+                const int page = kOnePage ? pages : __shfl(pages, slot / kPageSize);
+                return side + (((((int64_t)page * H + (rem >> vs)) * kPageSize + slot % kPageSize) << vs) + (rem & ((1 << vs) - 1)));
+            };
+            // loads without conditions, back to back (past the end: the last vector again, not stored)
+            vec16 r[kLinkUnroll];
+#pragma unroll
+            for (int u = 0; u < kLinkUnroll; ++u) {
+                const int v = min(v0 + u * kMoveThreads, total - 1);
+                r[u] = __builtin_nontemporal_load(kToPool ? contig + v : in_pool(v));
+            }
+            // All of them before the first store: the compiler then sees no load outstanding at the head of the loop and puts
+            // no wait there, which would be one for the stores as well (45 GB/s with 8 workgroups instead of 57).
+            __builtin_amdgcn_s_waitcnt(0x0F70);
+#pragma unroll
+            for (int u = 0; u < kLinkUnroll; ++u) {
+                const int v = min(v0 + u * kMoveThreads, total - 1);
+                vec16 *dst = kToPool ? in_pool(v) : contig + v;
+                if (v0 + u * kMoveThreads < total) __builtin_nontemporal_store(r[u], dst);
+            }
+        }
+    }
+}
+
 // The new turn of conversation `seq`: everything but the pointers is in the plan's metadata, so the arguments are a few
 // words whatever the batch (a launch with 2.6 KB of per-conversation arguments costs the host 0.4 to 1.3 us more).
 __device__ inline Piece new_turn(const MoveShape &s, int seq, const uint8_t *from, uint8_t *second) {
-    const int q = s.cu_q[seq];
-    return Piece{const_cast<uint8_t *>(from), q, s.n_keep[seq], s.cu_q[seq + 1] - q, seq, second};
+    const int q = load_uniform(s.cu_q + seq);
+    return Piece{const_cast<uint8_t *>(from), q, load_uniform(s.n_keep + seq), load_uniform(s.cu_q + seq + 1) - q, seq, second};
 }
 
 __global__ __launch_bounds__(kMoveThreads) void append_kernel(MoveShape s, const uint8_t *__restrict__ new_k, const uint8_t *__restrict__ new_v,
@@ -163,14 +230,31 @@ hipError_t launch_move(bool to_pool, const MoveArgs &args, const MoveShape &shap
                        uint8_t *v_pool, hipStream_t stream) {
     if (shape.n_in_launch <= 0 || shape.max_pages_touched <= 0) return hipSuccess;
     const int slices = (shape.n_kv_heads + shape.heads_per_wg - 1) / shape.heads_per_wg;
-    int rows = std::min(shape.max_pages_touched, kMoveMaxGridY);
-    if (shape.max_grid_y > 0) rows = std::min(rows, shape.max_grid_y);
+    const int rows = std::min(shape.max_pages_touched, kMoveMaxGridY);
     dim3 grid(2 * slices, rows, shape.n_in_launch);
     // nontemporal accesses: every byte is touched once (measured ~5 % faster than cached ones)
     if (to_pool)
         hipLaunchKernelGGL((move_kernel<true, true>), grid, dim3(kMoveThreads), 0, stream, args, shape, k_pool, v_pool);
     else
         hipLaunchKernelGGL((move_kernel<false, true>), grid, dim3(kMoveThreads), 0, stream, args, shape, k_pool, v_pool);
+    return hipGetLastError();
+}
+
+hipError_t launch_link(bool to_pool, const MoveArgs &args, const MoveShape &shape, int workgroups, uint8_t *k_pool, uint8_t *v_pool,
+                       hipStream_t stream) {
+    LinkUnits units;
+    units.pages = std::max(1, std::min(64, 2048 / ((kPageSize * shape.n_kv_heads) << shape.vec_shift)));     // 2048 vectors = 32 KB
+    units.first[0] = 0;
+    for (int i = 0; i < shape.n_in_launch; ++i) {
+        const int pages = args.count[i] > 0 ? (args.ctx_tok0[i] + args.count[i] - 1) / kPageSize - args.ctx_tok0[i] / kPageSize + 1 : 0;
+        units.first[i + 1] = units.first[i] + (pages + units.pages - 1) / units.pages;
+    }
+    const int n = units.first[shape.n_in_launch];
+    if (n <= 0) return hipSuccess;
+    const dim3 grid(2 * std::min(n, std::max(1, workgroups / 2)));
+    const auto kernel = to_pool ? (units.pages == 1 ? link_kernel<true, true> : link_kernel<true, false>)
+                                : (units.pages == 1 ? link_kernel<false, true> : link_kernel<false, false>);
+    hipLaunchKernelGGL(kernel, grid, dim3(kMoveThreads), 0, stream, args, units, shape, k_pool, v_pool);
     return hipGetLastError();
 }
 

@@ -25,8 +25,8 @@ def check(run):
             assert err.max() <= 2e-2 and err.mean() <= 2e-3, (l, c)
 
 
-# kept tokens x 1 KiB (two KV heads of 128, keys and values): 512 and 513 KiB to load; new tokens: 256 and 257 KiB to save
-SIZES = {"shortest": ([1], [1]), "at-the-line": ([500, 12], [250, 6]), "past-it": ([500, 13], [250, 7])}
+# kept tokens x 1 KiB (two KV heads of 128, keys and values): 512 and 513 KiB to load; new tokens: 128 and 129 KiB to save
+SIZES = {"shortest": ([1], [1]), "at-the-line": ([500, 12], [122, 6]), "past-it": ([500, 13], [122, 7])}
 
 
 @pytest.mark.parametrize("tier", ["pinned", "device"])
@@ -97,3 +97,27 @@ def test_two_contexts_in_turn_share_the_internal_streams():
     finally:
         for run in runs:
             run.close()
+
+
+@pytest.mark.parametrize("hist", [[3000, 17, 0, 2900], [6000]], ids=["ragged", "one"])
+@pytest.mark.parametrize("heads", [(2, 1, 64), (8, 4, 64), (10, 5, 128), (16, 16, 128)], ids=lambda h: "hkv%d-d%d" % h[1:])
+def test_moves_across_the_link(heads, hist):
+    """past the short ones: a few workgroups walk groups of pages (16 pages of one head of 64 down to one page), ranges that
+    start and end inside a page"""
+    Hq, Hkv, D = heads
+    case = Case(hist, [130 + 17 * i for i in range(len(hist))], [min(h, 5) for h in hist], Hq, Hkv, D, seed=85, window=8192)
+    run = GpuRun(case, tier="pinned")
+    try:
+        run.rebase()
+        run.load(0)
+        run.append(0)
+        run.save(0)
+        run.finish()
+        for which, pool, host in (("k", run.k_pool[0], run.host_k[0]), ("v", run.v_pool[0], run.host_v[0])):
+            assert np.array_equal(torch_to_bits(pool), case.oracle_pool(0, which)), which
+            for c in range(case.B):
+                got = torch_to_bits(host[c])
+                assert np.array_equal(got[:case.hist_len[c]], case.tensor(0, f"{which}_hist", c)), (which, c)
+                assert np.array_equal(got[case.hist_len[c]:], case.tensor(0, f"{which}_new", c)), (which, c)
+    finally:
+        run.close()
