@@ -40,6 +40,7 @@
 //   * Keys past the end of the context are not zero-filled (a load cannot write zeros): the source
 //     row is clamped to the last valid key, the causal mask gives those columns probability 0 and
 //     the clamped V rows are finite data, so they contribute exactly nothing.
+#include "ca_device.h"
 #include "ca_internal.h"
 
 #include <type_traits>
@@ -48,87 +49,7 @@ namespace ca {
 
 namespace {
 
-typedef __attribute__((ext_vector_type(8))) __bf16 bf16x8;
-typedef __attribute__((ext_vector_type(2))) __bf16 bf16x2;
-typedef __attribute__((ext_vector_type(16))) float f32x16;
-typedef __attribute__((ext_vector_type(4))) short s16x4;
-typedef __attribute__((ext_vector_type(8))) short s16x8;
-
 constexpr int kMaxPagesLds = 2048;   // page ids kept in LDS at a time: a window of 32768 tokens that moves with the walk
-
-__device__ inline float bf_lo(uint32_t u) { return __uint_as_float(u << 16); }
-__device__ inline float bf_hi(uint32_t u) { return __uint_as_float(u & 0xffff0000u); }
-__device__ inline uint32_t pack_bf16(float a, float b) {
-    bf16x2 v = {(__bf16)a, (__bf16)b};
-    return __builtin_bit_cast(uint32_t, v);
-}
-
-// 16 bytes per lane, global -> LDS at lds_base + lane*16, no register in between.  Written as inline
-// assembly on purpose: the compiler then knows nothing of the outstanding load and does not guard
-// every later LDS read with s_waitcnt vmcnt(0) (it cannot tell which LDS bytes the load will write);
-// the waits are placed by hand with CA_WAIT_VMCNT, which the in-order completion of these loads
-// makes exact.  lds_base must be wave-uniform.
-__device__ inline void dma16(const void *src, uint32_t lds_base) {
-    asm volatile("s_mov_b32 m0, %0\n\tglobal_load_lds_dwordx4 %1, off" : : "s"(lds_base), "v"(src) : "memory", "m0");
-}
-
-// same, with the address split into a wave-uniform 64-bit base (scalar registers) and a 32-bit
-// per-lane byte offset: no vector arithmetic per load
-__device__ inline void dma16_sbase(const void *base_uniform, uint32_t lane_off, uint32_t lds_base) {
-    asm volatile("s_mov_b32 m0, %0\n\tglobal_load_lds_dwordx4 %1, %2"
-                 : : "s"(lds_base), "v"(lane_off), "s"(base_uniform) : "memory", "m0");
-}
-
-__device__ inline uint32_t lds_offset(const void *p) {
-    return (uint32_t)(uintptr_t)(const __attribute__((address_space(3))) void *)p;
-}
-
-// s_waitcnt with only the vector-memory counter constrained (gfx9 encoding: vmcnt in bits 3:0 and
-// 15:14, expcnt 6:4 and lgkmcnt 11:8 left at "don't wait")
-#define CA_WAIT_VMCNT(n) __builtin_amdgcn_s_waitcnt(0x0F70 | ((n) & 15) | (((n) >> 4) << 14))
-
-template <int D, int STYLE>
-__device__ inline void load_cs(const float2 *__restrict__ rope, int pos, int piece, float2 (&cs)[8]) {
-    constexpr int HALF = D / 2;
-    const float2 *row = rope + (int64_t)pos * HALF;
-    if (STYLE == 0) {
-        const float4 *p = reinterpret_cast<const float4 *>(row + 8 * piece);
-#pragma unroll
-        for (int w = 0; w < 4; ++w) {
-            const float4 v = p[w];
-            cs[2 * w] = make_float2(v.x, v.y);
-            cs[2 * w + 1] = make_float2(v.z, v.w);
-        }
-    } else {
-        const float4 *p = reinterpret_cast<const float4 *>(row + 4 * piece);
-        const float4 *q = reinterpret_cast<const float4 *>(row + HALF / 2 + 4 * piece);
-#pragma unroll
-        for (int w = 0; w < 2; ++w) {
-            const float4 v = p[w], u = q[w];
-            cs[2 * w] = make_float2(v.x, v.y);
-            cs[2 * w + 1] = make_float2(v.z, v.w);
-            cs[4 + 2 * w] = make_float2(u.x, u.y);
-            cs[4 + 2 * w + 1] = make_float2(u.z, u.w);
-        }
-    }
-}
-
-// one dword (2 elements) of each of the two 16-byte pieces a (dims d0..) and b (dims d0 + D/2..)
-// (f = a factor applied to the rotated values before they are rounded)
-template <int STYLE>
-__device__ inline void rotate_dword(uint32_t &pa, uint32_t &pb, const float2 (&cs)[8], int w, float f = 1.0f) {
-    const float a0 = bf_lo(pa), a1 = bf_hi(pa);
-    const float b0 = bf_lo(pb), b1 = bf_hi(pb);
-    if (STYLE == 0) {
-        const float2 c0 = cs[2 * w], c1 = cs[2 * w + 1];
-        pa = pack_bf16((a0 * c0.x - b0 * c0.y) * f, (a1 * c1.x - b1 * c1.y) * f);
-        pb = pack_bf16((b0 * c0.x + a0 * c0.y) * f, (b1 * c1.x + a1 * c1.y) * f);
-    } else {
-        const float2 ca_ = cs[w], cb_ = cs[4 + w];
-        pa = pack_bf16((a0 * ca_.x - a1 * ca_.y) * f, (a1 * ca_.x + a0 * ca_.y) * f);
-        pb = pack_bf16((b0 * cb_.x - b1 * cb_.y) * f, (b1 * cb_.x + b0 * cb_.y) * f);
-    }
-}
 
 // NW wavefronts (32 stacked query rows each) per workgroup, key tiles of BN.  Two shapes are built:
 // NW = 8, BN = 64 (one workgroup per compute unit, 256-row tiles) and NW = 4, BN = 32 (two independent

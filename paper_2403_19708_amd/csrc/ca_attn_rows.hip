@@ -1,0 +1,324 @@
+// Causal attention for plans in which every (conversation, kv head) has few stacked query rows (3 to 32: decode steps of
+// grouped-query models, very short turns; Sections 2.1, 3.2.2, 3.4).  Each key and value byte is used for a few rows only,
+// so the kernel is bound by HBM: it streams the context once, at the rate of a large copy, and keeps the matrix cores fed
+// on the side.
+//
+//   * Nothing is shared between the wavefronts of a workgroup while they walk: wavefront w takes pages w, w + NWV, ... of
+//     the item for ALL its rows, through an LDS ring of its own (a page of K and V per stage, 8 KiB at D = 128), filled by
+//     global_load_lds and released by its own s_waitcnt.  No barrier until the end of an item; eight wavefronts of a
+//     compute unit keep about 100 KiB in flight, which is what HBM's latency asks for at 6 TB/s.  (The tile kernel of
+//     ca_attn_dma.hip walks 32-key tiles in lock step and pads 8 rows to 32: 139 us for 64 conversations of 1024 to 4096
+//     tokens, 8 kv heads, 671 MB, where this kernel takes about 110.)
+//   * S^T = K Q^T with v_mfma_f32_16x16x32_bf16 (16 keys x 16 rows), O^T += V^T P^T with v_mfma_f32_16x16x16_bf16: the C
+//     registers of the first, rounded to bf16, are the B operand of the second.  Softmax as in the tile kernel: scale and
+//     log2(e) folded into the rotated query, the reference maximum enters as the accumulator and is raised lazily.
+//   * Keys are rotated in registers between the LDS read and the matrix instruction: a lane's operand pieces of one key
+//     hold both members of every rotary pair.  (cos, sin) advance by a constant rotation from page to page.
+//   * With enough to stream the pages of all (conversation, kv head) units, laid end to end, are cut into equal runs, one per
+//     workgroup of four wavefronts, two workgroups per compute unit: all have the same number of bytes whatever the lengths.
+//     With less (one conversation: 11 MB) the time is the chain of dependent memory accesses, and workgroups of eight
+//     wavefronts take one share of at least 16 pages each, whose description brings everything the first loads need.
+//   * A share that is not a whole unit leaves unnormalised sums, maximum and denominator, and the workgroup that finishes a
+//     unit's last share merges them: no second launch (a combine kernel behind a decode step's attention cost 4 us plus the
+//     gap in front of it).  Shares are written through to memory; with release fences instead, each of which writes back a
+//     die's L2, the kernel took 335 us instead of 121.
+#include "ca_internal.h"
+#include "ca_device.h"
+
+namespace ca {
+
+namespace {
+
+// D, rotary style, NB = 16-row blocks (rows <= 16 NB), NWV = wavefronts of a workgroup
+template <int D, int STYLE, int NB, int NWV>
+__global__ __launch_bounds__(64 * NWV, 2) void attn_rows_kernel(AttnArgs a) {
+    constexpr int HALF = D / 2;
+    constexpr int PPR = D / 8;                // 16-byte pieces per row
+    constexpr int KPC = 64 / PPR;             // keys per 1 KiB chunk
+    constexpr int CPP = kPageSize / KPC;      // chunks of a page per array
+    constexpr int CH = 1024 + KPC * 16;       // chunk stride in LDS
+    constexpr int PAGE = CPP * CH;            // bytes of one page of K (or V) in LDS
+    constexpr int STAGE = 2 * PAGE;
+    constexpr int NS = D == 128 ? 2 : 4;      // stages: 16 KiB in flight per wavefront at most
+    constexpr int LOADS = 2 * CPP;            // load instructions per page
+    constexpr int KK = D / 32;                // k-steps of the score product
+    constexpr int DB = D / 16;                // 16-dim blocks of O^T
+    constexpr int ROWS = 16 * NB;
+    constexpr int OSTR = D + 4;               // row stride of the merge buffer (floats): conflict-free 16-byte accesses
+    constexpr int RING = NWV * NS * STAGE, MERGE = NWV * ROWS * OSTR * 4;
+    constexpr int SMEM = RING > MERGE ? RING : MERGE;
+    static_assert(SMEM + NWV * ROWS * 8 + 256 <= (NWV == 4 ? 80 : 160) * 1024, "LDS budget");
+
+    __shared__ __attribute__((aligned(16))) uint8_t smem[SMEM];
+    __shared__ float red_m[NWV][ROWS], red_l[NWV][ROWS];
+    __shared__ int32_t is_last;
+
+    const int tid = threadIdx.x;
+    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int lane = tid & 63;
+    const int q4 = lane >> 4, m16 = lane & 15;
+    const int G = a.n_q_heads / a.n_kv_heads;
+    const int Hkv = a.n_kv_heads;
+    const float cscale = a.softmax_scale * 1.4426950408889634f;
+    const uint32_t ring = __builtin_amdgcn_readfirstlane(lds_offset(smem)) + (uint32_t)(wave * NS * STAGE);
+    const uint8_t *const ring_p = smem + wave * NS * STAGE;
+
+    // LDS offsets inside a stage.  K operand: key m16, piece q4 + 4 kk.  V^T operand (transposing read): lane s of a
+    // 16-lane group points at key 4 q4 + s / 4, dims 16 db + 4 (s % 4) .. and receives dim 16 db + s of keys 4 q4 .. + 3.
+    const int k_rd = (m16 / KPC) * CH + (q4 * KPC + m16 % KPC) * 16;
+    const int v_key = 4 * q4 + (m16 >> 2);
+    const int v_rd = PAGE + (v_key / KPC) * CH + (((m16 & 3) >> 1) * KPC + v_key % KPC) * 16 + (m16 & 1) * 8;
+    // loads: lane -> key lane % KPC of the chunk, piece lane / KPC
+    const int ld_key = lane % KPC, ld_piece = lane / KPC;
+
+    // constant rotation from a wavefront's page to its next one
+    float2 step[KK / 2][8];
+#pragma unroll
+    for (int p = 0; p < KK / 2; ++p) load_cs<D, STYLE>(a.rope, NWV * kPageSize, q4 + 4 * p, step[p]);
+
+    // eight wavefronts: the item is the workgroup's only one and its first pages (one or two per wavefront) are in it
+    constexpr bool ONE = NWV == 8;
+    const int it_end = ONE ? (int)blockIdx.x + 1 : load_uniform(a.wg_first + blockIdx.x + 1);
+    for (int it = ONE ? (int)blockIdx.x : load_uniform(a.wg_first + blockIdx.x); it < it_end; ++it) {
+        const int32_t *iw = reinterpret_cast<const int32_t *>(a.rows_items + it);
+        const int32_t near_page[2] = {load_uniform(iw + 16 + wave), load_uniform(iw + 16 + (wave + NWV) % 16)};
+        const int c = load_uniform(iw), g = load_uniform(iw + 1), n_rows = load_uniform(iw + 2);
+        const int key_begin = load_uniform(iw + 3), key_end = load_uniform(iw + 4), part = load_uniform(iw + 5);
+        const int n = load_uniform(iw + 6), q0 = load_uniform(iw + 7);
+        const int32_t *table = a.block_table + (int64_t)c * a.max_pages;
+        const int kmax = min(n + (n_rows - 1) / G + 1, key_end);       // exclusive end of the keys this item reads
+        const int last_page = (kmax - 1) / kPageSize;
+        int pg = key_begin / kPageSize + wave;
+
+        auto issue = [&](int stage, int page_idx, int page) __attribute__((always_inline)) {
+            const int64_t block = ((int64_t)page * Hkv + g) * kPageSize * D;
+            const uint16_t *kb = a.k_pool + block, *vb = a.v_pool + block;
+            const uint32_t at = ring + (uint32_t)(stage * STAGE);
+            const int last_slot = kmax - 1 - page_idx * kPageSize;      // keys past the end: the last one again (finite data)
+#pragma unroll
+            for (int ch = 0; ch < CPP; ++ch) {
+                const uint32_t off = (uint32_t)(min(ch * KPC + ld_key, last_slot) * D + ld_piece * 8) * 2u;
+                dma16_sbase_nt(kb, off, at + ch * CH);
+                dma16_sbase_nt(vb, off, at + PAGE + ch * CH);
+            }
+        };
+
+        // ---- the first pages go out, then the query rows are fetched and rotated behind them -----------------------
+#pragma unroll
+        for (int s = 0; s < NS; ++s)
+            if (pg + s * NWV <= last_page) issue(s, pg + s * NWV, s < 2 ? near_page[s] : load_uniform(table + pg + s * NWV));
+
+        bf16x8 Qf[NB][KK];
+        int qpos[NB];
+#pragma unroll
+        for (int nb = 0; nb < NB; ++nb) {
+            const int r = min(nb * 16 + m16, n_rows - 1);
+            const int j = r / G;
+            qpos[nb] = n + j;
+            const uint16_t *qrow = a.q + ((int64_t)(q0 + j) * a.n_q_heads + g * G + (r - j * G)) * D;
+#pragma unroll
+            for (int p = 0; p < KK / 2; ++p) {
+                const int piece = q4 + 4 * p;
+                uint4 x = *reinterpret_cast<const uint4 *>(qrow + 8 * piece);
+                uint4 y = *reinterpret_cast<const uint4 *>(qrow + HALF + 8 * piece);
+                float2 cs[8];
+                load_cs<D, STYLE>(a.rope, qpos[nb], piece, cs);
+                uint32_t *px = reinterpret_cast<uint32_t *>(&x), *py = reinterpret_cast<uint32_t *>(&y);
+#pragma unroll
+                for (int w = 0; w < 4; ++w) rotate_dword<STYLE>(px[w], py[w], cs, w, cscale);
+                Qf[nb][p] = __builtin_bit_cast(bf16x8, x);
+                Qf[nb][p + KK / 2] = __builtin_bit_cast(bf16x8, y);
+            }
+        }
+        float2 cs[KK / 2][8];
+#pragma unroll
+        for (int p = 0; p < KK / 2; ++p) load_cs<D, STYLE>(a.rope, min(pg * kPageSize + m16, kmax - 1), q4 + 4 * p, cs[p]);
+
+        f32x4 O[NB][DB];
+        float m_run[NB], l_run[NB];           // reference maximum of this lane's row (exponent units), its part of the denominator
+#pragma unroll
+        for (int nb = 0; nb < NB; ++nb) {
+            m_run[nb] = -INFINITY;
+            l_run[nb] = 0.f;
+#pragma unroll
+            for (int db = 0; db < DB; ++db) O[nb][db] = f32x4{0.f, 0.f, 0.f, 0.f};
+        }
+        const bf16x2 ones2 = {(__bf16)1.0f, (__bf16)1.0f};
+
+        // Everything the compiler loaded has arrived: it would otherwise wait for it at the first use inside the loop, every
+        // time round, and with it for the pages just asked for.
+        CA_WAIT_VMCNT(0);
+
+        // ---- the walk ---------------------------------------------------------------------------------------------
+        for (int stage = 0; pg <= last_page; pg += NWV, stage = (stage + 1) % NS) {
+            // the pages behind this one may stay in flight
+            if (pg + (NS - 1) * NWV <= last_page) { CA_WAIT_VMCNT((NS - 1) * LOADS); } else { CA_WAIT_VMCNT(0); }
+            const uint8_t *st = ring_p + stage * STAGE;
+            uint4 k[KK];
+            s16x4 v[DB];
+#pragma unroll
+            for (int kk = 0; kk < KK; ++kk) k[kk] = *reinterpret_cast<const uint4 *>(st + k_rd + kk * (4 * KPC * 16));
+#pragma unroll
+            for (int db = 0; db < DB; ++db)
+                v[db] = __builtin_amdgcn_ds_read_tr16_b64_v4i16((s16x4 __attribute__((address_space(3))) *)(st + v_rd + db * (2 * KPC * 16)));
+            asm volatile("s_waitcnt lgkmcnt(0)" : : : "memory");       // read out: the stage is free
+            if (pg + NS * NWV <= last_page) issue(stage, pg + NS * NWV, load_uniform(table + pg + NS * NWV));
+
+#pragma unroll
+            for (int p = 0; p < KK / 2; ++p) {
+                uint32_t *px = reinterpret_cast<uint32_t *>(&k[p]), *py = reinterpret_cast<uint32_t *>(&k[p + KK / 2]);
+#pragma unroll
+                for (int w = 0; w < 4; ++w) rotate_dword<STYLE>(px[w], py[w], cs[p], w);
+#pragma unroll
+                for (int e = 0; e < 8; ++e) {
+                    const float2 o = cs[p][e], s = step[p][e];
+                    cs[p][e] = make_float2(o.x * s.x - o.y * s.y, o.y * s.x + o.x * s.y);
+                }
+            }
+#pragma unroll
+            for (int nb = 0; nb < NB; ++nb) {
+                const float nm = m_run[nb] == -INFINITY ? 0.f : -m_run[nb];
+                f32x4 S = {nm, nm, nm, nm};
+#pragma unroll
+                for (int kk = 0; kk < KK; ++kk)
+                    S = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8, k[kk]), Qf[nb][kk], S, 0, 0, 0);
+                const int key0 = pg * kPageSize + 4 * q4;
+                if (pg * kPageSize + kPageSize - 1 > n) {               // some key of the page may be hidden from some row
+#pragma unroll
+                    for (int i = 0; i < 4; ++i)
+                        if (key0 + i > qpos[nb]) S[i] = -INFINITY;
+                }
+                const float mx = fmaxf(fmaxf(S[0], S[1]), fmaxf(S[2], S[3]));
+                const bool unseen = m_run[nb] == -INFINITY;
+                if (__builtin_amdgcn_ballot_w64(mx > (unseen ? -INFINITY : 8.0f)) != 0) {
+                    float all = fmaxf(mx, __shfl_xor(mx, 16));
+                    all = fmaxf(all, __shfl_xor(all, 32));               // over the four lanes of the row
+                    const bool raise = all > (unseen ? -INFINITY : 8.0f);
+                    const float delta = raise ? all : 0.f;
+                    const float alpha = raise && !unseen ? __builtin_amdgcn_exp2f(-delta) : 1.0f;
+                    if (raise) m_run[nb] = (unseen ? 0.f : m_run[nb]) + all;
+                    l_run[nb] *= alpha;
+#pragma unroll
+                    for (int i = 0; i < 4; ++i) S[i] -= delta;
+#pragma unroll
+                    for (int db = 0; db < DB; ++db)
+#pragma unroll
+                        for (int i = 0; i < 4; ++i) O[nb][db][i] *= alpha;
+                }
+                uint32_t pk[2];
+#pragma unroll
+                for (int w = 0; w < 2; ++w) {
+                    pk[w] = pack_bf16(__builtin_amdgcn_exp2f(S[2 * w]), __builtin_amdgcn_exp2f(S[2 * w + 1]));
+                    // the denominator sums the rounded probabilities, the very values the second product uses
+                    l_run[nb] = __builtin_amdgcn_fdot2_f32_bf16(__builtin_bit_cast(bf16x2, pk[w]), ones2, l_run[nb], false);
+                }
+                const s16x4 pb = __builtin_bit_cast(s16x4, make_uint2(pk[0], pk[1]));
+#pragma unroll
+                for (int db = 0; db < DB; ++db) O[nb][db] = __builtin_amdgcn_mfma_f32_16x16x16bf16_1k(v[db], pb, O[nb][db], 0, 0, 0);
+            }
+        }
+
+        // ---- merge the wavefronts -----------------------------------------------------------------------------------
+        __syncthreads();                       // the rings are free
+        float *mo = reinterpret_cast<float *>(smem) + wave * ROWS * OSTR;
+#pragma unroll
+        for (int nb = 0; nb < NB; ++nb) {
+            float l = l_run[nb] + __shfl_xor(l_run[nb], 16);
+            l += __shfl_xor(l, 32);
+            const int row = nb * 16 + m16;
+            if (row < n_rows) {
+#pragma unroll
+                for (int db = 0; db < DB; ++db) *reinterpret_cast<f32x4 *>(mo + row * OSTR + db * 16 + 4 * q4) = O[nb][db];
+                if (q4 == 0) {
+                    red_m[wave][row] = m_run[nb];
+                    red_l[wave][row] = l;
+                }
+            }
+        }
+        __syncthreads();
+        constexpr int VPR = D / 4;
+        float *const part_base = a.partial + (int64_t)max(part, 0) * ROWS * (D + 2);
+        for (int i = tid; i < n_rows * VPR; i += 64 * NWV) {
+            const int row = i / VPR, d = 4 * (i % VPR);
+            float M = red_m[0][row];
+#pragma unroll
+            for (int w = 1; w < NWV; ++w) M = fmaxf(M, red_m[w][row]);
+            f32x4 acc = {0.f, 0.f, 0.f, 0.f};
+            float l = 0.f;
+#pragma unroll
+            for (int w = 0; w < NWV; ++w) {
+                const float f = red_m[w][row] == -INFINITY ? 0.f : __builtin_amdgcn_exp2f(red_m[w][row] - M);
+                acc += f * *reinterpret_cast<const f32x4 *>(reinterpret_cast<const float *>(smem) + (w * ROWS + row) * OSTR + d);
+                l += f * red_l[w][row];
+            }
+            if (part < 0) {
+                store_out_row4<D>(a, q0, g, G, row, d, acc, 1.f / l);
+            } else {
+                store_agent4(part_base + row * D + d, acc);
+                if (d == 0) {
+                    store_agent(part_base + ROWS * D + row, M);
+                    store_agent(part_base + ROWS * (D + 1) + row, l);
+                }
+            }
+        }
+        if (part >= 0) {
+            // the workgroup that brings a unit's last share merges them all
+            const int ci = load_uniform(iw + 8), first = load_uniform(iw + 9), n_parts = load_uniform(iw + 10);
+            if (arrive_last(a.arrived + ci, n_parts, &is_last)) {
+                const float *base = a.partial + (int64_t)first * ROWS * (D + 2);
+                constexpr int64_t STRIDE = (int64_t)ROWS * (D + 2);
+                for (int i = tid; i < n_rows * VPR; i += 64 * NWV) {
+                    const int row = i / VPR, d = 4 * (i % VPR);
+                    float M = -INFINITY, l = 0.f;
+                    f32x4 acc = {0.f, 0.f, 0.f, 0.f};
+                    constexpr int U = 8;                                // shares in flight
+                    for (int s0 = 0; s0 < n_parts; s0 += U) {
+                        float ms[U], ls[U];
+                        f32x4 os[U];
+#pragma unroll
+                        for (int u = 0; u < U; ++u) {
+                            const float *p = base + min(s0 + u, n_parts - 1) * STRIDE;
+                            ms[u] = load_agent(p + ROWS * D + row);
+                            ls[u] = load_agent(p + ROWS * (D + 1) + row);
+                            os[u] = load_agent4(p + row * D + d);
+                        }
+#pragma unroll
+                        for (int u = 0; u < U; ++u) {
+                            if (s0 + u >= n_parts || ms[u] == -INFINITY) continue;
+                            const float M2 = fmaxf(M, ms[u]);
+                            const float fa = M == -INFINITY ? 0.f : __builtin_amdgcn_exp2f(M - M2), fb = __builtin_amdgcn_exp2f(ms[u] - M2);
+                            acc = acc * fa + os[u] * fb;
+                            l = l * fa + ls[u] * fb;
+                            M = M2;
+                        }
+                    }
+                    store_out_row4<D>(a, q0, g, G, row, d, acc, 1.f / l);
+                }
+            }
+        }
+        __syncthreads();                       // the next item's loads overwrite the merge buffer
+    }
+}
+
+template <int NB, int NWV>
+hipError_t launch_blocks(const AttnArgs &a, hipStream_t stream) {
+    const dim3 grid(a.n_wgs), block(64 * NWV);
+    if (a.head_dim == 128 && a.rope_style == 0) hipLaunchKernelGGL((attn_rows_kernel<128, 0, NB, NWV>), grid, block, 0, stream, a);
+    else if (a.head_dim == 128 && a.rope_style == 1) hipLaunchKernelGGL((attn_rows_kernel<128, 1, NB, NWV>), grid, block, 0, stream, a);
+    else if (a.head_dim == 64 && a.rope_style == 0) hipLaunchKernelGGL((attn_rows_kernel<64, 0, NB, NWV>), grid, block, 0, stream, a);
+    else if (a.head_dim == 64 && a.rope_style == 1) hipLaunchKernelGGL((attn_rows_kernel<64, 1, NB, NWV>), grid, block, 0, stream, a);
+    else return hipErrorInvalidValue;
+    return hipGetLastError();
+}
+
+}  // namespace
+
+hipError_t launch_attn_rows(const AttnArgs &a, int wavefronts, hipStream_t stream) {
+    if (a.n_wgs <= 0) return hipSuccess;
+    if (!a.wg_first || !a.rows_items || (a.n_combine > 0 && (!a.partial || !a.arrived))) return hipErrorInvalidValue;
+    if (a.tile_rows == 16) return wavefronts == 8 ? launch_blocks<1, 8>(a, stream) : launch_blocks<1, 4>(a, stream);
+    if (a.tile_rows == 32) return wavefronts == 8 ? launch_blocks<2, 8>(a, stream) : launch_blocks<2, 4>(a, stream);
+    return hipErrorInvalidValue;
+}
+
+}  // namespace ca

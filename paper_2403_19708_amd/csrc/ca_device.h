@@ -1,0 +1,146 @@
+// Device helpers shared by the attention kernels.
+#pragma once
+
+#include "ca_internal.h"
+
+namespace ca {
+
+namespace {
+
+typedef __attribute__((ext_vector_type(8))) __bf16 bf16x8;
+typedef __attribute__((ext_vector_type(2))) __bf16 bf16x2;
+typedef __attribute__((ext_vector_type(16))) float f32x16;
+typedef __attribute__((ext_vector_type(4))) float f32x4;
+typedef __attribute__((ext_vector_type(4))) short s16x4;
+typedef __attribute__((ext_vector_type(8))) short s16x8;
+
+__device__ inline float bf_lo(uint32_t u) { return __uint_as_float(u << 16); }
+__device__ inline float bf_hi(uint32_t u) { return __uint_as_float(u & 0xffff0000u); }
+__device__ inline uint32_t pack_bf16(float a, float b) {
+    bf16x2 v = {(__bf16)a, (__bf16)b};
+    return __builtin_bit_cast(uint32_t, v);
+}
+
+// s_waitcnt with only the vector-memory counter constrained (gfx9 encoding: vmcnt in bits 3:0 and
+// 15:14, expcnt 6:4 and lgkmcnt 11:8 left at "don't wait")
+#define CA_WAIT_VMCNT(n) __builtin_amdgcn_s_waitcnt(0x0F70 | ((n) & 15) | (((n) >> 4) << 14))
+
+// *p through the scalar cache: p is uniform and nothing writes *p while the kernel runs
+__device__ inline int32_t load_uniform(const int32_t *p) {
+    return *reinterpret_cast<const __attribute__((address_space(4))) int32_t *>(reinterpret_cast<uintptr_t>(p));
+}
+
+// 16 bytes per lane, global -> LDS at lds_base + lane*16, no register in between.  Written as inline
+// assembly on purpose: the compiler then knows nothing of the outstanding load and does not guard
+// every later LDS read with s_waitcnt vmcnt(0) (it cannot tell which LDS bytes the load will write);
+// the waits are placed by hand with CA_WAIT_VMCNT, which the in-order completion of these loads
+// makes exact.  lds_base must be wave-uniform.
+__device__ inline void dma16(const void *src, uint32_t lds_base) {
+    asm volatile("s_mov_b32 m0, %0\n\tglobal_load_lds_dwordx4 %1, off" : : "s"(lds_base), "v"(src) : "memory", "m0");
+}
+
+// same, with the address split into a wave-uniform 64-bit base (scalar registers) and a 32-bit
+// per-lane byte offset: no vector arithmetic per load
+__device__ inline void dma16_sbase(const void *base_uniform, uint32_t lane_off, uint32_t lds_base) {
+    asm volatile("s_mov_b32 m0, %0\n\tglobal_load_lds_dwordx4 %1, %2"
+                 : : "s"(lds_base), "v"(lane_off), "s"(base_uniform) : "memory", "m0");
+}
+
+// same, for data that is read once
+__device__ inline void dma16_sbase_nt(const void *base_uniform, uint32_t lane_off, uint32_t lds_base) {
+    asm volatile("s_mov_b32 m0, %0\n\tglobal_load_lds_dwordx4 %1, %2 nt"
+                 : : "s"(lds_base), "v"(lane_off), "s"(base_uniform) : "memory", "m0");
+}
+
+__device__ inline uint32_t lds_offset(const void *p) {
+    return (uint32_t)(uintptr_t)(const __attribute__((address_space(3))) void *)p;
+}
+
+// Results that a workgroup on another die reads inside the same launch: written through and read past the dies' own caches
+// (agent scope).  A release fence instead would write back a die's whole L2, once per wavefront.
+__device__ inline void store_agent(float *p, float v) { __hip_atomic_store(p, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT); }
+__device__ inline float load_agent(const float *p) { return __hip_atomic_load(p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT); }
+__device__ inline void store_agent4(float *p, f32x4 v) {      // p: 8-byte aligned
+    uint64_t *q = reinterpret_cast<uint64_t *>(p);
+    const float2 lo = make_float2(v[0], v[1]), hi = make_float2(v[2], v[3]);
+    __hip_atomic_store(q, __builtin_bit_cast(uint64_t, lo), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    __hip_atomic_store(q + 1, __builtin_bit_cast(uint64_t, hi), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+}
+__device__ inline f32x4 load_agent4(const float *p) {
+    const uint64_t *q = reinterpret_cast<const uint64_t *>(p);
+    const float2 lo = __builtin_bit_cast(float2, __hip_atomic_load(q, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT));
+    const float2 hi = __builtin_bit_cast(float2, __hip_atomic_load(q + 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT));
+    return f32x4{lo.x, lo.y, hi.x, hi.y};
+}
+// Counts a workgroup in whose stores of this kind are done; true in the one that is the n-th (which may then read the
+// others').  Called by every thread of the workgroup; `flag` is in LDS.  The count is back at zero afterwards.
+__device__ inline bool arrive_last(int32_t *count, int n, int32_t *flag) {
+    CA_WAIT_VMCNT(0);                              // this wavefront's stores have been acknowledged
+    __syncthreads();
+    if (threadIdx.x == 0) {
+        const int32_t before = __hip_atomic_fetch_add(count, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        if (before == n - 1) __hip_atomic_store(count, 0, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        *flag = before == n - 1;
+    }
+    __syncthreads();
+    return *flag != 0;
+}
+
+// (cos, sin) of position pos for the eight rotary pairs that the 16-byte pieces `piece` and `piece` + D/16 of a row hold
+template <int D, int STYLE>
+__device__ inline void load_cs(const float2 *__restrict__ rope, int pos, int piece, float2 (&cs)[8]) {
+    constexpr int HALF = D / 2;
+    const float2 *row = rope + (int64_t)pos * HALF;
+    if (STYLE == 0) {
+        const float4 *p = reinterpret_cast<const float4 *>(row + 8 * piece);
+#pragma unroll
+        for (int w = 0; w < 4; ++w) {
+            const float4 v = p[w];
+            cs[2 * w] = make_float2(v.x, v.y);
+            cs[2 * w + 1] = make_float2(v.z, v.w);
+        }
+    } else {
+        const float4 *p = reinterpret_cast<const float4 *>(row + 4 * piece);
+        const float4 *q = reinterpret_cast<const float4 *>(row + HALF / 2 + 4 * piece);
+#pragma unroll
+        for (int w = 0; w < 2; ++w) {
+            const float4 v = p[w], u = q[w];
+            cs[2 * w] = make_float2(v.x, v.y);
+            cs[2 * w + 1] = make_float2(v.z, v.w);
+            cs[4 + 2 * w] = make_float2(u.x, u.y);
+            cs[4 + 2 * w + 1] = make_float2(u.z, u.w);
+        }
+    }
+}
+
+// one dword (2 elements) of each of the two 16-byte pieces a (dims d0..) and b (dims d0 + D/2..)
+// (f = a factor applied to the rotated values before they are rounded)
+template <int STYLE>
+__device__ inline void rotate_dword(uint32_t &pa, uint32_t &pb, const float2 (&cs)[8], int w, float f = 1.0f) {
+    const float a0 = bf_lo(pa), a1 = bf_hi(pa);
+    const float b0 = bf_lo(pb), b1 = bf_hi(pb);
+    if (STYLE == 0) {
+        const float2 c0 = cs[2 * w], c1 = cs[2 * w + 1];
+        pa = pack_bf16((a0 * c0.x - b0 * c0.y) * f, (a1 * c1.x - b1 * c1.y) * f);
+        pb = pack_bf16((b0 * c0.x + a0 * c0.y) * f, (b1 * c1.x + a1 * c1.y) * f);
+    } else {
+        const float2 ca_ = cs[w], cb_ = cs[4 + w];
+        pa = pack_bf16((a0 * ca_.x - a1 * ca_.y) * f, (a1 * ca_.x + a0 * ca_.y) * f);
+        pb = pack_bf16((b0 * cb_.x - b1 * cb_.y) * f, (b1 * cb_.x + b0 * cb_.y) * f);
+    }
+}
+
+// four head dimensions d.. of stacked row `row` of a (conversation with first new token q0, kv head g), normalised
+template <int D>
+__device__ inline void store_out_row4(const AttnArgs &a, int q0, int g, int G, int row, int d, f32x4 o, float inv) {
+    const int j = row / G;
+    const int head = g * G + (row - j * G);
+    uint2 b;
+    b.x = pack_bf16(o[0] * inv, o[1] * inv);
+    b.y = pack_bf16(o[2] * inv, o[3] * inv);
+    *reinterpret_cast<uint2 *>(a.out + ((int64_t)(q0 + j) * a.n_q_heads + head) * D + d) = b;
+}
+
+}  // namespace
+
+}  // namespace ca

@@ -94,6 +94,16 @@ struct CombineItem {   // a row tile whose keys were split: shares first_part ..
     int32_t reserved[2];
 };
 
+// What a workgroup of launch_attn_rows needs to start streaming an item, in one piece: the item, where its conversation lies,
+// its merge, and the page ids of its first pages (nothing else has to be looked up before the first loads go out).
+struct RowsItem {
+    int32_t seq, kv_head, n_rows, key_begin, key_end, part;
+    int32_t n_keep, cu_q;                  // of the conversation
+    int32_t merge, first_part, n_parts;    // shares first_part .. of the unit; `merge` numbers its counter
+    int32_t reserved[5];
+    int32_t page[16];                      // page ids of the 16 pages from key_begin on, as far as the item has them
+};
+
 struct AttnArgs {
     const uint16_t *q;       // bf16 bits
     uint16_t *out;
@@ -121,12 +131,17 @@ struct AttnArgs {
     int32_t prerotate;
     int32_t max_positions;
     int32_t n_items;
+    const RowsItem *rows_items;  // launch_attn_rows
+    const int32_t *wg_first;     // launch_attn_rows, four wavefronts: workgroup w takes items [wg_first[w], wg_first[w + 1]);
+                                 // eight: workgroup w takes item w
+    int32_t *arrived;            // launch_attn_rows: shares of each merge that are there already; zero between calls
+    int32_t n_wgs;
     int32_t n_combine;
     int32_t total_q;
     int32_t max_pages;
     int32_t n_q_heads, n_kv_heads, head_dim;
     int32_t rope_style;
-    int32_t tile_rows;       // stacked query rows per workgroup: 128 (4 wavefronts) or 256 (8)
+    int32_t tile_rows;       // stacked query rows per workgroup: 128 (4 wavefronts), 256 (8), launch_attn_rows 16 or 32
     float softmax_scale;
 };
 
@@ -144,6 +159,10 @@ hipError_t launch_attn_combine(const AttnArgs &args, hipStream_t stream);
 // registers instead of matrix-core tiles
 constexpr int kAttnDecodeMaxRows = 2;
 hipError_t launch_attn_decode(const AttnArgs &args, int max_rows, hipStream_t stream);
+// few rows: every item has at most kAttnRowsMax stacked rows starting at row 0 (tile_rows 16 or 32); the context is streamed
+// once through LDS rings of single wavefronts; merges its shares itself
+constexpr int kAttnRowsMax = 32;
+hipError_t launch_attn_rows(const AttnArgs &args, int wavefronts, hipStream_t stream);
 constexpr int kAttnMaxParts = 1024;           // shares of split row tiles per batch (sizes the partial-result buffer)
 constexpr int kAttnMaxPartsPerTile = 16;
 constexpr int kAttnMinPartKeys = 256;         // a share is at least this many keys

@@ -91,6 +91,10 @@ struct ca_ctx {
     bool has_plan = false;
     int32_t n_seqs = 0, max_pages = 0, num_pages = 0, n_items = 0, n_combine = 0, tile_rows = 128;
     int32_t max_unit_rows = 0;   // most stacked query rows of any (conversation, kv head) of the plan
+    // plan of the few-rows kernel (launch_attn_rows): its workgroups' item ranges, and one counter per merge (zero between calls)
+    int32_t n_wgs = 0, wg_wavefronts = 0;
+    size_t off_wg_first = 0, off_rows_items = 0;
+    int32_t *arrived = nullptr;
     int32_t n_split_parts = 0;   // shares of split row tiles of the plan (slots of the partial-result buffer in use)
     float *static_partial = nullptr;   // this device's copy of the static scratch array (ca_cached_prefill_attn_static)
     int64_t total_q = 0, total_k = 0, total_n = 0;
@@ -139,6 +143,9 @@ ca_status fail(ca_ctx *ctx, ca_status st, const char *fmt, ...) {
         }                                                                                        \
     } while (0)
 
+// Workgroups of a few-rows plan that splits keys: two of four wavefronts per compute unit when there is that much to
+// stream, else at most one of eight (kAttnMaxParts / 2 bounds them: a workgroup's run of pages has two shares at most).
+constexpr int kRowsMaxWorkgroups = 512;
 constexpr size_t kMetaAlign = 64;            // alignment of the arrays of the metadata image
 // Workgroups of a kernel that moves between the pool and pinned host memory (32 KB in flight each), measured on MI355X with
 // 16 conversations of a grouped-query layer (169 MB to load, 18 MB to save), the attention of another layer beside it:
@@ -638,6 +645,7 @@ void ca_destroy(ca_ctx *ctx) {
     if (ctx->save_slots) (void)hipFree(ctx->save_slots);
     if (ctx->rope) (void)hipFree(ctx->rope);
     if (ctx->partial) (void)hipFree(ctx->partial);
+    if (ctx->arrived) (void)hipFree(ctx->arrived);
     if (ctx->k_rot) (void)hipFree(ctx->k_rot);
     if (ctx->v_t) (void)hipFree(ctx->v_t);
     if (ctx->d_meta) (void)hipFree(ctx->d_meta);
@@ -745,6 +753,7 @@ static ca_status create_impl(ca_ctx *ctx) {
         for (int i = 0; i < 3; ++i) add(ctx->k_rot_pages * 4);        // rot_src, rot_pos, rot_nvalid
         add((size_t)kAttnMaxParts * sizeof(CombineItem));
         add(max_items_padded * sizeof(WorkItem));
+        add((kRowsMaxWorkgroups + units + 1) * (4 + sizeof(WorkItem) + sizeof(RowsItem)));   // few-rows plan: one item per unit and cut
         ctx->upload_capacity = off = align_up(off, 256);
         ctx->off_q_pos = off;   off = align_up(off + (size_t)c.max_batch_q_tokens * 4, 256);
         ctx->off_q_seq = off;   off = align_up(off + (size_t)c.max_batch_q_tokens * 4, 256);
@@ -759,6 +768,8 @@ static ca_status create_impl(ca_ctx *ctx) {
     if (may_split) {
         const size_t bytes = (size_t)kAttnMaxParts * 256 * (size_t)(c.head_dim + 2) * sizeof(float);
         CA_HIP(ctx, hipMalloc((void **)&ctx->partial, bytes));
+        CA_HIP(ctx, hipMalloc((void **)&ctx->arrived, (size_t)kAttnMaxParts * sizeof(int32_t)));
+        CA_HIP(ctx, hipMemset(ctx->arrived, 0, (size_t)kAttnMaxParts * sizeof(int32_t)));
     }
     const bool may_direct = direct_variant(c);
     if (may_direct && c.attn_prerotate != 1) {
@@ -836,6 +847,95 @@ ca_status ca_join(ca_ctx *ctx, void *stream) {
 // ----------------------------------------------------------------------------------------------
 // Section 3.4: rebase
 // ----------------------------------------------------------------------------------------------
+// Does the few-rows kernel serve the current plan?  It reads a unit's keys once for up to 32 stacked rows; one or two rows
+// go to the streaming kernel of decode steps, which needs no matrix cores, more rows to the tile kernels.
+static bool rows_plan(const ca_ctx *ctx) {
+    const ca_config &c = ctx->cfg;
+    return c.attn_variant == 0 && c.attn_tile_rows == 0 && c.attn_prerotate != 2 && ctx->max_unit_rows > kAttnDecodeMaxRows &&
+           ctx->max_unit_rows <= kAttnRowsMax;
+}
+
+// Work list of the few-rows kernel.  Cuts inside a (conversation, kv head) unit lie on multiples of 64 keys.
+// Much to stream (eight pages per wavefront and more): the pages of all units, laid end to end, are cut into one run per
+// workgroup of four wavefronts; a cut leaves at least kAttnMinPartKeys on either side (a share costs a merge), so runs are
+// equal up to 256 keys.  Less: every unit of at least 512 keys is cut into shares of 16 pages, two per wavefront of a
+// workgroup of eight (both in flight from the start), more where that would be more shares than compute units.
+static void plan_rows(ca_ctx *ctx, size_t &up) {
+    const ca_config &c = ctx->cfg;
+    const int B = ctx->n_seqs, Hkv = c.n_kv_heads, G = c.n_q_heads / Hkv;
+    const auto put = [&up](size_t bytes) { const size_t at = up; up = align_up(up + bytes, kMetaAlign); return at; };
+    ctx->prerotate = ctx->pipelined = false;
+    ctx->n_dense_pages = 0;
+    ctx->tile_rows = ctx->max_unit_rows <= 16 ? 16 : 32;
+    constexpr int kCut = 64 / kPageSize, kMin = kAttnMinPartKeys / kPageSize;    // pages
+    int64_t total = 0;
+    for (int i = 0; i < B; ++i) total += (int64_t)((ctx->n_keep[i] + ctx->new_len[i] + kPageSize - 1) / kPageSize) * Hkv;
+    const int n_units = B * Hkv;
+    const bool split = ctx->partial != nullptr;
+    const bool runs = total >= (int64_t)2 * ctx->n_cus * 32;
+    const int wgs = !runs ? 0 : split ? std::min(kRowsMaxWorkgroups, 2 * ctx->n_cus) : n_units;
+    const int share = (int)std::max<int64_t>(kMin, (total / ctx->n_cus + kCut - 1) / kCut * kCut);   // pages, where there are no runs
+    const int cuts = !split ? 0 : runs ? wgs : (int)(total / share);      // at most
+    ctx->wg_wavefronts = runs ? 4 : 8;
+    ctx->off_wg_first = put((size_t)(wgs + 1) * 4);
+    ctx->off_items = put((size_t)(n_units + cuts) * sizeof(WorkItem));
+    ctx->off_rows_items = put((size_t)(n_units + cuts) * sizeof(RowsItem));
+    int32_t *wg_first = (int32_t *)(ctx->h_meta + ctx->off_wg_first);
+    WorkItem *items = (WorkItem *)(ctx->h_meta + ctx->off_items);
+    RowsItem *rows_items = (RowsItem *)(ctx->h_meta + ctx->off_rows_items);
+    int n_items = 0, n_merges = 0, n_parts = 0, w = 0;
+    int64_t done = 0;                       // pages of the units before this one
+    wg_first[0] = 0;
+    for (int i = 0; i < B; ++i) {
+        const int keys = ctx->n_keep[i] + ctx->new_len[i], rows = ctx->new_len[i] * G;
+        const int pages = (keys + kPageSize - 1) / kPageSize;
+        const int32_t *table = (const int32_t *)(ctx->h_meta + ctx->off_table) + (size_t)i * ctx->max_pages;
+        for (int g = 0; g < Hkv; ++g, done += pages) {
+            const int first_item = n_items;
+            for (int at = 0; at < pages;) {
+                int cut = pages;
+                bool next_wg = false;
+                if (!split) {
+                    next_wg = true;
+                } else if (runs) {
+                    const int64_t end = (w + 1) * total / wgs - done;        // of workgroup w's run, as a page of this unit
+                    if (end < pages) {
+                        cut = end <= 0 ? 0 : (int)((end + kCut / 2) / kCut * kCut);
+                        if (cut - at < kMin) cut = at;
+                        else if (keys / kPageSize - cut < kMin) cut = pages;
+                    }
+                    next_wg = end <= pages;
+                } else if (pages >= 2 * kMin) {
+                    cut = std::min(pages, at + share);
+                }
+                if (cut > at) {
+                    items[n_items] = WorkItem{i, g, 0, rows, at * kPageSize, cut == pages ? keys : cut * kPageSize, -1, 0};
+                    RowsItem &r = rows_items[n_items++];
+                    r = RowsItem{i, g, rows, at * kPageSize, cut == pages ? keys : cut * kPageSize, -1, ctx->n_keep[i], ctx->cu_q[i], 0, 0, 0, {}, {}};
+                    for (int p = 0; p < 16; ++p) r.page[p] = table[std::min(at + p, pages - 1)];
+                }
+                at = cut;
+                if (next_wg && w + 1 < wgs) wg_first[++w] = n_items;
+            }
+            if (n_items - first_item > 1) {
+                const int first_part = n_parts;
+                for (int k = first_item; k < n_items; ++k) {
+                    items[k].part = rows_items[k].part = n_parts++;
+                    rows_items[k].merge = n_merges;
+                    rows_items[k].first_part = first_part;
+                    rows_items[k].n_parts = n_items - first_item;
+                }
+                ++n_merges;
+            }
+        }
+    }
+    while (w < wgs) wg_first[++w] = n_items;
+    ctx->n_wgs = runs ? wgs : n_items;
+    ctx->n_items = n_items;
+    ctx->n_combine = n_merges;
+    ctx->n_split_parts = n_parts;
+}
+
 ca_status ca_rope_rebase(ca_ctx *ctx, const ca_batch *b, void *stream_) {
     if (!ctx) return CA_ERR_INVALID_ARG;
     char msg[384] = {0};
@@ -909,7 +1009,14 @@ ca_status ca_rope_rebase(ca_ctx *ctx, const ca_batch *b, void *stream_) {
     std::memcpy(ctx->h_meta + ctx->off_cu_q, ctx->cu_q.data(), (size_t)(B + 1) * 4);
     std::memcpy(ctx->h_meta + ctx->off_cu_k, ctx->cu_k.data(), (size_t)(B + 1) * 4);
 
-    // ---- attention work list: tiles of stacked query rows, placed die by die ------------------
+    // ---- attention work list ------------------------------------------------------------------
+    ctx->n_wgs = 0;
+    ctx->max_unit_rows = 0;
+    for (int i = 0; i < B; ++i) ctx->max_unit_rows = std::max(ctx->max_unit_rows, b->new_len[i] * (c.n_q_heads / c.n_kv_heads));
+    if (rows_plan(ctx)) {
+        plan_rows(ctx, up);
+    } else
+    // Tiles of stacked query rows, placed die by die.
     // All tiles of one (conversation, kv head) read the same keys/values, so they are given to the
     // same die (workgroup i runs on die i % 8) in consecutive launch slots and share its L2.
     // Units go longest-first to the least loaded die; dies are padded to equal length.
@@ -918,9 +1025,7 @@ ca_status ca_rope_rebase(ca_ctx *ctx, const ca_batch *b, void *stream_) {
         // 256-row tiles (8 wavefronts) halve the K/V re-reads and the rotary work per row when a
         // (conversation, kv head) has more than 128 stacked rows; small turns keep 128-row tiles
         int tile = c.attn_tile_rows;
-        int most = 0;
-        for (int i = 0; i < B; ++i) most = std::max(most, b->new_len[i] * G);
-        ctx->max_unit_rows = most;
+        const int most = ctx->max_unit_rows;
         if (tile == 0) tile = most > 128 ? 256 : 128;
         const bool direct_for_rot = direct_variant(c);
         {   // rotate the keys once per layer when on average three or more row tiles would each rotate them
@@ -1645,6 +1750,10 @@ static ca_status attn_impl(ca_ctx *ctx, int32_t layer, const void *q, const void
     a.n_combine = ctx->n_combine;
     a.rope = ctx->rope;
     a.n_items = ctx->n_items;
+    a.wg_first = (const int32_t *)(ctx->d_meta + ctx->off_wg_first);
+    a.rows_items = (const RowsItem *)(ctx->d_meta + ctx->off_rows_items);
+    a.arrived = ctx->arrived;
+    a.n_wgs = ctx->n_wgs;
     a.total_q = (int32_t)ctx->total_q;
     a.max_pages = ctx->max_pages;
     a.n_q_heads = c.n_q_heads;
@@ -1667,6 +1776,8 @@ static ca_status attn_impl(ca_ctx *ctx, int32_t layer, const void *q, const void
     }
     if (c.attn_variant == 1) {
         CA_HIP(ctx, launch_attn_ref(a, stream));
+    } else if (ctx->n_wgs > 0) {
+        CA_HIP(ctx, launch_attn_rows(a, ctx->wg_wavefronts, stream));
     } else if (decode) {
         CA_HIP(ctx, launch_attn_decode(a, ctx->max_unit_rows, stream));
     } else if (direct && ctx->pipelined) {

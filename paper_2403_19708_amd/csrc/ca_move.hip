@@ -8,6 +8,7 @@
 // contiguous side, so both sides move in full 256-byte segments; all heads of a page together are
 // one contiguous run on either side (n_kv_heads * 4 KiB in the pool, 16 whole token rows in the
 // contiguous layout).
+#include "ca_device.h"
 #include "ca_internal.h"
 
 namespace ca {
@@ -17,14 +18,9 @@ namespace {
 typedef __attribute__((ext_vector_type(4))) unsigned int vec16;  // one 16-byte piece
 
 constexpr int kMoveThreads = 256;
-
-// *p through the scalar cache: p is uniform and nothing writes *p while the kernel runs
-__device__ inline int32_t load_uniform(const int32_t *p) {
-    return *reinterpret_cast<const __attribute__((address_space(4))) int32_t *>(reinterpret_cast<uintptr_t>(p));
-}
-
 constexpr int kUnroll = kMoveUnroll;
 constexpr int kMoveMaxGridY = 32768;
+
 
 // One contiguous range of context tokens of one conversation, for keys or for values, and where it lies outside the pool.
 struct Piece {

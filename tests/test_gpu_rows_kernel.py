@@ -1,0 +1,75 @@
+"""The kernel for few stacked query rows per (conversation, kv head) (3 to 32: grouped-query decode steps, very short
+turns): outputs against the oracle where it can go wrong -- one and two 16-row blocks, contexts that end anywhere in a page
+or have fewer pages than a workgroup has wavefronts, rows that see different ends, both head sizes and pair conventions,
+key splitting on and off, runs of pages that cover many units and units cut into many runs -- and repeatedly on one plan
+(the merge counters must be back at zero)."""
+import numpy as np
+import pytest
+
+from harness import Case, GpuRun, torch_to_bits
+from test_gpu_parity import check_contract, check_tight
+
+pytestmark = pytest.mark.gpu
+
+
+def run_case(case, calls=1, tight=True, **knobs):
+    run = GpuRun(case, tier="device", **knobs)
+    try:
+        run.rebase()
+        run.load(0)
+        run.append(0)
+        bits = []
+        for _ in range(calls):
+            run.out[0].zero_()
+            run.attn(0)
+            run.finish()
+            bits.append(torch_to_bits(run.out[0]).copy())
+        for c in range(case.B):
+            check_contract(run.out_f64(0, c), case.oracle_out(0, c), c)
+            if tight:
+                check_tight(run.out_f64(0, c), case.oracle_out(0, c), int(case.n_keep[c]), c)
+        items = run.ctx.rebase_read(6).reshape(-1, 8)
+        return items, bits
+    finally:
+        run.close()
+
+
+SHAPES = [  # Hq, Hkv, D, style, new tokens: rows = new * Hq / Hkv
+    (8, 1, 128, 0, 1), (8, 2, 128, 1, 1), (16, 1, 64, 0, 1), (32, 1, 128, 0, 1), (4, 4, 128, 0, 32), (4, 4, 64, 1, 17),
+    (3, 1, 64, 1, 1), (8, 1, 128, 0, 4), (6, 2, 64, 0, 3),
+]
+
+
+@pytest.mark.parametrize("split", [0, 1], ids=["split", "whole"])
+@pytest.mark.parametrize("shape", SHAPES, ids=lambda s: "hq%d-hkv%d-d%d-style%d-new%d" % s)
+def test_ends_and_rows(shape, split):
+    Hq, Hkv, D, style, new = shape
+    hist = [0, 1, 15, 16, 17, 63, 200, 333, 1000, 1027]
+    keep = [0, 0, 3, 0, 16, 0, 77, 0, 500, 0]
+    lens = [max(1, new - c % 3) for c in range(len(hist))]
+    case = Case(hist, lens, keep, Hq, Hkv, D, seed=60 + D + style, style=style, window=2048)
+    run_case(case, attn_split=split)
+
+
+@pytest.mark.parametrize("shape", [(8, 1, 128, 0, 1), (16, 2, 64, 1, 4)], ids=["one-block", "two-blocks"])
+def test_units_cut_into_many_runs(shape):
+    Hq, Hkv, D, style, new = shape
+    case = Case([9000, 700, 4100], [new] * 3, [0, 0, 37], Hq, Hkv, D, seed=62, style=style, window=16384)
+    items, bits = run_case(case, calls=3)
+    assert (items[:, 6] >= 0).sum() >= 8
+    assert np.array_equal(bits[0], bits[1]) and np.array_equal(bits[0], bits[2])
+
+
+def test_runs_over_many_units():
+    """enough to stream for two workgroups of four wavefronts per compute unit: most runs cover a whole unit and a share on
+    either side"""
+    hist = [int(h) for h in np.random.default_rng(63).integers(100, 700, 48)]
+    case = Case(hist, [1] * 48, [0] * 48, 64, 16, 64, seed=63, window=1024)
+    items, bits = run_case(case, calls=2)
+    assert (items[:, 6] < 0).any() and (items[:, 6] >= 0).any()
+    assert np.array_equal(bits[0], bits[1])
+
+
+def test_peaky_scores():
+    case = Case([500, 77], [1, 1], [0, 0], 8, 1, 128, seed=64, window=1024, q_scale=2.0)
+    run_case(case, tight=False)      # (softmax on a few keys: the rounding of the rotated operands is over the tighter bar)
