@@ -1,4 +1,5 @@
-"""ctypes binding of include/ca.h.  Argument marshalling only.
+"""Binding of include/ca.h.  Argument marshalling only: ctypes, and for the calls made per layer the native module
+_ca_native (csrc/ca_binding.cpp).
 
 Tensors are passed as anything with .data_ptr() (torch tensors) or as integer addresses; streams
 as anything with .cuda_stream (torch.cuda.Stream), an integer hipStream_t, or None for the
@@ -15,6 +16,7 @@ import numpy as np
 _HERE = os.path.dirname(os.path.abspath(__file__))
 _LIB_PATH = os.path.join(_HERE, "libca_hip.so")
 _lib = None
+_native = None
 
 STATUS = {0: "CA_OK", 1: "CA_ERR_INVALID_ARG", 2: "CA_ERR_OUT_OF_RANGE", 3: "CA_ERR_UNSUPPORTED",
           4: "CA_ERR_NOMEM", 5: "CA_ERR_NOT_READY", 6: "CA_ERR_HIP"}
@@ -59,7 +61,7 @@ def lib_path() -> str:
 
 def load_library():
     """Loads libca_hip.so; raises if it has not been built.  There is no fallback path."""
-    global _lib
+    global _lib, _native
     if _lib is not None:
         return _lib
     if not os.path.exists(_LIB_PATH):
@@ -115,6 +117,8 @@ def load_library():
     lib.ca_tier_compact.argtypes = [C.c_int32, C.POINTER(C.c_int32), C.POINTER(C.c_int32), C.POINTER(C.c_int32), C.POINTER(C.c_int32),
                                     C.c_int64, C.POINTER(C.c_void_p), C.POINTER(C.c_void_p), C.POINTER(C.c_int32)]
     lib.ca_tier_compact.restype = C.c_int
+    from . import _ca_native        # linked against the library just loaded
+    _native = _ca_native
     _lib = lib
     return lib
 
@@ -282,6 +286,7 @@ class Context:
         self._lib = load_library()
         self.cfg = cfg
         self._h = C.c_void_p()
+        self._address = 0           # the handle as the native calls take it
         c = cfg.to_c()
         st = self._lib.ca_create(C.byref(c), C.byref(self._h))
         if st != 0:
@@ -289,10 +294,12 @@ class Context:
             buf = C.create_string_buffer(512)
             self._lib.ca_config_validate(C.byref(c), buf, 512)
             raise CaError(st, buf.value.decode() or "ca_create failed (see stderr)")
+        self._address = self._h.value
         self.n_seqs = 0
 
     def close(self):
         if getattr(self, "_h", None) is not None and self._h.value:
+            self._address = 0
             self._lib.ca_destroy(self._h)
             self._h = C.c_void_p()
 
@@ -314,6 +321,13 @@ class Context:
 
     # ---- Section 3.4 ------------------------------------------------------------------------
     def rope_rebase(self, hist_len, keep_start, new_len, block_table, num_pages: int, stream=None, keep_ranges=None):
+        if keep_ranges is None:
+            st = _native.rope_rebase(self._address, hist_len, keep_start, new_len, block_table, num_pages, stream)
+            if st == 0:
+                self.n_seqs = len(hist_len)
+                return
+            if st is not None:
+                self._check(st)
         b, keep = _make_batch(hist_len, keep_start, new_len, block_table, num_pages, keep_ranges)
         st = self._lib.ca_rope_rebase(self._h, C.byref(b), _stream(stream))
         del keep
@@ -330,53 +344,42 @@ class Context:
         return out[:cnt.value].copy()
 
     # ---- Section 3.2.1 ----------------------------------------------------------------------
-    def _ptr_array(self, ptrs):
-        return pointer_array(ptrs)
-
     def kv_load_layer(self, layer: int, src_k, src_v, k_pool, v_pool):
-        ak, av = self._ptr_array(src_k), self._ptr_array(src_v)
-        if self.n_seqs and (len(ak) != self.n_seqs or len(av) != self.n_seqs):
-            raise ValueError("src_k/src_v need one pointer per conversation of the current plan")
-        self._check(self._lib.ca_kv_load_layer(self._h, int(layer), ak, av, _ptr(k_pool), _ptr(v_pool)))
+        st = _native.load_layer(self._address, self.n_seqs, layer, src_k, src_v, k_pool, v_pool)
+        if st:
+            self._check(st)
 
     def kv_append_layer(self, layer: int, new_k, new_v, k_pool, v_pool, stream=None):
-        self._check(self._lib.ca_kv_append_layer(self._h, int(layer), _ptr(new_k), _ptr(new_v),
-                                                 _ptr(k_pool), _ptr(v_pool), _stream(stream)))
+        st = _native.append_layer(self._address, layer, new_k, new_v, k_pool, v_pool, stream)
+        if st:
+            self._check(st)
 
     # ---- Sections 2.1 / 3.1 / 3.4 -----------------------------------------------------------
     def cached_prefill_attn(self, layer: int, q, k_pool, v_pool, out, softmax_scale: float, stream=None):
-        self._check(self._lib.ca_cached_prefill_attn(self._h, int(layer), _ptr(q), _ptr(k_pool), _ptr(v_pool),
-                                                     _ptr(out), float(softmax_scale), _stream(stream)))
+        st = _native.prefill_attn(self._address, layer, q, k_pool, v_pool, out, softmax_scale, stream)
+        if st:
+            self._check(st)
 
     def cached_prefill_attn_static(self, layer: int, q, k_pool, v_pool, out, softmax_scale: float, stream=None):
-        self._check(self._lib.ca_cached_prefill_attn_static(self._h, int(layer), _ptr(q), _ptr(k_pool), _ptr(v_pool),
-                                                            _ptr(out), float(softmax_scale), _stream(stream)))
+        st = _native.prefill_attn_static(self._address, layer, q, k_pool, v_pool, out, softmax_scale, stream)
+        if st:
+            self._check(st)
 
     # ---- Section 3.2.2 ----------------------------------------------------------------------
     def kv_save_layer(self, layer: int, k_pool, v_pool, dst_k, dst_v, tok_begin=None, tok_end=None,
                       dst_tok_offset=None, after_stream=None):
-        ak, av = self._ptr_array(dst_k), self._ptr_array(dst_v)
-        if self.n_seqs and (len(ak) != self.n_seqs or len(av) != self.n_seqs):
-            raise ValueError("dst_k/dst_v need one pointer per conversation of the current plan")
-        keep = []
-        def opt(a, dtype):
-            if a is None:
-                return None
-            arr = np.ascontiguousarray(a, dtype=dtype)
-            if arr.shape != (self.n_seqs,):
-                raise ValueError("per-conversation arrays must have n_seqs entries")
-            keep.append(arr)
-            return arr.ctypes.data
-        tb, te, off = opt(tok_begin, np.int32), opt(tok_end, np.int32), opt(dst_tok_offset, np.int64)
-        self._check(self._lib.ca_kv_save_layer(self._h, int(layer), tb, te, _ptr(k_pool), _ptr(v_pool), ak, av,
-                                               off, _stream(after_stream)))
+        st = _native.save_layer(self._address, self.n_seqs, layer, k_pool, v_pool, dst_k, dst_v, tok_begin, tok_end, dst_tok_offset, after_stream)
+        if st is None:          # an array is not contiguous int32 / int64 yet
+            opt = lambda a, dtype: None if a is None else np.ascontiguousarray(a, dtype=dtype)
+            st = _native.save_layer(self._address, self.n_seqs, layer, k_pool, v_pool, dst_k, dst_v, opt(tok_begin, np.int32), opt(tok_end, np.int32),
+                                    opt(dst_tok_offset, np.int64), after_stream)
+        if st:
+            self._check(st)
 
     def kv_append_save_layer(self, layer: int, new_k, new_v, k_pool, v_pool, dst_k, dst_v, stream=None):
-        ak, av = self._ptr_array(dst_k), self._ptr_array(dst_v)
-        if self.n_seqs and (len(ak) != self.n_seqs or len(av) != self.n_seqs):
-            raise ValueError("dst_k/dst_v need one pointer per conversation of the current plan")
-        self._check(self._lib.ca_kv_append_save_layer(self._h, int(layer), _ptr(new_k), _ptr(new_v), _ptr(k_pool),
-                                                      _ptr(v_pool), ak, av, _stream(stream)))
+        st = _native.append_save_layer(self._address, self.n_seqs, layer, new_k, new_v, k_pool, v_pool, dst_k, dst_v, stream)
+        if st:
+            self._check(st)
 
     def sync(self):
         self._check(self._lib.ca_sync(self._h))

@@ -1,0 +1,249 @@
+// Native half of paper_2403_19708_amd/binding.py: the calls a serving program makes per layer and per step, from Python
+// objects to include/ca.h without ctypes in between.  A decode step of an 80-layer model is 240 such calls of 3 to 6 us
+// each; marshalling them in Python (attribute checks, numpy views, ctypes conversions) cost another 1 to 4 us a call.
+// Arguments are what the Python methods document: tensors are anything with data_ptr(), or integer addresses; streams
+// anything with cuda_stream, integers or None; pointer lists a ctypes array of c_void_p, or any sequence.
+#define PY_SSIZE_T_CLEAN
+#include <Python.h>
+
+#include <cstdint>
+#include <vector>
+
+#include "../../include/ca.h"
+
+namespace {
+
+PyObject *s_data_ptr, *s_cuda_stream;
+
+// Integer value of o, o.data_ptr() or o.cuda_stream.  false: a Python error is set.
+bool address(PyObject *o, void **out) {
+    if (o == Py_None) { *out = nullptr; return true; }
+    if (PyLong_CheckExact(o)) {
+        *out = PyLong_AsVoidPtr(o);
+        return *out != nullptr || !PyErr_Occurred();
+    }
+    PyObject *v = PyObject_CallMethodNoArgs(o, s_data_ptr);
+    if (!v) {
+        if (!PyErr_ExceptionMatches(PyExc_AttributeError)) return false;
+        PyErr_Clear();
+        v = PyNumber_Long(o);
+        if (!v) return false;
+    }
+    *out = PyLong_AsVoidPtr(v);
+    Py_DECREF(v);
+    return *out != nullptr || !PyErr_Occurred();
+}
+
+bool stream_of(PyObject *o, void **out) {
+    if (o == Py_None) { *out = nullptr; return true; }
+    if (PyLong_CheckExact(o)) return address(o, out);
+    PyObject *v = PyObject_GetAttr(o, s_cuda_stream);
+    if (!v) {
+        if (!PyErr_ExceptionMatches(PyExc_AttributeError)) return false;
+        PyErr_Clear();
+        v = PyNumber_Long(o);
+        if (!v) return false;
+    }
+    *out = PyLong_AsVoidPtr(v);
+    Py_DECREF(v);
+    return *out != nullptr || !PyErr_Occurred();
+}
+
+// One pointer per conversation: the memory of a ctypes array as it is, or a list converted.
+struct Pointers {
+    std::vector<void *> own;
+    void **p = nullptr;
+    bool take(PyObject *o, long long n_seqs, const char *what) {
+        Py_ssize_t n = 0;
+        Py_buffer view;
+        if (!PyList_CheckExact(o) && !PyTuple_CheckExact(o) && PyObject_CheckBuffer(o)) {
+            if (PyObject_GetBuffer(o, &view, PyBUF_SIMPLE) != 0) return false;
+            p = (void **)view.buf;                  // (the caller's reference keeps the array alive over the call)
+            n = view.len / (Py_ssize_t)sizeof(void *);
+            PyBuffer_Release(&view);
+        } else {
+            PyObject *seq = PySequence_Fast(o, "one pointer per conversation expected");
+            if (!seq) return false;
+            n = PySequence_Fast_GET_SIZE(seq);
+            own.resize((size_t)n);
+            for (Py_ssize_t i = 0; i < n; ++i)
+                if (!address(PySequence_Fast_GET_ITEM(seq, i), &own[(size_t)i])) { Py_DECREF(seq); return false; }
+            Py_DECREF(seq);
+            p = own.data();
+        }
+        if (n_seqs && n != n_seqs) {
+            PyErr_Format(PyExc_ValueError, "%s need one pointer per conversation of the current plan", what);
+            return false;
+        }
+        return true;
+    }
+};
+
+// A contiguous buffer of 32-bit or 64-bit integers; take() is false for anything else, without a Python error.  The memory
+// stays alive over the call through the caller's reference.
+struct Ints {
+    void *p = nullptr;
+    int ndim = 0;
+    Py_ssize_t shape[2] = {0, 0};
+    bool take(PyObject *o, int bytes) {
+        Py_buffer view;
+        if (!PyObject_CheckBuffer(o)) return false;
+        if (PyObject_GetBuffer(o, &view, PyBUF_ND | PyBUF_FORMAT) != 0) {      // (not contiguous, for one)
+            PyErr_Clear();
+            return false;
+        }
+        const char f = view.format && view.format[0] && !view.format[1] ? view.format[0] : 0;
+        const bool fits = view.itemsize == bytes && (bytes == 4 ? f == 'i' || f == 'l' : f == 'l' || f == 'q') && (view.ndim == 1 || view.ndim == 2);
+        p = view.buf;
+        ndim = view.ndim;
+        for (int i = 0; fits && i < ndim; ++i) shape[i] = view.shape[i];
+        PyBuffer_Release(&view);
+        return fits;
+    }
+};
+
+bool want(Py_ssize_t n, Py_ssize_t expected) {
+    if (n == expected) return true;
+    PyErr_SetString(PyExc_TypeError, "wrong number of arguments");
+    return false;
+}
+
+bool layer_of(PyObject *o, int32_t *layer) {
+    const long v = PyLong_AsLong(o);
+    if (v == -1 && PyErr_Occurred()) return false;
+    *layer = (int32_t)v;
+    return true;
+}
+
+ca_ctx *context(PyObject *o) { return (ca_ctx *)PyLong_AsVoidPtr(o); }      // (NULL is an argument error of the library's)
+
+// Other Python threads run while the library does: a launch can wait for room in a hardware queue.
+template <class Call>
+PyObject *status_of(Call call) {
+    ca_status st;
+    Py_BEGIN_ALLOW_THREADS
+    st = call();
+    Py_END_ALLOW_THREADS
+    return PyLong_FromLong(st);
+}
+
+// (handle, hist_len, keep_start, new_len, block_table, num_pages, stream).  None is returned, and nothing done, unless the
+// arrays are contiguous int32 of matching lengths.
+PyObject *rope_rebase(PyObject *, PyObject *const *a, Py_ssize_t n) {
+    if (!want(n, 7)) return nullptr;
+    Ints x[4];
+    for (int i = 0; i < 4; ++i)
+        if (!x[i].take(a[1 + i], 4)) Py_RETURN_NONE;
+    for (int i = 0; i < 3; ++i)
+        if (x[i].ndim != 1 || x[i].shape[0] != x[0].shape[0]) Py_RETURN_NONE;
+    if (x[3].ndim != 2 || x[3].shape[0] != x[0].shape[0]) Py_RETURN_NONE;
+    const long pages = PyLong_AsLong(a[5]);
+    if (pages == -1 && PyErr_Occurred()) return nullptr;
+    void *stream;
+    if (!stream_of(a[6], &stream)) return nullptr;
+    ca_batch b{};
+    b.n_seqs = (int32_t)x[0].shape[0];
+    b.hist_len = (const int32_t *)x[0].p;
+    b.keep_start = (const int32_t *)x[1].p;
+    b.new_len = (const int32_t *)x[2].p;
+    b.block_table = (const int32_t *)x[3].p;
+    b.max_pages = (int32_t)x[3].shape[1];
+    b.num_pages = (int32_t)pages;
+    ca_ctx *ctx = context(a[0]);
+    return status_of([&] { return ca_rope_rebase(ctx, &b, stream); });
+}
+
+// (handle, layer, new_k, new_v, k_pool, v_pool, stream)
+PyObject *append_layer(PyObject *, PyObject *const *a, Py_ssize_t n) {
+    int32_t layer;
+    void *p[4], *stream;
+    if (!want(n, 7) || !layer_of(a[1], &layer)) return nullptr;
+    for (int i = 0; i < 4; ++i) if (!address(a[2 + i], &p[i])) return nullptr;
+    if (!stream_of(a[6], &stream)) return nullptr;
+    ca_ctx *ctx = context(a[0]);
+    return status_of([&] { return ca_kv_append_layer(ctx, layer, p[0], p[1], p[2], p[3], stream); });
+}
+
+// (handle, layer, q, k_pool, v_pool, out, scale, stream)
+PyObject *attention(PyObject *const *a, Py_ssize_t n, decltype(ca_cached_prefill_attn) *call) {
+    int32_t layer;
+    void *p[4], *stream;
+    if (!want(n, 8) || !layer_of(a[1], &layer)) return nullptr;
+    for (int i = 0; i < 4; ++i) if (!address(a[2 + i], &p[i])) return nullptr;
+    const double scale = PyFloat_AsDouble(a[6]);
+    if (scale == -1.0 && PyErr_Occurred()) return nullptr;
+    if (!stream_of(a[7], &stream)) return nullptr;
+    ca_ctx *ctx = context(a[0]);
+    return status_of([&] { return call(ctx, layer, p[0], p[1], p[2], p[3], (float)scale, stream); });
+}
+PyObject *prefill_attn(PyObject *, PyObject *const *a, Py_ssize_t n) { return attention(a, n, &ca_cached_prefill_attn); }
+PyObject *prefill_attn_static(PyObject *, PyObject *const *a, Py_ssize_t n) { return attention(a, n, &ca_cached_prefill_attn_static); }
+
+// (handle, n_seqs, layer, src_k, src_v, k_pool, v_pool)
+PyObject *load_layer(PyObject *, PyObject *const *a, Py_ssize_t n) {
+    int32_t layer;
+    void *p[2];
+    Pointers k, v;
+    if (!want(n, 7) || !layer_of(a[2], &layer)) return nullptr;
+    const long long seqs = PyLong_AsLongLong(a[1]);
+    if (!k.take(a[3], seqs, "src_k/src_v") || !v.take(a[4], seqs, "src_k/src_v")) return nullptr;
+    for (int i = 0; i < 2; ++i) if (!address(a[5 + i], &p[i])) return nullptr;
+    ca_ctx *ctx = context(a[0]);
+    return status_of([&] { return ca_kv_load_layer(ctx, layer, (const void *const *)k.p, (const void *const *)v.p, p[0], p[1]); });
+}
+
+// (handle, n_seqs, layer, k_pool, v_pool, dst_k, dst_v, tok_begin, tok_end, dst_tok_offset, stream); the three arrays are
+// None or contiguous buffers of int32, int32 and int64.  None is returned, and nothing done, where one has to be converted.
+PyObject *save_layer(PyObject *, PyObject *const *a, Py_ssize_t n) {
+    int32_t layer;
+    void *p[2], *stream;
+    Pointers k, v;
+    if (!want(n, 11) || !layer_of(a[2], &layer)) return nullptr;
+    const long long seqs = PyLong_AsLongLong(a[1]);
+    for (int i = 0; i < 2; ++i) if (!address(a[3 + i], &p[i])) return nullptr;
+    if (!k.take(a[5], seqs, "dst_k/dst_v") || !v.take(a[6], seqs, "dst_k/dst_v")) return nullptr;
+    const void *opt[3] = {nullptr, nullptr, nullptr};
+    for (int i = 0; i < 3; ++i) {
+        if (a[7 + i] == Py_None) continue;
+        Ints x;
+        if (!x.take(a[7 + i], i < 2 ? 4 : 8)) Py_RETURN_NONE;
+        if (x.ndim != 1 || x.shape[0] != seqs) {
+            PyErr_SetString(PyExc_ValueError, "per-conversation arrays must have n_seqs entries");
+            return nullptr;
+        }
+        opt[i] = x.p;
+    }
+    if (!stream_of(a[10], &stream)) return nullptr;
+    ca_ctx *ctx = context(a[0]);
+    return status_of([&] {
+        return ca_kv_save_layer(ctx, layer, (const int32_t *)opt[0], (const int32_t *)opt[1], p[0], p[1], k.p, v.p, (const int64_t *)opt[2], stream);
+    });
+}
+
+// (handle, n_seqs, layer, new_k, new_v, k_pool, v_pool, dst_k, dst_v, stream)
+PyObject *append_save_layer(PyObject *, PyObject *const *a, Py_ssize_t n) {
+    int32_t layer;
+    void *p[4], *stream;
+    Pointers k, v;
+    if (!want(n, 10) || !layer_of(a[2], &layer)) return nullptr;
+    const long long seqs = PyLong_AsLongLong(a[1]);
+    for (int i = 0; i < 4; ++i) if (!address(a[3 + i], &p[i])) return nullptr;
+    if (!k.take(a[7], seqs, "dst_k/dst_v") || !v.take(a[8], seqs, "dst_k/dst_v")) return nullptr;
+    if (!stream_of(a[9], &stream)) return nullptr;
+    ca_ctx *ctx = context(a[0]);
+    return status_of([&] { return ca_kv_append_save_layer(ctx, layer, p[0], p[1], p[2], p[3], k.p, v.p, stream); });
+}
+
+#define CA_METHOD(name) {#name, (PyCFunction)(void (*)(void))name, METH_FASTCALL, nullptr}
+PyMethodDef methods[] = {CA_METHOD(rope_rebase), CA_METHOD(append_layer), CA_METHOD(prefill_attn), CA_METHOD(prefill_attn_static), CA_METHOD(load_layer),
+                         CA_METHOD(save_layer), CA_METHOD(append_save_layer), {nullptr, nullptr, 0, nullptr}};
+PyModuleDef module = {PyModuleDef_HEAD_INIT, "_ca_native", nullptr, -1, methods, nullptr, nullptr, nullptr, nullptr};
+
+}  // namespace
+
+PyMODINIT_FUNC PyInit__ca_native() {
+    s_data_ptr = PyUnicode_InternFromString("data_ptr");
+    s_cuda_stream = PyUnicode_InternFromString("cuda_stream");
+    if (!s_data_ptr || !s_cuda_stream) return nullptr;
+    return PyModule_Create(&module);
+}
