@@ -1120,22 +1120,34 @@ ca_status ca_rope_rebase(ca_ctx *ctx, const ca_batch *b, void *stream_) {
         if (ctx->partial && direct_kernel && n_live < (size_t)(decode_plan ? 1 : 6) * ctx->n_cus) {
             const int bins = std::max(1, ctx->n_cus / kXcds) * (tile == 128 ? 2 : 1);
             std::vector<double> heap;
+            // sorts the items and returns the makespan of their longest-first list schedule over `bins` compute units
+            // (min-heap of their loads)
+            const auto schedule = [&](std::vector<Item> &v, double &total) {
+                std::stable_sort(v.begin(), v.end(), by_cost);
+                heap.assign(bins, 0.0);
+                total = 0;
+                for (const Item &it : v) {
+                    std::pop_heap(heap.begin(), heap.end(), std::greater<double>());
+                    heap.back() += it.cost;
+                    std::push_heap(heap.begin(), heap.end(), std::greater<double>());
+                    total += it.cost;
+                }
+                return *std::max_element(heap.begin(), heap.end());
+            };
+            std::vector<Item> whole, shares, best;
             for (int d = 0; d < kXcds; ++d) {
                 auto &v = per_die[d];
+                const int32_t parts_before = n_split_parts;
+                double uncut = 0;
                 for (int round = 0; round < 4 && !v.empty(); ++round) {
-                    std::stable_sort(v.begin(), v.end(), by_cost);
-                    // longest-first list schedule over `bins` compute units (min-heap of their loads)
-                    heap.assign(bins, 0.0);
-                    double total = 0;
-                    for (const Item &it : v) {
-                        std::pop_heap(heap.begin(), heap.end(), std::greater<double>());
-                        heap.back() += it.cost;
-                        std::push_heap(heap.begin(), heap.end(), std::greater<double>());
-                        total += it.cost;
-                    }
-                    const double makespan = *std::max_element(heap.begin(), heap.end());
+                    double total;
+                    const double makespan = schedule(v, total);
                     const double ideal = total / bins;
                     if (makespan <= 1.12 * ideal + 1.0) break;   // (cutting further was measured to cost more than it gains)
+                    if (round == 0) {
+                        whole = v;
+                        uncut = ideal;
+                    }
                     const size_t n_before = v.size();
                     bool cut_any = false;
                     for (size_t k = 0; k < n_before && v[k].cost > 0.7 * ideal; ++k) {
@@ -1158,7 +1170,49 @@ ca_status ca_rope_rebase(ca_ctx *ctx, const ca_batch *b, void *stream_) {
                     }
                     if (!cut_any) break;
                 }
-                std::stable_sort(v.begin(), v.end(), by_cost);
+                if (uncut <= 0) continue;           // nothing was cut, and the schedule has left the items sorted
+                double total;
+                double makespan = schedule(v, total);
+                // Halving leaves shares of like length, whose number need not divide well among the compute units: one
+                // conversation of 31003 + 301 tokens on 8 kv heads gets 76 shares a die for 32 compute units, three rounds
+                // where 2.4 would do.  So equal shares of at most a few fractions of a compute unit's ideal load are tried
+                // as well, and taken where their schedule is at least 5 % shorter and they need no more scratch than
+                // halving.  Below sixteen tiles between halving and ideal the search costs the host what it could gain.
+                // (That conversation, 8 layers: 3327 -> 2905 us a pass.)
+                const double halved = makespan;
+                if (halved < 1.05 * uncut + 16.0) continue;
+                bool found = false;
+                for (const double fraction : {1.18, 1.02, 0.87, 0.70, 0.56}) {
+                    const double cap = std::max(fraction * uncut - item_cost(1, 0), 1.0);
+                    int32_t parts = parts_before;
+                    shares.clear();
+                    for (const Item &it : whole) {
+                        const int len = it.w.key_end - it.w.key_begin, tiles64 = len / 64;
+                        const int n = (int)std::max<int64_t>(1, std::min<int64_t>({(int64_t)kAttnMaxPartsPerTile, len / kAttnMinPartKeys,
+                                                                                 (int64_t)std::ceil((it.cost - item_cost(1, 0)) / cap)}));
+                        if (n > 1) parts += n;
+                        for (int k = 0; k < n; ++k) {
+                            Item share = it;
+                            share.w.key_begin = it.w.key_begin + (int)((int64_t)tiles64 * k / n) * 64;
+                            if (k + 1 < n) share.w.key_end = it.w.key_begin + (int)((int64_t)tiles64 * (k + 1) / n) * 64;
+                            share.cost = item_cost(it.w.n_rows, share.w.key_end - share.w.key_begin);
+                            shares.push_back(share);
+                        }
+                    }
+                    if (parts > n_split_parts) continue;
+                    const double with_shares = schedule(shares, total);
+                    if (with_shares >= makespan || with_shares > 0.95 * halved) continue;
+                    makespan = with_shares;
+                    best.swap(shares);
+                    found = true;
+                }
+                if (!found) continue;
+                for (const Item &it : whole) parts_of[it.parent] = 0;
+                for (const Item &it : best) ++parts_of[it.parent];
+                n_split_parts = parts_before;
+                for (const Item &it : whole)
+                    if (parts_of[it.parent] > 1) n_split_parts += parts_of[it.parent];
+                v.swap(best);
             }
         }
         // number the shares of split row tiles consecutively and list the tiles for the merge

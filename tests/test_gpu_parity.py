@@ -207,6 +207,38 @@ def test_small_batch_splits_keys_over_workgroups(shape, split):
         run.close()
 
 
+@pytest.mark.parametrize("hist,n_items,window", [(9000, 240, 16384), (8999, 240, 16384), (3000, None, 4096)])
+def test_long_tiles_split_into_equal_shares(hist, n_items, window):
+    """One conversation of ten row tiles on each of eight kv heads: halving gives 76 shares a die, equal shares of a third of
+    the keys take their place where the context is long enough for that to matter (three a tile).  Shares tile the keys of
+    every row tile without gaps, and a first, a middle and the last head agree with the oracle."""
+    case = Case([hist], [300], [0], 64, 8, 64, seed=32, window=window)
+    run = GpuRun(case, tier="device")
+    try:
+        run.rebase()
+        items = run.ctx.rebase_read(6).reshape(-1, 8)
+        live = items[items[:, 0] >= 0]
+        slots = np.sort(live[live[:, 6] >= 0][:, 6])
+        assert np.array_equal(slots, np.arange(len(slots))) and (n_items is None or len(live) == n_items)
+        tiles = {}
+        for _, head, row0, n_rows, k0, k1, part, _ in live:
+            tiles.setdefault((head, row0, n_rows), []).append((k0, k1, part))
+        assert sorted(t[:2] for t in tiles) == [(h, 256 * t) for h in range(8) for t in range(10)]
+        for (head, row0, n_rows), parts in tiles.items():
+            parts.sort()
+            assert parts[0][0] == 0 and parts[-1][1] >= hist + (row0 + n_rows - 1) // 8 + 1
+            for (a0, a1, pa), (b0, b1, pb) in zip(parts, parts[1:]):
+                assert a1 == b0 and a1 % 64 == 0 and a1 - a0 >= 256 and b1 - b0 >= 256 and abs(pa - pb) < 16
+        run.run_layer(0)
+        run.finish()
+        heads = [0, 29, 63]
+        got, want = run.out_f64(0, 0)[:, heads], case.oracle_out(0, 0, heads=heads)
+        check_contract(got, want, hist)
+        check_tight(got, want, hist, hist)
+    finally:
+        run.close()
+
+
 @pytest.mark.parametrize("variant", [2, 12, 13], ids=["direct", "pipelined", "direct-prerotated"])
 def test_context_fills_the_largest_window_of_the_direct_kernel(variant):
     """One conversation whose context is exactly 32768 tokens: every entry of the LDS-direct kernel's page
