@@ -283,7 +283,9 @@ ca_status ca_kv_append_save_layer(ca_ctx *ctx, int32_t layer, const void *new_k,
 /* Blocks the host until every load and save queued so far is done. */
 ca_status ca_sync(ca_ctx *ctx);
 
-/* Makes `stream` wait (device side) for every load and save queued so far. */
+/* Makes `stream` wait (device side) for every load and save queued so far.  NULL: the default stream
+ * of the context's GPU and, if that is not the current one, of the current GPU as well.  Neither this
+ * call nor ca_sync changes which GPU is current. */
 ca_status ca_join(ca_ctx *ctx, void *stream);
 
 /* ---- timing of the library's own GPU work ------------------------------------------------ */

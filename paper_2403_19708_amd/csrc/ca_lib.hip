@@ -51,7 +51,7 @@ struct ca_ctx {
     bool copy_waits_plan = false, unpack_waits_plan = false, save_waits_plan = false;   // the stream has not yet been told to wait for ev_plan
     hipEvent_t load_done = nullptr;    // event behind the newest load on the unpack stream (one of ev_ready), null: none outstanding
     bool save_pending = false;         // ev_saved stands behind work on the save stream that may be unfinished
-    bool joined_null = false;          // the default stream already waits for all of it
+    bool joined_null = false;          // the default stream (of the context's GPU) already waits for all of it
     // short moves run on a stream of the caller's instead (see runs_inline): the newest one, and the event behind it (null on
     // the default stream, which outlives the context and can be asked or recorded on when it matters)
     bool inline_pending = false;
@@ -187,6 +187,22 @@ hipError_t prof_end(ca_ctx *ctx, int idx, hipStream_t stream) {
     if (idx < 0) return hipSuccess;
     return hipEventRecord(ctx->intervals[idx].stop, stream);
 }
+
+// Makes a GPU current for the length of a scope.
+class OnDevice {
+public:
+    hipError_t enter(int device) {
+        const hipError_t e = hipGetDevice(&before_);
+        if (e != hipSuccess || before_ == device) { before_ = -1; return e; }
+        return hipSetDevice(device);
+    }
+    bool other() const { return before_ >= 0; }      // another GPU was current
+    void leave() { if (before_ >= 0) (void)hipSetDevice(before_); before_ = -1; }
+    ~OnDevice() { leave(); }
+
+private:
+    int before_ = -1;
+};
 
 size_t align_up(size_t x, size_t a) { return (x + a - 1) / a * a; }
 
@@ -816,6 +832,8 @@ ca_status ca_create(const ca_config *cfg, ca_ctx **out) {
 
 ca_status ca_sync(ca_ctx *ctx) {
     if (!ctx) return CA_ERR_INVALID_ARG;
+    OnDevice on;
+    CA_HIP(ctx, on.enter(ctx->cfg.device));
     if (ctx->load_done) CA_HIP(ctx, hipEventSynchronize(ctx->load_done));
     ctx->load_done = nullptr;
     if (ctx->save_pending) CA_HIP(ctx, hipEventSynchronize(ctx->ev_saved));
@@ -831,15 +849,27 @@ ca_status ca_sync(ca_ctx *ctx) {
 ca_status ca_join(ca_ctx *ctx, void *stream) {
     if (!ctx) return CA_ERR_INVALID_ARG;
     hipStream_t s = (hipStream_t)stream;
+    // The default stream is the context's GPU's, as in every other call, and where another GPU is current that one's as well.
+    OnDevice on;
+    CA_HIP(ctx, on.enter(ctx->cfg.device));
+    const bool other_too = on.other() && (s == nullptr || s == hipStreamLegacy || s == hipStreamPerThread);
+    hipEvent_t short_moves = nullptr;
+    if (ctx->inline_pending && (s != nullptr || ctx->inline_stream != nullptr || other_too)) {
+        if (!ctx->inline_done) CA_HIP(ctx, hipEventRecord(ctx->ev_inline, nullptr));
+        short_moves = ctx->inline_done ? ctx->inline_done : ctx->ev_inline;
+    }
     // (the copies of a staged load are in front of its unpack kernel, which waits for both halves)
     if ((ctx->load_done || ctx->save_pending) && !(s == nullptr && ctx->joined_null)) {
         if (ctx->load_done) CA_HIP(ctx, hipStreamWaitEvent(s, ctx->load_done, 0));
         if (ctx->save_pending) CA_HIP(ctx, hipStreamWaitEvent(s, ctx->ev_saved, 0));
         if (s == nullptr) ctx->joined_null = true;
     }
-    if (ctx->inline_pending && !(s == nullptr && ctx->inline_stream == nullptr)) {
-        if (!ctx->inline_done) CA_HIP(ctx, hipEventRecord(ctx->ev_inline, nullptr));
-        CA_HIP(ctx, hipStreamWaitEvent(s, ctx->inline_done ? ctx->inline_done : ctx->ev_inline, 0));
+    if (short_moves && !(s == nullptr && ctx->inline_stream == nullptr)) CA_HIP(ctx, hipStreamWaitEvent(s, short_moves, 0));
+    if (other_too) {
+        on.leave();
+        if (ctx->load_done) CA_HIP(ctx, hipStreamWaitEvent(s, ctx->load_done, 0));
+        if (ctx->save_pending) CA_HIP(ctx, hipStreamWaitEvent(s, ctx->ev_saved, 0));
+        if (short_moves) CA_HIP(ctx, hipStreamWaitEvent(s, short_moves, 0));
     }
     return CA_OK;
 }

@@ -1,0 +1,61 @@
+"""What the library queues where, and what waits for it, on a model of the HIP runtime in which nothing is done before
+something waits for it (hip_model.py): the host code of the C ABI, without a GPU."""
+import pytest
+
+from hip_model import PER_THREAD, Turn, in_model
+
+
+@in_model
+def test_a_whole_turn_runs_on_the_model(m):
+    """the model itself: a pinned and a device tier, every load and save done after sync, joined work in front of the stream"""
+    for tier in (0, 1):
+        t = Turn(m, [4000, 30], [200, 1], tier=tier)
+        s = m.stream()
+        ops = m.queued(lambda: (t.rebase(s), t.load(), t.append(s), t.attn(s), t.save(s)))
+        moves = m.named(ops, "link_kernel") + m.named(ops, "move_kernel")
+        assert len(moves) == 2 and not any(m.done(op) for op in ops)
+        attn, = m.named(ops, "attn_dma_kernel")
+        assert m.behind(attn, moves[0]) and m.behind(moves[1], m.named(ops, "append_kernel")[0])
+        other = m.stream()
+        t.ctx.join(other)
+        assert all(m.stream_behind(other, op) for op in moves)
+        t.ctx.sync()
+        assert all(m.done(op) for op in moves)
+        t.ctx.close()
+
+
+# ---- ca_sync and ca_join with another GPU current ---------------------------------------------------------------
+@in_model
+def test_sync_covers_a_short_save_with_another_gpu_current(m):
+    t = Turn(m, [0], [2], tier=1, device=1)
+    t.rebase()
+    t.append()
+    save, = m.queued(t.save)
+    m.device(0)
+    t.ctx.sync()
+    assert m.done(save) and m.current() == 0
+
+
+@in_model
+def test_join_covers_a_short_save_with_another_gpu_current(m):
+    t = Turn(m, [0], [2], tier=1, device=1)
+    t.rebase()
+    t.append()
+    save, = m.queued(t.save)
+    s1 = m.stream()
+    m.device(0)
+    s0 = m.stream()
+    for s in (s0, s1, None):
+        t.ctx.join(s)
+        assert m.current() == 0 and m.stream_behind(s, save)
+
+
+@in_model
+def test_a_plan_waits_for_the_last_one_after_a_join_with_another_gpu_current(m):
+    t = Turn(m, [4000], [200], tier=1, device=1)
+    t.rebase()
+    load, = m.queued(t.load)
+    m.device(0)
+    t.ctx.join(None)
+    plan, = m.queued(t.rebase)
+    assert m.behind(plan, load)
