@@ -228,15 +228,15 @@ MemKind mem_kind(const void *p) {
 // (never longer, an allocation may be gone by the next one).
 class MemMap {
 public:
-    // kind of p; *inside = [p, p + bytes) does not leave its allocation (true where the runtime cannot tell)
-    MemKind look(const void *p, size_t bytes, bool *inside) {
+    // kind of p; *room = bytes from p to the end of its allocation (SIZE_MAX where the runtime cannot tell)
+    MemKind look(const void *p, size_t *room) {
         const uint8_t *q = (const uint8_t *)p;
         if (base_ && q >= base_ && q < base_ + size_) {
-            *inside = bytes <= (size_t)(base_ + size_ - q);
+            *room = (size_t)(base_ + size_ - q);
             return kind_;
         }
         const MemKind k = mem_kind(p);
-        *inside = true;
+        *room = SIZE_MAX;
         if (k == MemKind::kUnknown) return k;
         hipDeviceptr_t base = nullptr;
         size_t size = 0;
@@ -245,15 +245,18 @@ public:
             return k;
         }
         const uint8_t *b = (const uint8_t *)base;
-        if (q < b || q >= b + size) { *inside = false; return k; }
+        if (q < b || q >= b + size) {       // host memory the GPU has at another address: the range does not say where p ends
+            if (k == MemKind::kDevice) *room = 0;
+            return k;
+        }
         base_ = b; size_ = size; kind_ = k;
-        *inside = bytes <= (size_t)(b + size - q);
+        *room = (size_t)(b + size - q);
         return k;
     }
     // true if [p, p+bytes) lies inside one device allocation
     bool device_range_ok(const void *p, size_t bytes) {
-        bool inside = false;
-        return p && look(p, bytes, &inside) == MemKind::kDevice && inside;
+        size_t room = 0;
+        return p && look(p, &room) == MemKind::kDevice && bytes <= room;
     }
 
 private:
@@ -1471,14 +1474,15 @@ ca_status ca_kv_load_layer(ca_ctx *ctx, int32_t layer, const void *const *src_k,
     for (int i = 0; i < B; ++i) {
         if (ctx->n_keep[i] == 0) continue;
         if (!src_k[i] || !src_v[i]) return fail(ctx, CA_ERR_INVALID_ARG, "ca_kv_load_layer: source of conversation %d is NULL", i);
-        const size_t need = (size_t)ctx->hist_len[i] * rb;
-        bool k_in, v_in;
-        const MemKind kk = map_k.look(src_k[i], need, &k_in), kv = map.look(src_v[i], need, &v_in);
+        // device memory holds the saved history; of pinned memory only what is read has to be there, up to the last kept range
+        const size_t saved = (size_t)ctx->hist_len[i] * rb, read = (size_t)ctx->keep_rng[ctx->keep_rng_at[i + 1] - 1].second * rb;
+        size_t k_room, v_room;
+        const MemKind kk = map_k.look(src_k[i], &k_room), kv = map.look(src_v[i], &v_room);
         if (kk == MemKind::kUnknown || kv == MemKind::kUnknown) any_unknown = true;
         if (kk == MemKind::kPinnedHost || kv == MemKind::kPinnedHost) any_host = true;
-        if (kk == MemKind::kDevice && !k_in)
+        if (k_room < (kk == MemKind::kDevice ? saved : read))
             return fail(ctx, CA_ERR_INVALID_ARG, "ca_kv_load_layer: K source of conversation %d is smaller than hist_len tokens", i);
-        if (kv == MemKind::kDevice && !v_in)
+        if (v_room < (kv == MemKind::kDevice ? saved : read))
             return fail(ctx, CA_ERR_INVALID_ARG, "ca_kv_load_layer: V source of conversation %d is smaller than hist_len tokens", i);
     }
     if (any_unknown)
@@ -1620,12 +1624,12 @@ ca_status ca_kv_save_layer(ca_ctx *ctx, int32_t layer, const int32_t *tok_begin,
         if (r[i].e == r[i].b) continue;
         if (!dst_k[i] || !dst_v[i]) return fail(ctx, CA_ERR_INVALID_ARG, "ca_kv_save_layer: destination of conversation %d is NULL", i);
         const size_t need = (size_t)(r[i].off + (r[i].e - r[i].b)) * rb;
-        bool k_in, v_in;
-        const MemKind kk = map_k.look(dst_k[i], need, &k_in), kv = map.look(dst_v[i], need, &v_in);
+        size_t k_room, v_room;
+        const MemKind kk = map_k.look(dst_k[i], &k_room), kv = map.look(dst_v[i], &v_room);
         if (kk == MemKind::kUnknown || kv == MemKind::kUnknown)
             return fail(ctx, CA_ERR_INVALID_ARG, "ca_kv_save_layer: destination of conversation %d is neither pinned host nor device memory", i);
         if (kk == MemKind::kPinnedHost || kv == MemKind::kPinnedHost) any_host = true;
-        if ((kk == MemKind::kDevice && !k_in) || (kv == MemKind::kDevice && !v_in))
+        if (k_room < need || v_room < need)
             return fail(ctx, CA_ERR_INVALID_ARG, "ca_kv_save_layer: destination of conversation %d is smaller than offset + count tokens", i);
         total += r[i].e - r[i].b;
     }
@@ -1721,12 +1725,12 @@ ca_status ca_kv_append_save_layer(ca_ctx *ctx, int32_t layer, const void *new_k,
     for (int i = 0; i < B; ++i) {
         if (!dst_k[i] || !dst_v[i]) return fail(ctx, CA_ERR_INVALID_ARG, "ca_kv_append_save_layer: destination of conversation %d is NULL", i);
         const size_t need = (size_t)(ctx->hist_len[i] + ctx->new_len[i]) * rb;
-        bool k_in, v_in;
-        const MemKind kk = map_k.look(dst_k[i], need, &k_in), kv = map.look(dst_v[i], need, &v_in);
+        size_t k_room, v_room;
+        const MemKind kk = map_k.look(dst_k[i], &k_room), kv = map.look(dst_v[i], &v_room);
         if (kk == MemKind::kUnknown || kv == MemKind::kUnknown)
             return fail(ctx, CA_ERR_INVALID_ARG, "ca_kv_append_save_layer: destination of conversation %d is neither pinned host nor device memory", i);
         if (kk == MemKind::kPinnedHost || kv == MemKind::kPinnedHost) any_host = true;
-        if ((kk == MemKind::kDevice && !k_in) || (kv == MemKind::kDevice && !v_in))
+        if (k_room < need || v_room < need)
             return fail(ctx, CA_ERR_INVALID_ARG, "ca_kv_append_save_layer: destination of conversation %d is smaller than hist_len + new_len tokens", i);
     }
     hipStream_t stream = (hipStream_t)stream_;

@@ -6,6 +6,8 @@ import numpy as np
 import pytest
 import torch
 
+import paper_2403_19708_amd as ca
+
 from harness import Case, GpuRun, torch_to_bits
 
 pytestmark = pytest.mark.gpu
@@ -119,5 +121,27 @@ def test_moves_across_the_link(heads, hist):
                 got = torch_to_bits(host[c])
                 assert np.array_equal(got[:case.hist_len[c]], case.tensor(0, f"{which}_hist", c)), (which, c)
                 assert np.array_equal(got[case.hist_len[c]:], case.tensor(0, f"{which}_new", c)), (which, c)
+    finally:
+        run.close()
+
+
+@pytest.mark.parametrize("hist,new", [(40, 2), (900, 200)], ids=["short", "long"])
+def test_a_pinned_tier_that_ends_too_early_is_refused(hist, new):
+    """the runtime knows where pinned memory ends: one row less than a call needs, and nothing is launched"""
+    case = Case([hist], [new], [0], 4, 2, 128, seed=86, window=2048)
+    row = 2 * 128 * 2
+    run = GpuRun(case, tier="pinned")
+    try:
+        block = torch.empty(1 << 21, dtype=torch.uint8, pin_memory=True)          # the allocator's blocks are powers of two
+        end = block.data_ptr() + block.numel()
+        run.rebase()
+        for rows, call in ((hist, lambda p: run.ctx.kv_load_layer(0, p, p, run.k_pool[0], run.v_pool[0])),
+                           (hist + new, lambda p: run.ctx.kv_save_layer(0, run.k_pool[0], run.v_pool[0], p, p)),
+                           (hist + new, lambda p: run.ctx.kv_append_save_layer(0, run.k_new[0], run.v_new[0], run.k_pool[0], run.v_pool[0], p, p))):
+            with pytest.raises(ca.CaError) as e:
+                call([end - (rows - 1) * row])
+            assert e.value.status_name == "CA_ERR_INVALID_ARG"
+            call([end - rows * row])
+        run.finish()
     finally:
         run.close()

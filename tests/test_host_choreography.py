@@ -59,3 +59,49 @@ def test_a_plan_waits_for_the_last_one_after_a_join_with_another_gpu_current(m):
     t.ctx.join(None)
     plan, = m.queued(t.rebase)
     assert m.behind(plan, load)
+
+
+# ---- a tier that is too small --------------------------------------------------------------------------------
+def refused(m, call):
+    import paper_2403_19708_amd as ca
+    at = m.lib.model_ops()
+    with pytest.raises(ca.CaError) as e:
+        call()
+    assert e.value.status_name == "CA_ERR_INVALID_ARG" and m.lib.model_ops() == at       # nothing was queued
+
+
+@pytest.mark.parametrize("tier", [0, 1], ids=["device", "pinned"])
+@pytest.mark.parametrize("mode", [0, 1, 2])
+@pytest.mark.parametrize("hist,new", [(40, 2), (4000, 200)], ids=["short", "long"])
+@in_model
+def test_a_tier_that_is_too_small_is_refused(m, hist, new, mode, tier):
+    fits = Turn(m, [5, hist], [3, new], tier=tier, load_mode=mode, save_mode=mode)
+    fits.rebase()
+    fits.load(); fits.append(); fits.save(); fits.append_save()
+    t = Turn(m, [5, hist], [3, new], tier=tier, tier_rows=[8, hist + new - 1], load_mode=mode, save_mode=mode)
+    t.rebase()
+    t.load()
+    refused(m, t.save)
+    refused(m, t.append_save)
+    t = Turn(m, [5, hist], [3, new], tier=tier, tier_rows=[8, hist - 1], load_mode=mode)
+    t.rebase()
+    refused(m, t.load)
+
+
+@in_model
+def test_a_pinned_tier_has_to_hold_what_is_read(m):
+    """the end of the history is discarded: its rows need not be there in pinned memory (device memory holds the history)"""
+    for tier in (1, 0):
+        t = Turn(m, [4000], [200], tier=tier, tier_rows=[3000])
+        t.rebase(keep_ranges=[[(0, 4), (1000, 3000)]])
+        if tier:
+            assert len(m.queued(t.load)) == 1
+        else:
+            refused(m, t.load)
+
+
+@in_model
+def test_pinned_memory_of_unknown_extent_is_taken(m):
+    t = Turn(m, [4000, 30], [200, 1], tier=2)
+    t.rebase()
+    assert len(m.queued(lambda: (t.load(), t.append_save()))) == 3
