@@ -210,15 +210,21 @@ int64_t row_bytes(const ca_config &c) { return (int64_t)c.n_kv_heads * c.head_di
 
 enum class MemKind { kDevice, kPinnedHost, kUnknown };
 
-MemKind mem_kind(const void *p) {
+// *shift = where the GPU addresses p, as a distance from p: zero but for host memory that was allocated without the runtime and
+// registered with it later, for which the two addresses may differ
+MemKind mem_kind(const void *p, ptrdiff_t *shift) {
     hipPointerAttribute_t attr;
+    *shift = 0;
     hipError_t e = hipPointerGetAttributes(&attr, p);
     if (e != hipSuccess) {
         (void)hipGetLastError();
         return MemKind::kUnknown;
     }
     if (attr.type == hipMemoryTypeDevice) return MemKind::kDevice;
-    if (attr.type == hipMemoryTypeHost) return MemKind::kPinnedHost;
+    if (attr.type == hipMemoryTypeHost) {
+        if (attr.devicePointer) *shift = (const uint8_t *)attr.devicePointer - (const uint8_t *)p;
+        return MemKind::kPinnedHost;
+    }
     if (attr.type == hipMemoryTypeManaged) return MemKind::kDevice;
     return MemKind::kUnknown;
 }
@@ -228,15 +234,19 @@ MemKind mem_kind(const void *p) {
 // (never longer, an allocation may be gone by the next one).
 class MemMap {
 public:
-    // kind of p; *room = bytes from p to the end of its allocation (SIZE_MAX where the runtime cannot tell)
-    MemKind look(const void *p, size_t *room) {
+    // kind of p; *room = bytes from p to the end of its allocation (SIZE_MAX where the runtime cannot tell); *gpu = p as the GPU
+    // addresses it
+    MemKind look(const void *p, size_t *room, uint8_t **gpu) {
         const uint8_t *q = (const uint8_t *)p;
         if (base_ && q >= base_ && q < base_ + size_) {
             *room = (size_t)(base_ + size_ - q);
+            *gpu = const_cast<uint8_t *>(q) + shift_;
             return kind_;
         }
-        const MemKind k = mem_kind(p);
+        ptrdiff_t shift;
+        const MemKind k = mem_kind(p, &shift);
         *room = SIZE_MAX;
+        *gpu = const_cast<uint8_t *>(q) + shift;
         if (k == MemKind::kUnknown) return k;
         hipDeviceptr_t base = nullptr;
         size_t size = 0;
@@ -249,20 +259,22 @@ public:
             if (k == MemKind::kDevice) *room = 0;
             return k;
         }
-        base_ = b; size_ = size; kind_ = k;
+        base_ = b; size_ = size; kind_ = k; shift_ = shift;
         *room = (size_t)(b + size - q);
         return k;
     }
     // true if [p, p+bytes) lies inside one device allocation
     bool device_range_ok(const void *p, size_t bytes) {
         size_t room = 0;
-        return p && look(p, &room) == MemKind::kDevice && bytes <= room;
+        uint8_t *gpu;
+        return p && look(p, &room, &gpu) == MemKind::kDevice && bytes <= room;
     }
 
 private:
     const uint8_t *base_ = nullptr;
     size_t size_ = 0;
     MemKind kind_ = MemKind::kUnknown;
+    ptrdiff_t shift_ = 0;
 };
 
 // ---- which stream a move runs on, and what waits for it ---------------------------------------------------------
@@ -1470,6 +1482,7 @@ ca_status ca_kv_load_layer(ca_ctx *ctx, int32_t layer, const void *const *src_k,
     const int B = ctx->n_seqs;
     const int64_t rb = row_bytes(c);
     bool any_host = false, any_unknown = false;
+    std::vector<uint8_t *> gpu_k(B), gpu_v(B);      // the sources as a kernel reads them
     MemMap map_k;          // (keys and values may be in an allocation each)
     for (int i = 0; i < B; ++i) {
         if (ctx->n_keep[i] == 0) continue;
@@ -1477,7 +1490,7 @@ ca_status ca_kv_load_layer(ca_ctx *ctx, int32_t layer, const void *const *src_k,
         // device memory holds the saved history; of pinned memory only what is read has to be there, up to the last kept range
         const size_t saved = (size_t)ctx->hist_len[i] * rb, read = (size_t)ctx->keep_rng[ctx->keep_rng_at[i + 1] - 1].second * rb;
         size_t k_room, v_room;
-        const MemKind kk = map_k.look(src_k[i], &k_room), kv = map.look(src_v[i], &v_room);
+        const MemKind kk = map_k.look(src_k[i], &k_room, &gpu_k[i]), kv = map.look(src_v[i], &v_room, &gpu_v[i]);
         if (kk == MemKind::kUnknown || kv == MemKind::kUnknown) any_unknown = true;
         if (kk == MemKind::kPinnedHost || kv == MemKind::kPinnedHost) any_host = true;
         if (k_room < (kk == MemKind::kDevice ? saved : read))
@@ -1547,7 +1560,7 @@ ca_status ca_kv_load_layer(ca_ctx *ctx, int32_t layer, const void *const *src_k,
             int32_t at = 0;      // context token the range starts at
             for (int r = ctx->keep_rng_at[i]; r < ctx->keep_rng_at[i + 1]; ++r) {
                 const int32_t len = ctx->keep_rng[r].second - ctx->keep_rng[r].first;
-                segs.push_back({(uint8_t *)src_k[i], (uint8_t *)src_v[i], ctx->keep_rng[r].first, at, len, i});
+                segs.push_back({gpu_k[i], gpu_v[i], ctx->keep_rng[r].first, at, len, i});
                 at += len;
             }
         }
@@ -1610,6 +1623,7 @@ ca_status ca_kv_save_layer(ca_ctx *ctx, int32_t layer, const int32_t *tok_begin,
     const int64_t rb = row_bytes(c);
     struct Range { int32_t b, e; int64_t off; };
     std::vector<Range> r(B);
+    std::vector<uint8_t *> gpu_k(B), gpu_v(B);      // the destinations as a kernel writes them
     bool any_host = false;
     int64_t total = 0;
     for (int i = 0; i < B; ++i) {
@@ -1625,7 +1639,7 @@ ca_status ca_kv_save_layer(ca_ctx *ctx, int32_t layer, const int32_t *tok_begin,
         if (!dst_k[i] || !dst_v[i]) return fail(ctx, CA_ERR_INVALID_ARG, "ca_kv_save_layer: destination of conversation %d is NULL", i);
         const size_t need = (size_t)(r[i].off + (r[i].e - r[i].b)) * rb;
         size_t k_room, v_room;
-        const MemKind kk = map_k.look(dst_k[i], &k_room), kv = map.look(dst_v[i], &v_room);
+        const MemKind kk = map_k.look(dst_k[i], &k_room, &gpu_k[i]), kv = map.look(dst_v[i], &v_room, &gpu_v[i]);
         if (kk == MemKind::kUnknown || kv == MemKind::kUnknown)
             return fail(ctx, CA_ERR_INVALID_ARG, "ca_kv_save_layer: destination of conversation %d is neither pinned host nor device memory", i);
         if (kk == MemKind::kPinnedHost || kv == MemKind::kPinnedHost) any_host = true;
@@ -1686,7 +1700,7 @@ ca_status ca_kv_save_layer(ca_ctx *ctx, int32_t layer, const int32_t *tok_begin,
         for (int i = 0; i < B; ++i) {
             const int32_t cnt = r[i].e - r[i].b;
             if (cnt == 0) continue;
-            segs.push_back({(uint8_t *)dst_k[i], (uint8_t *)dst_v[i], r[i].off, r[i].b, cnt, i});
+            segs.push_back({gpu_k[i], gpu_v[i], r[i].off, r[i].b, cnt, i});
         }
         int iv_pack;
         CA_HIP(ctx, prof_begin(ctx, kProfPack, saver, &iv_pack));
@@ -1721,12 +1735,13 @@ ca_status ca_kv_append_save_layer(ca_ctx *ctx, int32_t layer, const void *new_k,
     if (!map.device_range_ok(new_k, bytes) || !map.device_range_ok(new_v, bytes))
         return fail(ctx, CA_ERR_INVALID_ARG, "ca_kv_append_save_layer: new_k/new_v must be device memory of %zu bytes", bytes);
     const int B = ctx->n_seqs;
+    std::vector<uint8_t *> gpu_k(B), gpu_v(B);      // the destinations as a kernel writes them
     bool any_host = false;
     for (int i = 0; i < B; ++i) {
         if (!dst_k[i] || !dst_v[i]) return fail(ctx, CA_ERR_INVALID_ARG, "ca_kv_append_save_layer: destination of conversation %d is NULL", i);
         const size_t need = (size_t)(ctx->hist_len[i] + ctx->new_len[i]) * rb;
         size_t k_room, v_room;
-        const MemKind kk = map_k.look(dst_k[i], &k_room), kv = map.look(dst_v[i], &v_room);
+        const MemKind kk = map_k.look(dst_k[i], &k_room, &gpu_k[i]), kv = map.look(dst_v[i], &v_room, &gpu_v[i]);
         if (kk == MemKind::kUnknown || kv == MemKind::kUnknown)
             return fail(ctx, CA_ERR_INVALID_ARG, "ca_kv_append_save_layer: destination of conversation %d is neither pinned host nor device memory", i);
         if (kk == MemKind::kPinnedHost || kv == MemKind::kPinnedHost) any_host = true;
@@ -1748,7 +1763,7 @@ ca_status ca_kv_append_save_layer(ca_ctx *ctx, int32_t layer, const void *new_k,
             std::vector<Segment> segs;
             for (int i = 0; i < B; ++i)
                 if (ctx->new_len[i] > 0)
-                    segs.push_back({(uint8_t *)dst_k[i], (uint8_t *)dst_v[i], ctx->hist_len[i], ctx->n_keep[i], ctx->new_len[i], i});
+                    segs.push_back({gpu_k[i], gpu_v[i], ctx->hist_len[i], ctx->n_keep[i], ctx->new_len[i], i});
             if (ctx->loaded[layer]) CA_HIP(ctx, after_load(ctx, layer, ctx->s_save));
             CA_HIP(ctx, prof_begin(ctx, kProfPack, ctx->s_save, &iv));
             st = run_move(ctx, false, segs, k_pool, v_pool, ctx->s_save, kLinkSaveWorkgroups);
@@ -1775,8 +1790,8 @@ ca_status ca_kv_append_save_layer(ca_ctx *ctx, int32_t layer, const void *new_k,
         MoveArgs2 second;
         const int n = std::min(kMaxSeqsPerLaunch, B - at);
         for (int i = 0; i < n; ++i) {       // new token j is saved behind the history, at token hist_len + j
-            second.dst_k[i] = (uint8_t *)dst_k[at + i] + (size_t)ctx->hist_len[at + i] * rb;
-            second.dst_v[i] = (uint8_t *)dst_v[at + i] + (size_t)ctx->hist_len[at + i] * rb;
+            second.dst_k[i] = gpu_k[at + i] + (size_t)ctx->hist_len[at + i] * rb;
+            second.dst_v[i] = gpu_v[at + i] + (size_t)ctx->hist_len[at + i] * rb;
         }
         CA_HIP(ctx, launch_append_save(new_turn_shape(ctx, at, n), at, second, (const uint8_t *)new_k, (const uint8_t *)new_v,
                                        (uint8_t *)k_pool, (uint8_t *)v_pool, stream));

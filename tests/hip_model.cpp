@@ -32,7 +32,7 @@ struct Op {
     std::string what;
     Stream *stream;
     std::set<int> behind;
-    std::vector<char> args;    // attention kernels: their AttnArgs
+    std::vector<char> args;    // attention kernels: their AttnArgs; moves: their MoveArgs or MoveArgs2
 };
 struct Range {
     size_t size;
@@ -184,7 +184,11 @@ hipError_t hipLaunchKernel(const void *f, dim3, dim3, void **args, size_t, hipSt
     if (!x) return hipErrorInvalidHandle;
     if (launches_until_failure >= 0 && launches_until_failure-- == 0) return hipErrorLaunchFailure;
     const int op = queue(kernels[f], x);
-    if (ops[op].what.find("8AttnArgs") != std::string::npos) ops[op].args.assign((char *)args[0], (char *)args[0] + sizeof(ca::AttnArgs));
+    const std::string &name = ops[op].what;
+    const size_t bytes = name.find("8AttnArgs") != std::string::npos ? sizeof(ca::AttnArgs)
+                         : name.find("9MoveArgs2") != std::string::npos ? sizeof(ca::MoveArgs2)
+                         : name.find("8MoveArgs") != std::string::npos ? sizeof(ca::MoveArgs) : 0;
+    ops[op].args.assign((char *)args[0], (char *)args[0] + bytes);
     return hipSuccess;
 }
 
@@ -206,6 +210,17 @@ void *model_attn_pointer(int op, int which) {
     MODEL;
     const ca::AttnArgs *a = (const ca::AttnArgs *)ops[op].args.data();
     return which == 0 ? (void *)a->partial : (void *)a->arrived;
+}
+
+// the tier pointers of conversation i of a move (keys, values)
+void *model_move_pointer(int op, int i, int values) {
+    MODEL;
+    if (ops[op].args.size() == sizeof(ca::MoveArgs2)) {
+        const ca::MoveArgs2 *a = (const ca::MoveArgs2 *)ops[op].args.data();
+        return values ? a->dst_v[i] : a->dst_k[i];
+    }
+    const ca::MoveArgs *a = (const ca::MoveArgs *)ops[op].args.data();
+    return values ? a->contig_v[i] : a->contig_k[i];
 }
 
 }  // extern "C"

@@ -7,7 +7,6 @@ import pytest
 import torch
 
 import paper_2403_19708_amd as ca
-
 from harness import Case, GpuRun, torch_to_bits
 
 pytestmark = pytest.mark.gpu

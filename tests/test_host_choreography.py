@@ -100,8 +100,17 @@ def test_a_pinned_tier_has_to_hold_what_is_read(m):
             refused(m, t.load)
 
 
+REGISTERED = 2          # host memory the GPU addresses 2^40 bytes further on; the runtime does not know its extent
+
+
+@pytest.mark.parametrize("hist,new", [(40, 2), (4000, 200)], ids=["short", "long"])
 @in_model
-def test_pinned_memory_of_unknown_extent_is_taken(m):
-    t = Turn(m, [4000, 30], [200, 1], tier=2)
+def test_kernels_reach_registered_memory_where_the_gpu_has_it(m, hist, new):
+    t = Turn(m, [5, hist], [3, new], tier=REGISTERED)
     t.rebase()
-    assert len(m.queued(lambda: (t.load(), t.append_save()))) == 3
+    for call in (t.load, t.save, t.append_save):
+        op = m.queued(call)[-1]
+        for c in range(2):
+            at = int(t.hist[c]) * t.row if "append_save" in m.what(op) else 0
+            assert m.lib.model_move_pointer(op, c, 0) == t.tk[c] + (1 << 40) + at, m.what(op)
+            assert m.lib.model_move_pointer(op, c, 1) == t.tv[c] + (1 << 40) + at
