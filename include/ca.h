@@ -235,7 +235,10 @@ ca_status ca_kv_append_layer(ca_ctx *ctx, int32_t layer, const void *new_k, cons
 /* out[j, h, :] = sum_t softmax_t( RoPE(q[j,h], n_keep+j) . RoPE(k[t, h/G], t) * softmax_scale ) v[t, h/G]
  * over context tokens t <= n_keep + j of the same conversation.  The rotary encoding is applied
  * to keys as they are read from the pool; the pool is not modified.  bf16 in, fp32 accumulate,
- * bf16 out.  q, out: device.  Waits (on `stream`) for the load of `layer` if one was issued.   */
+ * bf16 out.  q, out: device.  Waits (on `stream`) for the load of `layer` if one was issued.
+ * Partial results of a plan that splits keys are kept in one buffer of the context: calls of this
+ * entry point on one context must not overlap in time (one stream, or streams that wait for each
+ * other).  A call of the _static entry point below may run beside one of this.                  */
 ca_status ca_cached_prefill_attn(ca_ctx *ctx, int32_t layer, const void *q, const void *k_pool,
                                  const void *v_pool, void *out, float softmax_scale, void *stream);
 
@@ -249,7 +252,8 @@ ca_status ca_cached_prefill_attn(ca_ctx *ctx, int32_t layer, const void *q, cons
  * 32 MiB (n_shares * tile_rows * (head_dim + 2) * 4 bytes) is refused with CA_ERR_OUT_OF_RANGE
  * and nothing is launched.  Every call on a GPU, from any context, uses that GPU's one array:
  * calls that overlap in time on one GPU race (serialise them on one stream); nothing in the array
- * needs clearing between calls, every share is written before it is read.                      */
+ * needs clearing between calls, every share is written before it is read.  (What counts the shares
+ * that have arrived is the context's, set to zero with every plan and by every call that ends.)   */
 ca_status ca_cached_prefill_attn_static(ca_ctx *ctx, int32_t layer, const void *q, const void *k_pool,
                                         const void *v_pool, void *out, float softmax_scale, void *stream);
 

@@ -73,15 +73,12 @@ __device__ inline f32x4 load_agent4(const float *p) {
     return f32x4{lo.x, lo.y, hi.x, hi.y};
 }
 // Counts a workgroup in whose stores of this kind are done; true in the one that is the n-th (which may then read the
-// others').  Called by every thread of the workgroup; `flag` is in LDS.  The count is back at zero afterwards.
-__device__ inline bool arrive_last(int32_t *count, int n, int32_t *flag) {
+// others').  Called by every thread of the workgroup; `flag` is in LDS.  The n-th brings the count back to zero in the same
+// atomic operation: no count in between can be lost.
+__device__ inline bool arrive_last(uint32_t *count, int n, int32_t *flag) {
     CA_WAIT_VMCNT(0);                              // this wavefront's stores have been acknowledged
     __syncthreads();
-    if (threadIdx.x == 0) {
-        const int32_t before = __hip_atomic_fetch_add(count, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-        if (before == n - 1) __hip_atomic_store(count, 0, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-        *flag = before == n - 1;
-    }
+    if (threadIdx.x == 0) *flag = atomicInc(count, (unsigned)(n - 1)) == (unsigned)(n - 1);
     __syncthreads();
     return *flag != 0;
 }

@@ -71,6 +71,8 @@ struct RebaseArgs {
     int32_t *q_pos;              // device [sum new]
     int32_t *q_seq;              // device [sum new]
     int32_t *slot_map;           // device [sum context]
+    uint32_t *arrived[2];        // merge counters of the two attention entry points: the first n_merges of each are set to zero
+    int32_t n_merges;
 };
 hipError_t launch_rebase(const RebaseArgs &args, hipStream_t stream);
 
@@ -134,7 +136,7 @@ struct AttnArgs {
     const RowsItem *rows_items;  // launch_attn_rows
     const int32_t *wg_first;     // launch_attn_rows, four wavefronts: workgroup w takes items [wg_first[w], wg_first[w + 1]);
                                  // eight: workgroup w takes item w
-    int32_t *arrived;            // launch_attn_rows: shares of each merge that are there already; zero between calls
+    uint32_t *arrived;           // launch_attn_rows: shares of each merge that are there already; zero between calls
     int32_t n_wgs;
     int32_t n_combine;
     int32_t total_q;

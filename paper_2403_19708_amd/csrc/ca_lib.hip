@@ -91,10 +91,11 @@ struct ca_ctx {
     bool has_plan = false;
     int32_t n_seqs = 0, max_pages = 0, num_pages = 0, n_items = 0, n_combine = 0, tile_rows = 128;
     int32_t max_unit_rows = 0;   // most stacked query rows of any (conversation, kv head) of the plan
-    // plan of the few-rows kernel (launch_attn_rows): its workgroups' item ranges, and one counter per merge (zero between calls)
+    // plan of the few-rows kernel (launch_attn_rows): its workgroups' item ranges, and one counter per merge for each of the
+    // two attention entry points, which may run at once (zero between calls, and set to zero with every plan)
     int32_t n_wgs = 0, wg_wavefronts = 0;
     size_t off_wg_first = 0, off_rows_items = 0;
-    int32_t *arrived = nullptr;
+    uint32_t *arrived = nullptr, *static_arrived = nullptr;
     int32_t n_split_parts = 0;   // shares of split row tiles of the plan (slots of the partial-result buffer in use)
     float *static_partial = nullptr;   // this device's copy of the static scratch array (ca_cached_prefill_attn_static)
     int64_t total_q = 0, total_k = 0, total_n = 0;
@@ -799,8 +800,8 @@ static ca_status create_impl(ca_ctx *ctx) {
     if (may_split) {
         const size_t bytes = (size_t)kAttnMaxParts * 256 * (size_t)(c.head_dim + 2) * sizeof(float);
         CA_HIP(ctx, hipMalloc((void **)&ctx->partial, bytes));
-        CA_HIP(ctx, hipMalloc((void **)&ctx->arrived, (size_t)kAttnMaxParts * sizeof(int32_t)));
-        CA_HIP(ctx, hipMemset(ctx->arrived, 0, (size_t)kAttnMaxParts * sizeof(int32_t)));
+        CA_HIP(ctx, hipMalloc((void **)&ctx->arrived, (size_t)2 * kAttnMaxParts * sizeof(uint32_t)));
+        ctx->static_arrived = ctx->arrived + kAttnMaxParts;
     }
     const bool may_direct = direct_variant(c);
     if (may_direct && c.attn_prerotate != 1) {
@@ -1312,6 +1313,9 @@ ca_status ca_rope_rebase(ca_ctx *ctx, const ca_batch *b, void *stream_) {
     ra.q_pos = (int32_t *)(ctx->d_meta + ctx->off_q_pos);
     ra.q_seq = (int32_t *)(ctx->d_meta + ctx->off_q_seq);
     ra.slot_map = (int32_t *)(ctx->d_meta + ctx->off_slot_map);
+    ra.arrived[0] = ctx->arrived;
+    ra.arrived[1] = ctx->static_arrived;
+    ra.n_merges = ctx->n_wgs > 0 ? ctx->n_combine : 0;
     CA_HIP(ctx, launch_rebase(ra, stream));
 
     // internal streams start work of this plan only after the metadata exists (each waits when it is first used)
@@ -1805,10 +1809,10 @@ ca_status ca_kv_append_save_layer(ca_ctx *ctx, int32_t layer, const void *new_k,
 // ----------------------------------------------------------------------------------------------
 // Sections 2.1 / 3.1 / 3.4: attention of the new tokens
 // ----------------------------------------------------------------------------------------------
-// partial: where the shares of split row tiles go (the context's buffer, or the static scratch array);
+// partial, arrived: where the shares of split row tiles go and are counted (the context's buffer, or the static scratch array);
 // timed: bracket the launch with profiling events when profiling is on (creating an event may allocate)
 static ca_status attn_impl(ca_ctx *ctx, int32_t layer, const void *q, const void *k_pool, const void *v_pool, void *out,
-                           float softmax_scale, void *stream_, float *partial, bool timed) {
+                           float softmax_scale, void *stream_, float *partial, uint32_t *arrived, bool timed) {
     ca_status st = check_layer_plan(ctx, "ca_cached_prefill_attn", layer);
     if (st != CA_OK) return st;
     const ca_config &c = ctx->cfg;
@@ -1855,7 +1859,7 @@ static ca_status attn_impl(ca_ctx *ctx, int32_t layer, const void *q, const void
     a.n_items = ctx->n_items;
     a.wg_first = (const int32_t *)(ctx->d_meta + ctx->off_wg_first);
     a.rows_items = (const RowsItem *)(ctx->d_meta + ctx->off_rows_items);
-    a.arrived = ctx->arrived;
+    a.arrived = arrived;
     a.n_wgs = ctx->n_wgs;
     a.total_q = (int32_t)ctx->total_q;
     a.max_pages = ctx->max_pages;
@@ -1897,7 +1901,7 @@ static ca_status attn_impl(ca_ctx *ctx, int32_t layer, const void *q, const void
 ca_status ca_cached_prefill_attn(ca_ctx *ctx, int32_t layer, const void *q, const void *k_pool, const void *v_pool,
                                  void *out, float softmax_scale, void *stream) {
     if (!ctx) return CA_ERR_INVALID_ARG;
-    return attn_impl(ctx, layer, q, k_pool, v_pool, out, softmax_scale, stream, ctx->partial, true);
+    return attn_impl(ctx, layer, q, k_pool, v_pool, out, softmax_scale, stream, ctx->partial, ctx->arrived, true);
 }
 
 ca_status ca_cached_prefill_attn_static(ca_ctx *ctx, int32_t layer, const void *q, const void *k_pool, const void *v_pool,
@@ -1911,7 +1915,7 @@ ca_status ca_cached_prefill_attn_static(ca_ctx *ctx, int32_t layer, const void *
             return fail(ctx, CA_ERR_OUT_OF_RANGE, "ca_cached_prefill_attn_static: the plan's %d shares of split row tiles need %zu bytes of "
                         "partial results, the static scratch holds %zu", ctx->n_split_parts, need, kStaticScratchBytes);
     }
-    return attn_impl(ctx, layer, q, k_pool, v_pool, out, softmax_scale, stream, ctx->static_partial, false);
+    return attn_impl(ctx, layer, q, k_pool, v_pool, out, softmax_scale, stream, ctx->static_partial, ctx->static_arrived, false);
 }
 
 // ----------------------------------------------------------------------------------------------

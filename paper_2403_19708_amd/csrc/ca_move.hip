@@ -202,6 +202,7 @@ __global__ __launch_bounds__(kRebaseThreads) void rebase_kernel(RebaseArgs a, in
         const vec16 *src = reinterpret_cast<const vec16 *>(a.image);
         vec16 *dst = reinterpret_cast<vec16 *>(a.meta);
         for (int64_t i = (int64_t)blockIdx.x * kRebaseThreads + threadIdx.x; i < a.image_vecs; i += (int64_t)copy_wgs * kRebaseThreads) dst[i] = src[i];
+        for (int i = blockIdx.x * kRebaseThreads + threadIdx.x; i < a.n_merges; i += copy_wgs * kRebaseThreads) a.arrived[0][i] = a.arrived[1][i] = 0;
         return;
     }
     const int at = blockIdx.x - copy_wgs;

@@ -5,6 +5,7 @@ key splitting on and off, runs of pages that cover many units and units cut into
 (the merge counters must be back at zero)."""
 import numpy as np
 import pytest
+import torch
 
 from harness import Case, GpuRun, torch_to_bits
 from test_gpu_parity import check_contract, check_tight
@@ -73,3 +74,28 @@ def test_runs_over_many_units():
 def test_peaky_scores():
     case = Case([500, 77], [1, 1], [0, 0], 8, 1, 128, seed=64, window=1024, q_scale=2.0)
     run_case(case, tight=False)      # (softmax on a few keys: the rounding of the rotated operands is over the tighter bar)
+
+
+def test_the_two_entry_points_at_once():
+    """an ordinary and a static call of one context on two streams, again and again: scratch and counters are their own"""
+    case = Case([9000, 700, 4100], [1] * 3, [0, 0, 37], 8, 1, 128, seed=65, window=16384)
+    run = GpuRun(case, tier="device")
+    try:
+        run.rebase()
+        run.load(0)
+        run.append(0)
+        run.attn(0)
+        run.finish()
+        want = torch_to_bits(run.out[0]).copy()
+        streams = torch.cuda.Stream(), torch.cuda.Stream()
+        outs = [[torch.zeros_like(run.out[0]) for _ in range(50)] for _ in streams]
+        torch.cuda.synchronize()
+        s = 1.0 / np.sqrt(case.head_dim)
+        for a, b in zip(*outs):
+            run.ctx.cached_prefill_attn(0, run.q[0], run.k_pool[0], run.v_pool[0], a, s, streams[0])
+            run.ctx.cached_prefill_attn_static(0, run.q[0], run.k_pool[0], run.v_pool[0], b, s, streams[1])
+        torch.cuda.synchronize()
+        for out in outs[0] + outs[1]:
+            assert np.array_equal(torch_to_bits(out), want)
+    finally:
+        run.close()

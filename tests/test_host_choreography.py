@@ -114,3 +114,16 @@ def test_kernels_reach_registered_memory_where_the_gpu_has_it(m, hist, new):
             at = int(t.hist[c]) * t.row if "append_save" in m.what(op) else 0
             assert m.lib.model_move_pointer(op, c, 0) == t.tk[c] + (1 << 40) + at, m.what(op)
             assert m.lib.model_move_pointer(op, c, 1) == t.tv[c] + (1 << 40) + at
+
+
+# ---- scratch of the two attention entry points -----------------------------------------------------------------
+@in_model
+def test_the_two_attention_entry_points_share_no_scratch(m):
+    """a plan of the few-rows kernel that splits keys: partial results and merge counters are an entry point's own"""
+    t = Turn(m, [9000, 50], [1, 1], heads=(8, 1, 128), require_load=0)
+    t.rebase()
+    ordinary, static = m.queued(lambda: (t.attn(), t.attn(static=True)))
+    assert "attn_rows_kernel" in m.what(ordinary)
+    for which in range(2):
+        a, b = m.lib.model_attn_pointer(ordinary, which), m.lib.model_attn_pointer(static, which)
+        assert a and b and a != b
