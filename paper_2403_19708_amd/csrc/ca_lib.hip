@@ -7,6 +7,7 @@
 #include "ca_internal.h"
 
 #include <algorithm>
+#include <atomic>
 #include <cmath>
 #include <cstdarg>
 #include <cstdio>
@@ -56,6 +57,7 @@ struct ca_ctx {
     // the default stream, which outlives the context and can be asked or recorded on when it matters)
     bool inline_pending = false;
     hipStream_t inline_stream = nullptr;
+    uint64_t inline_owner = 0;         // see stream_owner
     hipEvent_t inline_done = nullptr, ev_inline = nullptr;
     hipStream_t plan_stream = nullptr; // the stream ca_rope_rebase was given
     std::vector<uint8_t> ready_inline; // per layer: loaded on the plan's stream
@@ -297,9 +299,18 @@ bool stream_alive(hipStream_t stream) {
     return e == hipErrorNotReady;
 }
 
+// hipStreamPerThread is one handle for a stream in each thread: a number of the calling thread's own, 0 for other streams
+uint64_t stream_owner(hipStream_t stream) {
+    static std::atomic<uint64_t> threads{0};
+    static thread_local uint64_t own = 0;
+    if (stream != hipStreamPerThread) return 0;
+    if (own == 0) own = ++threads;
+    return own;
+}
+
 // May the next short move run on `stream`?  Only one stream's inline moves are kept track of at a time.
 bool inline_free(ca_ctx *ctx, hipStream_t stream) {
-    if (!ctx->inline_pending || ctx->inline_stream == stream) return true;
+    if (!ctx->inline_pending || (ctx->inline_stream == stream && ctx->inline_owner == stream_owner(stream))) return true;
     if (ctx->inline_stream != nullptr ? hipEventQuery(ctx->inline_done) == hipSuccess : hipStreamQuery(nullptr) == hipSuccess) {
         ctx->inline_pending = false;
         return true;
@@ -312,6 +323,7 @@ bool inline_free(ca_ctx *ctx, hipStream_t stream) {
 void note_inline(ca_ctx *ctx, hipStream_t stream, hipEvent_t done) {
     ctx->inline_pending = true;
     ctx->inline_stream = stream;
+    ctx->inline_owner = stream_owner(stream);
     ctx->inline_done = done;
 }
 

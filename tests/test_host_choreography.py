@@ -127,3 +127,25 @@ def test_the_two_attention_entry_points_share_no_scratch(m):
     for which in range(2):
         a, b = m.lib.model_attn_pointer(ordinary, which), m.lib.model_attn_pointer(static, which)
         assert a and b and a != b
+
+
+# ---- one stream handle, several streams -------------------------------------------------------------------------
+@pytest.mark.parametrize("fused", [False, True], ids=["save", "append-save"])
+@in_model
+def test_short_moves_of_two_threads_on_their_own_default_streams(m, fused):
+    """hipStreamPerThread is one handle for a stream in each thread: a context handed on keeps track of both"""
+    import threading
+    t = Turn(m, [0], [2], tier=1)
+    t.rebase(PER_THREAD)
+    t.append(PER_THREAD)
+    call = (lambda: t.append_save(PER_THREAD)) if fused else (lambda: t.save(PER_THREAD))
+    saves = []
+    for _ in range(2):
+        thread = threading.Thread(target=lambda: saves.append(m.queued(call)[-1]))
+        thread.start()
+        thread.join()
+    s = m.stream()
+    t.ctx.join(s)
+    assert all(m.stream_behind(s, op) for op in saves)
+    t.ctx.sync()
+    assert all(m.done(op) for op in saves)
