@@ -276,15 +276,17 @@ ca_status ca_kv_save_layer(ca_ctx *ctx, int32_t layer, const int32_t *tok_begin,
  * what is appended, keys without positional encoding (Sections 3.2.2, 3.4), so the pool is not read
  * back.  Device destinations, and pinned ones of at most 128 KB or under save_mode 2: one kernel on
  * `stream` stores every vector twice, to its page and to its row of the tier.  Pinned destinations
- * otherwise: the append kernel runs on `stream`; then the pack kernel follows on the internal save
- * stream and writes the tier in place, or with save_mode 1 one copy per conversation straight from
+ * otherwise (and every destination while a short move on another stream is under way): the append
+ * kernel runs on `stream`; then the pack kernel follows on the internal save stream and writes the
+ * tier in place, or with save_mode 1 one copy per conversation straight from
  * new_k / new_v (no pack kernel, no staging slot; new_k / new_v must then stay unchanged until
  * ca_sync or ca_join).  Same arguments, checks and statuses as the two calls it replaces.          */
 ca_status ca_kv_append_save_layer(ca_ctx *ctx, int32_t layer, const void *new_k, const void *new_v,
                                   void *k_pool, void *v_pool, void *const *dst_k, void *const *dst_v,
                                   void *stream);
 
-/* Blocks the host until every load and save queued so far is done. */
+/* Blocks the host until every load and save queued so far is done (what was queued into a graph under
+ * capture is the caller's to wait for). */
 ca_status ca_sync(ca_ctx *ctx);
 
 /* Makes `stream` wait (device side) for every load and save queued so far.  NULL: the default stream

@@ -290,6 +290,15 @@ constexpr int64_t kInlineDeviceBytes = (int64_t)16 << 20;
 constexpr int64_t kInlineHostSaveBytes = (int64_t)128 << 10;
 constexpr int64_t kInlineHostLoadBytes = (int64_t)512 << 10;
 
+// Work queued on a stream that is being captured becomes part of a graph: the caller orders it where the graph is launched, and
+// nothing outside can wait for it.
+bool is_captured(hipStream_t stream) {
+    if (stream == nullptr) return false;
+    hipStreamCaptureStatus st = hipStreamCaptureStatusNone;
+    if (hipStreamIsCapturing(stream, &st) != hipSuccess) (void)hipGetLastError();
+    return st != hipStreamCaptureStatusNone;
+}
+
 // the caller may have destroyed the stream it made the plan on
 bool stream_alive(hipStream_t stream) {
     if (stream == nullptr) return true;
@@ -1731,9 +1740,9 @@ ca_status ca_kv_save_layer(ca_ctx *ctx, int32_t layer, const int32_t *tok_begin,
 
 // Appending and saving the new turn in one call: the saved bytes ARE the appended bytes (keys without positions,
 // Section 3.4), so the pool need not be read back.  Device destinations (and pinned ones under save_mode 2, or when the
-// turn is short): one kernel
-// reads new_k/new_v once and stores every vector twice (pool and tier).  Pinned destinations by default: append kernel,
-// then the pack kernel writes the tier in place from the save stream.  Pinned destinations with staged saving: the
+// turn is short): one kernel reads new_k/new_v once and stores every vector twice (pool and tier).  Pinned destinations by
+// default, and all while another stream's short move is under way: append kernel, then the pack kernel writes the tier in place
+// from the save stream.  Pinned destinations with staged saving: the
 // copy-out on the save stream reads new_k/new_v directly; no pack kernel, no staging slot.
 ca_status ca_kv_append_save_layer(ca_ctx *ctx, int32_t layer, const void *new_k, const void *new_v, void *k_pool,
                                   void *v_pool, void *const *dst_k, void *const *dst_v, void *stream_) {
@@ -1765,8 +1774,9 @@ ca_status ca_kv_append_save_layer(ca_ctx *ctx, int32_t layer, const void *new_k,
             return fail(ctx, CA_ERR_INVALID_ARG, "ca_kv_append_save_layer: destination of conversation %d is smaller than hist_len + new_len tokens", i);
     }
     hipStream_t stream = (hipStream_t)stream_;
-    const bool one_kernel = any_host ? c.save_mode == 2 || (save_is_short(ctx, any_host, 2 * (int64_t)bytes) && inline_free(ctx, stream))
-                                     : c.save_mode != 1;
+    const bool captured = is_captured(stream);
+    const bool one_kernel = (any_host ? c.save_mode == 2 || save_is_short(ctx, any_host, 2 * (int64_t)bytes) : c.save_mode != 1) &&
+                            (captured || inline_free(ctx, stream));
     if (!one_kernel) {
         // the append kernel on the caller's stream (which must not wait for stores that cross the host link); the write-back
         // follows it on the save stream
@@ -1774,7 +1784,7 @@ ca_status ca_kv_append_save_layer(ca_ctx *ctx, int32_t layer, const void *new_k,
         if (st == CA_OK) st = save_follows(ctx, stream);
         if (st != CA_OK) return st;
         int iv;
-        if (c.save_mode == 0) {
+        if (c.save_mode != 1) {
             // the pack kernel writes the new tokens to the tier in place
             std::vector<Segment> segs;
             for (int i = 0; i < B; ++i)
@@ -1782,7 +1792,7 @@ ca_status ca_kv_append_save_layer(ca_ctx *ctx, int32_t layer, const void *new_k,
                     segs.push_back({gpu_k[i], gpu_v[i], ctx->hist_len[i], ctx->n_keep[i], ctx->new_len[i], i});
             if (ctx->loaded[layer]) CA_HIP(ctx, after_load(ctx, layer, ctx->s_save));
             CA_HIP(ctx, prof_begin(ctx, kProfPack, ctx->s_save, &iv));
-            st = run_move(ctx, false, segs, k_pool, v_pool, ctx->s_save, kLinkSaveWorkgroups);
+            st = run_move(ctx, false, segs, k_pool, v_pool, ctx->s_save, any_host ? kLinkSaveWorkgroups : 0);
             if (st != CA_OK) return st;
         } else {
             // one copy per conversation, straight from new_k / new_v
@@ -1814,7 +1824,7 @@ ca_status ca_kv_append_save_layer(ca_ctx *ctx, int32_t layer, const void *new_k,
     }
     CA_HIP(ctx, prof_end(ctx, iv_back, stream));
     CA_HIP(ctx, prof_end(ctx, iv, stream));
-    if (any_host && c.save_mode != 2) CA_HIP(ctx, note_inline(ctx, stream));    // ca_sync and ca_join cover it, as they would the save stream
+    if (!captured) CA_HIP(ctx, note_inline(ctx, stream));    // ca_sync and ca_join cover it, as they would the save stream
     return CA_OK;
 }
 

@@ -144,3 +144,67 @@ def test_a_pinned_tier_that_ends_too_early_is_refused(hist, new):
         run.finish()
     finally:
         run.close()
+
+
+@pytest.mark.parametrize("tier,mode", [("device", 0), ("pinned", 2), ("pinned", 0)])
+@pytest.mark.parametrize("new", [(2, 30), (900, 700)], ids=["short", "long"])
+def test_sync_and_join_cover_append_save(new, tier, mode):
+    """the tier rows are there after ca_sync alone, and for work on another stream behind ca_join alone"""
+    case = Case([40, 3], list(new), [0, 0], 4, 4, 64, seed=87, window=1024)
+    for stream in (None, torch.cuda.Stream()):
+        for joined in (False, True):
+            run = GpuRun(case, tier=tier, save_mode=mode)
+            try:
+                run.rebase(stream)
+                run.ctx.kv_append_save_layer(0, run.k_new[0], run.v_new[0], run.k_pool[0], run.v_pool[0], run.host_k[0], run.host_v[0], stream)
+                reader = torch.cuda.Stream()
+                if joined:
+                    run.ctx.join(reader)
+                else:
+                    run.ctx.sync()
+                with torch.cuda.stream(reader):
+                    got = [[t.to(run.dev, non_blocking=True, copy=True) for t in h[0]] for h in (run.host_k, run.host_v)]
+                    torch.cuda.current_stream().synchronize()
+                for which, rows in zip(("k", "v"), got):
+                    for c in range(case.B):
+                        assert np.array_equal(torch_to_bits(rows[c])[case.hist_len[c]:], case.tensor(0, f"{which}_new", c)), (which, c)
+            finally:
+                run.close()
+
+
+def test_append_save_and_static_attention_in_a_graph():
+    """captured once and replayed on new inputs, with the library's other calls in between"""
+    case = Case([300, 77], [1, 1], [0, 0], 8, 1, 128, seed=88, window=1024)
+    run = GpuRun(case, tier="device", require_load=0)
+    try:
+        s = torch.cuda.Stream()
+        run.rebase(s)
+        run.ctx.kv_load_layer(0, run.host_k[0], run.host_v[0], run.k_pool[0], run.v_pool[0])
+        run.finish()
+        run.rebase(s)
+        torch.cuda.synchronize()
+
+        def step():
+            run.ctx.kv_append_save_layer(0, run.k_new[0], run.v_new[0], run.k_pool[0], run.v_pool[0], run.host_k[0], run.host_v[0], s)
+            run.ctx.cached_prefill_attn_static(0, run.q[0], run.k_pool[0], run.v_pool[0], run.out[0], 1.0 / np.sqrt(128), s)
+
+        step()
+        graph = torch.cuda.CUDAGraph()
+        with torch.cuda.graph(graph, stream=s, capture_error_mode="thread_local"):
+            step()
+        for i in range(4):
+            run.q[0].mul_(-1.0 if i % 2 else 0.5); run.v_new[0].add_(1.0)
+            torch.cuda.synchronize()
+            with torch.cuda.stream(s):
+                graph.replay()
+            run.ctx.join(None)
+            run.finish()
+            got = torch_to_bits(run.out[0]).copy(), [torch_to_bits(t).copy() for t in run.host_v[0]], torch_to_bits(run.v_pool[0]).copy()
+            run.out[0].zero_(); run.host_v[0][0][-1].zero_()
+            torch.cuda.synchronize()
+            step()
+            run.finish()
+            assert np.array_equal(got[0], torch_to_bits(run.out[0])), i
+            assert all(np.array_equal(a, torch_to_bits(b)) for a, b in zip(got[1], run.host_v[0])) and np.array_equal(got[2], torch_to_bits(run.v_pool[0]))
+    finally:
+        run.close()

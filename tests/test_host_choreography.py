@@ -149,3 +149,34 @@ def test_short_moves_of_two_threads_on_their_own_default_streams(m, fused):
     assert all(m.stream_behind(s, op) for op in saves)
     t.ctx.sync()
     assert all(m.done(op) for op in saves)
+
+
+# ---- ca_sync and ca_join cover a save by the append kernel ------------------------------------------------------
+@pytest.mark.parametrize("tier,mode", [(0, 0), (1, 2), (1, 0)], ids=["device", "pinned-mode2", "pinned"])
+@pytest.mark.parametrize("new", [2, 20000], ids=["short", "long"])
+@pytest.mark.parametrize("own", [False, True], ids=["default-stream", "own-stream"])
+@in_model
+def test_sync_and_join_cover_append_save(m, own, new, tier, mode):
+    t = Turn(m, [0], [new], tier=tier, save_mode=mode)
+    s, s2, other = (m.stream() if own else None), m.stream(), m.stream()
+    t.rebase(s)
+    saves = [m.queued(lambda: t.append_save(x))[-1] for x in (s, s, s2)]        # (the third while the others are under way)
+    t.ctx.join(other)
+    assert all(m.stream_behind(other, op) for op in saves)
+    t.ctx.sync()
+    assert all(m.done(op) for op in saves)
+
+
+@in_model
+def test_append_save_can_be_captured(m):
+    """the caller orders a graph it launches: nothing queued into one may be waited for by the calls outside"""
+    t = Turn(m, [0], [2])
+    s, s2 = m.stream(), m.stream()
+    t.rebase(s)
+    t.append_save(s2)
+    m.lib.model_capture(s, 1)
+    assert len(m.queued(lambda: (t.append_save(s), t.attn(s, static=True)))) == 2
+    m.lib.model_capture(s, 0)
+    t.ctx.join(s2)
+    t.ctx.sync()
+    t.rebase(s)
