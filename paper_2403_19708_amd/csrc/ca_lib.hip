@@ -299,9 +299,11 @@ bool is_captured(hipStream_t stream) {
     return st != hipStreamCaptureStatusNone;
 }
 
-// the caller may have destroyed the stream it made the plan on
-bool stream_alive(hipStream_t stream) {
+// May a move be queued on the stream the plan was made on?  The caller may have destroyed it, or be capturing it (a capture
+// would take the move in, and would not survive being asked whether the stream is done).
+bool stream_usable(hipStream_t stream) {
     if (stream == nullptr) return true;
+    if (is_captured(stream)) return false;
     const hipError_t e = hipStreamQuery(stream);
     if (e == hipSuccess) return true;
     (void)hipGetLastError();
@@ -1528,7 +1530,7 @@ ca_status ca_kv_load_layer(ca_ctx *ctx, int32_t layer, const void *const *src_k,
     const int64_t move_bytes = 2 * ctx->total_n * rb;
     const bool small = move_bytes <= (any_host ? kInlineHostLoadBytes : kInlineDeviceBytes);
     const bool staged = c.load_mode == 1;
-    const bool on_caller = small && !staged && stream_alive(ctx->plan_stream) && inline_free(ctx, ctx->plan_stream);
+    const bool on_caller = small && !staged && stream_usable(ctx->plan_stream) && inline_free(ctx, ctx->plan_stream);
     hipStream_t mover = on_caller ? ctx->plan_stream : ctx->s_unpack;
     if (on_caller) CA_HIP(ctx, caller_after_plan(ctx, mover));
     else CA_HIP(ctx, after_plan(ctx, ctx->s_unpack, &ctx->unpack_waits_plan));

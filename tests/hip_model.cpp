@@ -21,7 +21,7 @@ namespace {
 struct Stream {
     int device;
     std::set<int> behind;      // operations a new one on this stream is behind
-    bool alive = true, capturing = false;
+    bool alive = true, capturing = false, spoilt = false;      // spoilt: a call that a capture does not survive
 };
 struct Event {
     int device;
@@ -145,7 +145,7 @@ hipError_t hipMemGetAddressRange(hipDeviceptr_t *base, size_t *size, hipDevicept
 }
 hipError_t hipStreamCreateWithFlags(hipStream_t *s, unsigned) { MODEL; Stream *x = new Stream{current}; streams.insert(x); *s = (hipStream_t)x; return hipSuccess; }
 hipError_t hipStreamDestroy(hipStream_t s) { MODEL; Stream *x = stream_of(s); if (!x) return hipErrorInvalidHandle; x->alive = false; return hipSuccess; }
-hipError_t hipStreamQuery(hipStream_t s) { MODEL; Stream *x = stream_of(s); return !x ? hipErrorInvalidHandle : finished(x->behind) ? hipSuccess : hipErrorNotReady; }
+hipError_t hipStreamQuery(hipStream_t s) { MODEL; Stream *x = stream_of(s); if (x && x->capturing) { x->spoilt = true; return hipErrorStreamCaptureUnsupported; } return !x ? hipErrorInvalidHandle : finished(x->behind) ? hipSuccess : hipErrorNotReady; }
 hipError_t hipStreamSynchronize(hipStream_t s) { MODEL; Stream *x = stream_of(s); if (!x) return hipErrorInvalidHandle; finish(x->behind); return hipSuccess; }
 hipError_t hipStreamIsCapturing(hipStream_t s, hipStreamCaptureStatus *st) { MODEL; Stream *x = stream_of(s); if (!x) return hipErrorInvalidHandle; *st = x->capturing ? hipStreamCaptureStatusActive : hipStreamCaptureStatusNone; return hipSuccess; }
 hipError_t hipDeviceSynchronize() { MODEL; for (int i = 0; i < (int)ops.size(); ++i) if (ops[i].stream->device == current) finish({i}); return hipSuccess; }
@@ -164,7 +164,7 @@ hipError_t hipStreamWaitEvent(hipStream_t s, hipEvent_t e, unsigned) {
     MODEL;
     Stream *x = stream_of(s);
     if (!x) return hipErrorInvalidHandle;
-    if (x->capturing != ((Event *)e)->captured) return hipErrorStreamCaptureIsolation;
+    if (x->capturing != ((Event *)e)->captured) { x->spoilt |= x->capturing; return hipErrorStreamCaptureIsolation; }
     x->behind.insert(((Event *)e)->ops.begin(), ((Event *)e)->ops.end());
     return hipSuccess;
 }
@@ -195,7 +195,7 @@ hipError_t hipLaunchKernel(const void *f, dim3, dim3, void **args, size_t, hipSt
 // ---- what the tests ask ----
 // kind: 0 device memory, 1 pinned host memory, 2 pinned at another device address, of unknown extent (registered memory)
 void *model_alloc(size_t size, int kind) { return allocate(size, kind ? hipMemoryTypeHost : hipMemoryTypeDevice, kind == 2 ? (ptrdiff_t)1 << 40 : 0, kind != 2); }
-void model_capture(hipStream_t s, int on) { stream_of(s)->capturing = on; }
+int model_capture(hipStream_t s, int on) { stream_of(s)->capturing = on; return !stream_of(s)->spoilt; }      // 1: the capture is whole
 void model_fail_launch(int after) { launches_until_failure = after; }
 int model_ops() { MODEL; return (int)ops.size(); }
 const char *model_what(int op) { MODEL; return ops[op].what.c_str(); }

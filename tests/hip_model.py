@@ -51,7 +51,7 @@ class Model:
         self.lib = C.CDLL(LIB, mode=C.RTLD_GLOBAL)
         for f, res, args in (("model_alloc", C.c_void_p, [C.c_size_t, C.c_int]), ("model_what", C.c_char_p, [C.c_int]),
                              ("model_stream", C.c_void_p, [C.c_int]), ("model_stream_behind", C.c_int, [C.c_void_p, C.c_int]),
-                             ("model_capture", None, [C.c_void_p, C.c_int]), ("model_device_bytes", C.c_size_t, []),
+                             ("model_capture", C.c_int, [C.c_void_p, C.c_int]), ("model_device_bytes", C.c_size_t, []),
                              ("model_attn_pointer", C.c_void_p, [C.c_int, C.c_int]),
                              ("model_move_pointer", C.c_void_p, [C.c_int, C.c_int, C.c_int])):
             getattr(self.lib, f).restype, getattr(self.lib, f).argtypes = res, args

@@ -176,7 +176,21 @@ def test_append_save_can_be_captured(m):
     t.append_save(s2)
     m.lib.model_capture(s, 1)
     assert len(m.queued(lambda: (t.append_save(s), t.attn(s, static=True)))) == 2
-    m.lib.model_capture(s, 0)
+    assert m.lib.model_capture(s, 0)
     t.ctx.join(s2)
     t.ctx.sync()
     t.rebase(s)
+
+
+@pytest.mark.parametrize("tier", [0, 1], ids=["device", "pinned"])
+@in_model
+def test_a_load_stays_out_of_a_capture_of_the_plans_stream(m, tier):
+    """the next job's read buffer fills while the current job's step is captured on the stream both plans were made on"""
+    t = Turn(m, [40], [2], tier=tier)
+    s = m.stream()
+    t.rebase(s)
+    m.lib.model_capture(s, 1)
+    load, = m.queued(t.load)
+    assert not m.stream_behind(s, load) and m.lib.model_capture(s, 0)
+    t.ctx.join(s)
+    assert m.stream_behind(s, load)
