@@ -52,6 +52,7 @@ struct ca_ctx {
     bool copy_waits_plan = false, unpack_waits_plan = false, save_waits_plan = false;   // the stream has not yet been told to wait for ev_plan
     hipEvent_t load_done = nullptr;    // event behind the newest load on the unpack stream (one of ev_ready), null: none outstanding
     bool save_pending = false;         // ev_saved stands behind work on the save stream that may be unfinished
+    bool saves_under_plan = false;     // some of it was queued under the current plan
     bool joined_null = false;          // the default stream (of the context's GPU) already waits for all of it
     // short moves run on a stream of the caller's instead (see runs_inline): the newest one, and the event behind it (null on
     // the default stream, which outlives the context and can be asked or recorded on when it matters)
@@ -1345,6 +1346,7 @@ ca_status ca_rope_rebase(ca_ctx *ctx, const ca_batch *b, void *stream_) {
     CA_HIP(ctx, hipEventRecord(ctx->ev_plan, stream));
     ctx->meta_in_flight = true;
     ctx->copy_waits_plan = ctx->unpack_waits_plan = ctx->save_waits_plan = true;
+    ctx->saves_under_plan = false;
     ctx->plan_stream = stream;
     std::fill(ctx->loaded.begin(), ctx->loaded.end(), 0);
     std::fill(ctx->ready_inline.begin(), ctx->ready_inline.end(), 0);
@@ -1469,8 +1471,25 @@ bool save_is_short(const ca_ctx *ctx, bool to_host, int64_t bytes) {
     return ctx->cfg.save_mode != 1 && bytes <= (to_host ? kInlineHostSaveBytes : kInlineDeviceBytes);
 }
 
-// the save stream continues behind the plan and the work queued so far on `after`
+// Saves are done in the order they were asked for (two may write the same rows of the tier): none goes to the caller's stream
+// while another under this plan is on the save stream, and the save stream waits for those on the caller's streams.  (Earlier
+// plans' saves are in front of the plan.)
+bool save_stream_idle(ca_ctx *ctx) {
+    if (!ctx->saves_under_plan) return true;
+    if (hipEventQuery(ctx->ev_saved) != hipSuccess) {
+        (void)hipGetLastError();
+        return false;
+    }
+    ctx->saves_under_plan = false;
+    return true;
+}
+
+// the save stream continues behind the plan, the work queued so far on `after` and the short moves on other streams
 ca_status save_follows(ca_ctx *ctx, hipStream_t after) {
+    if (ctx->inline_pending && (ctx->inline_stream != after || ctx->inline_owner != stream_owner(after))) {
+        if (!ctx->inline_done) CA_HIP(ctx, hipEventRecord(ctx->ev_inline, nullptr));
+        CA_HIP(ctx, hipStreamWaitEvent(ctx->s_save, ctx->inline_done ? ctx->inline_done : ctx->ev_inline, 0));
+    }
     if (after != nullptr || ctx->plan_stream != nullptr) CA_HIP(ctx, after_plan(ctx, ctx->s_save, &ctx->save_waits_plan));
     ctx->save_waits_plan = false;          // (behind the default stream: the plan is in front there)
     CA_HIP(ctx, hipEventRecord(ctx->ev_after, after));
@@ -1479,7 +1498,7 @@ ca_status save_follows(ca_ctx *ctx, hipStream_t after) {
 }
 
 hipError_t note_save(ca_ctx *ctx) {
-    ctx->save_pending = true;
+    ctx->save_pending = ctx->saves_under_plan = true;
     ctx->joined_null = false;
     return hipEventRecord(ctx->ev_saved, ctx->s_save);
 }
@@ -1676,7 +1695,7 @@ ca_status ca_kv_save_layer(ca_ctx *ctx, int32_t layer, const int32_t *tok_begin,
     }
     if (total > c.max_batch_kv_tokens) return fail(ctx, CA_ERR_OUT_OF_RANGE, "ca_kv_save_layer: %lld tokens exceed a staging slot", (long long)total);
     hipStream_t after = (hipStream_t)after_stream;
-    const bool on_caller = save_is_short(ctx, any_host, 2 * total * rb) && inline_free(ctx, after);
+    const bool on_caller = save_is_short(ctx, any_host, 2 * total * rb) && save_stream_idle(ctx) && inline_free(ctx, after);
     const bool staged = c.save_mode == 1;
 
     // saving starts after the producer of this layer's K/V: the work queued on `after_stream`, and the load of
@@ -1777,8 +1796,8 @@ ca_status ca_kv_append_save_layer(ca_ctx *ctx, int32_t layer, const void *new_k,
     }
     hipStream_t stream = (hipStream_t)stream_;
     const bool captured = is_captured(stream);
-    const bool one_kernel = (any_host ? c.save_mode == 2 || save_is_short(ctx, any_host, 2 * (int64_t)bytes) : c.save_mode != 1) &&
-                            (captured || inline_free(ctx, stream));
+    const bool one_kernel = (any_host ? c.save_mode == 2 || (save_is_short(ctx, any_host, 2 * (int64_t)bytes) && (captured || save_stream_idle(ctx)))
+                                      : c.save_mode != 1) && (captured || inline_free(ctx, stream));
     if (!one_kernel) {
         // the append kernel on the caller's stream (which must not wait for stores that cross the host link); the write-back
         // follows it on the save stream

@@ -194,3 +194,16 @@ def test_a_load_stays_out_of_a_capture_of_the_plans_stream(m, tier):
     assert not m.stream_behind(s, load) and m.lib.model_capture(s, 0)
     t.ctx.join(s)
     assert m.stream_behind(s, load)
+
+
+# ---- the order of saves ---------------------------------------------------------------------------------------------
+@pytest.mark.parametrize("streams", ["one", "two"])
+@pytest.mark.parametrize("sizes", [(4000, 2), (2, 4000), (2, 2, 4000), (4000, 2, 2)], ids=str)
+@in_model
+def test_saves_of_a_plan_are_done_in_the_order_they_were_asked_for(m, sizes, streams):
+    """also where a short one, on the caller's stream, meets a long one on the save stream: both may write the same rows"""
+    t = Turn(m, [0], [4000], tier=1)
+    s = [m.stream()] * 3 if streams == "one" else [m.stream() for _ in range(3)]
+    t.rebase(s[0])
+    saves = [m.queued(lambda: t.save(x, tok_begin=[4000 - n], tok_end=[4000], dst_tok_offset=[0]))[-1] for n, x in zip(sizes, s)]
+    assert all(m.behind(b, a) for a, b in zip(saves, saves[1:]))
