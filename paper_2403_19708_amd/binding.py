@@ -373,6 +373,8 @@ class Context:
             opt = lambda a, dtype: None if a is None else np.ascontiguousarray(a, dtype=dtype)
             st = _native.save_layer(self._address, self.n_seqs, layer, k_pool, v_pool, dst_k, dst_v, opt(tok_begin, np.int32), opt(tok_end, np.int32),
                                     opt(dst_tok_offset, np.int64), after_stream)
+            if st is None:
+                raise ValueError("per-conversation arrays must have n_seqs entries")
         if st:
             self._check(st)
 

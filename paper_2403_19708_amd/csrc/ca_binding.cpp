@@ -7,13 +7,27 @@
 #include <Python.h>
 
 #include <cstdint>
+#include <cstring>
 #include <vector>
 
 #include "../../include/ca.h"
 
 namespace {
 
-PyObject *s_data_ptr, *s_cuda_stream;
+PyObject *s_data_ptr, *s_cuda_stream, *ctypes_array, *ctypes_error;
+
+// what int(v) gives, as an address; takes the reference to v (NULL: a Python error is set)
+bool as_address(PyObject *v, void **out) {
+    if (v && !PyLong_Check(v)) {
+        PyObject *number = PyNumber_Long(v);
+        Py_DECREF(v);
+        v = number;
+    }
+    if (!v) return false;
+    *out = PyLong_AsVoidPtr(v);
+    Py_DECREF(v);
+    return *out != nullptr || !PyErr_Occurred();
+}
 
 // Integer value of o, o.data_ptr() or o.cuda_stream.  false: a Python error is set.
 bool address(PyObject *o, void **out) {
@@ -23,45 +37,34 @@ bool address(PyObject *o, void **out) {
         return *out != nullptr || !PyErr_Occurred();
     }
     PyObject *v = PyObject_CallMethodNoArgs(o, s_data_ptr);
-    if (!v) {
-        if (!PyErr_ExceptionMatches(PyExc_AttributeError)) return false;
+    if (!v && PyErr_ExceptionMatches(PyExc_AttributeError)) {
         PyErr_Clear();
         v = PyNumber_Long(o);
-        if (!v) return false;
     }
-    *out = PyLong_AsVoidPtr(v);
-    Py_DECREF(v);
-    return *out != nullptr || !PyErr_Occurred();
+    return as_address(v, out);
 }
 
 bool stream_of(PyObject *o, void **out) {
     if (o == Py_None) { *out = nullptr; return true; }
     if (PyLong_CheckExact(o)) return address(o, out);
     PyObject *v = PyObject_GetAttr(o, s_cuda_stream);
-    if (!v) {
-        if (!PyErr_ExceptionMatches(PyExc_AttributeError)) return false;
+    if (!v && PyErr_ExceptionMatches(PyExc_AttributeError)) {
         PyErr_Clear();
         v = PyNumber_Long(o);
-        if (!v) return false;
     }
-    *out = PyLong_AsVoidPtr(v);
-    Py_DECREF(v);
-    return *out != nullptr || !PyErr_Occurred();
+    return as_address(v, out);
 }
 
-// One pointer per conversation: the memory of a ctypes array as it is, or a list converted.
+// One pointer per conversation: the memory of a ctypes array of c_void_p or of a contiguous one-dimensional buffer of 64-bit
+// integers as it is, any other sequence converted element by element.  Other ctypes arrays are refused, as ctypes would.
 struct Pointers {
     std::vector<void *> own;
     void **p = nullptr;
     bool take(PyObject *o, long long n_seqs, const char *what) {
         Py_ssize_t n = 0;
-        Py_buffer view;
-        if (!PyList_CheckExact(o) && !PyTuple_CheckExact(o) && PyObject_CheckBuffer(o)) {
-            if (PyObject_GetBuffer(o, &view, PyBUF_SIMPLE) != 0) return false;
-            p = (void **)view.buf;                  // (the caller's reference keeps the array alive over the call)
-            n = view.len / (Py_ssize_t)sizeof(void *);
-            PyBuffer_Release(&view);
-        } else {
+        if (!as_it_is(o, &n)) {
+            if (PyErr_Occurred()) return false;
+            if (PyObject_Size(o) < 0) return false;
             PyObject *seq = PySequence_Fast(o, "one pointer per conversation expected");
             if (!seq) return false;
             n = PySequence_Fast_GET_SIZE(seq);
@@ -76,6 +79,25 @@ struct Pointers {
             return false;
         }
         return true;
+    }
+
+private:
+    bool as_it_is(PyObject *o, Py_ssize_t *n) {
+        if (PyList_CheckExact(o) || PyTuple_CheckExact(o) || !PyObject_CheckBuffer(o)) return false;
+        Py_buffer view;
+        bool fits = false;
+        if (PyObject_GetBuffer(o, &view, PyBUF_ND | PyBUF_FORMAT) == 0) {
+            const char *f = view.format ? view.format : "B";
+            fits = view.ndim == 1 && view.itemsize == (Py_ssize_t)sizeof(void *) &&
+                   (!std::strcmp(f, "<P") || !std::strcmp(f, "P") || (f[0] && !f[1] && std::strchr("lLqQ", f[0])));
+            p = (void **)view.buf;                  // (the caller's reference keeps the array alive over the call)
+            *n = fits ? view.shape[0] : 0;
+            PyBuffer_Release(&view);
+        } else {
+            PyErr_Clear();                          // (strided, for one)
+        }
+        if (!fits && PyObject_IsInstance(o, ctypes_array) == 1) PyErr_SetString(ctypes_error, "an array of c_void_p expected");
+        return fits;
     }
 };
 
@@ -108,10 +130,14 @@ bool want(Py_ssize_t n, Py_ssize_t expected) {
     return false;
 }
 
-bool layer_of(PyObject *o, int32_t *layer) {
-    const long v = PyLong_AsLong(o);
+// int(o), as the C call's 32-bit argument
+bool int32_of(PyObject *o, int32_t *out) {
+    PyObject *number = PyNumber_Long(o);
+    if (!number) return false;
+    const long v = PyLong_AsLong(number);
+    Py_DECREF(number);
     if (v == -1 && PyErr_Occurred()) return false;
-    *layer = (int32_t)v;
+    *out = (int32_t)v;
     return true;
 }
 
@@ -137,8 +163,8 @@ PyObject *rope_rebase(PyObject *, PyObject *const *a, Py_ssize_t n) {
     for (int i = 0; i < 3; ++i)
         if (x[i].ndim != 1 || x[i].shape[0] != x[0].shape[0]) Py_RETURN_NONE;
     if (x[3].ndim != 2 || x[3].shape[0] != x[0].shape[0]) Py_RETURN_NONE;
-    const long pages = PyLong_AsLong(a[5]);
-    if (pages == -1 && PyErr_Occurred()) return nullptr;
+    int32_t pages;
+    if (!int32_of(a[5], &pages)) return nullptr;
     void *stream;
     if (!stream_of(a[6], &stream)) return nullptr;
     ca_batch b{};
@@ -148,7 +174,7 @@ PyObject *rope_rebase(PyObject *, PyObject *const *a, Py_ssize_t n) {
     b.new_len = (const int32_t *)x[2].p;
     b.block_table = (const int32_t *)x[3].p;
     b.max_pages = (int32_t)x[3].shape[1];
-    b.num_pages = (int32_t)pages;
+    b.num_pages = pages;
     ca_ctx *ctx = context(a[0]);
     return status_of([&] { return ca_rope_rebase(ctx, &b, stream); });
 }
@@ -157,7 +183,7 @@ PyObject *rope_rebase(PyObject *, PyObject *const *a, Py_ssize_t n) {
 PyObject *append_layer(PyObject *, PyObject *const *a, Py_ssize_t n) {
     int32_t layer;
     void *p[4], *stream;
-    if (!want(n, 7) || !layer_of(a[1], &layer)) return nullptr;
+    if (!want(n, 7) || !int32_of(a[1], &layer)) return nullptr;
     for (int i = 0; i < 4; ++i) if (!address(a[2 + i], &p[i])) return nullptr;
     if (!stream_of(a[6], &stream)) return nullptr;
     ca_ctx *ctx = context(a[0]);
@@ -168,7 +194,7 @@ PyObject *append_layer(PyObject *, PyObject *const *a, Py_ssize_t n) {
 PyObject *attention(PyObject *const *a, Py_ssize_t n, decltype(ca_cached_prefill_attn) *call) {
     int32_t layer;
     void *p[4], *stream;
-    if (!want(n, 8) || !layer_of(a[1], &layer)) return nullptr;
+    if (!want(n, 8) || !int32_of(a[1], &layer)) return nullptr;
     for (int i = 0; i < 4; ++i) if (!address(a[2 + i], &p[i])) return nullptr;
     const double scale = PyFloat_AsDouble(a[6]);
     if (scale == -1.0 && PyErr_Occurred()) return nullptr;
@@ -184,7 +210,7 @@ PyObject *load_layer(PyObject *, PyObject *const *a, Py_ssize_t n) {
     int32_t layer;
     void *p[2];
     Pointers k, v;
-    if (!want(n, 7) || !layer_of(a[2], &layer)) return nullptr;
+    if (!want(n, 7) || !int32_of(a[2], &layer)) return nullptr;
     const long long seqs = PyLong_AsLongLong(a[1]);
     if (!k.take(a[3], seqs, "src_k/src_v") || !v.take(a[4], seqs, "src_k/src_v")) return nullptr;
     for (int i = 0; i < 2; ++i) if (!address(a[5 + i], &p[i])) return nullptr;
@@ -198,7 +224,7 @@ PyObject *save_layer(PyObject *, PyObject *const *a, Py_ssize_t n) {
     int32_t layer;
     void *p[2], *stream;
     Pointers k, v;
-    if (!want(n, 11) || !layer_of(a[2], &layer)) return nullptr;
+    if (!want(n, 11) || !int32_of(a[2], &layer)) return nullptr;
     const long long seqs = PyLong_AsLongLong(a[1]);
     for (int i = 0; i < 2; ++i) if (!address(a[3 + i], &p[i])) return nullptr;
     if (!k.take(a[5], seqs, "dst_k/dst_v") || !v.take(a[6], seqs, "dst_k/dst_v")) return nullptr;
@@ -225,7 +251,7 @@ PyObject *append_save_layer(PyObject *, PyObject *const *a, Py_ssize_t n) {
     int32_t layer;
     void *p[4], *stream;
     Pointers k, v;
-    if (!want(n, 10) || !layer_of(a[2], &layer)) return nullptr;
+    if (!want(n, 10) || !int32_of(a[2], &layer)) return nullptr;
     const long long seqs = PyLong_AsLongLong(a[1]);
     for (int i = 0; i < 4; ++i) if (!address(a[3 + i], &p[i])) return nullptr;
     if (!k.take(a[7], seqs, "dst_k/dst_v") || !v.take(a[8], seqs, "dst_k/dst_v")) return nullptr;
@@ -244,6 +270,11 @@ PyModuleDef module = {PyModuleDef_HEAD_INIT, "_ca_native", nullptr, -1, methods,
 PyMODINIT_FUNC PyInit__ca_native() {
     s_data_ptr = PyUnicode_InternFromString("data_ptr");
     s_cuda_stream = PyUnicode_InternFromString("cuda_stream");
-    if (!s_data_ptr || !s_cuda_stream) return nullptr;
+    PyObject *ctypes = PyImport_ImportModule("ctypes");
+    if (!s_data_ptr || !s_cuda_stream || !ctypes) return nullptr;
+    ctypes_array = PyObject_GetAttrString(ctypes, "Array");
+    ctypes_error = PyObject_GetAttrString(ctypes, "ArgumentError");
+    Py_DECREF(ctypes);
+    if (!ctypes_array || !ctypes_error) return nullptr;
     return PyModule_Create(&module);
 }

@@ -1,5 +1,7 @@
 """What the library queues where, and what waits for it, on a model of the HIP runtime in which nothing is done before
 something waits for it (hip_model.py): the host code of the C ABI, without a GPU."""
+import ctypes as C
+
 import pytest
 
 from hip_model import PER_THREAD, Turn, in_model
@@ -207,3 +209,80 @@ def test_saves_of_a_plan_are_done_in_the_order_they_were_asked_for(m, sizes, str
     t.rebase(s[0])
     saves = [m.queued(lambda: t.save(x, tok_begin=[4000 - n], tok_end=[4000], dst_tok_offset=[0]))[-1] for n, x in zip(sizes, s)]
     assert all(m.behind(b, a) for a, b in zip(saves, saves[1:]))
+
+
+# ---- what the binding takes as an argument ----------------------------------------------------------------------------
+class _Holder:
+    """an object with an address or a stream that is a numpy integer"""
+
+    def __init__(self, value):
+        import numpy as np
+        self.cuda_stream = np.int64(value)
+
+    def data_ptr(self):
+        return self.cuda_stream
+
+
+def _padded(np, kind, p):
+    wide = np.zeros((len(p), 3), kind)
+    wide[:, 1] = p
+    return wide[:, 1]
+
+
+POINTERS = {
+    "list": lambda np, p: p,
+    "tensors": lambda np, p: [_Holder(x) for x in p],
+    "c_void_p": lambda np, p: (C.c_void_p * len(p))(*p),
+    "uint64": lambda np, p: np.array(p, np.uint64),
+    "int64-strided": lambda np, p: _padded(np, np.int64, p),
+    "int64-swapped": lambda np, p: np.array(p, ">i8"),
+    "objects": lambda np, p: np.array(p, object),
+    "float64": lambda np, p: np.array(p, np.float64),
+    "column": lambda np, p: np.array(p).reshape(-1, 1),
+}
+
+
+@pytest.mark.parametrize("form", POINTERS)
+@in_model
+def test_pointers_reach_the_library_in_every_form(m, form):
+    import numpy as np
+    t = Turn(m, [40, 50, 60], [2, 3, 4], tier=1)
+    want = [list(t.tk), list(t.tv)]
+    t.rebase()
+    t.tk, t.tv = (POINTERS[form](np, p) for p in want)
+    for call in (t.load, t.save, t.append_save):
+        op = m.queued(call)[-1]
+        for c in range(3):
+            at = int(t.hist[c]) * t.row if "append_save" in m.what(op) else 0
+            assert [m.lib.model_move_pointer(op, c, v) for v in range(2)] == [want[v][c] + at for v in range(2)], (form, m.what(op))
+
+
+@in_model
+def test_pointer_arrays_that_are_refused(m):
+    import numpy as np
+    t = Turn(m, [40, 50], [2, 3], tier=1)
+    t.rebase()
+    tk = list(t.tk)
+    for bad, error in (((C.c_uint64 * 2)(*tk), C.ArgumentError), ((C.c_int32 * 2)(1, 2), C.ArgumentError), (iter(tk), TypeError),
+                       (None, TypeError), (np.array(tk[:1]), ValueError), (tk + tk, ValueError)):
+        t.tk = bad
+        for call in (t.load, t.save, t.append_save):
+            with pytest.raises(error):
+                call()
+    t.tk = tk
+    with pytest.raises(ValueError):
+        t.save(tok_begin=np.zeros((1, 1, 2)))
+
+
+@in_model
+def test_numbers_reach_the_library_in_every_form(m):
+    import numpy as np
+    t = Turn(m, [40], [2], layers=2)
+    s = m.stream()
+    t.num_pages = float(t.num_pages)
+    plan, = m.queued(lambda: t.rebase(_Holder(s)))
+    assert m.lib.model_stream(plan) == s
+    t.nk = _Holder(t.nk)
+    for layer in (1.0, np.int16(1)):
+        op, = m.queued(lambda: t.append(_Holder(s), layer))
+        assert m.lib.model_stream(op) == s
