@@ -13,6 +13,7 @@
 #include <cstdio>
 #include <cstring>
 #include <functional>
+#include <list>
 #include <mutex>
 #include <new>
 #include <string>
@@ -29,24 +30,31 @@ static __device__ __align__(256) uint8_t scratch[kStaticScratchBytes];
 constexpr int kMaxDevices = 64;
 static void *static_scratch_ptr[kMaxDevices] = {nullptr};   // [device ordinal], filled by ca_create with that device current
 
-// The internal streams (copy-in, unpack, save) of a GPU, shared by every context of the process on it.  A process has
-// four hardware queues here, and streams that share one wait for each other's unfinished work: with three streams per
-// context the append of one context's turn sat behind another context's loads as soon as a second context existed
-// (three contexts in turn, 236 MB of pinned history each: 6.4 ms a turn, 4.6 ms with one context's three streams).  One
-// set plus the caller's stream is four.  Contexts on different threads may use the set at once: enqueueing is thread-safe,
-// and every wait is on an event recorded right behind the work it stands for, so another context's work only ever queues
-// in front or behind.  Created for the first context of a GPU, destroyed with its last.
-struct StreamSet {
-    hipStream_t copy = nullptr, unpack = nullptr, save = nullptr;
+// The internal streams (copy-in, unpack, save) of a GPU, shared by the contexts of the process that work behind the same
+// stream of the caller: the stream a plan is made on for loads, the one a save follows for saves.  A process has four
+// hardware queues here, and streams that share one wait for each other's unfinished work: with three streams per context the
+// append of one context's turn sat behind another context's loads as soon as a second context existed (three contexts in
+// turn, 236 MB of pinned history each: 6.4 ms a turn, 4.6 ms with one context's three streams).  Contexts behind different
+// streams of the caller have streams of their own: an internal stream waits for its caller's, and what another context queued
+// behind that wait would wait too.  Contexts on different threads may use a stream at once: enqueueing is thread-safe, and
+// every wait is on an event recorded right behind the work it stands for.
+// There are at most as many of a kind as there were contexts at once.  A stream goes with the context that used it last; one
+// that a context left for another serves the next context that needs one, or goes with the GPU's last context.
+enum StreamKind { kCopyStream = 0, kUnpackStream = 1, kSaveStream = 2, kStreamKinds = 3 };
+struct SharedStream {
+    hipStream_t stream = nullptr, caller = nullptr;
+    uint64_t owner = 0;                // see stream_owner
     int users = 0;
 };
-static std::mutex stream_sets_mutex;
-static StreamSet stream_sets[kMaxDevices];   // [device ordinal]
+static std::mutex shared_streams_mutex;
+static std::list<SharedStream> shared_streams[kMaxDevices][kStreamKinds];   // [device ordinal]
+static int contexts_on[kMaxDevices];
 
 struct ca_ctx {
     ca_config cfg{};
-    hipStream_t s_copy = nullptr, s_unpack = nullptr, s_save = nullptr;   // of the device's set
-    bool holds_streams = false;
+    SharedStream *held[kStreamKinds] = {nullptr, nullptr, nullptr};
+    hipStream_t s_copy = nullptr, s_unpack = nullptr, s_save = nullptr;   // their handles (s_copy: with staged loads only)
+    bool counted = false;              // in contexts_on
     // What the streams still owe this context.  An event costs the stream it is recorded on about 3 us and a wait across
     // streams about 11 us of host time and 20 us from one stream's kernel to the other's, so none is made that nothing needs.
     bool copy_waits_plan = false, unpack_waits_plan = false, save_waits_plan = false;   // the stream has not yet been told to wait for ev_plan
@@ -318,6 +326,75 @@ uint64_t stream_owner(hipStream_t stream) {
     if (stream != hipStreamPerThread) return 0;
     if (own == 0) own = ++threads;
     return own;
+}
+
+// ctx->held[kind] becomes the internal stream that works behind the caller's stream `caller`
+hipError_t stream_for(ca_ctx *ctx, StreamKind kind, hipStream_t caller) {
+    SharedStream *&held = ctx->held[kind];
+    const uint64_t owner = stream_owner(caller);
+    if (held && held->caller == caller && held->owner == owner) return hipSuccess;     // (changed by its only user alone)
+    std::lock_guard<std::mutex> hold(shared_streams_mutex);
+    auto &all = shared_streams[ctx->cfg.device][kind];
+    SharedStream *take = nullptr, *spare = held && held->users == 1 ? held : nullptr;
+    for (SharedStream &s : all) {
+        if (s.users > 0 && s.caller == caller && s.owner == owner) take = &s;
+        if (s.users == 0 && !spare) spare = &s;
+    }
+    if (!take && !spare) {
+        hipStream_t created;
+        const hipError_t e = hipStreamCreateWithFlags(&created, hipStreamNonBlocking);
+        if (e != hipSuccess) return e;
+        all.emplace_back();
+        spare = &all.back();
+        spare->stream = created;
+    }
+    if (!take) {
+        take = spare;
+        take->caller = caller;
+        take->owner = owner;
+    }
+    if (held != take) {
+        if (held) --held->users;
+        ++take->users;
+        held = take;
+    }
+    return hipSuccess;
+}
+
+// the streams for loads under a plan made on `caller`
+hipError_t load_streams_for(ca_ctx *ctx, hipStream_t caller) {
+    hipError_t e = stream_for(ctx, kUnpackStream, caller);
+    if (e == hipSuccess && ctx->cfg.load_mode == 1) e = stream_for(ctx, kCopyStream, caller);
+    if (e != hipSuccess) return e;
+    ctx->s_unpack = ctx->held[kUnpackStream]->stream;
+    ctx->s_copy = ctx->held[kCopyStream] ? ctx->held[kCopyStream]->stream : nullptr;
+    return hipSuccess;
+}
+
+// the stream for saves behind `caller`; one that takes over continues behind the plan and the saves so far
+hipError_t save_stream_for(ca_ctx *ctx, hipStream_t caller) {
+    hipError_t e = stream_for(ctx, kSaveStream, caller);
+    if (e != hipSuccess || ctx->s_save == ctx->held[kSaveStream]->stream) return e;
+    ctx->s_save = ctx->held[kSaveStream]->stream;
+    if (ctx->save_pending) e = hipStreamWaitEvent(ctx->s_save, ctx->ev_saved, 0);
+    ctx->save_waits_plan = ctx->has_plan;
+    return e;
+}
+
+void leave_streams(ca_ctx *ctx) {
+    if (!ctx->counted) return;
+    std::lock_guard<std::mutex> hold(shared_streams_mutex);
+    const bool last = --contexts_on[ctx->cfg.device] == 0;
+    for (int kind = 0; kind < kStreamKinds; ++kind) {
+        SharedStream *held = ctx->held[kind];
+        if (held) --held->users;
+        auto &all = shared_streams[ctx->cfg.device][kind];
+        for (auto s = all.begin(); s != all.end();) {
+            if (s->users > 0 || (&*s != held && !last)) { ++s; continue; }
+            (void)hipStreamDestroy(s->stream);
+            s = all.erase(s);
+        }
+    }
 }
 
 // May the next short move run on `stream`?  Only one stream's inline moves are kept track of at a time.
@@ -706,16 +783,7 @@ void ca_destroy(ca_ctx *ctx) {
     if (ctx->v_t) (void)hipFree(ctx->v_t);
     if (ctx->d_meta) (void)hipFree(ctx->d_meta);
     if (ctx->h_meta) (void)hipHostFree(ctx->h_meta);
-    if (ctx->holds_streams) {
-        std::lock_guard<std::mutex> hold(stream_sets_mutex);
-        StreamSet &set = stream_sets[ctx->cfg.device];
-        if (--set.users == 0) {
-            (void)hipStreamDestroy(set.copy);
-            (void)hipStreamDestroy(set.unpack);
-            (void)hipStreamDestroy(set.save);
-            set = StreamSet{};
-        }
-    }
+    leave_streams(ctx);
     delete ctx;
 }
 
@@ -731,24 +799,12 @@ static ca_status create_impl(ca_ctx *ctx) {
     CA_HIP(ctx, hipSetDevice(c.device));
     if (c.device >= kMaxDevices) return fail(ctx, CA_ERR_OUT_OF_RANGE, "device %d: at most %d are served", c.device, kMaxDevices);
     {
-        std::lock_guard<std::mutex> hold(stream_sets_mutex);
-        StreamSet &set = stream_sets[c.device];
-        if (set.users == 0) {
-            hipError_t e = hipSuccess;
-            for (hipStream_t *s : {&set.copy, &set.unpack, &set.save})
-                if (e == hipSuccess && (e = hipStreamCreateWithFlags(s, hipStreamNonBlocking)) != hipSuccess) *s = nullptr;
-            if (e != hipSuccess) {
-                for (hipStream_t s : {set.copy, set.unpack, set.save}) if (s) (void)hipStreamDestroy(s);
-                set = StreamSet{};
-                CA_HIP(ctx, e);
-            }
-        }
-        ++set.users;
-        ctx->holds_streams = true;
-        ctx->s_copy = set.copy;
-        ctx->s_unpack = set.unpack;
-        ctx->s_save = set.save;
+        std::lock_guard<std::mutex> hold(shared_streams_mutex);
+        ++contexts_on[c.device];
+        ctx->counted = true;
     }
+    CA_HIP(ctx, load_streams_for(ctx, nullptr));       // (most programs plan on one stream; a plan on another changes them)
+    CA_HIP(ctx, save_stream_for(ctx, nullptr));
     const int depth = c.pipeline_depth;
     ctx->half_slot_bytes = align_up((size_t)c.max_batch_kv_tokens * (size_t)row_bytes(c), 256);
     ctx->slot_bytes = 2 * ctx->half_slot_bytes;
@@ -1324,6 +1380,7 @@ ca_status ca_rope_rebase(ca_ctx *ctx, const ca_batch *b, void *stream_) {
     if (up > ctx->upload_capacity) return fail(ctx, CA_ERR_OUT_OF_RANGE, "ca_rope_rebase: internal: image of %zu bytes exceeds %zu", up, ctx->upload_capacity);
     st = ca_join(ctx, stream_);
     if (st != CA_OK) return st;
+    CA_HIP(ctx, load_streams_for(ctx, stream));
     RebaseArgs ra{};
     ra.n_seqs = B;
     ra.max_pages = cols;
@@ -1486,6 +1543,7 @@ bool save_stream_idle(ca_ctx *ctx) {
 
 // the save stream continues behind the plan, the work queued so far on `after` and the short moves on other streams
 ca_status save_follows(ca_ctx *ctx, hipStream_t after) {
+    CA_HIP(ctx, save_stream_for(ctx, after));
     if (ctx->inline_pending && (ctx->inline_stream != after || ctx->inline_owner != stream_owner(after))) {
         if (!ctx->inline_done) CA_HIP(ctx, hipEventRecord(ctx->ev_inline, nullptr));
         CA_HIP(ctx, hipStreamWaitEvent(ctx->s_save, ctx->inline_done ? ctx->inline_done : ctx->ev_inline, 0));
@@ -1701,13 +1759,13 @@ ca_status ca_kv_save_layer(ca_ctx *ctx, int32_t layer, const int32_t *tok_begin,
     // saving starts after the producer of this layer's K/V: the work queued on `after_stream`, and the load of
     // this layer if one was issued (its unpack runs on an internal stream and may still be writing the pages a
     // range of kept-history tokens reads)
-    hipStream_t saver = on_caller ? after : ctx->s_save;
     if (on_caller) {
         CA_HIP(ctx, caller_after_plan(ctx, after));
     } else {
         st = save_follows(ctx, after);
         if (st != CA_OK) return st;
     }
+    hipStream_t saver = on_caller ? after : ctx->s_save;
     if (ctx->loaded[layer]) CA_HIP(ctx, after_load(ctx, layer, saver));
 
     std::vector<Segment> segs;

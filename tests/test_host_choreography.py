@@ -286,3 +286,81 @@ def test_numbers_reach_the_library_in_every_form(m):
     for layer in (1.0, np.int16(1)):
         op, = m.queued(lambda: t.append(_Holder(s), layer))
         assert m.lib.model_stream(op) == s
+
+
+# ---- internal streams of several contexts ---------------------------------------------------------------------------
+MODES = pytest.mark.parametrize("load_mode,save_mode", [(0, 0), (1, 1), (2, 2)], ids=["kernel", "staged", "in-place"])
+
+
+@MODES
+@in_model
+def test_contexts_behind_different_streams_do_not_wait_for_each_other(m, load_mode, save_mode):
+    a, b = (Turn(m, [4000], [200], tier=1, load_mode=load_mode, save_mode=save_mode) for _ in range(2))
+    sa, sb = m.stream(), m.stream()
+
+    def turn(t, s):
+        t.rebase(s); t.load(); t.append(s); t.attn(s); t.save(s); t.append_save(s)
+        t.ctx.join(s)
+    for _ in range(2):
+        first = m.queued(lambda: turn(a, sa))
+        second = m.queued(lambda: turn(b, sb))
+        assert not any(m.behind(y, x) for x in first for y in second)
+
+
+@in_model
+def test_contexts_planned_on_one_stream_that_save_behind_different_ones(m):
+    a, b = (Turn(m, [0], [4000], tier=1) for _ in range(2))
+    sa, sb = m.stream(), m.stream()
+    a.rebase(); b.rebase()
+    m.queued(lambda: (a.append(sa), a.save(sa)))
+    append_a, = m.queued(lambda: a.append(sa))
+    a.save(sa)
+    save = m.queued(lambda: (b.append(sb), b.save(sb)))[-1]
+    assert not m.behind(save, append_a)
+
+
+@MODES
+@in_model
+def test_contexts_behind_one_stream_share_the_internal_ones(m, load_mode, save_mode):
+    def turn(t, s):
+        t.rebase(s); t.load(); t.append_save(s); t.save(s)
+        t.ctx.join(s)
+    before = m.lib.model_streams_alive()
+    turns = [Turn(m, [4000], [200], tier=1, load_mode=load_mode, save_mode=save_mode) for _ in range(3)]
+    per_set = 3 if load_mode == 1 else 2
+    s = m.stream()
+    for t in turns:
+        turn(t, None)
+    assert m.lib.model_streams_alive() == before + 1 + per_set
+    for t in turns:
+        turn(t, s)
+    for t in turns:                 # (one set was left for the first context's change)
+        turn(t, None)
+    assert m.lib.model_streams_alive() <= before + 1 + 2 * per_set
+    for t in turns:
+        t.ctx.close()
+    assert m.lib.model_streams_alive() == before + 1
+
+
+@MODES
+@in_model
+def test_moves_keep_their_order_when_the_callers_stream_changes(m, load_mode, save_mode):
+    """a second context keeps the first internal streams in use, so that the first one has to change them"""
+    t, other = (Turn(m, [4000], [4000], tier=1, load_mode=load_mode, save_mode=save_mode) for _ in range(2))
+    streams = [None, m.stream(), m.stream(), None]
+    moves = []
+    for s in streams:
+        other.rebase(None); other.append_save(None)
+        plan, = m.queued(lambda: t.rebase(s))
+        assert all(m.behind(plan, op) for op in moves)
+        new = m.queued(t.load)
+        for x in streams:
+            new += [op for op in m.queued(lambda: t.save(x)) if m.lib.model_stream(op) != x]
+        assert all(m.behind(op, plan) for op in new)
+        moves += new
+        saves = new[1:] if load_mode != 1 else new[3:]
+        assert len(saves) >= 4 and all(m.behind(y, x) for x, y in zip(saves, saves[1:]))
+    t.ctx.join(streams[1])
+    assert all(m.stream_behind(streams[1], op) for op in moves)
+    t.ctx.sync()
+    assert all(m.done(op) for op in moves)
