@@ -70,7 +70,7 @@ typedef struct {
     int32_t max_positions;   /* context window W: largest context (kept history + new) + 0    */
     float   rope_base;       /* 10000                                                         */
     int32_t rope_style;      /* 0: pairs (i, i + head_dim/2); 1: pairs (2i, 2i+1)             */
-    int32_t pipeline_depth;  /* staging slots for loads (read buffer) and for saves, >= 1     */
+    int32_t pipeline_depth;  /* staging slots of load_mode 1 (read buffer) and of save_mode 1, >= 1 */
     int32_t max_seqs;        /* largest batch                                                 */
     int64_t max_batch_kv_tokens; /* largest sum over the batch of context tokens; sizes one   */
                                  /* staging slot and the metadata                             */
@@ -148,8 +148,8 @@ void ca_config_default(ca_config *cfg);
 ca_status ca_config_validate(const ca_config *cfg, char *err, int32_t err_len);
 ca_status ca_batch_validate(const ca_config *cfg, const ca_batch *batch, char *err, int32_t err_len);
 
-/* Allocates the context on cfg->device: streams, events, staging ring
- * (2 * pipeline_depth slots of 2 * max_batch_kv_tokens * n_kv_heads * head_dim * 2 bytes),
+/* Allocates the context on cfg->device: streams, events, staging rings (pipeline_depth slots of
+ * 2 * max_batch_kv_tokens * n_kv_heads * head_dim * 2 bytes for load_mode 1, as many for save_mode 1),
  * rotary table (max_positions * head_dim/2 cos/sin pairs, fp32, computed in fp64), metadata. */
 ca_status ca_create(const ca_config *cfg, ca_ctx **out);
 void ca_destroy(ca_ctx *ctx);

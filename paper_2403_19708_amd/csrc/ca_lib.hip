@@ -71,7 +71,7 @@ struct ca_ctx {
     hipStream_t plan_stream = nullptr; // the stream ca_rope_rebase was given
     std::vector<uint8_t> ready_inline; // per layer: loaded on the plan's stream
     hipEvent_t ev_saved = nullptr;
-    // staging ring: `depth` slots for loads, `depth` for saves; slot = [K tokens | V tokens]
+    // staging rings, each for its staged mode only: `depth` slots for loads, `depth` for saves; slot = [K tokens | V tokens]
     uint8_t *load_slots = nullptr, *save_slots = nullptr;
     size_t slot_bytes = 0, half_slot_bytes = 0;
     std::vector<hipEvent_t> ev_slot_copied, ev_slot_copied2, ev_slot_free;  // per load slot
@@ -808,16 +808,18 @@ static ca_status create_impl(ca_ctx *ctx) {
     const int depth = c.pipeline_depth;
     ctx->half_slot_bytes = align_up((size_t)c.max_batch_kv_tokens * (size_t)row_bytes(c), 256);
     ctx->slot_bytes = 2 * ctx->half_slot_bytes;
-    CA_HIP(ctx, hipMalloc((void **)&ctx->load_slots, ctx->slot_bytes * depth));
-    CA_HIP(ctx, hipMalloc((void **)&ctx->save_slots, ctx->slot_bytes * depth));
-    ctx->ev_slot_copied.assign(depth, nullptr);
-    ctx->ev_slot_copied2.assign(depth, nullptr);
-    ctx->ev_slot_free.assign(depth, nullptr);
-    ctx->slot_used.assign(depth, 0);
-    for (int i = 0; i < depth; ++i) {
-        CA_HIP(ctx, hipEventCreateWithFlags(&ctx->ev_slot_copied[i], hipEventDisableTiming));
-        CA_HIP(ctx, hipEventCreateWithFlags(&ctx->ev_slot_copied2[i], hipEventDisableTiming));
-        CA_HIP(ctx, hipEventCreateWithFlags(&ctx->ev_slot_free[i], hipEventDisableTiming));
+    if (c.save_mode == 1) CA_HIP(ctx, hipMalloc((void **)&ctx->save_slots, ctx->slot_bytes * depth));
+    if (c.load_mode == 1) {
+        CA_HIP(ctx, hipMalloc((void **)&ctx->load_slots, ctx->slot_bytes * depth));
+        ctx->ev_slot_copied.assign(depth, nullptr);
+        ctx->ev_slot_copied2.assign(depth, nullptr);
+        ctx->ev_slot_free.assign(depth, nullptr);
+        ctx->slot_used.assign(depth, 0);
+        for (int i = 0; i < depth; ++i) {
+            CA_HIP(ctx, hipEventCreateWithFlags(&ctx->ev_slot_copied[i], hipEventDisableTiming));
+            CA_HIP(ctx, hipEventCreateWithFlags(&ctx->ev_slot_copied2[i], hipEventDisableTiming));
+            CA_HIP(ctx, hipEventCreateWithFlags(&ctx->ev_slot_free[i], hipEventDisableTiming));
+        }
     }
     ctx->ev_ready.assign(c.n_layers, nullptr);
     ctx->loaded.assign(c.n_layers, 0);

@@ -364,3 +364,21 @@ def test_moves_keep_their_order_when_the_callers_stream_changes(m, load_mode, sa
     assert all(m.stream_behind(streams[1], op) for op in moves)
     t.ctx.sync()
     assert all(m.done(op) for op in moves)
+
+
+# ---- staging rings ------------------------------------------------------------------------------------------------------
+@in_model
+def test_only_staged_moves_have_a_staging_ring(m):
+    def bytes_of(**modes):
+        before = m.lib.model_device_bytes()
+        t = Turn(m, [4000], [200], tier=1, pipeline_depth=4, **modes)
+        made = m.lib.model_device_bytes() - before
+        t.rebase(); t.load(); t.append(); t.save(); t.append_save()
+        t.ctx.close()
+        return made
+    ring = 4 * 2 * (4200 + 64) * 2 * 128 * 2        # slots x (keys, values) x tokens x row
+    bytes_of()                                      # (the first context finds the library's static memory)
+    least = bytes_of()
+    assert bytes_of(load_mode=2, save_mode=2) == least
+    for modes, rings in ((dict(load_mode=1), 1), (dict(save_mode=1), 1), (dict(load_mode=1, save_mode=1), 2)):
+        assert bytes_of(**modes) - least == rings * ring
