@@ -315,7 +315,6 @@ class Job:
             sync()
         ctx.profile_enable(False)
         f_ms, f_n = ctx.profile_read("append")
-        ctx.profile_read("copy_out")
         fused_us = f_ms / f_n * 1e3 if f_n else None
         for kname, nbytes in (("attn", self.attn_bytes), ("unpack", self.unpack_bytes), ("append", self.append_bytes), ("pack", self.pack_bytes)):
             ms, cnt = sep[kname] if kname in sep else ctx.profile_read(kname)

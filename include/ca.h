@@ -302,7 +302,7 @@ ca_status ca_join(ca_ctx *ctx, void *stream);
  * kind: 0 load copy-in (one interval per layer), 1 unpack kernel(s), 2 append kernel(s),
  *       3 attention kernel, 4 pack kernel(s), 5 save copy-out (one interval per layer).
  * A load that one kernel brings across the host link counts as copy-in, with an empty unpack
- * interval behind it; a short write-back by the append kernel also as copy-out.
+ * interval behind it; a write-back by the append kernel is part of its interval.
  * on: 0 off; 1 every kind; any other value 2 * mask times only the kinds k with bit k of mask
  *     set (events cost a few per cent of a step of short kernels; a caller that needs one
  *     kernel's duration inside a timed region can restrict them to that kind).                 */

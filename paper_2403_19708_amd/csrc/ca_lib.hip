@@ -1888,11 +1888,9 @@ ca_status ca_kv_append_save_layer(ca_ctx *ctx, int32_t layer, const void *new_k,
         CA_HIP(ctx, note_save(ctx));
         return CA_OK;
     }
-    // one pass: every vector of the new turn goes to its page and to its row of the tier.  A short turn written across the
-    // host link this way also counts as the write-back it replaces.
-    int iv, iv_back = -1;
+    // one pass: every vector of the new turn goes to its page and to its row of the tier
+    int iv;
     CA_HIP(ctx, prof_begin(ctx, kProfAppend, stream, &iv));
-    if (any_host && c.save_mode != 2) CA_HIP(ctx, prof_begin(ctx, kProfCopyOut, stream, &iv_back));
     for (int at = 0; at < B; at += kMaxSeqsPerLaunch) {
         MoveArgs2 second;
         const int n = std::min(kMaxSeqsPerLaunch, B - at);
@@ -1903,7 +1901,6 @@ ca_status ca_kv_append_save_layer(ca_ctx *ctx, int32_t layer, const void *new_k,
         CA_HIP(ctx, launch_append_save(new_turn_shape(ctx, at, n), at, second, (const uint8_t *)new_k, (const uint8_t *)new_v,
                                        (uint8_t *)k_pool, (uint8_t *)v_pool, stream));
     }
-    CA_HIP(ctx, prof_end(ctx, iv_back, stream));
     CA_HIP(ctx, prof_end(ctx, iv, stream));
     if (!captured) CA_HIP(ctx, note_inline(ctx, stream));    // ca_sync and ca_join cover it, as they would the save stream
     return CA_OK;
