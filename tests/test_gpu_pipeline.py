@@ -47,11 +47,11 @@ def run_stack(case, tier, depth, mode, sync_every_op=False, tile=0, variant=0, *
 
 def test_pipeline_orderings_give_identical_bits():
     """Missing stream waits show up as differences between a fully synchronous run and the
-    overlapped one: staging slots are reused every `depth` layers, pools start as NaN patterns."""
+    overlapped one: with load_mode 1 staging slots are reused every `depth` layers, pools start as NaN patterns."""
     case = Case([300, 64, 0, 777], [40, 130, 9, 257], [20, 0, 0, 300], 4, 2, 128, seed=51, n_layers=6, window=1024)
     ref_out, ref_tier = run_stack(case, "pinned", depth=1, mode=1, sync_every_op=True)
     for tier, depth, mode, save_mode in (("pinned", 1, 0, 0), ("pinned", 2, 0, 0), ("pinned", 3, 0, 1), ("pinned", 2, 2, 2), ("pinned", 2, 0, 1),
-                                         ("device", 2, 0, 0), ("device", 2, 1, 1)):
+                                         ("pinned", 1, 1, 1), ("pinned", 2, 1, 0), ("pinned", 3, 1, 1), ("device", 2, 0, 0), ("device", 2, 1, 1)):
         out, saved = run_stack(case, tier, depth, mode, save_mode=save_mode)
         for l in range(case.n_layers):
             assert np.array_equal(out[l], ref_out[l]), (tier, depth, mode, save_mode, l)
@@ -66,10 +66,12 @@ def test_pipeline_orderings_give_identical_bits():
             at += int(case.new_len[c])
 
 
-def test_next_job_preloads_while_the_current_job_computes():
-    """Section 3.2.1's read buffer across jobs: the first layers of job 2 are loaded (its own context,
-    its own staging slots and streams) while job 1 is still in its layers.  Both jobs must produce the
-    bits they produce when run alone, one after the other."""
+@pytest.mark.parametrize("load_mode", [0, 1], ids=["in-place", "staged"])
+@pytest.mark.parametrize("one_stream", [False, True], ids=["two-streams", "one-stream"])
+def test_next_job_preloads_while_the_current_job_computes(one_stream, load_mode):
+    """Section 3.2.1's read buffer across jobs: the first layers of job 2 are loaded (its own context and staging slots,
+    its own internal streams where it has a stream of its own) while job 1 is still in its layers.  Both jobs must
+    produce the bits they produce when run alone, one after the other."""
     job1 = Case([400, 90], [70, 200], [0, 30], 4, 2, 128, seed=57, n_layers=4, window=1024)
     job2 = Case([150, 600, 20], [33, 5, 140], [10, 0, 0], 4, 2, 128, seed=58, n_layers=4, window=1024)
     alone = [run_stack(job, "pinned", depth=2, mode=0, sync_every_op=True) for job in (job1, job2)]
@@ -79,9 +81,10 @@ def test_next_job_preloads_while_the_current_job_computes():
             for c in range(job.B):
                 check_contract(bf16_bits_to_f64(ref_out[l][at:at + int(job.new_len[c])]), job.oracle_out(l, c), (l, c))
                 at += int(job.new_len[c])
-    a, b = GpuRun(job1, tier="pinned", pipeline_depth=2), GpuRun(job2, tier="pinned", pipeline_depth=2)
+    a, b = (GpuRun(job, tier="pinned", pipeline_depth=2, load_mode=load_mode) for job in (job1, job2))
     try:
-        s1, s2 = torch.cuda.Stream(), torch.cuda.Stream()
+        s1 = torch.cuda.Stream()
+        s2 = s1 if one_stream else torch.cuda.Stream()
         a.rebase(s1)
         for l in range(job1.n_layers):
             a.load(l)
