@@ -61,14 +61,44 @@ def test_units_cut_into_many_runs(shape):
     assert np.array_equal(bits[0], bits[1]) and np.array_equal(bits[0], bits[2])
 
 
-def test_runs_over_many_units():
-    """enough to stream for two workgroups of four wavefronts per compute unit: most runs cover a whole unit and a share on
-    either side"""
-    hist = [int(h) for h in np.random.default_rng(63).integers(100, 700, 48)]
-    case = Case(hist, [1] * 48, [0] * 48, 64, 16, 64, seed=63, window=1024)
-    items, bits = run_case(case, calls=2)
-    assert (items[:, 6] < 0).any() and (items[:, 6] >= 0).any()
-    assert np.array_equal(bits[0], bits[1])
+@pytest.mark.parametrize("split", [0, 1], ids=["split", "whole"])
+@pytest.mark.parametrize("shape", [(64, 16, 64, 0, 1), (64, 8, 64, 1, 3), (64, 8, 128, 0, 1), (64, 8, 128, 1, 1), (32, 4, 128, 0, 4), (24, 8, 128, 1, 6)],
+                         ids=lambda s: "hq%d-hkv%d-d%d-style%d-new%d" % s)
+def test_runs_over_many_units(shape, split):
+    """Enough to stream for two workgroups of four wavefronts per compute unit (16384 pages over all kv heads): most runs
+    cover a whole unit and a share on either side.  Sampled conversations and heads against the oracle; the static entry
+    point gives the same bits."""
+    Hq, Hkv, D, style, new = shape
+    pages, hist, rng = 0, [], np.random.default_rng(63)
+    while pages * Hkv < 16500:
+        hist.append(int(rng.integers(100, 2000 if D == 128 else 700)))
+        pages += (hist[-1] + 15) // 16
+    lens = [max(1, new - c % 3) for c in range(len(hist))]
+    case = Case(hist, lens, [0] * len(hist), Hq, Hkv, D, seed=63, style=style, window=2048)
+    run = GpuRun(case, tier="device", attn_split=split)
+    try:
+        run.rebase()
+        run.load(0)
+        run.append(0)
+        bits = []
+        s = 1.0 / np.sqrt(D)
+        for call in (run.ctx.cached_prefill_attn, run.ctx.cached_prefill_attn, run.ctx.cached_prefill_attn_static):
+            run.out[0].view(torch.int16).fill_(0x7FC0)          # NaN pattern: every element must be rewritten
+            call(0, run.q[0], run.k_pool[0], run.v_pool[0], run.out[0], s)
+            run.finish()
+            bits.append(torch_to_bits(run.out[0]).copy())
+        assert np.array_equal(bits[0], bits[1]) and np.array_equal(bits[0], bits[2])
+        assert not np.any(bits[0] == 0x7FC0)
+        shares = run.ctx.rebase_read(6).reshape(-1, 8)[:, 6]
+        assert (shares < 0).any() and (shares >= 0).any() == (split == 0)
+        ends = [int(np.argmax(hist)), int(np.argmin(hist)), 0, case.B - 1]
+        for c in ends + [int(x) for x in rng.choice(case.B, 4, replace=False)]:
+            heads = [int(h) for h in rng.choice(Hq, 6, replace=False)]
+            got, want = run.out_f64(0, c)[:, heads], case.oracle_out(0, c, heads=heads)
+            check_contract(got, want, c)
+            check_tight(got, want, int(case.n_keep[c]), c)
+    finally:
+        run.close()
 
 
 def test_peaky_scores():
