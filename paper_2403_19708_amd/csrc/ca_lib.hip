@@ -308,12 +308,41 @@ bool is_captured(hipStream_t stream) {
     return st != hipStreamCaptureStatusNone;
 }
 
+// What a capture does not survive (measured): hipEventQuery and hipStreamQuery while some other stream is under capture (by any
+// thread, if in global mode), unless the calling thread is in relaxed mode; and in every mode a query of, or a host's wait
+// for, an event whose stream has come under capture since it was recorded.  Another stream's wait for such an event is refused
+// with hipErrorStreamCaptureIsolation, the capture stays whole; the host then waits instead.
+class RelaxedCapture {
+public:
+    RelaxedCapture() { (void)hipThreadExchangeStreamCaptureMode(&mode_); }
+    ~RelaxedCapture() { (void)hipThreadExchangeStreamCaptureMode(&mode_); }
+
+private:
+    hipStreamCaptureMode mode_ = hipStreamCaptureModeRelaxed;
+};
+// The host waits for the GPU, as hipFree does, which a capture survives in relaxed mode (hipDeviceSynchronize it does not).
+hipError_t finish_device() {
+    RelaxedCapture relaxed;
+    void *p = nullptr;
+    const hipError_t e = hipMalloc(&p, 256);
+    return e == hipSuccess ? hipFree(p) : e;
+}
+// `stream` waits for an event that was recorded on a stream of the caller's, which may have come under capture since
+hipError_t wait_for(hipStream_t stream, hipEvent_t event) {
+    const hipError_t e = hipStreamWaitEvent(stream, event, 0);
+    if (e != hipErrorStreamCaptureIsolation || is_captured(stream)) return e;
+    (void)hipGetLastError();
+    return finish_device();
+}
+hipError_t query(hipEvent_t event) { RelaxedCapture relaxed; return hipEventQuery(event); }
+hipError_t query(hipStream_t stream) { RelaxedCapture relaxed; return hipStreamQuery(stream); }
+
 // May a move be queued on the stream the plan was made on?  The caller may have destroyed it, or be capturing it (a capture
 // would take the move in, and would not survive being asked whether the stream is done).
 bool stream_usable(hipStream_t stream) {
     if (stream == nullptr) return true;
     if (is_captured(stream)) return false;
-    const hipError_t e = hipStreamQuery(stream);
+    const hipError_t e = query(stream);
     if (e == hipSuccess) return true;
     (void)hipGetLastError();
     return e == hipErrorNotReady;
@@ -397,10 +426,16 @@ void leave_streams(ca_ctx *ctx) {
     }
 }
 
+// Is the stream of the newest short move under capture?  (That of another thread's hipStreamPerThread cannot be asked.)
+bool inline_captured(const ca_ctx *ctx) {
+    return ctx->inline_owner == stream_owner(ctx->inline_stream) && is_captured(ctx->inline_stream);
+}
+
 // May the next short move run on `stream`?  Only one stream's inline moves are kept track of at a time.
 bool inline_free(ca_ctx *ctx, hipStream_t stream) {
     if (!ctx->inline_pending || (ctx->inline_stream == stream && ctx->inline_owner == stream_owner(stream))) return true;
-    if (ctx->inline_stream != nullptr ? hipEventQuery(ctx->inline_done) == hipSuccess : hipStreamQuery(nullptr) == hipSuccess) {
+    if (inline_captured(ctx)) return false;
+    if ((ctx->inline_stream != nullptr ? query(ctx->inline_done) : query((hipStream_t) nullptr)) == hipSuccess) {
         ctx->inline_pending = false;
         return true;
     }
@@ -428,13 +463,14 @@ hipError_t note_inline(ca_ctx *ctx, hipStream_t stream) {
 // first use of an internal stream under a plan: it waits for the plan's metadata
 hipError_t after_plan(ca_ctx *ctx, hipStream_t stream, bool *waits) {
     if (!*waits) return hipSuccess;
-    *waits = false;
-    return hipStreamWaitEvent(stream, ctx->ev_plan, 0);
+    const hipError_t e = wait_for(stream, ctx->ev_plan);
+    if (e == hipSuccess) *waits = false;
+    return e;
 }
 
 // a stream of the caller's waits for the plan's metadata (nothing to do for HIP on the stream the plan was made on)
 hipError_t caller_after_plan(ca_ctx *ctx, hipStream_t stream) {
-    return stream == nullptr && ctx->plan_stream == nullptr ? hipSuccess : hipStreamWaitEvent(stream, ctx->ev_plan, 0);
+    return stream == nullptr && ctx->plan_stream == nullptr ? hipSuccess : wait_for(stream, ctx->ev_plan);
 }
 
 // `stream` waits for the load of `layer`
@@ -444,7 +480,7 @@ hipError_t after_load(ca_ctx *ctx, int32_t layer, hipStream_t stream) {
         const hipError_t e = hipEventRecord(ctx->ev_ready[layer], nullptr);
         if (e != hipSuccess) return e;
     }
-    return hipStreamWaitEvent(stream, ctx->ev_ready[layer], 0);   // (nothing to do for HIP on the stream it was recorded on)
+    return wait_for(stream, ctx->ev_ready[layer]);   // (nothing to do for HIP on the stream it was recorded on)
 }
 
 }  // namespace
@@ -937,7 +973,8 @@ ca_status ca_sync(ca_ctx *ctx) {
     if (ctx->save_pending) CA_HIP(ctx, hipEventSynchronize(ctx->ev_saved));
     ctx->save_pending = false;
     if (ctx->inline_pending) {
-        if (ctx->inline_done) CA_HIP(ctx, hipEventSynchronize(ctx->inline_done));
+        if (inline_captured(ctx)) CA_HIP(ctx, finish_device());
+        else if (ctx->inline_done) CA_HIP(ctx, hipEventSynchronize(ctx->inline_done));
         else CA_HIP(ctx, hipStreamSynchronize(nullptr));
     }
     ctx->inline_pending = false;
@@ -962,12 +999,12 @@ ca_status ca_join(ca_ctx *ctx, void *stream) {
         if (ctx->save_pending) CA_HIP(ctx, hipStreamWaitEvent(s, ctx->ev_saved, 0));
         if (s == nullptr) ctx->joined_null = true;
     }
-    if (short_moves && !(s == nullptr && ctx->inline_stream == nullptr)) CA_HIP(ctx, hipStreamWaitEvent(s, short_moves, 0));
+    if (short_moves && !(s == nullptr && ctx->inline_stream == nullptr)) CA_HIP(ctx, wait_for(s, short_moves));
     if (other_too) {
         on.leave();
         if (ctx->load_done) CA_HIP(ctx, hipStreamWaitEvent(s, ctx->load_done, 0));
         if (ctx->save_pending) CA_HIP(ctx, hipStreamWaitEvent(s, ctx->ev_saved, 0));
-        if (short_moves) CA_HIP(ctx, hipStreamWaitEvent(s, short_moves, 0));
+        if (short_moves) CA_HIP(ctx, wait_for(s, short_moves));
     }
     return CA_OK;
 }
@@ -1535,7 +1572,7 @@ bool save_is_short(const ca_ctx *ctx, bool to_host, int64_t bytes) {
 // plans' saves are in front of the plan.)
 bool save_stream_idle(ca_ctx *ctx) {
     if (!ctx->saves_under_plan) return true;
-    if (hipEventQuery(ctx->ev_saved) != hipSuccess) {
+    if (query(ctx->ev_saved) != hipSuccess) {
         (void)hipGetLastError();
         return false;
     }
@@ -1548,7 +1585,7 @@ ca_status save_follows(ca_ctx *ctx, hipStream_t after) {
     CA_HIP(ctx, save_stream_for(ctx, after));
     if (ctx->inline_pending && (ctx->inline_stream != after || ctx->inline_owner != stream_owner(after))) {
         if (!ctx->inline_done) CA_HIP(ctx, hipEventRecord(ctx->ev_inline, nullptr));
-        CA_HIP(ctx, hipStreamWaitEvent(ctx->s_save, ctx->inline_done ? ctx->inline_done : ctx->ev_inline, 0));
+        CA_HIP(ctx, wait_for(ctx->s_save, ctx->inline_done ? ctx->inline_done : ctx->ev_inline));
     }
     if (after != nullptr || ctx->plan_stream != nullptr) CA_HIP(ctx, after_plan(ctx, ctx->s_save, &ctx->save_waits_plan));
     ctx->save_waits_plan = false;          // (behind the default stream: the plan is in front there)

@@ -27,6 +27,7 @@ struct Event {
     int device;
     std::set<int> ops;
     bool captured = false;
+    Stream *stream = nullptr;  // it was recorded on
 };
 struct Op {
     std::string what;
@@ -66,6 +67,21 @@ Stream *stream_of(hipStream_t s) {
 void finish(const std::set<int> &what) {
     for (int op : what)
         if (done.insert(op).second) finish(ops[op].behind);
+}
+// A call that is not allowed while a stream is under capture (in global mode): unless its thread is in relaxed mode it ends
+// the capture.
+thread_local hipStreamCaptureMode capture_mode = hipStreamCaptureModeGlobal;
+bool spoils() {
+    bool any = false;
+    if (capture_mode != hipStreamCaptureModeRelaxed)
+        for (Stream *s : streams) if (s->capturing) any = s->spoilt = true;
+    return any;
+}
+// its stream has come under capture since the event was recorded: no capture survives being asked about it
+bool out_of_reach(const Event *e) { return e->stream && e->stream->capturing && !e->captured; }
+bool spoils(const Event *e) {
+    if (out_of_reach(e)) e->stream->spoilt = true;
+    return spoils() || out_of_reach(e);
 }
 bool finished(const std::set<int> &what) {
     for (int op : what) if (!done.count(op)) return false;
@@ -108,9 +124,9 @@ hipError_t hipSetDevice(int d) { if (d < 0 || d >= n_devices) return hipErrorInv
 hipError_t hipGetLastError() { return hipSuccess; }
 const char *hipGetErrorString(hipError_t) { return "error of the model"; }
 hipError_t hipGetDevicePropertiesR0600(hipDeviceProp_tR0600 *p, int) { std::memset(p, 0, sizeof *p); p->multiProcessorCount = 256; return hipSuccess; }
-hipError_t hipMalloc(void **p, size_t n) { *p = allocate(n, hipMemoryTypeDevice); return *p ? hipSuccess : hipErrorOutOfMemory; }
+hipError_t hipMalloc(void **p, size_t n) { if (spoils()) return hipErrorStreamCaptureUnsupported; *p = allocate(n, hipMemoryTypeDevice); return *p ? hipSuccess : hipErrorOutOfMemory; }
 hipError_t hipHostMalloc(void **p, size_t n, unsigned) { *p = allocate(n, hipMemoryTypeHost); return *p ? hipSuccess : hipErrorOutOfMemory; }
-hipError_t hipFree(void *p) { MODEL; finish([] { std::set<int> all; for (int i = 0; i < (int)ops.size(); ++i) all.insert(i); return all; }()); ranges.erase((uintptr_t)p); return hipSuccess; }
+hipError_t hipFree(void *p) { MODEL; if (spoils()) return hipErrorStreamCaptureUnsupported; finish([] { std::set<int> all; for (int i = 0; i < (int)ops.size(); ++i) all.insert(i); return all; }()); ranges.erase((uintptr_t)p); return hipSuccess; }
 hipError_t hipHostFree(void *p) { return hipFree(p); }
 hipError_t hipHostGetDevicePointer(void **d, void *h, unsigned) { *d = h; return hipSuccess; }
 hipError_t hipGetSymbolAddress(void **p, const void *) { static void *held[64]; if (!held[current]) held[current] = allocate(32 << 20, hipMemoryTypeDevice); *p = held[current]; return hipSuccess; }
@@ -145,8 +161,9 @@ hipError_t hipMemGetAddressRange(hipDeviceptr_t *base, size_t *size, hipDevicept
 }
 hipError_t hipStreamCreateWithFlags(hipStream_t *s, unsigned) { MODEL; Stream *x = new Stream{current}; streams.insert(x); *s = (hipStream_t)x; return hipSuccess; }
 hipError_t hipStreamDestroy(hipStream_t s) { MODEL; Stream *x = stream_of(s); if (!x) return hipErrorInvalidHandle; x->alive = false; return hipSuccess; }
-hipError_t hipStreamQuery(hipStream_t s) { MODEL; Stream *x = stream_of(s); if (x && x->capturing) { x->spoilt = true; return hipErrorStreamCaptureUnsupported; } return !x ? hipErrorInvalidHandle : finished(x->behind) ? hipSuccess : hipErrorNotReady; }
-hipError_t hipStreamSynchronize(hipStream_t s) { MODEL; Stream *x = stream_of(s); if (!x) return hipErrorInvalidHandle; finish(x->behind); return hipSuccess; }
+hipError_t hipThreadExchangeStreamCaptureMode(hipStreamCaptureMode *m) { std::swap(*m, capture_mode); return hipSuccess; }
+hipError_t hipStreamQuery(hipStream_t s) { MODEL; Stream *x = stream_of(s); if (s && spoils()) return hipErrorStreamCaptureUnsupported; if (x && x->capturing) { x->spoilt = true; return hipErrorStreamCaptureUnsupported; } return !x ? hipErrorInvalidHandle : finished(x->behind) ? hipSuccess : hipErrorNotReady; }
+hipError_t hipStreamSynchronize(hipStream_t s) { MODEL; Stream *x = stream_of(s); if (s && spoils()) return hipErrorStreamCaptureUnsupported; if (!x) return hipErrorInvalidHandle; finish(x->behind); return hipSuccess; }
 hipError_t hipStreamIsCapturing(hipStream_t s, hipStreamCaptureStatus *st) { MODEL; Stream *x = stream_of(s); if (!x) return hipErrorInvalidHandle; *st = x->capturing ? hipStreamCaptureStatusActive : hipStreamCaptureStatusNone; return hipSuccess; }
 hipError_t hipDeviceSynchronize() { MODEL; for (int i = 0; i < (int)ops.size(); ++i) if (ops[i].stream->device == current) finish({i}); return hipSuccess; }
 hipError_t hipEventCreateWithFlags(hipEvent_t *e, unsigned) { *e = (hipEvent_t) new Event{current}; return hipSuccess; }
@@ -158,18 +175,20 @@ hipError_t hipEventRecord(hipEvent_t e, hipStream_t s) {
     if (!x || x->device != ((Event *)e)->device) return hipErrorInvalidHandle;
     ((Event *)e)->ops = x->behind;
     ((Event *)e)->captured = x->capturing;
+    ((Event *)e)->stream = x;
     return hipSuccess;
 }
 hipError_t hipStreamWaitEvent(hipStream_t s, hipEvent_t e, unsigned) {
     MODEL;
     Stream *x = stream_of(s);
     if (!x) return hipErrorInvalidHandle;
+    if (out_of_reach((Event *)e)) return hipErrorStreamCaptureIsolation;
     if (x->capturing != ((Event *)e)->captured) { x->spoilt |= x->capturing; return hipErrorStreamCaptureIsolation; }
     x->behind.insert(((Event *)e)->ops.begin(), ((Event *)e)->ops.end());
     return hipSuccess;
 }
-hipError_t hipEventQuery(hipEvent_t e) { MODEL; return ((Event *)e)->captured ? hipErrorCapturedEvent : finished(((Event *)e)->ops) ? hipSuccess : hipErrorNotReady; }
-hipError_t hipEventSynchronize(hipEvent_t e) { MODEL; if (((Event *)e)->captured) return hipErrorCapturedEvent; finish(((Event *)e)->ops); return hipSuccess; }
+hipError_t hipEventQuery(hipEvent_t e) { MODEL; if (spoils((Event *)e)) return hipErrorStreamCaptureUnsupported; return ((Event *)e)->captured ? hipErrorCapturedEvent : finished(((Event *)e)->ops) ? hipSuccess : hipErrorNotReady; }
+hipError_t hipEventSynchronize(hipEvent_t e) { MODEL; if (spoils((Event *)e)) return hipErrorStreamCaptureUnsupported; if (((Event *)e)->captured) return hipErrorCapturedEvent; finish(((Event *)e)->ops); return hipSuccess; }
 hipError_t hipEventElapsedTime(float *ms, hipEvent_t, hipEvent_t) { *ms = 0.001f; return hipSuccess; }
 void **__hipRegisterFatBinary(const void *) { static void *module; return &module; }
 void __hipUnregisterFatBinary(void **) {}

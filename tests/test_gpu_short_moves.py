@@ -208,3 +208,48 @@ def test_append_save_and_static_attention_in_a_graph():
             assert all(np.array_equal(a, torch_to_bits(b)) for a, b in zip(got[1], run.host_v[0])) and np.array_equal(got[2], torch_to_bits(run.v_pool[0]))
     finally:
         run.close()
+
+
+@pytest.mark.parametrize("mode", ["global", "thread_local"])
+@pytest.mark.parametrize("plan", ["default", "own", "captured"])
+@pytest.mark.parametrize("tier,hist,new", [("device", [50, 60], [2, 3]), ("pinned", [50, 60], [2, 3]), ("pinned", [2000, 900], [300, 200])],
+                         ids=["device", "pinned", "long"])
+def test_moves_of_another_job_leave_a_capture_whole(tier, hist, new, plan, mode):
+    """while one job's step is captured, another one's layers are loaded, attended and saved on other streams; its short moves
+    and its plan may be on the very stream that is captured"""
+    case = Case(hist, new, [0, 0], 4, 2, 128, seed=89, n_layers=2, window=4096)
+    run = GpuRun(case, tier=tier)
+    try:
+        captured, own, other = (torch.cuda.Stream() for _ in range(3))
+        s, after = {"default": (None, None), "own": (own, own), "captured": (captured, other)}[plan]
+        x = torch.zeros(1024, device="cuda")
+        run.rebase(s)
+        run.load(0)
+        run.append(0, s)
+        run.save(0, after_stream=other)
+        run.save(0, after_stream=s)
+        graph = torch.cuda.CUDAGraph()
+        with torch.cuda.graph(graph, stream=captured, capture_error_mode=mode):
+            x.add_(1)
+            run.load(1)
+            run.append(1, after)
+            run.attn(0, after)
+            run.attn(1, after)
+            run.ctx.kv_append_save_layer(1, run.k_new[1], run.v_new[1], run.k_pool[1], run.v_pool[1], run.host_k[1], run.host_v[1], after)
+            run.save(0, after_stream=after)
+            run.ctx.join(other)
+        run.finish()
+        for i in range(3):
+            graph.replay()
+            torch.cuda.synchronize()
+            assert float(x[0]) == i + 1
+        for l in range(2):
+            for c in range(case.B):
+                err = np.abs(run.out_f64(l, c) - case.oracle_out(l, c))
+                assert err.max() <= 2e-2 and err.mean() <= 2e-3, (l, c)
+                for which, host in (("k", run.host_k[l]), ("v", run.host_v[l])):
+                    got = torch_to_bits(host[c])
+                    assert np.array_equal(got[:case.hist_len[c]], case.tensor(l, f"{which}_hist", c)), (l, which, c)
+                    assert np.array_equal(got[case.hist_len[c]:], case.tensor(l, f"{which}_new", c)), (l, which, c)
+    finally:
+        run.close()

@@ -198,6 +198,40 @@ def test_a_load_stays_out_of_a_capture_of_the_plans_stream(m, tier):
     assert m.stream_behind(s, load)
 
 
+@pytest.mark.parametrize("tier", [0, 1], ids=["device", "pinned"])
+@pytest.mark.parametrize("hist,new", [(40, 2), (4000, 200)], ids=["short", "long"])
+@pytest.mark.parametrize("plan", ["default", "own", "captured"])
+@in_model
+def test_moves_of_another_job_leave_a_capture_whole(m, plan, hist, new, tier):
+    """a step is captured on one stream (in global mode) while another job's layers are loaded and saved on others, with short
+    moves and saves of that job under way on further streams"""
+    t = Turn(m, [hist], [new], tier=tier, layers=4)
+    captured, own, other = m.stream(), m.stream(), m.stream()
+    s = {"default": None, "own": own, "captured": captured}[plan]
+    after = own if plan == "own" else None
+    t.rebase(s)
+    ops = m.queued(lambda: (t.load(0), t.append(after), t.save(other), t.save(after, tok_begin=[0], tok_end=[hist], dst_tok_offset=[0])))
+    load0, saves = ops[0], [ops[2], ops[3]]
+
+    def during_capture(call):
+        m.lib.model_capture(captured, 1)
+        op = (m.queued(call) or [None])[-1]
+        assert m.lib.model_capture(captured, 0)
+        return op
+    load1 = during_capture(lambda: t.load(1))
+    during_capture(lambda: t.append(after, 1))
+    for call in (lambda: t.save(after), lambda: t.save(other), lambda: t.append_save(after), lambda: t.append_save(other)):
+        saves.append(during_capture(call))
+    for layer, load in ((0, load0), (1, load1)):
+        for x in (after, other):
+            attn = during_capture(lambda: t.attn(x, layer))
+            assert m.behind(attn, load) or m.done(load)
+    t.rebase(s)
+    t.load(0); t.append_save(s)
+    during_capture(lambda: t.ctx.join(other))
+    assert all(m.stream_behind(other, op) or m.done(op) for op in saves)
+
+
 # ---- the order of saves ---------------------------------------------------------------------------------------------
 @pytest.mark.parametrize("streams", ["one", "two"])
 @pytest.mark.parametrize("sizes", [(4000, 2), (2, 4000), (2, 2, 4000), (4000, 2, 2)], ids=str)
