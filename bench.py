@@ -67,11 +67,11 @@ def parse():
     ap.add_argument("--no-decode", action="store_true", help="skip the decode-phase leg")
     ap.add_argument("--decode-steps", type=int, default=20)
     ap.add_argument("--no-check", action="store_true", help="skip the sampled parity check against the oracle")
-    ap.add_argument("--load-mode", type=int, default=0, help="library load_mode (0 staged copies for a host tier, 2 kernels read the tier in place)")
+    ap.add_argument("--load-mode", type=int, default=0, help="library load_mode (0, 2: a kernel reads the tier in place; 1: staged copies)")
     ap.add_argument("--save-mode", type=int, default=0)
     ap.add_argument("--loads-ahead", type=int, default=0, help="layers whose loads are queued ahead of the compute calls (0: all first)")
     ap.add_argument("--two-call-save", action="store_true", help="append and save the new turn with the two separate calls in every leg")
-    ap.add_argument("--depth", type=int, default=4, help="staging slots of the read stream (pipeline_depth) in the headline leg")
+    ap.add_argument("--depth", type=int, default=4, help="pipeline_depth (staging slots, used with --load-mode 1 and --save-mode 1) of the headline leg")
     ap.add_argument("--timeline-file", type=str, default="", help="write the per-interval timeline of the instrumented step here")
     ap.add_argument("--layers", type=int, default=0, help="override the number of layers (debugging only; marks the result invalid)")
     return ap.parse_args()
@@ -253,7 +253,7 @@ class Job:
             ctx.kv_save_layer(l, self.k_pool[l], self.v_pool[l], src_k[l], src_v[l], after_stream=stream)
 
     def step(self, ctx, src_k, src_v, stream):
-        """the whole path for one batch: the read stream runs ahead as far as its staging slots allow"""
+        """the whole path for one batch: the loads run ahead of the compute calls"""
         self.rebase(ctx, stream)
         # All loads are queued first.  That keeps the host busy for about 6 ms before the first attention is queued (a
         # load is 2 copies per conversation), but queueing them a few layers ahead of the compute calls instead was
@@ -344,15 +344,14 @@ class Job:
                 "frac_hbm_peak": gbs / HBM_PEAK_GBS, "binding_roofline": self.attn_bound, "roofline_floor_us": self.attn_floor_us,
                 "frac_binding_roofline": self.attn_floor_us / us}
 
-    def move_figures(self, prof, fused_device_tier=False):
-        """fused_device_tier: the append figure is the one-pass append + save kernel (read N, write 2N bytes)"""
+    def move_figures(self, prof, fused_device_tier=False, link_loads=False):
+        """fused_device_tier: the append figure is the one-pass append + save kernel (read N, write 2N bytes); link_loads: one
+        kernel brings a layer across the host link and scatters it, its unpack intervals are empty"""
         out = {}
         app = self.append_bytes * 1.5 if fused_device_tier else self.append_bytes
         for k, nbytes in (("unpack", self.unpack_bytes), ("append", app), ("pack", self.pack_bytes)):
             ms, n = prof[k]
-            us = ms / n * 1e3 if n else None
-            if us is not None and us < 2.0:      # a load across the host link scatters as it copies: its unpack intervals are empty
-                us = None
+            us = ms / n * 1e3 if n and not (k == "unpack" and link_loads) else None
             out[k] = {"avg_launch_us": us, "gbs": nbytes / (us * 1e-6) / 1e9 if us else None,
                       "frac_hbm_peak": nbytes / (us * 1e-6) / 1e9 / HBM_PEAK_GBS if us else None}
         return out
@@ -509,12 +508,12 @@ def timeline_figures(tl, path=None):
 
 
 def depth_sweep(torch, ca, job, host_k, host_v, stream, depths, args):
-    """the same host-tier step with 1, 2, 4, ... staging slots on the read stream"""
+    """the same host-tier step with staged loads (load_mode 1) and 1, 2, 4, ... staging slots on the read stream"""
     out = []
     for d in depths:
-        ctx = ca.Context(job.config(pipeline_depth=d, load_mode=args.load_mode, save_mode=args.save_mode))
+        ctx = ca.Context(job.config(pipeline_depth=d, load_mode=1, save_mode=args.save_mode))
         try:
-            dt, prof = job.timed(ctx, host_k, host_v, stream, 1, 2, f"pinned tier, pipeline_depth {d}", kinds=["copy_in", "attn"])
+            dt, prof = job.timed(ctx, host_k, host_v, stream, 1, 2, f"pinned tier, staged loads, pipeline_depth {d}", kinds=["copy_in", "attn"])
             cin_ms, _ = prof["copy_in"]
             out.append(dict(pipeline_depth=d, ms_per_step=dt / 2 * 1e3, copy_in_ms=cin_ms / 2))
         finally:
@@ -805,7 +804,7 @@ def main():
 
     # every kernel bracketed, same tier: in-step durations of the move kernels
     dt_i, prof_i = job.timed(ctx, src_k, src_v, stream, 0, 1, f"{tier_name} tier, every kernel timed", timeline=True)
-    kv_move = job.move_figures(prof_i)
+    kv_move = job.move_figures(prof_i, link_loads=args.tier == "pinned" and args.load_mode != 1)
     if pipeline is not None and prof_i.get("timeline"):
         pipeline["timeline"] = timeline_figures(prof_i["timeline"], args.timeline_file or None)
         pipeline["timeline"]["ms_step_instrumented"] = dt_i * 1e3
