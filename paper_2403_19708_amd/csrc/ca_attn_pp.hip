@@ -35,14 +35,11 @@
 // (vector work, LDS reads, loads, barrier) shortens the kernel by about that ingredient's own time: the parts do
 // not hide behind each other.  Kept selectable (attn_schedule = 1) because it has no window limit.
 #include "ca_internal.h"
+#include "ca_device.h"
 
 namespace ca {
 
 namespace {
-
-typedef __attribute__((ext_vector_type(8))) __bf16 bf16x8;
-typedef __attribute__((ext_vector_type(2))) __bf16 bf16x2;
-typedef __attribute__((ext_vector_type(16))) float f32x16;
 
 constexpr int kD = 128;                  // head dimension this kernel is built for
 constexpr int kBN = 64;                  // keys per tile
@@ -54,71 +51,6 @@ constexpr int kNS = 4;                   // ring slots per array
 #define CA_PP_AHEAD 8
 #endif
 constexpr int kAhead = CA_PP_AHEAD;      // LDS operand reads in flight ahead of the matrix instruction that uses them
-
-__device__ inline float bf_lo(uint32_t u) { return __uint_as_float(u << 16); }
-__device__ inline float bf_hi(uint32_t u) { return __uint_as_float(u & 0xffff0000u); }
-__device__ inline uint32_t pack_bf16(float a, float b) {
-    bf16x2 v = {(__bf16)a, (__bf16)b};
-    return __builtin_bit_cast(uint32_t, v);
-}
-
-// 16 bytes per lane, global -> LDS at lds_base + lane*16, address = wave-uniform 64-bit base + per-lane byte
-// offset.  Inline assembly so that the compiler does not guard later LDS reads with s_waitcnt vmcnt(0); the
-// waits are placed by hand (these loads complete in order).
-__device__ inline void dma16_sbase(const void *base_uniform, uint32_t lane_off, uint32_t lds_base) {
-    asm volatile("s_mov_b32 m0, %0\n\tglobal_load_lds_dwordx4 %1, %2"
-                 : : "s"(lds_base), "v"(lane_off), "s"(base_uniform) : "memory", "m0");
-}
-
-__device__ inline uint32_t lds_offset(const void *p) {
-    return (uint32_t)(uintptr_t)(const __attribute__((address_space(3))) void *)p;
-}
-
-#define CA_WAIT_VMCNT(n) __builtin_amdgcn_s_waitcnt(0x0F70 | ((n) & 15) | (((n) >> 4) << 14))
-
-// (cos, sin) of the 8 pairs a thread rotates: STYLE 0 pairs (d, d + 64) of piece `piece` (dims 8*piece ..) and
-// its partner piece + 8; STYLE 1 pairs (2i, 2i+1) inside piece `piece` (cs[0..3]) and inside piece + 8 (cs[4..7])
-template <int STYLE>
-__device__ inline void load_cs(const float2 *__restrict__ rope, int pos, int piece, float2 (&cs)[8]) {
-    constexpr int HALF = kD / 2;
-    const float2 *row = rope + (int64_t)pos * HALF;
-    if (STYLE == 0) {
-        const float4 *p = reinterpret_cast<const float4 *>(row + 8 * piece);
-#pragma unroll
-        for (int w = 0; w < 4; ++w) {
-            const float4 v = p[w];
-            cs[2 * w] = make_float2(v.x, v.y);
-            cs[2 * w + 1] = make_float2(v.z, v.w);
-        }
-    } else {
-        const float4 *p = reinterpret_cast<const float4 *>(row + 4 * piece);
-        const float4 *q = reinterpret_cast<const float4 *>(row + HALF / 2 + 4 * piece);
-#pragma unroll
-        for (int w = 0; w < 2; ++w) {
-            const float4 v = p[w], u = q[w];
-            cs[2 * w] = make_float2(v.x, v.y);
-            cs[2 * w + 1] = make_float2(v.z, v.w);
-            cs[4 + 2 * w] = make_float2(u.x, u.y);
-            cs[4 + 2 * w + 1] = make_float2(u.z, u.w);
-        }
-    }
-}
-
-// one dword (2 elements) of each of the two 16-byte pieces a (dims d0..) and b (dims d0 + 64..), times `scale`
-template <int STYLE>
-__device__ inline void rotate_dword(uint32_t &pa, uint32_t &pb, const float2 (&cs)[8], int w, float scale) {
-    const float a0 = bf_lo(pa), a1 = bf_hi(pa);
-    const float b0 = bf_lo(pb), b1 = bf_hi(pb);
-    if (STYLE == 0) {
-        const float2 c0 = cs[2 * w], c1 = cs[2 * w + 1];
-        pa = pack_bf16((a0 * c0.x - b0 * c0.y) * scale, (a1 * c1.x - b1 * c1.y) * scale);
-        pb = pack_bf16((b0 * c0.x + a0 * c0.y) * scale, (b1 * c1.x + a1 * c1.y) * scale);
-    } else {
-        const float2 ca_ = cs[w], cb_ = cs[4 + w];
-        pa = pack_bf16((a0 * ca_.x - a1 * ca_.y) * scale, (a1 * ca_.x + a0 * ca_.y) * scale);
-        pb = pack_bf16((b0 * cb_.x - b1 * cb_.y) * scale, (b1 * cb_.x + b0 * cb_.y) * scale);
-    }
-}
 
 // ---------------------------------------------------------------------------------------------------------
 // scratch copy of the batch context: rotated keys (piece-major blocks) and transposed values
@@ -144,7 +76,7 @@ __global__ __launch_bounds__(256) void prepare_kv_kernel(AttnArgs a) {
             x = *reinterpret_cast<const uint4 *>(a.k_pool + src + key * kD + 8 * pr);
             y = *reinterpret_cast<const uint4 *>(a.k_pool + src + key * kD + HALF + 8 * pr);
             float2 cs[8];
-            load_cs<STYLE>(a.rope, pos, pr, cs);
+            load_cs<kD, STYLE>(a.rope, pos, pr, cs);
             uint32_t *px = reinterpret_cast<uint32_t *>(&x), *py = reinterpret_cast<uint32_t *>(&y);
 #pragma unroll
             for (int w = 0; w < 4; ++w) rotate_dword<STYLE>(px[w], py[w], cs, w, 1.0f);
@@ -483,7 +415,7 @@ __global__ __launch_bounds__(64 * kNW, 2) void attn_pp_kernel(AttnArgs a) {
             uint4 x = *reinterpret_cast<const uint4 *>(qrow + 8 * piece);
             uint4 y = *reinterpret_cast<const uint4 *>(qrow + HALF + 8 * piece);
             float2 cs[8];
-            load_cs<STYLE>(a.rope, qpos, piece, cs);
+            load_cs<kD, STYLE>(a.rope, qpos, piece, cs);
             uint32_t *px = reinterpret_cast<uint32_t *>(&x), *py = reinterpret_cast<uint32_t *>(&y);
 #pragma unroll
             for (int w = 0; w < 4; ++w) rotate_dword<STYLE>(px[w], py[w], cs, w, cscale);
