@@ -253,3 +253,43 @@ def test_moves_of_another_job_leave_a_capture_whole(tier, hist, new, plan, mode)
                     assert np.array_equal(got[case.hist_len[c]:], case.tensor(l, f"{which}_new", c)), (l, which, c)
     finally:
         run.close()
+
+
+@pytest.mark.parametrize("tier", ["pinned", "device"])
+@pytest.mark.parametrize("offset", [2, 8])
+@pytest.mark.parametrize("hist,new", [([50, 60], [2, 3]), ([2000, 900], [300, 200])], ids=["short", "long"])
+def test_a_tier_of_any_alignment(hist, new, offset, tier):
+    """the tier's rows need the alignment of their elements only: kernels reach it in 16-byte pieces, copies took any address"""
+    case = Case(hist, new, [0, 7], 4, 2, 128, seed=90, window=4096)
+    row = 2 * 128 * 2
+    run = GpuRun(case, tier=tier)
+    try:
+        def shifted(t):
+            n = t.numel() * 2
+            raw = torch.zeros(n + 64, dtype=torch.uint8, pin_memory=True) if tier == "pinned" else torch.zeros(n + 64, dtype=torch.uint8, device=run.dev)
+            raw[offset:offset + n] = t.reshape(-1).view(torch.uint8)
+            return raw
+        raw = [[shifted(t) for t in h] for h in (run.host_k[0], run.host_v[0])]
+        torch.cuda.synchronize()
+        ptr = [[t.data_ptr() + offset for t in h] for h in raw]
+        for one_call in (False, True):
+            run.rebase()
+            run.ctx.kv_load_layer(0, *ptr, run.k_pool[0], run.v_pool[0])
+            if one_call:
+                run.ctx.kv_append_save_layer(0, run.k_new[0], run.v_new[0], run.k_pool[0], run.v_pool[0], *ptr)
+            else:
+                run.append(0)
+                run.ctx.kv_save_layer(0, run.k_pool[0], run.v_pool[0], *ptr)
+            run.finish()
+            for which, pool, host in (("k", run.k_pool[0], raw[0]), ("v", run.v_pool[0], raw[1])):
+                assert np.array_equal(torch_to_bits(pool), case.oracle_pool(0, which)), which
+                for c in range(case.B):
+                    all_bytes = host[c].cpu().numpy()
+                    at = offset + int(case.hist_len[c]) * row
+                    got = all_bytes[at:at + int(case.new_len[c]) * row].copy().view(np.uint16).reshape(-1, 2, 128)
+                    assert np.array_equal(got, case.tensor(0, f"{which}_new", c)), (which, c)
+                    assert not all_bytes[:offset].any() and not all_bytes[offset + (int(case.hist_len[c]) + int(case.new_len[c])) * row:].any()
+                    host[c][at:at + int(case.new_len[c]) * row] = 0
+            torch.cuda.synchronize()
+    finally:
+        run.close()
