@@ -20,13 +20,15 @@
  *     pin_memory).  Streams are hipStream_t passed as void*; NULL is the default stream.
  *   - The caller owns every tensor (pools, Q, output, host tier).  The library owns its
  *     context: events, a ring of staging slots in HBM, a rotary table and small per-batch
- *     metadata.  Three internal streams (copy-in, unpack, save) are shared by the contexts
- *     on a GPU.  It never frees or reallocates caller memory.
+ *     metadata.  Its internal streams (copy-in, unpack, save) are shared by the contexts of
+ *     a GPU that work behind the same stream of the caller.  It never frees or reallocates
+ *     caller memory.
  *   - Every call validates its arguments on the host BEFORE anything is launched and
  *     returns a ca_status; nothing throws or aborts.  ca_last_error() gives the text of
  *     the last failure on that context.  A context is not thread-safe.
  *   - All entry points except ca_create / ca_destroy / ca_sync / ca_rebase_read are
- *     asynchronous with respect to the host.
+ *     asynchronous with respect to the host (but for a call that has to wait for earlier work
+ *     on a stream that is under capture by then: the host waits).
  *
  * Layouts (element type bf16 = 2 bytes unless stated)
  *   paged pool   k_pool, v_pool : [num_pages][n_kv_heads][page_size][head_dim], one pair
@@ -85,9 +87,12 @@ typedef struct {
                              /* one copy per conversation on a copy engine; 2: as 0, but            */
                              /* ca_kv_append_save_layer writes a pinned tier from the one kernel    */
                              /* on the caller's stream whatever the size                            */
-    int32_t attn_variant;    /* 0: choose (the streaming kernel for a batch of decode steps, else the    */
-                             /* matrix-core kernel); 1: scalar fp32 kernel (slow, for checking); 2: the  */
-                             /* matrix-core kernel, K/V loaded straight into LDS, whatever the batch;    */
+    int32_t attn_variant;    /* 0: choose (the streaming kernel for a batch with at most 2 stacked query */
+                             /* rows per (conversation, kv head), the few-rows kernel for at most 32,    */
+                             /* else the matrix-core tile kernels; a batch's largest number of rows      */
+                             /* counts; attn_tile_rows asks for tiles from 3 rows on, attn_prerotate 2   */
+                             /* whatever the rows); 1: scalar fp32 kernel (slow, for checking); 2: the   */
+                             /* matrix-core tile kernels, whatever the batch;                            */
                              /* 4: as 0, but a batch in which some (conversation, kv head) has more than */
                              /* 2 stacked query rows (not a decode step) is refused by                   */
                              /* ca_cached_prefill_attn with CA_ERR_UNSUPPORTED.  (3 named a second       */

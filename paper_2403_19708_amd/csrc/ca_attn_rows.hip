@@ -8,7 +8,7 @@
 //     global_load_lds and released by its own s_waitcnt.  No barrier until the end of an item; eight wavefronts of a
 //     compute unit keep about 100 KiB in flight, which is what HBM's latency asks for at 6 TB/s.  (The tile kernel of
 //     ca_attn_dma.hip walks 32-key tiles in lock step and pads 8 rows to 32: 139 us for 64 conversations of 1024 to 4096
-//     tokens, 8 kv heads, 671 MB, where this kernel takes about 110.)
+//     tokens, 8 kv heads, 671 to 679 MB, where this kernel takes 118 back to back and 124 with other kernels between.)
 //   * S^T = K Q^T with v_mfma_f32_16x16x32_bf16 (16 keys x 16 rows), O^T += V^T P^T with v_mfma_f32_16x16x16_bf16: the C
 //     registers of the first, rounded to bf16, are the B operand of the second.  Softmax as in the tile kernel: scale and
 //     log2(e) folded into the rotated query, the reference maximum enters as the accumulator and is raised lazily.

@@ -36,7 +36,9 @@ static void *static_scratch_ptr[kMaxDevices] = {nullptr};   // [device ordinal],
 // append of one context's turn sat behind another context's loads as soon as a second context existed (three contexts in
 // turn, 236 MB of pinned history each: 6.4 ms a turn, 4.6 ms with one context's three streams).  Contexts behind different
 // streams of the caller have streams of their own: an internal stream waits for its caller's, and what another context queued
-// behind that wait would wait too.  Contexts on different threads may use a stream at once: enqueueing is thread-safe, and
+// behind that wait would wait too (with 16 hardware queues and one of two contexts behind a stream that is busy for 14 ms, the
+// other one's turn: 22.8 ms with one set, 5.6 with its own; with four queues the streams wait for each other either way).
+// Contexts on different threads may use a stream at once: enqueueing is thread-safe, and
 // every wait is on an event recorded right behind the work it stands for.
 // There are at most as many of a kind as there were contexts at once.  A stream goes with the context that used it last; one
 // that a context left for another serves the next context that needs one, or goes with the GPU's last context.
@@ -160,9 +162,10 @@ ca_status fail(ca_ctx *ctx, ca_status st, const char *fmt, ...) {
 constexpr int kRowsMaxWorkgroups = 512;
 constexpr size_t kMetaAlign = 64;            // alignment of the arrays of the metadata image
 // Workgroups of a kernel that moves between the pool and pinned host memory (32 KB in flight each), measured on MI355X with
-// 16 conversations of a grouped-query layer (169 MB to load, 18 MB to save), the attention of another layer beside it:
-//   loads   4: 46 GB/s   8: 57, attention 7 % slower   10: 57, 20 %    16: 56, 1.7 x   32: 57, 3.8 x
-//   saves   2: 34 GB/s   4: 44, attention undisturbed   8: 53, 1.2 x   16: 54
+// 16 conversations of a grouped-query layer (169 MB to load, 18 MB to save): the rate alone, the rate beside the attention of
+// another layer (563 us), and how that attention is slowed down (its own times differ by 7 % from run to run)
+//   loads   4: 46, 30 GB/s, not   8: 57, 51, not   10: 57, 54, not   16: 56, 56, 1.36 x   32: 57, 55, 2.0 x
+//   saves   2: 31, 31 GB/s, not   4: 45, 44, not    8: 52, 51, 1.4 x   16: 54, 54, 1.9 x
 // Past what the link holds the requests queue up in the memory system in front of everyone else's.  Whole turns (two layers
 // of 64 such conversations, us): 27648 with 6 load workgroups, 27006 with 8, 26780 with 10, 26706 with 12.
 constexpr int kLinkLoadWorkgroups = 10;
@@ -1343,7 +1346,10 @@ ca_status ca_rope_rebase(ca_ctx *ctx, const ca_batch *b, void *stream_) {
                 // where 2.4 would do.  So equal shares of at most a few fractions of a compute unit's ideal load are tried
                 // as well, and taken where their schedule is at least 5 % shorter and they need no more scratch than
                 // halving.  Below sixteen tiles between halving and ideal the search costs the host what it could gain.
-                // (That conversation, 8 layers: 3327 -> 2905 us a pass.)
+                // (That conversation, 8 layers: 3327 -> 2905 us a pass.  Of 52 batches, 13 length mixes of one to four
+                // conversations of 4100 to 60000 tokens on 64/8, 32/32 and 8/2 heads of 128 and 32/4 of 64, the rule changes
+                // the plan of 11: their attention takes 0.83 to 0.99 of what it took, 0.90 in the middle.  The search costs
+                // the host up to 27 us a plan.)
                 const double halved = makespan;
                 if (halved < 1.05 * uncut + 16.0) continue;
                 bool found = false;
@@ -2008,7 +2014,6 @@ static ca_status attn_impl(ca_ctx *ctx, int32_t layer, const void *q, const void
     a.softmax_scale = softmax_scale;
     int iv = -1;
     if (timed) CA_HIP(ctx, prof_begin(ctx, kProfAttn, stream, &iv));
-    // 0 picks the LDS-direct kernel whenever its page-id table holds the window
     const bool direct = direct_variant(c);
     // a decode step (one or two stacked rows per (conversation, kv head)) is a matrix-vector product: streamed
     const bool decode = direct && c.attn_variant != 2 && !ctx->prerotate && ctx->max_unit_rows >= 1 &&
