@@ -15,7 +15,7 @@ import sysconfig
 
 HERE = os.path.dirname(os.path.abspath(__file__))
 ROOT = os.path.dirname(HERE)
-SOURCES = ["ca_lib.hip", "ca_move.hip", "ca_attn_ref.hip", "ca_attn_dma.hip", "ca_attn_pp.hip", "ca_attn_decode.hip", "ca_attn_rows.hip",
+SOURCES = ["ca_lib.hip", "ca_move.hip", "ca_attn_ref.hip", "ca_attn_dma.hip", "ca_attn_prerot.hip", "ca_attn_pp.hip", "ca_attn_decode.hip", "ca_attn_rows.hip",
            "ca_store.cpp"]   # the last one is host code only (placement manager)
 LIB = os.path.join(HERE, "libca_hip.so")
 BINDING_SRC = os.path.join(HERE, "csrc", "ca_binding.cpp")         # CPython module next to it, linked against it

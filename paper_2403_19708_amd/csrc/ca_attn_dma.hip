@@ -32,7 +32,7 @@
 //     of K (32 keys x one 16-byte piece), the in-place rotary pass and the transposing reads of V
 //     are all bank-conflict free, and the offset of a piece is linear in the piece index, so the
 //     per-k-step offsets are instruction immediates.
-//   * K lands in LDS without positions; the workgroup rotates the NEXT tile in place (LDS -> fp32
+//   * K lands in LDS without positions (ca_attn_prerot.hip has the case of keys rotated beforehand); the workgroup rotates the NEXT tile in place (LDS -> fp32
 //     rotate -> bf16 -> same LDS bytes) while the matrix cores work on the current one.
 //   * V is never transposed by the ALUs: ds_read_b64_tr_b16 hands each lane 4 consecutive keys of
 //     one head dimension, which is exactly the A-operand layout of O^T += V^T P^T (two such reads
@@ -55,14 +55,11 @@ constexpr int kMaxPagesLds = 2048;   // page ids kept in LDS at a time: a window
 // NW = 8, BN = 64 (one workgroup per compute unit, 256-row tiles) and NW = 4, BN = 32 (two independent
 // workgroups per compute unit, 128-row tiles: the two wavefronts that share a SIMD then belong to
 // different workgroups, are not in lock step, and one's matrix products run under the other's softmax).
-// ROT = false: the keys come already rotated from a scratch copy of the context (rotate_keys_kernel below),
-// dense pages numbered per conversation; used when many row tiles share the keys of a (conversation, kv head)
-// and rotating them once beats rotating them in every tile.
 // NS = LDS stages of the tile ring: the loads of tile T+NS-1 go out in iteration T.
 // PGW = page ids kept in LDS at a time, OCC = wavefronts per SIMD the register budget is cut for.
-template <int D, int STYLE, int NW, int BN, bool ROT = true, int NS = 4, int PGW = kMaxPagesLds, int OCC = 2>
+template <int D, int STYLE, int NW, int BN, int NS = 4, int PGW = kMaxPagesLds, int OCC = 2>
 __global__ __launch_bounds__(64 * NW, OCC) void attn_dma_kernel(AttnArgs a) {
-    static_assert(ROT ? NS >= 4 : NS >= 2, "the in-place rotary pass needs a tile landed one iteration early");
+    static_assert(NS >= 4, "the in-place rotary pass needs a tile landed one iteration early");
     constexpr int NTHREADS = 64 * NW;
     constexpr int MB = BN / 32;              // 32-key blocks of S^T per tile
     constexpr int KS2 = BN / 16;             // 16-key steps of the second product per tile
@@ -79,9 +76,8 @@ __global__ __launch_bounds__(64 * NW, OCC) void attn_dma_kernel(AttnArgs a) {
     constexpr int ROT_TASKS = BN * PPR / 2;  // (key, piece pair) tasks of the rotary pass
     static_assert(2 * CHUNKS % NW == 0, "chunks divide evenly over the wavefronts");
     static_assert((NW == 8 ? 1 : OCC) * (NS * STAGE + PGW * 4) <= 160 * 1024, "LDS budget");
-    // loads that may still be in flight at the end of an interior iteration: with the rotary pass tile+2 must have
-    // landed (it is rotated next), without it only tile+1
-    constexpr int FLY = ROT ? (NS > 3 ? NI : 0) : (NS - 2) * NI;
+    // loads that may still be in flight at the end of an interior iteration: tile+2 must have landed (it is rotated next)
+    constexpr int FLY = NI;
 
     __shared__ __attribute__((aligned(16))) uint8_t ring[NS * STAGE];
     __shared__ int32_t pg[PGW];
@@ -135,7 +131,7 @@ __global__ __launch_bounds__(64 * NW, OCC) void attn_dma_kernel(AttnArgs a) {
     bf16x8 Qf[KSTEPS];          // loaded and rotated in the prologue, once the first key/value tiles are on their way
 
     // ---- rotary pass: this thread's (key, piece pair) of every K tile ------------------------------
-    const bool rot_active = ROT && (ROT_TASKS >= NTHREADS || tid < ROT_TASKS);
+    const bool rot_active = ROT_TASKS >= NTHREADS || tid < ROT_TASKS;
     // 16 consecutive lanes take the KPC keys of a chunk times consecutive pieces = 16 consecutive 16-byte
     // slots, so the 16-byte LDS accesses of the pass are free of bank conflicts (key-major lanes were 2-way)
     const int rot_kk = (tid / (KPC * (PPR / 2))) * KPC + tid % KPC;
@@ -143,12 +139,10 @@ __global__ __launch_bounds__(64 * NW, OCC) void attn_dma_kernel(AttnArgs a) {
     const int rot_off = (rot_kk / KPC) * CH + (rot_pr * KPC + rot_kk % KPC) * 16;   // piece rot_pr; partner +512
     constexpr int ROT_PARTNER = (PPR / 2) * KPC * 16;
     float2 k_step[8], k_cs[8];
-    if (ROT) load_cs<D, STYLE>(a.rope, BN, rot_pr, k_step);
+    load_cs<D, STYLE>(a.rope, BN, rot_pr, k_step);
     // first position of this thread's key; a thread whose first key lies past the visible range never sees a
     // visible one later either, so clamping it is harmless (and keeps the read inside the table)
-    if (ROT) load_cs<D, STYLE>(a.rope, rot_active ? min(t_begin * BN + rot_kk, kmax - 1) : 0, rot_pr, k_cs);
-    const uint16_t *const k_src = ROT ? a.k_pool : a.k_rot;
-    const int k_page0 = ROT ? 0 : a.dense_page0[c];          // ROT = false: key page i of the conversation is k_page0 + i
+    load_cs<D, STYLE>(a.rope, rot_active ? min(t_begin * BN + rot_kk, kmax - 1) : 0, rot_pr, k_cs);
     uint4 kx, ky;
 
     // ---- operand addresses inside a stage ---------------------------------------------------------------
@@ -189,8 +183,8 @@ __global__ __launch_bounds__(64 * NW, OCC) void attn_dma_kernel(AttnArgs a) {
 #pragma unroll
         for (int i = 0; i < NI; ++i) {
             const int t = min(kt0 + ld_tok[i], kmax - 1);
-            const int page = (ROT || ld_is_v[i]) ? pg[(t >> 4) - pg_base] : k_page0 + (t >> 4);
-            const uint16_t *base = ld_is_v[i] ? a.v_pool : k_src;
+            const int page = pg[(t >> 4) - pg_base];
+            const uint16_t *base = ld_is_v[i] ? a.v_pool : a.k_pool;
             const uint16_t *src = base + (((int64_t)page * Hkv + g) * kPageSize + (t & 15)) * D + ld_goff[i];
             dma16(src, __builtin_amdgcn_readfirstlane(lds_offset(stage + ld_loff[i])));
         }
@@ -207,7 +201,7 @@ __global__ __launch_bounds__(64 * NW, OCC) void attn_dma_kernel(AttnArgs a) {
 #pragma unroll
         for (int i = 0; i < NI; ++i) {
             const int pi = (kt0 + ((wave_u + NW * i) % CHUNKS) * KPC) >> 4;
-            page_v[i] = (ROT || wave_u + NW * i >= CHUNKS) ? pg[pi - pg_base] : k_page0 + pi;
+            page_v[i] = pg[pi - pg_base];
         }
 #pragma unroll
         for (int i = 0; i < NI; ++i) {
@@ -216,7 +210,7 @@ __global__ __launch_bounds__(64 * NW, OCC) void attn_dma_kernel(AttnArgs a) {
             const int jch = cid % CHUNKS;
             const int t0 = kt0 + jch * KPC;                                 // first key of the chunk
             const int page = __builtin_amdgcn_readfirstlane(page_v[i]);
-            const uint16_t *base = (is_v ? a.v_pool : k_src) + (((int64_t)page * Hkv + g) * kPageSize + (t0 & 15)) * D;
+            const uint16_t *base = (is_v ? a.v_pool : a.k_pool) + (((int64_t)page * Hkv + g) * kPageSize + (t0 & 15)) * D;
             dma16_sbase(base, ld_lane_off, stage + (uint32_t)((is_v ? TILE : 0) + jch * CH));
         }
     };
@@ -509,38 +503,6 @@ __global__ __launch_bounds__(256) void combine_kernel(AttnArgs a) {
     *reinterpret_cast<uint2 *>(a.out + ((int64_t)(a.cu_q[ci.seq] + j) * a.n_q_heads + head) * D + d) = ob;
 }
 
-// Rotates the keys of the whole batch context once (Section 3.4: the rebased positional encoding, applied
-// when the cache is used): dense page dp of the scratch copy = pool page rot_src_page[dp] with token slot s
-// rotated at position rot_pos0[dp] + s, in fp32 from the table, rounded to bf16 -- the same values the fused
-// path forms tile by tile (there with the rotation advanced by recurrence).  one workgroup per (dense page, kv head);
-// a thread owns one (token, pair of 16-byte pieces).  Slots past the end of a context hold whatever the pool
-// holds; nobody reads them.
-template <int D, int STYLE>
-__global__ __launch_bounds__(D) void rotate_keys_kernel(AttnArgs a) {
-    constexpr int HALF = D / 2;
-    constexpr int PAIRS = D / 16;                       // piece pairs per row
-    static_assert(kPageSize * PAIRS == D, "one thread per (token of the page, piece pair)");
-    // workgroup i runs on die i % 8: the heads of a page go to one die, one after the other, because they
-    // read the same 16 rows of the rotary table (its L2 then serves seven of the eight reads)
-    const int die = blockIdx.x % 8, k = blockIdx.x / 8;
-    const int dp = (k / a.n_kv_heads) * 8 + die, g = k % a.n_kv_heads;
-    if (dp >= a.n_dense_pages) return;
-    const int key = threadIdx.x / PAIRS, pr = threadIdx.x % PAIRS;
-    if (key >= kPageSize) return;
-    const int pos = min(a.rot_pos0[dp] + key, a.max_positions - 1);
-    const int64_t src = (((int64_t)a.rot_src_page[dp] * a.n_kv_heads + g) * kPageSize + key) * D;
-    const int64_t dst = (((int64_t)dp * a.n_kv_heads + g) * kPageSize + key) * D;
-    uint4 x = *reinterpret_cast<const uint4 *>(a.k_pool + src + 8 * pr);
-    uint4 y = *reinterpret_cast<const uint4 *>(a.k_pool + src + HALF + 8 * pr);
-    float2 cs[8];
-    load_cs<D, STYLE>(a.rope, pos, pr, cs);
-    uint32_t *px = reinterpret_cast<uint32_t *>(&x), *py = reinterpret_cast<uint32_t *>(&y);
-#pragma unroll
-    for (int w = 0; w < 4; ++w) rotate_dword<STYLE>(px[w], py[w], cs, w);
-    *reinterpret_cast<uint4 *>(a.k_rot + dst + 8 * pr) = x;
-    *reinterpret_cast<uint4 *>(a.k_rot + dst + HALF + 8 * pr) = y;
-}
-
 template <int NW, int BN>
 hipError_t launch_shape(const AttnArgs &a, hipStream_t stream) {
     dim3 grid(a.n_items), block(64 * NW);
@@ -563,25 +525,7 @@ hipError_t launch_attn_dma(const AttnArgs &a, hipStream_t stream) {
     if (a.n_items <= 0) return hipSuccess;
     if (a.n_combine > 0 && (a.partial == nullptr || a.combine == nullptr)) return hipErrorInvalidValue;
     hipError_t e;
-    if (a.prerotate) {
-        if ((a.tile_rows != 256 && a.tile_rows != 128) || !a.k_rot || !a.dense_page0 || !a.rot_src_page || !a.rot_pos0 || a.n_dense_pages <= 0)
-            return hipErrorInvalidValue;
-        const dim3 rgrid((uint32_t)((a.n_dense_pages + 7) / 8) * 8u * (uint32_t)a.n_kv_heads), grid(a.n_items);
-        const bool big = a.tile_rows == 256;
-#define CA_LAUNCH_PREROT(DD, ST)                                                                              \
-        do {                                                                                                  \
-            hipLaunchKernelGGL((rotate_keys_kernel<DD, ST>), rgrid, dim3(DD), 0, stream, a);                 \
-            if (big) hipLaunchKernelGGL((attn_dma_kernel<DD, ST, 8, 64, false>), grid, dim3(512), 0, stream, a); \
-            else hipLaunchKernelGGL((attn_dma_kernel<DD, ST, 4, 32, false>), grid, dim3(256), 0, stream, a);  \
-        } while (0)
-        if (a.head_dim == 128 && a.rope_style == 0) CA_LAUNCH_PREROT(128, 0);
-        else if (a.head_dim == 128) CA_LAUNCH_PREROT(128, 1);
-        else if (a.head_dim == 64 && a.rope_style == 0) CA_LAUNCH_PREROT(64, 0);
-        else if (a.head_dim == 64) CA_LAUNCH_PREROT(64, 1);
-        else return hipErrorInvalidValue;
-#undef CA_LAUNCH_PREROT
-        e = hipGetLastError();
-    } else if (a.tile_rows == 256) e = launch_shape<8, 64>(a, stream);
+    if (a.tile_rows == 256) e = launch_shape<8, 64>(a, stream);
     else if (a.tile_rows == 128) e = launch_shape<4, 32>(a, stream);
     else return hipErrorInvalidValue;
     if (e != hipSuccess || a.n_combine <= 0) return e;

@@ -152,6 +152,8 @@ constexpr int kRopeMinRows = 256;       // the kernels read table rows below thi
 
 hipError_t launch_attn_ref(const AttnArgs &args, hipStream_t stream);
 hipError_t launch_attn_dma(const AttnArgs &args, hipStream_t stream);
+// keys rotated once per layer into a scratch copy first (args.prerotate)
+hipError_t launch_attn_prerot(const AttnArgs &args, hipStream_t stream);
 // head_dim 128, 256-row tiles, keys rotated and values transposed once per layer into scratch copies; inside every
 // wavefront the matrix instructions of one key tile are pipelined with the softmax of the previous one
 hipError_t launch_attn_pp(const AttnArgs &args, hipStream_t stream);

@@ -2031,6 +2031,8 @@ static ca_status attn_impl(ca_ctx *ctx, int32_t layer, const void *q, const void
         CA_HIP(ctx, launch_attn_decode(a, ctx->max_unit_rows, stream));
     } else if (direct && ctx->pipelined) {
         CA_HIP(ctx, launch_attn_pp(a, stream));
+    } else if (direct && ctx->prerotate) {
+        CA_HIP(ctx, launch_attn_prerot(a, stream));
     } else if (direct) {
         CA_HIP(ctx, launch_attn_dma(a, stream));
     } else {
