@@ -108,7 +108,8 @@ typedef struct {
                              /* is cheaper to rotate the batch's keys once per layer into a      */
                              /* scratch copy first.  0: decide per batch (three or more 256-row  */
                              /* tiles per (conversation, kv head) on average); 1: never;         */
-                             /* 2: always (256-row tiles are then used whatever the batch)       */
+                             /* 2: always (256-row tiles are then used whatever the batch, but for */
+                             /* head_dim 64 with many tiles: 128)                                 */
     int32_t attn_schedule;   /* 0: the LDS-direct kernel, all wavefronts of a workgroup in lock step.      */
                              /* 1: when the keys are rotated once per layer (attn_prerotate), head_dim is  */
                              /* 128 and the tiles have 256 rows, the values are transposed into a scratch  */

@@ -1191,7 +1191,12 @@ ca_status ca_rope_rebase(ca_ctx *ctx, const ca_batch *b, void *stream_) {
     {
         const int G = c.n_q_heads / c.n_kv_heads;
         // 256-row tiles (8 wavefronts) halve the K/V re-reads and the rotary work per row when a
-        // (conversation, kv head) has more than 128 stacked rows; small turns keep 128-row tiles
+        // (conversation, kv head) has more than 128 stacked rows; small turns keep 128-row tiles.  Keys of 64 dimensions
+        // that were rotated beforehand are cheap to read again, and three workgroups of four wavefronts to a compute unit,
+        // none in step with another, beat one of eight: 16 first turns of 128-2048 tokens (32/4 heads) 158 -> 138 us a
+        // layer, 8 turns of 1000-3000 + 64-300 tokens 74 -> 62 (with heads of 128: 1750 -> 1975, the other way round).  Where
+        // the tiles are fewer than half the compute units, their keys are split many times over, and tiles of half the rows
+        // would need twice the shares.
         int tile = c.attn_tile_rows;
         const int most = ctx->max_unit_rows;
         if (tile == 0) tile = most > 128 ? 256 : 128;
@@ -1201,7 +1206,7 @@ ca_status ca_rope_rebase(ca_ctx *ctx, const ca_batch *b, void *stream_) {
             for (int i = 0; i < B; ++i) tiles256 += ((int64_t)b->new_len[i] * G + 255) / 256;
             ctx->prerotate = ctx->k_rot && direct_for_rot &&
                              (c.attn_prerotate == 2 || (c.attn_prerotate == 0 && tiles256 >= (int64_t)3 * B));
-            if (ctx->prerotate && c.attn_tile_rows == 0) tile = 256;
+            if (ctx->prerotate && c.attn_tile_rows == 0) tile = c.head_dim == 64 && tiles256 * c.n_kv_heads * 2 >= ctx->n_cus ? 128 : 256;
             ctx->pipelined = ctx->prerotate && ctx->v_t && tile == 256 && c.attn_variant != 3 && c.attn_variant != 1;
             size_t dense_pages = 0;
             if (ctx->prerotate)
