@@ -1291,7 +1291,7 @@ ca_status ca_rope_rebase(ca_ctx *ctx, const ca_batch *b, void *stream_) {
         int32_t n_split_parts = 0;          // shares that need a slot in the partial-result buffer
         const auto by_cost = [](const Item &x, const Item &y) { return x.cost > y.cost; };
         if (ctx->partial && direct_kernel && n_live < (size_t)(decode_plan ? 1 : 6) * ctx->n_cus) {
-            const int bins = std::max(1, ctx->n_cus / kXcds) * (tile == 128 ? 2 : 1);
+            const int bins = std::max(1, ctx->n_cus / kXcds) * (tile != 128 ? 1 : c.head_dim == 64 && ctx->prerotate ? 3 : 2);
             std::vector<double> heap;
             // sorts the items and returns the makespan of their longest-first list schedule over `bins` compute units
             // (min-heap of their loads)
@@ -1356,6 +1356,24 @@ ca_status ca_rope_rebase(ca_ctx *ctx, const ca_batch *b, void *stream_) {
                 // the plan of 11: their attention takes 0.83 to 0.99 of what it took, 0.90 in the middle.  The search costs
                 // the host up to 27 us a plan.)
                 const double halved = makespan;
+                // With all compute units busy an item costs more beside its tiles than a single one, five tiles of 1.9 us more
+                // (launch 6 us, page ids, first loads and Q 7, epilogue 2), and the merge costs a launch, about three tiles, and
+                // the traffic of the shares, 0.03 tiles for each of the eight dies' shares.  Where cutting gains less than
+                // that, the die's items stay whole.  (One layer of 8 conversations of 2048 tokens with 64-512 new ones, 32
+                // heads: 160 us in 384 shares, 150 whole; 4 of 1024 with 48-200: 48.0 and 45.5; 8 of 1000-3000 + 64-300,
+                // 32/4 heads of 64: 61 and 56.)
+                const auto busy_span = [&](std::vector<Item> &items) {
+                    for (Item &it : items) it.cost += 5.0;
+                    const double span = schedule(items, total);
+                    for (Item &it : items) it.cost -= 5.0;
+                    return span;
+                };
+                if (busy_span(whole) < busy_span(v) + 3.0 + 0.03 * kXcds * (n_split_parts - parts_before)) {
+                    for (const Item &it : whole) parts_of[it.parent] = 1;
+                    n_split_parts = parts_before;
+                    v.swap(whole);
+                    continue;
+                }
                 if (halved < 1.05 * uncut + 16.0) continue;
                 bool found = false;
                 for (const double fraction : {1.18, 1.02, 0.87, 0.70, 0.56}) {
