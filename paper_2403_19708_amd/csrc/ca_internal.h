@@ -58,6 +58,22 @@ hipError_t launch_append(const MoveShape &shape, const uint8_t *new_k, const uin
 hipError_t launch_append_save(const MoveShape &shape, int first, const MoveArgs2 &second, const uint8_t *new_k, const uint8_t *new_v,
                               uint8_t *k_pool, uint8_t *v_pool, hipStream_t stream);
 
+// One token per conversation (decode steps), with everything the kernel would look up in the plan worked out by the host:
+// where token i lies in the pool (page * kPageSize + slot), and for a save its row outside.
+struct TokenSlots {
+    int32_t slot[kMaxSeqsPerLaunch];
+};
+struct TokenRows {
+    uint8_t *k[kMaxSeqsPerLaunch];
+    uint8_t *v[kMaxSeqsPerLaunch];
+};
+// row i of new_k / new_v -> slot i of the pool, i < n
+hipError_t launch_append_tokens(const TokenSlots &slots, int n, const MoveShape &shape, const uint8_t *new_k, const uint8_t *new_v,
+                                uint8_t *k_pool, uint8_t *v_pool, hipStream_t stream);
+// slot i of the pool -> rows.k[i], rows.v[i]
+hipError_t launch_save_tokens(const TokenSlots &slots, const TokenRows &rows, int n, const MoveShape &shape, const uint8_t *k_pool,
+                              const uint8_t *v_pool, hipStream_t stream);
+
 // ---------------------------------------------------------------------------------------
 // Section 3.4: per-token metadata of the rebased plan
 // ---------------------------------------------------------------------------------------

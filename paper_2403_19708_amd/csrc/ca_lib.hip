@@ -1528,6 +1528,12 @@ MoveShape move_shape(const ca_ctx *ctx, int max_tokens) {
     return shape;
 }
 
+// where a context token of a conversation lies in the pool (the host copy of the plan's block table)
+int32_t token_slot(const ca_ctx *ctx, int seq, int token) {
+    const int32_t *table = (const int32_t *)(ctx->h_meta + ctx->off_table);
+    return table[(size_t)seq * ctx->max_pages + token / kPageSize] * kPageSize + token % kPageSize;
+}
+
 // link_workgroups > 0: the contiguous side is pinned host memory; a kernel of that many workgroups moves it
 ca_status run_move(ca_ctx *ctx, bool to_pool, const std::vector<Segment> &segs, void *k_pool, void *v_pool,
                    hipStream_t stream, int link_workgroups = 0) {
@@ -1554,6 +1560,21 @@ ca_status run_move(ca_ctx *ctx, bool to_pool, const std::vector<Segment> &segs, 
             CA_HIP(ctx, launch_link(to_pool, args, shape, link_workgroups, (uint8_t *)k_pool, (uint8_t *)v_pool, stream));
             continue;
         }
+        // A decode step's write-back: the host has looked up the slots.  (Not into a graph: its replays may follow another
+        // plan's table.)
+        if (!to_pool && max_tokens == 1 && !is_captured(stream)) {
+            TokenSlots slots;
+            TokenRows rows;
+            const int64_t rb = row_bytes(ctx->cfg);
+            for (int i = 0; i < n; ++i) {
+                const Segment &s = segs[at + i];
+                slots.slot[i] = token_slot(ctx, s.seq, s.ctx_tok0);
+                rows.k[i] = s.k + s.contig_tok0 * rb;
+                rows.v[i] = s.v + s.contig_tok0 * rb;
+            }
+            CA_HIP(ctx, launch_save_tokens(slots, rows, n, shape, (const uint8_t *)k_pool, (const uint8_t *)v_pool, stream));
+            continue;
+        }
         CA_HIP(ctx, launch_move(to_pool, args, shape, (uint8_t *)k_pool, (uint8_t *)v_pool, stream));
     }
     return CA_OK;
@@ -1576,6 +1597,16 @@ MoveShape new_turn_shape(const ca_ctx *ctx, int first, int n) {
 ca_status run_append(ca_ctx *ctx, const void *new_k, const void *new_v, void *k_pool, void *v_pool, hipStream_t stream) {
     int iv;
     CA_HIP(ctx, prof_begin(ctx, kProfAppend, stream, &iv));
+    // One new token per conversation, as many as the arguments hold: the host has looked up the slots.  (Not into a graph, whose
+    // replays read the plan of their time.)
+    if (ctx->total_q == ctx->n_seqs && ctx->n_seqs <= kMaxSeqsPerLaunch && !is_captured(stream)) {
+        TokenSlots slots;
+        for (int i = 0; i < ctx->n_seqs; ++i) slots.slot[i] = token_slot(ctx, i, ctx->n_keep[i]);
+        CA_HIP(ctx, launch_append_tokens(slots, ctx->n_seqs, move_shape(ctx, 1), (const uint8_t *)new_k, (const uint8_t *)new_v, (uint8_t *)k_pool,
+                                         (uint8_t *)v_pool, stream));
+        CA_HIP(ctx, prof_end(ctx, iv, stream));
+        return CA_OK;
+    }
     CA_HIP(ctx, launch_append(new_turn_shape(ctx, 0, ctx->n_seqs), (const uint8_t *)new_k, (const uint8_t *)new_v, (uint8_t *)k_pool,
                               (uint8_t *)v_pool, stream));
     CA_HIP(ctx, prof_end(ctx, iv, stream));
