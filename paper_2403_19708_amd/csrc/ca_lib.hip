@@ -1104,6 +1104,40 @@ static void plan_rows(ca_ctx *ctx, size_t &up) {
     ctx->n_split_parts = n_parts;
 }
 
+// A 64-key tile of a 256-row workgroup whose rows fill at most four of its wavefronts, in tiles of a full one.
+static constexpr double kHalfFullTile = 0.72;
+
+// Whether a plan that has units of more than 128 rows is better served by 128-row tiles, keys rotated in the kernel.  Two
+// such workgroups share a compute unit: one walks while the other loads its queries and first keys or writes its output,
+// and no wavefront is without rows; but units of more than 128 rows read and rotate their keys once more.  Per 64 keys and
+// compute unit a 128-row tile costs 0.60 of a full 256-row one (heads of 64: 0.65), and its fixed part one tile instead of
+// three, since the neighbour hides most of it.  Where the tiles do not fill both places of every compute unit they would be
+// cut into twice the shares, and with few rounds of them the last one is felt, hence the margin.  us a pass of 4 layers (first
+// turns and the 40-head ones of 32 alike), 256-row tiles -> 128-row ones, heads of 128 unless said, with ratio of costs and tiles:
+//   32 first turns of 20-140 tokens    299 -> 251 (0.50, 1088)     32 turns, 8-512 new, most below 128  2340 -> 2193 (0.89, 1840)
+//   16 turns, 20-140 new, 100-800 kept 435 -> 409 (0.70, 544)      16 such                              1607 -> 1535 (0.95, 1040)
+//   16 turns, 8-180 new, heads of 64   660 -> 633 (0.85, 544)      32 turns, 8-200 new                  1846 -> 1826 (0.96, 1568)
+// and the other way round:
+//   16 turns, 32-256 new                954 -> 965 (1.01, 832)     16 turns, 8-200 new, 2500-4000 kept  2022 -> 2085 (0.96, 704)
+//   32 turns, 130-256 new             2143 -> 2175 (1.11, 2048)    32 turns, 8-200 new, heads of 64     1093 -> 1154 (1.03, 1568)
+//   4 turns, 48-200 new                 343 -> 408 (0.93, 192)     8 turns, 100-150 new                   678 -> 735 (1.00, 384)
+static bool half_tiles_pay(const ca_ctx *ctx) {
+    const int G = ctx->cfg.n_q_heads / ctx->cfg.n_kv_heads;
+    const double half_tile = ctx->cfg.head_dim == 64 ? 0.65 : 0.60;
+    int64_t tiles128 = 0;
+    double cost128 = 0, cost256 = 0;
+    for (int i = 0; i < ctx->n_seqs; ++i) {
+        const int rows = ctx->new_len[i] * G;
+        const auto key_tiles = [&](int end_row) { return (ctx->n_keep[i] + (end_row - 1) / G + 64) / 64; };    // of 64, that rows below end_row see
+        for (int at = 0; at < rows; at += 128) cost128 += half_tile * key_tiles(std::min(rows, at + 128)) + 1.0;
+        for (int at = 0; at < rows; at += 256) cost256 += (rows - at <= 128 ? kHalfFullTile : 1.0) * key_tiles(std::min(rows, at + 256)) + 3.0;
+        tiles128 += (rows + 127) / 128;
+    }
+    tiles128 *= ctx->cfg.n_kv_heads;
+    const double rounds = (double)tiles128 / (2 * ctx->n_cus);
+    return rounds >= 1 && cost128 < (1 - 0.08 / rounds) * cost256;
+}
+
 ca_status ca_rope_rebase(ca_ctx *ctx, const ca_batch *b, void *stream_) {
     if (!ctx) return CA_ERR_INVALID_ARG;
     char msg[384] = {0};
@@ -1191,7 +1225,8 @@ ca_status ca_rope_rebase(ca_ctx *ctx, const ca_batch *b, void *stream_) {
     {
         const int G = c.n_q_heads / c.n_kv_heads;
         // 256-row tiles (8 wavefronts) halve the K/V re-reads and the rotary work per row when a
-        // (conversation, kv head) has more than 128 stacked rows; small turns keep 128-row tiles.  Keys of 64 dimensions
+        // (conversation, kv head) has more than 128 stacked rows; small turns keep 128-row tiles, and so do mixed batches in which
+        // these cost less (half_tiles_pay).  Keys of 64 dimensions
         // that were rotated beforehand are cheap to read again, and three workgroups of four wavefronts to a compute unit,
         // none in step with another, beat one of eight: 16 first turns of 128-2048 tokens (32/4 heads) 158 -> 138 us a
         // layer, 8 turns of 1000-3000 + 64-300 tokens 74 -> 62 (with heads of 128: 1750 -> 1975, the other way round).  Where
@@ -1207,6 +1242,7 @@ ca_status ca_rope_rebase(ca_ctx *ctx, const ca_batch *b, void *stream_) {
             ctx->prerotate = ctx->k_rot && direct_for_rot &&
                              (c.attn_prerotate == 2 || (c.attn_prerotate == 0 && tiles256 >= (int64_t)3 * B));
             if (ctx->prerotate && c.attn_tile_rows == 0) tile = c.head_dim == 64 && tiles256 * c.n_kv_heads * 2 >= ctx->n_cus ? 128 : 256;
+            if (c.attn_tile_rows == 0 && tile == 256 && direct_for_rot && !ctx->prerotate && half_tiles_pay(ctx)) tile = 128;
             ctx->pipelined = ctx->prerotate && ctx->v_t && tile == 256 && c.attn_variant != 3 && c.attn_variant != 1;
             size_t dense_pages = 0;
             if (ctx->prerotate)
@@ -1256,7 +1292,7 @@ ca_status ca_rope_rebase(ca_ctx *ctx, const ca_batch *b, void *stream_) {
         // per compute unit: shares (and the merge they need) only pay when there are fewer items than that.
         const bool decode_plan = direct_kernel && c.attn_variant != 2 && !ctx->prerotate && most >= 1 && most <= kAttnDecodeMaxRows;
         auto item_cost = [&](int n_rows, int keys) {
-            const double per_tile = (tile == 256 && n_rows <= 128) ? 0.72 : 1.0;
+            const double per_tile = (tile == 256 && n_rows <= 128) ? kHalfFullTile : 1.0;
             return per_tile * ((keys + 63) / 64) + 3.0;
         };
         std::vector<std::vector<Item>> per_die(kXcds);

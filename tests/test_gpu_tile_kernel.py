@@ -3,6 +3,7 @@ rings (one to six tiles, one key more or less), both groups of wavefronts live o
 so fast along the context that the reference has to move inside interior tiles, by more than a probability could hold."""
 import numpy as np
 import pytest
+import torch
 
 from harness import Case, GpuRun
 from test_gpu_parity import check_contract, check_tight
@@ -64,3 +65,31 @@ def test_reference_moves(D, rows, prerotate, steps):
     err = np.abs(got - want)
     assert np.median(err) < 0.05, np.median(err)
     assert err.mean() < 0.15, err.mean()
+
+
+@pytest.mark.parametrize("shape", SHAPES, ids=lambda s: "d%d-style%d" % s)
+@pytest.mark.parametrize("new", [[20] * 15 + [129], [20] * 14 + [128] * 2, [129] * 16, [20] * 11 + [129]],
+                         ids=["mixed", "short", "long", "few"])
+def test_tile_rows_of_a_batch(shape, new):
+    """128-row tiles for a batch with a longer turn among short ones, 256-row tiles where all are longer or the 128-row ones
+    would not fill two places of every compute unit (12 conversations of 32 heads: 416 tiles)."""
+    D, style = shape
+    hist = [(53 * c) % 200 for c in range(len(new))]
+    case = Case(hist, new, [0] * len(new), 32, 32, D, seed=90 + D + style, style=style, window=512)
+    run = GpuRun(case, tier="device", attn_variant=2, attn_prerotate=1)
+    try:
+        run.rebase()
+        items = run.ctx.rebase_read(6).reshape(-1, 8)
+        most = items[items[:, 0] >= 0][:, 3].max()          # rows of the largest item
+        run.load(0)
+        run.append(0)
+        run.attn(0)
+        run.finish()
+        got = [run.out_f64(0, c) for c in range(case.B)]
+    finally:
+        run.close()
+    full = 2 * torch.cuda.get_device_properties(0).multi_processor_count <= 32 * sum(-(-n // 128) for n in new)
+    assert most == (128 if min(new) < 128 and full else 129)
+    for c in (0, len(new) - 1):
+        check_contract(got[c], case.oracle_out(0, c), c)
+        check_tight(got[c], case.oracle_out(0, c), int(case.n_keep[c]), c)
