@@ -810,10 +810,10 @@ def main():
         pipeline["timeline"]["ms_step_instrumented"] = dt_i * 1e3
 
     # the dominant kernel of the step by GPU time: the attention call
-    attn_kernel = "attn_dma_kernel"
     G = job.Hq // job.Hkv
     # the library rotates the keys once per layer when on average three or more 256-row tiles share them
     prerot = job.W <= 32768 and int(np.sum((job.new.astype(np.int64) * G + 255) // 256)) >= 3 * job.B
+    attn_kernel = "attn_prerot_kernel" if prerot else "attn_dma_kernel"
     if job.attn_bound == "mfma":
         roof = dict(kernel=attn_kernel, bound="mfma", achieved=attn_live["tflops"], peak=MFMA_BF16_PEAK_TFLOPS, unit="TFLOP/s",
                     frac=attn_live["frac_mfma_peak"], traffic=None, algorithmic_flops_per_launch=job.flops_layer)
@@ -822,7 +822,7 @@ def main():
                     frac=attn_live["frac_hbm_peak"], traffic=None)
     roof["avg_launch_us"] = att_us_live
     roof["algorithmic_bytes_per_launch"] = job.attn_bytes
-    roof["launch"] = ("one ca_cached_prefill_attn call inside the timed steps: rotate_keys_kernel + attn_dma_kernel (+ combine_kernel "
+    roof["launch"] = ("one ca_cached_prefill_attn call inside the timed steps: rotate_keys_kernel + attn_prerot_kernel (+ combine_kernel "
                       "when keys are split)" if prerot else "one ca_cached_prefill_attn call inside the timed steps")
     sustained = mfma_rate_probe()
     if sustained:
