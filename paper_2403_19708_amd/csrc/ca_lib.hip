@@ -1395,7 +1395,9 @@ ca_status ca_rope_rebase(ca_ctx *ctx, const ca_batch *b, void *stream_) {
                 // With all compute units busy an item costs more beside its tiles than a single one, five tiles of 1.9 us more
                 // (launch 6 us, page ids, first loads and Q 7, epilogue 2), and the merge costs a launch, about three tiles, and
                 // the traffic of the shares, 0.03 tiles for each of the eight dies' shares.  Where cutting gains less than
-                // that, the die's items stay whole.  (One layer of 8 conversations of 2048 tokens with 64-512 new ones, 32
+                // that, the die's items stay whole.  Not so for decode plans, whose shares are a few hundred bytes and whose tiles
+                // are one or two rows: 12 conversations of 2000 tokens (16/8 heads of 64) took 19.5 us in 664 shares and 41.5
+                // in 96 whole items, 3 of 32 heads of 128 24.9 and 41.2.  (One layer of 8 conversations of 2048 tokens with 64-512 new ones, 32
                 // heads: 160 us in 384 shares, 150 whole; 4 of 1024 with 48-200: 48.0 and 45.5; 8 of 1000-3000 + 64-300,
                 // 32/4 heads of 64: 61 and 56.)
                 const auto busy_span = [&](std::vector<Item> &items) {
@@ -1404,7 +1406,7 @@ ca_status ca_rope_rebase(ca_ctx *ctx, const ca_batch *b, void *stream_) {
                     for (Item &it : items) it.cost -= 5.0;
                     return span;
                 };
-                if (busy_span(whole) < busy_span(v) + 3.0 + 0.03 * kXcds * (n_split_parts - parts_before)) {
+                if (!decode_plan && busy_span(whole) < busy_span(v) + 3.0 + 0.03 * kXcds * (n_split_parts - parts_before)) {
                     for (const Item &it : whole) parts_of[it.parent] = 1;
                     n_split_parts = parts_before;
                     v.swap(whole);

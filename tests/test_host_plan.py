@@ -1,0 +1,41 @@
+"""The attention work list of a plan, on the model of the HIP runtime (no GPU): which batches have their keys cut."""
+import numpy as np
+import pytest
+
+from hip_model import Turn, in_model
+
+
+def plan(m, hist, new, heads, **cfg):
+    """live items of the plan: rows (conversation, kv head, first row, rows, first key, end of keys, share, 0)"""
+    t = Turn(m, hist, new, heads=heads, **cfg)
+    t.rebase()
+    items = t.ctx.rebase_read(6).reshape(-1, 8)
+    t.ctx.close()
+    return items[items[:, 0] >= 0]
+
+
+def check_cover(items, hist, new, heads):
+    """every (conversation, kv head, row tile) is covered once, its shares end to end"""
+    G = heads[0] // heads[1]
+    tiles = {}
+    for seq, head, row0, rows, begin, end, part, _ in items.tolist():
+        tiles.setdefault((seq, head, row0, rows), []).append((begin, end, part))
+    rows = np.zeros((len(hist), heads[1]), np.int64)
+    for (seq, head, row0, n), shares in tiles.items():
+        rows[seq, head] += n
+        shares.sort()
+        assert shares[0][0] == 0 and shares[-1][1] == hist[seq] + (row0 + n - 1) // G + 1
+        assert all(a[1] == b[0] for a, b in zip(shares, shares[1:]))
+        assert all((p >= 0) == (len(shares) > 1) for _, _, p in shares)
+    assert (rows == np.asarray(new)[:, None] * G).all()
+
+
+# Batches with fewer (conversation, kv head) units than compute units: whole, they leave the others without work.
+@pytest.mark.parametrize("batch, heads, tokens", [(3, (32, 32, 128), 2000), (4, (32, 32, 128), 1000), (4, (32, 32, 128), 1500), (2, (40, 40, 128), 1000),
+                                                  (4, (40, 40, 128), 2000), (6, (32, 32, 128), 3000), (12, (16, 8, 64), 2000), (28, (8, 8, 128), 3000)])
+@in_model
+def test_a_small_decode_batch_is_cut(m, batch, heads, tokens):
+    hist = [tokens - 1 - 7 * c for c in range(batch)]
+    items = plan(m, hist, [1] * batch, heads)
+    check_cover(items, hist, [1] * batch, heads)
+    assert len(items) >= min(256, 2 * batch * heads[1]) and (items[:, 6] >= 0).all()
