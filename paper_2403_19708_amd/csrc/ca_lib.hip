@@ -1138,6 +1138,50 @@ static bool half_tiles_pay(const ca_ctx *ctx) {
     return rounds >= 1 && cost128 < (1 - 0.08 / rounds) * cost256;
 }
 
+// A row tile or a share of one, as the planner of the tile kernels handles it
+struct Item { WorkItem w; double cost; int32_t parent; };
+
+// Whether the row tiles of a plan are better left whole than cut into the shares found for them (`bins` workgroups run on a
+// die at a time).  Shares fill compute units that whole items would leave idle, but each is launched, fetches its queries and
+// fills its load pipeline, is written and read back (its valid rows), and the merge is a launch.  Both plans are laid out on
+// the dies in time: us per 64-key tile on a compute unit that other workgroups share and on one of a workgroup's own, and
+// per item, by kernel and shape; 3 us and 1.75 TB/s of shares for the merge, 7 us a launch in either case; `shares` is a factor
+// on the time with shares, where the decisions came out best.  Fitted to 1236 random plans (1 to 64 conversations, no history to
+// 31000 tokens, 2 to 2048 new, seven shapes of heads) timed whole and cut: whole is taken 391 times, for 0.51 to 1.08 of the
+// time with shares, 0.83 on average, and the plan taken is the slower one by more than 3 % in 19.  (One layer of 8 conversations
+// of 2048 tokens with 64-512 new ones, 32 heads: 160 us in 384 shares, 150 whole; of 13 of 2134-2392 with 9-45, 16/8 heads of
+// 64: 38 us in 832 shares, 72 whole.)
+static bool whole_items_pay(const ca_ctx *ctx, const std::vector<std::vector<Item>> &cut, const std::vector<std::vector<Item>> &whole,
+                            const std::vector<int32_t> &parts_of, int bins) {
+    struct Times { double tile, tile_alone, item, shares; };
+    const bool d64 = ctx->cfg.head_dim == 64, small = ctx->tile_rows == 128;
+    const Times t = ctx->prerotate ? (!d64 ? Times{1.65, 1.45, 9.2, 1.05} : small ? Times{1.25, 1.10, 5.5, 1.10} : Times{1.05, 0.95, 4.1, 0.95})
+                    : d64          ? (small ? Times{1.85, 1.65, 0.5, 1.05} : Times{1.45, 1.30, 2.5, 1.00})
+                                   : (small ? Times{2.60, 1.95, 3.0, 1.00} : Times{2.10, 1.85, 5.6, 1.00});
+    const size_t die_cus = std::max(1, ctx->n_cus / kXcds);
+    std::vector<double> heap;
+    const auto span = [&](const std::vector<std::vector<Item>> &dies) {
+        double longest = 0;
+        for (const auto &items : dies) {
+            const double tile = items.size() <= die_cus ? t.tile_alone : t.tile;
+            heap.assign(bins, 0.0);
+            for (const Item &it : items) {
+                const double part = !small && it.w.n_rows <= 128 ? 0.78 : 1.0;      // (four of eight wavefronts have rows)
+                std::pop_heap(heap.begin(), heap.end(), std::greater<double>());
+                heap.back() += t.item + part * tile * ((it.w.key_end + 63) / 64 - it.w.key_begin / 64);
+                longest = std::max(longest, heap.back());
+                std::push_heap(heap.begin(), heap.end(), std::greater<double>());
+            }
+        }
+        return longest + 7.0;
+    };
+    double share_bytes = 0;
+    for (const auto &items : cut)
+        for (const Item &it : items)
+            if (parts_of[it.parent] > 1) share_bytes += (double)it.w.n_rows * (ctx->cfg.head_dim + 2) * sizeof(float);
+    return span(whole) < t.shares * (span(cut) + 3.0 + share_bytes / 1.75e6);
+}
+
 ca_status ca_rope_rebase(ca_ctx *ctx, const ca_batch *b, void *stream_) {
     if (!ctx) return CA_ERR_INVALID_ARG;
     char msg[384] = {0};
@@ -1287,7 +1331,6 @@ ca_status ca_rope_rebase(ca_ctx *ctx, const ca_batch *b, void *stream_) {
         // Cost of an item in the time a full workgroup needs for one 64-key tile (measured on single items:
         // a 256-row workgroup whose rows fill at most four wavefronts, one per SIMD, takes 0.72 of that per
         // tile; rotating Q, filling the load pipeline and the epilogue cost about three tiles).
-        struct Item { WorkItem w; double cost; int32_t parent; };
         // A plan of decode steps goes to the streaming kernel, which reaches its bandwidth with one workgroup
         // per compute unit: shares (and the merge they need) only pay when there are fewer items than that.
         const bool decode_plan = direct_kernel && c.attn_variant != 2 && !ctx->prerotate && most >= 1 && most <= kAttnDecodeMaxRows;
@@ -1343,9 +1386,11 @@ ca_status ca_rope_rebase(ca_ctx *ctx, const ca_batch *b, void *stream_) {
                 }
                 return *std::max_element(heap.begin(), heap.end());
             };
-            std::vector<Item> whole, shares, best;
+            std::vector<Item> shares, best;
+            std::vector<std::vector<Item>> whole_of(kXcds);
             for (int d = 0; d < kXcds; ++d) {
                 auto &v = per_die[d];
+                std::vector<Item> &whole = whole_of[d];
                 const int32_t parts_before = n_split_parts;
                 double uncut = 0;
                 for (int round = 0; round < 4 && !v.empty(); ++round) {
@@ -1392,26 +1437,6 @@ ca_status ca_rope_rebase(ca_ctx *ctx, const ca_batch *b, void *stream_) {
                 // the plan of 11: their attention takes 0.83 to 0.99 of what it took, 0.90 in the middle.  The search costs
                 // the host up to 27 us a plan.)
                 const double halved = makespan;
-                // With all compute units busy an item costs more beside its tiles than a single one, five tiles of 1.9 us more
-                // (launch 6 us, page ids, first loads and Q 7, epilogue 2), and the merge costs a launch, about three tiles, and
-                // the traffic of the shares, 0.03 tiles for each of the eight dies' shares.  Where cutting gains less than
-                // that, the die's items stay whole.  Not so for decode plans, whose shares are a few hundred bytes and whose tiles
-                // are one or two rows: 12 conversations of 2000 tokens (16/8 heads of 64) took 19.5 us in 664 shares and 41.5
-                // in 96 whole items, 3 of 32 heads of 128 24.9 and 41.2.  (One layer of 8 conversations of 2048 tokens with 64-512 new ones, 32
-                // heads: 160 us in 384 shares, 150 whole; 4 of 1024 with 48-200: 48.0 and 45.5; 8 of 1000-3000 + 64-300,
-                // 32/4 heads of 64: 61 and 56.)
-                const auto busy_span = [&](std::vector<Item> &items) {
-                    for (Item &it : items) it.cost += 5.0;
-                    const double span = schedule(items, total);
-                    for (Item &it : items) it.cost -= 5.0;
-                    return span;
-                };
-                if (!decode_plan && busy_span(whole) < busy_span(v) + 3.0 + 0.03 * kXcds * (n_split_parts - parts_before)) {
-                    for (const Item &it : whole) parts_of[it.parent] = 1;
-                    n_split_parts = parts_before;
-                    v.swap(whole);
-                    continue;
-                }
                 if (halved < 1.05 * uncut + 16.0) continue;
                 bool found = false;
                 for (const double fraction : {1.18, 1.02, 0.87, 0.70, 0.56}) {
@@ -1445,6 +1470,15 @@ ca_status ca_rope_rebase(ca_ctx *ctx, const ca_batch *b, void *stream_) {
                 for (const Item &it : whole)
                     if (parts_of[it.parent] > 1) n_split_parts += parts_of[it.parent];
                 v.swap(best);
+            }
+            if (n_split_parts > 0 && !decode_plan) {
+                for (int d = 0; d < kXcds; ++d)
+                    if (whole_of[d].empty()) whole_of[d] = per_die[d];          // not cut, or cut in vain
+                if (whole_items_pay(ctx, per_die, whole_of, parts_of, bins)) {
+                    for (int d = 0; d < kXcds; ++d) per_die[d].swap(whole_of[d]);
+                    parts_of.assign(n_parents, 1);
+                    n_split_parts = 0;
+                }
             }
         }
         // number the shares of split row tiles consecutively and list the tiles for the merge

@@ -39,3 +39,29 @@ def test_a_small_decode_batch_is_cut(m, batch, heads, tokens):
     items = plan(m, hist, [1] * batch, heads)
     check_cover(items, hist, [1] * batch, heads)
     assert len(items) >= min(256, 2 * batch * heads[1]) and (items[:, 6] >= 0).all()
+
+
+# Turns on the tile kernels (four and more stacked rows; few enough for the few-rows kernel only in the first conversation of
+# some).  Times are us of one attention call, cut and whole.
+CUT = [(13, (16, 8, 64), 2134, 2392, 9, 45),           # 38, 72
+       (33, (4, 4, 64), 3209, 3355, 5, 128),           # 60, 102
+       (28, (4, 4, 64), 2184, 2335, 24, 197),          # 47, 62
+       (46, (8, 2, 128), 2217, 2409, 5, 39),           # 64, 80
+       (3, (16, 8, 64), 2048, 2048, 399, 416)]         # 47, 52
+WHOLE = [(6, (64, 8, 128), 423, 586, 113, 134),        # 68, 41
+         (3, (40, 40, 128), 284, 671, 423, 483),       # 90, 56
+         (9, (32, 4, 64), 1024, 1024, 97, 151),        # 56, 35
+         (5, (32, 32, 128), 1500, 1563, 75, 258),      # 102, 74
+         (4, (32, 4, 64), 0, 0, 300, 703),             # 26, 22
+         (8, (32, 32, 128), 2048, 2048, 64, 512)]      # 160, 150
+
+
+@pytest.mark.parametrize("batch, heads, hist_lo, hist_hi, new_lo, new_hi", CUT + WHOLE)
+@in_model
+def test_items_stay_whole_where_shares_cost_more(m, batch, heads, hist_lo, hist_hi, new_lo, new_hi):
+    hist, new = (np.linspace(lo, hi, batch).round().astype(np.int32) for lo, hi in ((hist_lo, hist_hi), (new_lo, new_hi)))
+    np.random.default_rng(3).shuffle(new)
+    items = plan(m, hist, new, heads)
+    check_cover(items, hist, new, heads)
+    whole = (batch, heads, hist_lo, hist_hi, new_lo, new_hi) in WHOLE
+    assert (items[:, 6] >= 0).any() != whole
