@@ -1104,38 +1104,37 @@ static void plan_rows(ca_ctx *ctx, size_t &up) {
     ctx->n_split_parts = n_parts;
 }
 
-// A 64-key tile of a 256-row workgroup whose rows fill at most four of its wavefronts, in tiles of a full one.
-static constexpr double kHalfFullTile = 0.72;
-
 // Whether a plan that has units of more than 128 rows is better served by 128-row tiles, keys rotated in the kernel.  Two
 // such workgroups share a compute unit: one walks while the other loads its queries and first keys or writes its output,
-// and no wavefront is without rows; but units of more than 128 rows read and rotate their keys once more.  Per 64 keys and
-// compute unit a 128-row tile costs 0.60 of a full 256-row one (heads of 64: 0.65), and its fixed part one tile instead of
-// three, since the neighbour hides most of it.  Where the tiles do not fill both places of every compute unit they would be
-// cut into twice the shares, and with few rounds of them the last one is felt, hence the margin.  us a pass of 4 layers (first
-// turns and the 40-head ones of 32 alike), 256-row tiles -> 128-row ones, heads of 128 unless said, with ratio of costs and tiles:
-//   32 first turns of 20-140 tokens    299 -> 251 (0.50, 1088)     32 turns, 8-512 new, most below 128  2340 -> 2193 (0.89, 1840)
-//   16 turns, 20-140 new, 100-800 kept 435 -> 409 (0.70, 544)      16 such                              1607 -> 1535 (0.95, 1040)
-//   16 turns, 8-180 new, heads of 64   660 -> 633 (0.85, 544)      32 turns, 8-200 new                  1846 -> 1826 (0.96, 1568)
+// and no wavefront is without rows; but units of more than 128 rows read and rotate their keys once more.  Costs in 64-key tiles
+// of a full 256-row workgroup: per tile of a 128-row workgroup and of a 256-row one that has at most 128 rows, and the fixed part
+// of either, which the neighbour hides most of for 128 rows.  Where the tiles do not fill both places of every compute unit they
+// would be cut into twice the shares, and with few rounds of them the last one is felt, hence the margin.  Fitted to 133
+// random batches (2 to 64 conversations, no history to 4000 tokens, 4 to 2048 new) timed with either tile: 128 rows are taken for
+// 46 of them, for 0.70 to 1.02 of the time with 256, 0.88 on average, and 8 more would gain over 5 %.  us of one attention call, 256
+// and 128 rows, with ratio of costs and rounds:
+//   17 first turns of 303-311 tokens, 32 heads  103, 80 (0.76, 3.2)   32 turns, 8-512 new, most below 128, 40 heads  585, 548 (0.95, 3.6)
+//   40 first turns of 80-137, 40 heads          100, 70 (0.62, 3.6)   52 first turns of 18-114, 32/4 heads of 64     27, 23 (0.94, 2.0)
 // and the other way round:
-//   16 turns, 32-256 new                954 -> 965 (1.01, 832)     16 turns, 8-200 new, 2500-4000 kept  2022 -> 2085 (0.96, 704)
-//   32 turns, 130-256 new             2143 -> 2175 (1.11, 2048)    32 turns, 8-200 new, heads of 64     1093 -> 1154 (1.03, 1568)
-//   4 turns, 48-200 new                 343 -> 408 (0.93, 192)     8 turns, 100-150 new                   678 -> 735 (1.00, 384)
+//   16 turns of 1536 + 19-178, 32 heads         116, 137 (0.96, 1.3)  32 of 3080-3206 + 41-168, 32 heads             399, 460 (1.00, 2.6)
+//   10 of 347-383 + 168-369, 32 heads           75, 79 (0.91, 1.6)    64 of 343-417 + 279-344, 4 heads of 64         47, 56 (1.05, 1.5)
 static bool half_tiles_pay(const ca_ctx *ctx) {
+    struct Costs { double tile128, item128, half_full256, item256, margin; };
+    const Costs cost = ctx->cfg.head_dim == 64 ? Costs{0.61, 1.0, 0.48, 2.3, 0.04} : Costs{0.555, 1.3, 0.56, 3.2, 0.15};
     const int G = ctx->cfg.n_q_heads / ctx->cfg.n_kv_heads;
-    const double half_tile = ctx->cfg.head_dim == 64 ? 0.65 : 0.60;
     int64_t tiles128 = 0;
     double cost128 = 0, cost256 = 0;
     for (int i = 0; i < ctx->n_seqs; ++i) {
         const int rows = ctx->new_len[i] * G;
         const auto key_tiles = [&](int end_row) { return (ctx->n_keep[i] + (end_row - 1) / G + 64) / 64; };    // of 64, that rows below end_row see
-        for (int at = 0; at < rows; at += 128) cost128 += half_tile * key_tiles(std::min(rows, at + 128)) + 1.0;
-        for (int at = 0; at < rows; at += 256) cost256 += (rows - at <= 128 ? kHalfFullTile : 1.0) * key_tiles(std::min(rows, at + 256)) + 3.0;
+        for (int at = 0; at < rows; at += 128) cost128 += cost.tile128 * key_tiles(std::min(rows, at + 128)) + cost.item128;
+        for (int at = 0; at < rows; at += 256)
+            cost256 += (rows - at <= 128 ? cost.half_full256 : 1.0) * key_tiles(std::min(rows, at + 256)) + cost.item256;
         tiles128 += (rows + 127) / 128;
     }
     tiles128 *= ctx->cfg.n_kv_heads;
     const double rounds = (double)tiles128 / (2 * ctx->n_cus);
-    return rounds >= 1 && cost128 < (1 - 0.08 / rounds) * cost256;
+    return rounds >= 1 && cost128 < (1 - cost.margin / rounds) * cost256;
 }
 
 // A row tile or a share of one, as the planner of the tile kernels handles it
@@ -1335,7 +1334,7 @@ ca_status ca_rope_rebase(ca_ctx *ctx, const ca_batch *b, void *stream_) {
         // per compute unit: shares (and the merge they need) only pay when there are fewer items than that.
         const bool decode_plan = direct_kernel && c.attn_variant != 2 && !ctx->prerotate && most >= 1 && most <= kAttnDecodeMaxRows;
         auto item_cost = [&](int n_rows, int keys) {
-            const double per_tile = (tile == 256 && n_rows <= 128) ? kHalfFullTile : 1.0;
+            const double per_tile = (tile == 256 && n_rows <= 128) ? 0.72 : 1.0;
             return per_tile * ((keys + 63) / 64) + 3.0;
         };
         std::vector<std::vector<Item>> per_die(kXcds);

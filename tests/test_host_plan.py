@@ -65,3 +65,20 @@ def test_items_stay_whole_where_shares_cost_more(m, batch, heads, hist_lo, hist_
     check_cover(items, hist, new, heads)
     whole = (batch, heads, hist_lo, hist_hi, new_lo, new_hi) in WHOLE
     assert (items[:, 6] >= 0).any() != whole
+
+
+# Rows of the tiles of mixed batches; times are us of one attention call with tiles of 256 and of 128 rows.
+@pytest.mark.parametrize("batch, heads, hist_lo, hist_hi, new_lo, new_hi, rows",
+                         [(16, (32, 32, 128), 1536, 1536, 19, 178, 256),        # 116, 137
+                          (32, (32, 32, 128), 3080, 3206, 41, 168, 256),        # 399, 460
+                          (14, (32, 32, 128), 608, 612, 164, 370, 256),         # 127, 136
+                          (64, (4, 4, 64), 343, 417, 279, 344, 256),            # 47, 56
+                          (17, (32, 32, 128), 0, 0, 303, 311, 128),             # 103, 80
+                          (40, (40, 40, 128), 0, 0, 80, 137, 128),              # 100, 70
+                          (52, (32, 4, 64), 0, 0, 18, 114, 128)])               # 27, 23
+@in_model
+def test_tile_rows_of_mixed_batches(m, batch, heads, hist_lo, hist_hi, new_lo, new_hi, rows):
+    hist, new = (np.linspace(lo, hi, batch).round().astype(np.int32) for lo, hi in ((hist_lo, hist_hi), (new_lo, new_hi)))
+    items = plan(m, hist, new, heads)
+    check_cover(items, hist, new, heads)
+    assert (items[:, 3].max() <= 128) == (rows == 128)
