@@ -62,6 +62,7 @@ struct ca_ctx {
     bool copy_waits_plan = false, unpack_waits_plan = false, save_waits_plan = false;   // the stream has not yet been told to wait for ev_plan
     hipEvent_t load_done = nullptr;    // event behind the newest load on the unpack stream (one of ev_ready), null: none outstanding
     bool save_pending = false;         // ev_saved stands behind work on the save stream that may be unfinished
+    int32_t link_layer = -1;           // layer of the newest load across the host link under this plan (-1: none)
     bool saves_under_plan = false;     // some of it was queued under the current plan
     bool joined_null = false;          // the default stream (of the context's GPU) already waits for all of it
     // short moves run on a stream of the caller's instead (see runs_inline): the newest one, and the event behind it (null on
@@ -168,8 +169,10 @@ constexpr size_t kMetaAlign = 64;            // alignment of the arrays of the m
 //   saves   2: 31, 31 GB/s, not   4: 45, 44, not    8: 52, 51, 1.4 x   16: 54, 54, 1.9 x
 // Past what the link holds the requests queue up in the memory system in front of everyone else's.  Whole turns (two layers
 // of 64 such conversations, us): 27648 with 6 load workgroups, 27006 with 8, 26780 with 10, 26706 with 12.
+// (Measured with the attention that rotates keys itself; see save_workgroups for the one over keys rotated beforehand.)
 constexpr int kLinkLoadWorkgroups = 10;
 constexpr int kLinkSaveWorkgroups = 4;
+constexpr int kLinkSaveBesideLoads = 2;
 
 enum ProfileKind { kProfCopyIn = 0, kProfUnpack = 1, kProfAppend = 2, kProfAttn = 3, kProfPack = 4, kProfCopyOut = 5, kProfKinds = 6 };
 
@@ -1543,6 +1546,7 @@ ca_status ca_rope_rebase(ca_ctx *ctx, const ca_batch *b, void *stream_) {
     ctx->meta_in_flight = true;
     ctx->copy_waits_plan = ctx->unpack_waits_plan = ctx->save_waits_plan = true;
     ctx->saves_under_plan = false;
+    ctx->link_layer = -1;
     ctx->plan_stream = stream;
     std::fill(ctx->loaded.begin(), ctx->loaded.end(), 0);
     std::fill(ctx->ready_inline.begin(), ctx->ready_inline.end(), 0);
@@ -1691,6 +1695,18 @@ ca_status check_pools(ca_ctx *ctx, const char *who, const void *k_pool, const vo
         return fail(ctx, CA_ERR_INVALID_ARG, "%s: a pool is not device memory holding num_pages=%d pages (%zu bytes)", who,
                     ctx->num_pages, bytes);
     return CA_OK;
+}
+
+// Workgroups of a write-back of `tokens` of `layer` to pinned memory.  Both directions of the link at once hold up the attention
+// over keys rotated beforehand, which has a tile's time for its loads where the one that rotates them has two.  So beside
+// it and the loads of later layers two workgroups write back, as long as the loads, at twice their rate, bring at least
+// twice as much.  A step of 64 conversations of 1024-4096 + 64-512 tokens, 64/8 heads, 80 layers: attention 2705 us with four
+// and 2137 with two (1660 alone), the link 55.1 and 56.5 GB/s, the step 986.5 and 961.2 ms; nine other batches of such plans
+// 0.92 to 1.00 of their time.  Beside the other kernel four are the better: 16 conversations of 512-2048 + 32-256, 32 heads, 32
+// layers, 199 ms a step, 207 with two.
+int save_workgroups(const ca_ctx *ctx, int32_t layer, int64_t tokens) {
+    const bool beside_loads = ctx->link_layer >= 0 && ctx->link_layer != layer;
+    return ctx->prerotate && beside_loads && ctx->total_n >= 2 * tokens ? kLinkSaveBesideLoads : kLinkSaveWorkgroups;
 }
 
 // Is a save of `bytes` so short that it runs on the caller's stream?  (save_mode 1 keeps what it asks for, the staging slot.)
@@ -1847,6 +1863,7 @@ ca_status ca_kv_load_layer(ca_ctx *ctx, int32_t layer, const void *const *src_k,
         st = run_move(ctx, true, segs, k_pool, v_pool, mover, link ? kLinkLoadWorkgroups : 0);
         if (st != CA_OK) return st;
         CA_HIP(ctx, prof_end(ctx, iv_in, mover));
+        if (link) ctx->link_layer = layer;
         if (link) CA_HIP(ctx, prof_begin(ctx, kProfUnpack, mover, &iv_unpack));
         CA_HIP(ctx, prof_end(ctx, iv_unpack, mover));
     }
@@ -1978,7 +1995,7 @@ ca_status ca_kv_save_layer(ca_ctx *ctx, int32_t layer, const int32_t *tok_begin,
         }
         int iv_pack;
         CA_HIP(ctx, prof_begin(ctx, kProfPack, saver, &iv_pack));
-        st = run_move(ctx, false, segs, (void *)k_pool, (void *)v_pool, saver, any_host && !on_caller ? kLinkSaveWorkgroups : 0);
+        st = run_move(ctx, false, segs, (void *)k_pool, (void *)v_pool, saver, any_host && !on_caller ? save_workgroups(ctx, layer, total) : 0);
         if (st != CA_OK) return st;
         CA_HIP(ctx, prof_end(ctx, iv_pack, saver));
     }
@@ -2041,7 +2058,7 @@ ca_status ca_kv_append_save_layer(ca_ctx *ctx, int32_t layer, const void *new_k,
                     segs.push_back({gpu_k[i], gpu_v[i], ctx->hist_len[i], ctx->n_keep[i], ctx->new_len[i], i});
             if (ctx->loaded[layer]) CA_HIP(ctx, after_load(ctx, layer, ctx->s_save));
             CA_HIP(ctx, prof_begin(ctx, kProfPack, ctx->s_save, &iv));
-            st = run_move(ctx, false, segs, k_pool, v_pool, ctx->s_save, any_host ? kLinkSaveWorkgroups : 0);
+            st = run_move(ctx, false, segs, k_pool, v_pool, ctx->s_save, any_host ? save_workgroups(ctx, layer, ctx->total_q) : 0);
             if (st != CA_OK) return st;
         } else {
             // one copy per conversation, straight from new_k / new_v

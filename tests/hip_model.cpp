@@ -33,6 +33,7 @@ struct Op {
     std::string what;
     Stream *stream;
     std::set<int> behind;
+    unsigned workgroups;       // kernels: of the grid's first dimension
     std::vector<char> args;    // attention kernels: their AttnArgs; moves: their MoveArgs or MoveArgs2
 };
 struct Range {
@@ -88,7 +89,7 @@ bool finished(const std::set<int> &what) {
     return true;
 }
 int queue(const std::string &what, Stream *s) {
-    ops.push_back({what, s, s->behind, {}});
+    ops.push_back({what, s, s->behind, 0, {}});
     s->behind.insert((int)ops.size() - 1);
     return (int)ops.size() - 1;
 }
@@ -197,13 +198,14 @@ void __hipRegisterVar(void **, void *, char *, char *, int, size_t, int, int) {}
 namespace { thread_local struct { dim3 grid, block; size_t shared; hipStream_t stream; } call; }
 hipError_t __hipPushCallConfiguration(dim3 g, dim3 b, size_t m, hipStream_t s) { call = {g, b, m, s}; return hipSuccess; }
 hipError_t __hipPopCallConfiguration(dim3 *g, dim3 *b, size_t *m, hipStream_t *s) { *g = call.grid; *b = call.block; *m = call.shared; *s = call.stream; return hipSuccess; }
-hipError_t hipLaunchKernel(const void *f, dim3, dim3, void **args, size_t, hipStream_t s) {
+hipError_t hipLaunchKernel(const void *f, dim3 grid, dim3, void **args, size_t, hipStream_t s) {
     MODEL;
     Stream *x = stream_of(s);
     if (!x) return hipErrorInvalidHandle;
     if (launches_until_failure >= 0 && launches_until_failure-- == 0) return hipErrorLaunchFailure;
     const int op = queue(kernels[f], x);
     const std::string &name = ops[op].what;
+    ops[op].workgroups = grid.x;
     const size_t bytes = name.find("8AttnArgs") != std::string::npos ? sizeof(ca::AttnArgs)
                          : name.find("9MoveArgs2") != std::string::npos ? sizeof(ca::MoveArgs2)
                          : name.find("8MoveArgs") != std::string::npos ? sizeof(ca::MoveArgs) : 0;
@@ -223,6 +225,7 @@ void model_fail_launch(int after) { launches_until_failure = after; }
 int model_ops() { MODEL; return (int)ops.size(); }
 const char *model_what(int op) { MODEL; return ops[op].what.c_str(); }
 void *model_stream(int op) { MODEL; return ops[op].stream; }
+int model_workgroups(int op) { MODEL; return (int)ops[op].workgroups; }
 int model_device(int op) { MODEL; return ops[op].stream->device; }
 int model_done(int op) { MODEL; return done.count(op); }
 int model_behind(int op, int other) { MODEL; return ops[op].behind.count(other); }

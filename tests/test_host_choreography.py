@@ -416,3 +416,24 @@ def test_only_staged_moves_have_a_staging_ring(m):
     assert bytes_of(load_mode=2, save_mode=2) == least
     for modes, rings in ((dict(load_mode=1), 1), (dict(save_mode=1), 1), (dict(load_mode=1, save_mode=1), 2)):
         assert bytes_of(**modes) - least == rings * ring
+
+
+# ---- both directions of the host link at once ----------------------------------------------------------------------------
+@pytest.mark.parametrize("fused", [False, True], ids=["save", "append-save"])
+@pytest.mark.parametrize("hist, new, prerotate, beside", [(4000, 100, 2, 2), (4000, 100, 1, 4), (150, 100, 2, 4), (0, 100, 2, 4)],
+                         ids=["rotated", "rotary", "short-history", "first-turn"])
+@in_model
+def test_few_workgroups_write_back_beside_loads_and_attention_over_rotated_keys(m, hist, new, prerotate, beside, fused):
+    """the last layer's write-back, which runs beside no load, and write-backs as large as half the loads keep four"""
+    t = Turn(m, [hist] * 4, [new] * 4, tier=1, layers=3, heads=(8, 8, 128), attn_prerotate=prerotate)
+    t.rebase()
+    for layer in range(3):
+        t.load(layer=layer)
+    got = []
+    for layer in range(3):
+        if not fused:
+            t.append(layer=layer)
+        ops = m.queued(lambda: t.append_save(layer=layer) if fused else t.save(layer=layer))
+        got.append(m.lib.model_workgroups(m.named(ops, "link_kernel")[0]))
+        t.attn(layer=layer)
+    assert got == [beside, beside, 4]
