@@ -1373,6 +1373,11 @@ ca_status ca_rope_rebase(ca_ctx *ctx, const ca_batch *b, void *stream_) {
         const auto by_cost = [](const Item &x, const Item &y) { return x.cost > y.cost; };
         if (ctx->partial && direct_kernel && n_live < (size_t)(decode_plan ? 1 : 6) * ctx->n_cus) {
             const int bins = std::max(1, ctx->n_cus / kXcds) * (tile != 128 ? 1 : c.head_dim == 64 && ctx->prerotate ? 3 : 2);
+            // tiles of 128 rows where there would be 256-row ones: no more shares than the static scratch array holds, so that
+            // ca_cached_prefill_attn_static takes the plans it would take with 256-row tiles
+            const bool smaller = tile == 128 && most > 128 && c.attn_tile_rows == 0;
+            const int max_parts = smaller ? (int)std::min<size_t>(kAttnMaxParts, kStaticScratchBytes / (128 * (size_t)(c.head_dim + 2) * sizeof(float)))
+                                          : kAttnMaxParts;
             std::vector<double> heap;
             // sorts the items and returns the makespan of their longest-first list schedule over `bins` compute units
             // (min-heap of their loads)
@@ -1411,7 +1416,7 @@ ca_status ca_rope_rebase(ca_ctx *ctx, const ca_batch *b, void *stream_) {
                         const int len = it.w.key_end - it.w.key_begin;
                         const int extra = parts_of[it.parent] == 1 ? 2 : 1;   // slots a cut of this item adds
                         if (len < 2 * kAttnMinPartKeys || parts_of[it.parent] >= kAttnMaxPartsPerTile ||
-                            n_split_parts + extra > kAttnMaxParts) continue;
+                            n_split_parts + extra > max_parts) continue;
                         Item hi_half = it;
                         const int tiles64 = (len + 63) / 64;
                         const int mid = it.w.key_begin + (tiles64 / 2) * 64;

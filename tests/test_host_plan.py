@@ -82,3 +82,19 @@ def test_tile_rows_of_mixed_batches(m, batch, heads, hist_lo, hist_hi, new_lo, n
     items = plan(m, hist, new, heads)
     check_cover(items, hist, new, heads)
     assert (items[:, 3].max() <= 128) == (rows == 128)
+
+
+# Grouped heads of 64 with 128-row tiles: as many shares as the partial-result buffer holds would be more than the static scratch
+# array does (992 of 128 rows), and 256-row tiles need fewer.
+@pytest.mark.parametrize("batch, heads, hist_lo, hist_hi, new_lo, new_hi", [(3, (64, 8, 64), 19538, 35752, 327, 444), (3, (32, 4, 64), 8287, 29283, 304, 389),
+                                                                            (3, (64, 8, 64), 9000, 30000, 300, 500)])
+@in_model
+def test_the_static_entry_point_takes_plans_with_smaller_tiles(m, batch, heads, hist_lo, hist_hi, new_lo, new_hi):
+    hist, new = (np.linspace(lo, hi, batch).round().astype(np.int32) for lo, hi in ((hist_lo, hist_hi), (new_lo, new_hi)))
+    t = Turn(m, hist, new, heads=heads, require_load=0)
+    t.rebase()
+    items = t.ctx.rebase_read(6).reshape(-1, 8)
+    items = items[items[:, 0] >= 0]
+    check_cover(items, hist, new, heads)
+    assert items[:, 3].max() <= 128
+    t.attn(static=True)
