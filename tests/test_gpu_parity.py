@@ -152,8 +152,8 @@ def test_save_arbitrary_ranges_bit_exact(case):
 
 def variant_config(variant):
     """12: keys rotated (and, for head_dim 128, values transposed) once per layer into scratch copies, read by the
-    kernel that pipelines matrix instructions and softmax inside each wavefront; 13: the rotated keys read by the
-    LDS-direct kernel (2) with all wavefronts in lock step"""
+    kernel that pipelines matrix instructions and softmax inside each wavefront; 13: the rotated keys read by the kernel
+    for keys rotated beforehand (heads of 128: scores a tile ahead, two groups of wavefronts half a tile apart)"""
     if variant == 12:
         return dict(attn_variant=2, attn_prerotate=2, attn_schedule=1)
     if variant == 13:
