@@ -110,12 +110,14 @@ typedef struct {
                              /* tiles per (conversation, kv head) on average); 1: never;         */
                              /* 2: always (256-row tiles are then used whatever the batch, but for */
                              /* head_dim 64 with many tiles: 128)                                 */
-    int32_t attn_schedule;   /* 0: the LDS-direct kernel, all wavefronts of a workgroup in lock step.      */
-                             /* 1: when the keys are rotated once per layer (attn_prerotate), head_dim is  */
-                             /* 128 and the tiles have 256 rows, the values are transposed into a scratch  */
-                             /* copy in the same pass and a kernel runs that pipelines, inside every       */
-                             /* wavefront, the matrix instructions of one key tile with the softmax of the */
-                             /* previous one (any window; measured as fast as 0, plus the longer pre-pass)  */
+    int32_t attn_schedule;   /* 0: when the keys are rotated once per layer (attn_prerotate), the kernel    */
+                             /* for keys rotated beforehand: heads of 128 with the scores of a tile formed */
+                             /* under the softmax of the one before and, in 256-row tiles, two groups of   */
+                             /* wavefronts half a tile apart; else the kernel that rotates keys itself.    */
+                             /* 1: when besides head_dim is 128 and the tiles have 256 rows, the values are */
+                             /* transposed into a scratch copy in the same pass and a kernel runs that     */
+                             /* pipelines, inside every wavefront, the matrix instructions of one key tile */
+                             /* with the softmax of the previous one (any window; slower than 0)           */
     int32_t require_load;    /* 1: attention on a layer with kept history that was not loaded */
                              /* under the current plan fails with CA_ERR_NOT_READY            */
     int32_t device;          /* HIP device ordinal                                            */
@@ -244,16 +246,17 @@ ca_status ca_kv_append_layer(ca_ctx *ctx, int32_t layer, const void *new_k, cons
  * bf16 out.  q, out: device.  Waits (on `stream`) for the load of `layer` if one was issued.
  * Partial results of a plan that splits keys are kept in one buffer of the context: calls of this
  * entry point on one context must not overlap in time (one stream, or streams that wait for each
- * other).  A call of the _static entry point below may run beside one of this.                  */
+ * other).  A call of the _static entry point below may run beside one of this, unless the plan
+ * rotates keys once per layer: the rotated copy is one buffer of the context for both.           */
 ca_status ca_cached_prefill_attn(ca_ctx *ctx, int32_t layer, const void *q, const void *k_pool,
                                  const void *v_pool, void *out, float softmax_scale, void *stream);
 
 /* The same call for callers that cannot allocate device memory or tolerate a library that does:
  * code under HIP graph capture, tight serving loops, harnesses that forbid hipMalloc.  Identical
- * arguments, kernels and results; the one scratch buffer the attention kernels use beyond inputs
- * and outputs -- the partial results (fp32 sums, maxima, denominators) of row tiles whose keys the
- * plan split over several workgroups -- is taken from a fixed 32 MiB array inside the library's
- * code object (one copy per GPU, held until the process ends) instead of the context's buffer.
+ * arguments, kernels and results; the scratch buffer for the partial results (fp32 sums, maxima,
+ * denominators) of row tiles whose keys the plan split over several workgroups is taken from a
+ * fixed 32 MiB array inside the library's code object (one copy per GPU, held until the process
+ * ends) instead of the context's buffer.  (Keys rotated once per layer go to the context's copy.)
  * The call allocates nothing and records no timing intervals.  A plan whose shares need more than
  * 32 MiB (n_shares * tile_rows * (head_dim + 2) * 4 bytes) is refused with CA_ERR_OUT_OF_RANGE
  * and nothing is launched.  Every call on a GPU, from any context, uses that GPU's one array:

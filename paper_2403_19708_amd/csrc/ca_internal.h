@@ -137,7 +137,7 @@ struct AttnArgs {
     float *partial;          // shares of split row tiles: per part [tile_rows][head_dim] sums, [tile_rows] maxima,
                              // [tile_rows] denominators (fp32)
     const float2 *rope;      // [max_positions][head_dim/2] (cos, sin)
-    // keys rotated once per batch and layer instead of in every row tile (prerotate != 0):
+    // keys rotated once per batch and layer instead of in every row tile (launch_attn_prerot, launch_attn_pp):
     uint16_t *k_rot;             // scratch copy of the keys, dense pages [n_dense_pages][n_kv_heads][16][head_dim]
     uint16_t *v_t;               // scratch copy of the values, same pages, each block transposed (pipelined != 0 only)
     const int32_t *rot_nvalid;   // [n_dense_pages] context tokens in the page (16 except a conversation's last page)
@@ -146,7 +146,6 @@ struct AttnArgs {
     const int32_t *rot_src_page; // [n_dense_pages] pool page a dense page is rotated from
     const int32_t *rot_pos0;     // [n_dense_pages] position of its first token
     int32_t n_dense_pages;
-    int32_t prerotate;
     int32_t max_positions;
     int32_t n_items;
     const RowsItem *rows_items;  // launch_attn_rows
@@ -168,7 +167,7 @@ constexpr int kRopeMinRows = 256;       // the kernels read table rows below thi
 
 hipError_t launch_attn_ref(const AttnArgs &args, hipStream_t stream);
 hipError_t launch_attn_dma(const AttnArgs &args, hipStream_t stream);
-// keys rotated once per layer into a scratch copy first (args.prerotate)
+// keys rotated once per layer into a scratch copy first
 hipError_t launch_attn_prerot(const AttnArgs &args, hipStream_t stream);
 // head_dim 128, 256-row tiles, keys rotated and values transposed once per layer into scratch copies; inside every
 // wavefront the matrix instructions of one key tile are pipelined with the softmax of the previous one

@@ -169,7 +169,10 @@ constexpr size_t kMetaAlign = 64;            // alignment of the arrays of the m
 //   saves   2: 31, 31 GB/s, not   4: 45, 44, not    8: 52, 51, 1.4 x   16: 54, 54, 1.9 x
 // Past what the link holds the requests queue up in the memory system in front of everyone else's.  Whole turns (two layers
 // of 64 such conversations, us): 27648 with 6 load workgroups, 27006 with 8, 26780 with 10, 26706 with 12.
-// (Measured with the attention that rotates keys itself; see save_workgroups for the one over keys rotated beforehand.)
+// That is with the attention that rotates keys itself.  Beside the one over keys rotated beforehand and two save workgroups, a step of
+// 16 layers of 64 such conversations: 8 load workgroups 195.1 ms and 2150 to 2190 us of attention a layer, 10: 194.4 and 2200,
+// 12: 196.9 and 2375.  (Fewer and larger workgroups, which would leave more compute units alone, cannot have as many requests
+// under way: 3 of 1024 threads load 34 GB/s.)
 constexpr int kLinkLoadWorkgroups = 10;
 constexpr int kLinkSaveWorkgroups = 4;
 constexpr int kLinkSaveBesideLoads = 2;
@@ -2142,7 +2145,6 @@ static ca_status attn_impl(ca_ctx *ctx, int32_t layer, const void *q, const void
     a.rot_nvalid = (const int32_t *)(ctx->d_meta + ctx->off_rot_nvalid);
     a.pipelined = ctx->pipelined ? 1 : 0;
     a.n_dense_pages = ctx->n_dense_pages;
-    a.prerotate = ctx->prerotate ? 1 : 0;
     a.max_positions = c.max_positions;
     a.n_combine = ctx->n_combine;
     a.rope = ctx->rope;
