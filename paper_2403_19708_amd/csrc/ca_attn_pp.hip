@@ -29,11 +29,11 @@
 //   four 16 KiB slots.
 // * The softmax scale and log2(e) are folded into the rotated query before it is rounded to bf16.
 //
-// What it buys: nothing in time on the workloads measured (config 5: 1.8 ms per launch, as the lock-step kernel),
-// and the transposing pre-pass costs 0.13 ms more; three schedules of this arithmetic (lock step, two alternating
+// What it buys: nothing in time on the workloads measured (config 5: 1.8 ms per launch, where ca_attn_prerot.hip takes 1.6 to 1.8
+// and the tile kernel before that took as long), and the transposing pre-pass costs 0.13 ms more; three schedules of this arithmetic (lock step, two alternating
 // groups of wavefronts, this one) land within a few per cent of each other, and switching any one ingredient off
 // (vector work, LDS reads, loads, barrier) shortens the kernel by about that ingredient's own time: the parts do
-// not hide behind each other.  Kept selectable (attn_schedule = 1) because it has no window limit.
+// not hide behind each other.  Kept selectable (attn_schedule = 1) for the comparison.
 #include "ca_internal.h"
 #include "ca_device.h"
 

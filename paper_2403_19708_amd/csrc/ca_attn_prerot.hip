@@ -5,9 +5,12 @@
 // transposed formulation, the layout of a tile in LDS, the loads that bring it there and the shares of split keys are those
 // described at the head of that file.
 //
-// What bounds it (256 rows x 64 keys, heads of 128, one workgroup per compute unit): a tile is 2048 cycles of
-// matrix instructions per SIMD (two wavefronts x 32 instructions x 32 cycles), and with all compute units busy the card
-// lowers its clock from 2.4 to 1.6-1.75 GHz, so instructions taken out count as much as cycles.  Measured in cycles a
+// What bounds it (256 rows x 64 keys, heads of 128, one workgroup per compute unit): a tile is 2176 cycles of
+// matrix instructions per SIMD (two wavefronts x (32 instructions x 32 cycles + 8 of 8 for the row sums)), and with all compute
+// units busy the card lowers its clock from 2.4 to 1.6-1.75 GHz, so instructions taken out count as much as cycles.
+// Loads have to land within a tile of the one they were issued in (the rings hold no more): traffic over the host link in both
+// directions at once is felt (save_workgroups in ca_lib.hip).  With 255 registers nothing else runs on the unit; that
+// costs the attention 5 % beside 24 workgroups that only keep their places.  Measured in cycles a
 // tile, and us a layer for 64 conversations of 1024-4096 + 64-512 tokens, 64 query and 8 kv heads: looking for the
 // maximum of every tile, v_dot2c row sums and all wavefronts in lock step 3490 and 1860; probabilities checked instead
 // of scores and the scores of the next tile formed under the softmax of this one 3155; two groups of wavefronts half a

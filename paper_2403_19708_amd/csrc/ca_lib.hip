@@ -1285,7 +1285,9 @@ ca_status ca_rope_rebase(ca_ctx *ctx, const ca_batch *b, void *stream_) {
         const int most = ctx->max_unit_rows;
         if (tile == 0) tile = most > 128 ? 256 : 128;
         const bool direct_for_rot = direct_variant(c);
-        {   // rotate the keys once per layer when on average three or more row tiles would each rotate them
+        {   // rotate the keys once per layer when on average three or more row tiles would each rotate them (48 batches, 4 to 64
+            // conversations of 500 to 3000 tokens, four shapes of heads, rotated beforehand against in the kernel: with one tile
+            // 1.11 to 1.31 of the time, with two 0.94 to 1.15, three 0.90 to 1.07, four 0.85 to 1.10)
             int64_t tiles256 = 0;
             for (int i = 0; i < B; ++i) tiles256 += ((int64_t)b->new_len[i] * G + 255) / 256;
             ctx->prerotate = ctx->k_rot && direct_for_rot &&
