@@ -14,10 +14,17 @@
 //     log2(e) folded into the rotated query, the reference maximum enters as the accumulator and is raised lazily.
 //   * Keys are rotated in registers between the LDS read and the matrix instruction: a lane's operand pieces of one key
 //     hold both members of every rotary pair.  (cos, sin) advance by a constant rotation from page to page.
-//   * With enough to stream the pages of all (conversation, kv head) units, laid end to end, are cut into equal runs, one per
-//     workgroup of four wavefronts, two workgroups per compute unit: all have the same number of bytes whatever the lengths.
-//     With less (one conversation: 11 MB) the time is the chain of dependent memory accesses, and workgroups of eight
-//     wavefronts take one share of at least 16 pages each, whose description brings everything the first loads need.
+//   * Workgroups of four wavefronts, two to a compute unit (of eight where nothing is cut).  With enough to stream the pages of all (conversation, kv head)
+//     units, laid end to end, are cut into equal runs, one per workgroup: all have the same number of bytes whatever the lengths.
+//     With less (one conversation: 11 MB) the time is a chain of dependent steps and a workgroup has one share, whose
+//     description brings everything the first loads need.  Clock stamps of that chain (2777 tokens, 8 kv heads, 8 rows, 3 pages a
+//     wavefront): description 0.4 us, first loads landed 4.2, walk 7.1, wavefronts merged 7.8, share acknowledged and
+//     counted 9.4, shares merged 11.6.  A compute unit takes 16 cycles for a load instruction of 1 KiB and about 45 KB/us from
+//     beyond its cache, and a wavefront alone on its SIMD 0.9 us a page, most of it the rotation: hence few loads (each
+//     query row is fetched and rotated once per workgroup, and a share is read 16 bytes a lane) and few pages a wavefront.
+//     With eight wavefronts of 16 pages a share, each fetching the queries by itself, this took 14.4 us; the
+//     decode step of that conversation over 80 layers 1508 -> 1267 us, of 8 of 700 to 1800 tokens over 20 layers 620 -> 464, of 64 of
+//     200 to 600 tokens 733 -> 589.
 //   * A share that is not a whole unit leaves unnormalised sums, maximum and denominator, and the workgroup that finishes a
 //     unit's last share merges them: no second launch (a combine kernel behind a decode step's attention cost 4 us plus the
 //     gap in front of it).  Shares are written through to memory; with release fences instead, each of which writes back a
@@ -29,8 +36,9 @@ namespace ca {
 
 namespace {
 
-// D, rotary style, NB = 16-row blocks (rows <= 16 NB), NWV = wavefronts of a workgroup
-template <int D, int STYLE, int NB, int NWV>
+// D, rotary style, NB = 16-row blocks (rows <= 16 NB), NWV = wavefronts of a workgroup, ONE = workgroup w has item w only (else
+// the items [wg_first[w], wg_first[w + 1]))
+template <int D, int STYLE, int NB, int NWV, bool ONE>
 __global__ __launch_bounds__(64 * NWV, 2) void attn_rows_kernel(AttnArgs a) {
     constexpr int HALF = D / 2;
     constexpr int PPR = D / 8;                // 16-byte pieces per row
@@ -45,11 +53,13 @@ __global__ __launch_bounds__(64 * NWV, 2) void attn_rows_kernel(AttnArgs a) {
     constexpr int DB = D / 16;                // 16-dim blocks of O^T
     constexpr int ROWS = 16 * NB;
     constexpr int OSTR = D + 4;               // row stride of the merge buffer (floats): conflict-free 16-byte accesses
+    constexpr int QSTR = 2 * D + 16;          // row stride of the rotated queries (bytes): conflict-free 16-byte accesses
     constexpr int RING = NWV * NS * STAGE, MERGE = NWV * ROWS * OSTR * 4;
     constexpr int SMEM = RING > MERGE ? RING : MERGE;
-    static_assert(SMEM + NWV * ROWS * 8 + 256 <= (NWV == 4 ? 80 : 160) * 1024, "LDS budget");
+    static_assert(SMEM + ROWS * QSTR + NWV * ROWS * 8 + 256 <= (NWV == 4 ? 80 : 160) * 1024, "LDS budget");
 
     __shared__ __attribute__((aligned(16))) uint8_t smem[SMEM];
+    __shared__ __attribute__((aligned(16))) uint8_t q_rot[ROWS * QSTR];
     __shared__ float red_m[NWV][ROWS], red_l[NWV][ROWS];
     __shared__ int32_t is_last;
 
@@ -73,15 +83,20 @@ __global__ __launch_bounds__(64 * NWV, 2) void attn_rows_kernel(AttnArgs a) {
 
     // constant rotation from a wavefront's page to its next one
     float2 step[KK / 2][8];
+    const auto load_step = [&]() __attribute__((always_inline)) {
 #pragma unroll
-    for (int p = 0; p < KK / 2; ++p) load_cs<D, STYLE>(a.rope, NWV * kPageSize, q4 + 4 * p, step[p]);
+        for (int p = 0; p < KK / 2; ++p) load_cs<D, STYLE>(a.rope, NWV * kPageSize, q4 + 4 * p, step[p]);
+    };
+    if (!ONE) load_step();
 
-    // eight wavefronts: the item is the workgroup's only one and its first pages (one or two per wavefront) are in it
-    constexpr bool ONE = NWV == 8;
     const int it_end = ONE ? (int)blockIdx.x + 1 : load_uniform(a.wg_first + blockIdx.x + 1);
     for (int it = ONE ? (int)blockIdx.x : load_uniform(a.wg_first + blockIdx.x); it < it_end; ++it) {
         const int32_t *iw = reinterpret_cast<const int32_t *>(a.rows_items + it);
-        const int32_t near_page[2] = {load_uniform(iw + 16 + wave), load_uniform(iw + 16 + (wave + NWV) % 16)};
+        // the ids of a wavefront's first pages are in the item (of sixteen pages in all)
+        constexpr int NEAR = NS < 16 / NWV ? NS : 16 / NWV;
+        int32_t near_page[NEAR];
+#pragma unroll
+        for (int s = 0; s < NEAR; ++s) near_page[s] = load_uniform(iw + 16 + wave + s * NWV);
         const int c = load_uniform(iw), g = load_uniform(iw + 1), n_rows = load_uniform(iw + 2);
         const int key_begin = load_uniform(iw + 3), key_end = load_uniform(iw + 4), part = load_uniform(iw + 5);
         const int n = load_uniform(iw + 6), q0 = load_uniform(iw + 7);
@@ -106,33 +121,27 @@ __global__ __launch_bounds__(64 * NWV, 2) void attn_rows_kernel(AttnArgs a) {
         // ---- the first pages go out, then the query rows are fetched and rotated behind them -----------------------
 #pragma unroll
         for (int s = 0; s < NS; ++s)
-            if (pg + s * NWV <= last_page) issue(s, pg + s * NWV, s < 2 ? near_page[s] : load_uniform(table + pg + s * NWV));
+            if (pg + s * NWV <= last_page) issue(s, pg + s * NWV, s < NEAR ? near_page[s < NEAR ? s : 0] : load_uniform(table + pg + s * NWV));
 
-        bf16x8 Qf[NB][KK];
-        int qpos[NB];
-#pragma unroll
-        for (int nb = 0; nb < NB; ++nb) {
-            const int r = min(nb * 16 + m16, n_rows - 1);
-            const int j = r / G;
-            qpos[nb] = n + j;
+        // Each row is fetched and rotated once per workgroup and handed on through LDS: a thread has one row's pair of pieces.
+        for (int i = tid; i < n_rows * (PPR / 2); i += 64 * NWV) {
+            const int r = i / (PPR / 2), piece = i % (PPR / 2), j = r / G;
             const uint16_t *qrow = a.q + ((int64_t)(q0 + j) * a.n_q_heads + g * G + (r - j * G)) * D;
+            uint4 x = *reinterpret_cast<const uint4 *>(qrow + 8 * piece);
+            uint4 y = *reinterpret_cast<const uint4 *>(qrow + HALF + 8 * piece);
+            float2 qcs[8];
+            load_cs<D, STYLE>(a.rope, n + j, piece, qcs);
+            uint32_t *px = reinterpret_cast<uint32_t *>(&x), *py = reinterpret_cast<uint32_t *>(&y);
 #pragma unroll
-            for (int p = 0; p < KK / 2; ++p) {
-                const int piece = q4 + 4 * p;
-                uint4 x = *reinterpret_cast<const uint4 *>(qrow + 8 * piece);
-                uint4 y = *reinterpret_cast<const uint4 *>(qrow + HALF + 8 * piece);
-                float2 cs[8];
-                load_cs<D, STYLE>(a.rope, qpos[nb], piece, cs);
-                uint32_t *px = reinterpret_cast<uint32_t *>(&x), *py = reinterpret_cast<uint32_t *>(&y);
-#pragma unroll
-                for (int w = 0; w < 4; ++w) rotate_dword<STYLE>(px[w], py[w], cs, w, cscale);
-                Qf[nb][p] = __builtin_bit_cast(bf16x8, x);
-                Qf[nb][p + KK / 2] = __builtin_bit_cast(bf16x8, y);
-            }
+            for (int w = 0; w < 4; ++w) rotate_dword<STYLE>(px[w], py[w], qcs, w, cscale);
+            *reinterpret_cast<uint4 *>(q_rot + r * QSTR + 16 * piece) = x;
+            *reinterpret_cast<uint4 *>(q_rot + r * QSTR + D + 16 * piece) = y;
         }
         float2 cs[KK / 2][8];
 #pragma unroll
         for (int p = 0; p < KK / 2; ++p) load_cs<D, STYLE>(a.rope, min(pg * kPageSize + m16, kmax - 1), q4 + 4 * p, cs[p]);
+        if (ONE && pg + NWV <= last_page) load_step();
+        int32_t next_page = load_uniform(table + min(pg + NS * NWV, last_page));      // id of the next page to ask for
 
         f32x4 O[NB][DB];
         float m_run[NB], l_run[NB];           // reference maximum of this lane's row (exponent units), its part of the denominator
@@ -148,6 +157,16 @@ __global__ __launch_bounds__(64 * NWV, 2) void attn_rows_kernel(AttnArgs a) {
         // Everything the compiler loaded has arrived: it would otherwise wait for it at the first use inside the loop, every
         // time round, and with it for the pages just asked for.
         CA_WAIT_VMCNT(0);
+        __syncthreads();
+        bf16x8 Qf[NB][KK];
+        int qpos[NB];
+#pragma unroll
+        for (int nb = 0; nb < NB; ++nb) {
+            const int r = min(nb * 16 + m16, n_rows - 1);
+            qpos[nb] = n + r / G;
+#pragma unroll
+            for (int kk = 0; kk < KK; ++kk) Qf[nb][kk] = *reinterpret_cast<const bf16x8 *>(q_rot + r * QSTR + 16 * (q4 + 4 * kk));
+        }
 
         // ---- the walk ---------------------------------------------------------------------------------------------
         for (int stage = 0; pg <= last_page; pg += NWV, stage = (stage + 1) % NS) {
@@ -162,17 +181,22 @@ __global__ __launch_bounds__(64 * NWV, 2) void attn_rows_kernel(AttnArgs a) {
             for (int db = 0; db < DB; ++db)
                 v[db] = __builtin_amdgcn_ds_read_tr16_b64_v4i16((s16x4 __attribute__((address_space(3))) *)(st + v_rd + db * (2 * KPC * 16)));
             asm volatile("s_waitcnt lgkmcnt(0)" : : : "memory");       // read out: the stage is free
-            if (pg + NS * NWV <= last_page) issue(stage, pg + NS * NWV, load_uniform(table + pg + NS * NWV));
+            if (pg + NS * NWV <= last_page) {
+                issue(stage, pg + NS * NWV, next_page);
+                next_page = load_uniform(table + min(pg + (NS + 1) * NWV, last_page));
+            }
 
 #pragma unroll
             for (int p = 0; p < KK / 2; ++p) {
                 uint32_t *px = reinterpret_cast<uint32_t *>(&k[p]), *py = reinterpret_cast<uint32_t *>(&k[p + KK / 2]);
 #pragma unroll
                 for (int w = 0; w < 4; ++w) rotate_dword<STYLE>(px[w], py[w], cs[p], w);
+                if (!ONE || pg + NWV <= last_page) {
 #pragma unroll
-                for (int e = 0; e < 8; ++e) {
-                    const float2 o = cs[p][e], s = step[p][e];
-                    cs[p][e] = make_float2(o.x * s.x - o.y * s.y, o.y * s.x + o.x * s.y);
+                    for (int e = 0; e < 8; ++e) {
+                        const float2 o = cs[p][e], s = step[p][e];
+                        cs[p][e] = make_float2(o.x * s.x - o.y * s.y, o.y * s.x + o.x * s.y);
+                    }
                 }
             }
 #pragma unroll
@@ -237,7 +261,9 @@ __global__ __launch_bounds__(64 * NWV, 2) void attn_rows_kernel(AttnArgs a) {
         }
         __syncthreads();
         constexpr int VPR = D / 4;
-        float *const part_base = a.partial + (int64_t)max(part, 0) * ROWS * (D + 2);
+        // a share: [ROWS][D] sums, [ROWS] (maximum, denominator)
+        constexpr int PART = ROWS * (D + 2) * 4;
+        const auto shares = buffer_at(a.partial);
         for (int i = tid; i < n_rows * VPR; i += 64 * NWV) {
             const int row = i / VPR, d = 4 * (i % VPR);
             float M = red_m[0][row];
@@ -254,43 +280,53 @@ __global__ __launch_bounds__(64 * NWV, 2) void attn_rows_kernel(AttnArgs a) {
             if (part < 0) {
                 store_out_row4<D>(a, q0, g, G, row, d, acc, 1.f / l);
             } else {
-                store_agent4(part_base + row * D + d, acc);
-                if (d == 0) {
-                    store_agent(part_base + ROWS * D + row, M);
-                    store_agent(part_base + ROWS * (D + 1) + row, l);
-                }
+                store_agent4(shares, part * PART + (row * D + d) * 4, acc);
+                if (d == 0) store_agent2(shares, part * PART + (ROWS * D + 2 * row) * 4, make_float2(M, l));
             }
         }
         if (part >= 0) {
             // the workgroup that brings a unit's last share merges them all
             const int ci = load_uniform(iw + 8), first = load_uniform(iw + 9), n_parts = load_uniform(iw + 10);
             if (arrive_last(a.arrived + ci, n_parts, &is_last)) {
-                const float *base = a.partial + (int64_t)first * ROWS * (D + 2);
-                constexpr int64_t STRIDE = (int64_t)ROWS * (D + 2);
                 for (int i = tid; i < n_rows * VPR; i += 64 * NWV) {
                     const int row = i / VPR, d = 4 * (i % VPR);
                     float M = -INFINITY, l = 0.f;
                     f32x4 acc = {0.f, 0.f, 0.f, 0.f};
-                    constexpr int U = 8;                                // shares in flight
-                    for (int s0 = 0; s0 < n_parts; s0 += U) {
-                        float ms[U], ls[U];
-                        f32x4 os[U];
+                    constexpr int U = 8, BATCHES = ONE ? 2 : 1;         // shares of a batch, batches in flight
+                    float2 ml0[U], ml1[U];                              // maximum, denominator
+                    f32x4 os0[U], os1[U];
+                    const auto fetch = [&](float2 (&ml)[U], f32x4 (&os)[U], int s0) __attribute__((always_inline)) {
 #pragma unroll
                         for (int u = 0; u < U; ++u) {
-                            const float *p = base + min(s0 + u, n_parts - 1) * STRIDE;
-                            ms[u] = load_agent(p + ROWS * D + row);
-                            ls[u] = load_agent(p + ROWS * (D + 1) + row);
-                            os[u] = load_agent4(p + row * D + d);
+                            const int at = (first + min(s0 + u, n_parts - 1)) * PART;
+                            ml[u] = load_agent2(shares, at + (ROWS * D + 2 * row) * 4);
+                            os[u] = load_agent4(shares, at + (row * D + d) * 4);
                         }
+                    };
+                    const auto add = [&](float2 (&ml)[U], const f32x4 (&os)[U], int s0) __attribute__((always_inline)) {
+                        float M2 = M;
 #pragma unroll
                         for (int u = 0; u < U; ++u) {
-                            if (s0 + u >= n_parts || ms[u] == -INFINITY) continue;
-                            const float M2 = fmaxf(M, ms[u]);
-                            const float fa = M == -INFINITY ? 0.f : __builtin_amdgcn_exp2f(M - M2), fb = __builtin_amdgcn_exp2f(ms[u] - M2);
-                            acc = acc * fa + os[u] * fb;
-                            l = l * fa + ls[u] * fb;
-                            M = M2;
+                            if (s0 + u >= n_parts) ml[u].x = -INFINITY;
+                            M2 = fmaxf(M2, ml[u].x);
                         }
+                        if (M2 == -INFINITY) return;
+                        const float fa = __builtin_amdgcn_exp2f(M - M2);
+                        acc *= fa;
+                        l *= fa;
+                        M = M2;
+#pragma unroll
+                        for (int u = 0; u < U; ++u) {
+                            const float fb = __builtin_amdgcn_exp2f(ml[u].x - M2);       // (0 where the share has seen no key)
+                            if (ml[u].x != -INFINITY) acc += fb * os[u];
+                            l += fb * (ml[u].x != -INFINITY ? ml[u].y : 0.f);
+                        }
+                    };
+                    for (int s0 = 0; s0 < n_parts; s0 += BATCHES * U) {
+                        fetch(ml0, os0, s0);
+                        if (BATCHES == 2 && s0 + U < n_parts) fetch(ml1, os1, s0 + U);
+                        add(ml0, os0, s0);
+                        if (BATCHES == 2 && s0 + U < n_parts) add(ml1, os1, s0 + U);
                     }
                     store_out_row4<D>(a, q0, g, G, row, d, acc, 1.f / l);
                 }
@@ -300,24 +336,24 @@ __global__ __launch_bounds__(64 * NWV, 2) void attn_rows_kernel(AttnArgs a) {
     }
 }
 
-template <int NB, int NWV>
+template <int NB, int NWV, bool ONE>
 hipError_t launch_blocks(const AttnArgs &a, hipStream_t stream) {
     const dim3 grid(a.n_wgs), block(64 * NWV);
-    if (a.head_dim == 128 && a.rope_style == 0) hipLaunchKernelGGL((attn_rows_kernel<128, 0, NB, NWV>), grid, block, 0, stream, a);
-    else if (a.head_dim == 128 && a.rope_style == 1) hipLaunchKernelGGL((attn_rows_kernel<128, 1, NB, NWV>), grid, block, 0, stream, a);
-    else if (a.head_dim == 64 && a.rope_style == 0) hipLaunchKernelGGL((attn_rows_kernel<64, 0, NB, NWV>), grid, block, 0, stream, a);
-    else if (a.head_dim == 64 && a.rope_style == 1) hipLaunchKernelGGL((attn_rows_kernel<64, 1, NB, NWV>), grid, block, 0, stream, a);
+    if (a.head_dim == 128 && a.rope_style == 0) hipLaunchKernelGGL((attn_rows_kernel<128, 0, NB, NWV, ONE>), grid, block, 0, stream, a);
+    else if (a.head_dim == 128 && a.rope_style == 1) hipLaunchKernelGGL((attn_rows_kernel<128, 1, NB, NWV, ONE>), grid, block, 0, stream, a);
+    else if (a.head_dim == 64 && a.rope_style == 0) hipLaunchKernelGGL((attn_rows_kernel<64, 0, NB, NWV, ONE>), grid, block, 0, stream, a);
+    else if (a.head_dim == 64 && a.rope_style == 1) hipLaunchKernelGGL((attn_rows_kernel<64, 1, NB, NWV, ONE>), grid, block, 0, stream, a);
     else return hipErrorInvalidValue;
     return hipGetLastError();
 }
 
 }  // namespace
 
-hipError_t launch_attn_rows(const AttnArgs &a, int wavefronts, hipStream_t stream) {
+hipError_t launch_attn_rows(const AttnArgs &a, int wavefronts, bool runs, hipStream_t stream) {
     if (a.n_wgs <= 0) return hipSuccess;
     if (!a.wg_first || !a.rows_items || (a.n_combine > 0 && (!a.partial || !a.arrived))) return hipErrorInvalidValue;
-    if (a.tile_rows == 16) return wavefronts == 8 ? launch_blocks<1, 8>(a, stream) : launch_blocks<1, 4>(a, stream);
-    if (a.tile_rows == 32) return wavefronts == 8 ? launch_blocks<2, 8>(a, stream) : launch_blocks<2, 4>(a, stream);
+    if (a.tile_rows == 16) return runs ? launch_blocks<1, 4, false>(a, stream) : wavefronts == 8 ? launch_blocks<1, 8, true>(a, stream) : launch_blocks<1, 4, true>(a, stream);
+    if (a.tile_rows == 32) return runs ? launch_blocks<2, 4, false>(a, stream) : wavefronts == 8 ? launch_blocks<2, 8, true>(a, stream) : launch_blocks<2, 4, true>(a, stream);
     return hipErrorInvalidValue;
 }
 

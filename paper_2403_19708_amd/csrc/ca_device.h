@@ -58,25 +58,29 @@ __device__ inline uint32_t lds_offset(const void *p) {
 
 // Results that a workgroup on another die reads inside the same launch: written through and read past the dies' own caches
 // (agent scope).  A release fence instead would write back a die's whole L2, once per wavefront.
-__device__ inline void store_agent(float *p, float v) { __hip_atomic_store(p, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT); }
-__device__ inline float load_agent(const float *p) { return __hip_atomic_load(p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT); }
-__device__ inline void store_agent4(float *p, f32x4 v) {      // p: 8-byte aligned
-    uint64_t *q = reinterpret_cast<uint64_t *>(p);
-    const float2 lo = make_float2(v[0], v[1]), hi = make_float2(v[2], v[3]);
-    __hip_atomic_store(q, __builtin_bit_cast(uint64_t, lo), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-    __hip_atomic_store(q + 1, __builtin_bit_cast(uint64_t, hi), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+// Through a buffer descriptor (`base` wave-uniform, `at` in bytes): one instruction moves 16 bytes, where an atomic access
+// moves 8 at most.
+typedef __attribute__((ext_vector_type(4))) uint32_t u32x4;
+typedef __attribute__((ext_vector_type(2))) uint32_t u32x2;
+constexpr int kAgentScope = 16;                    // sc1
+__device__ inline __amdgpu_buffer_rsrc_t buffer_at(float *base) { return __builtin_amdgcn_make_buffer_rsrc(base, 0, -1, 0x00020000); }
+__device__ inline void store_agent4(__amdgpu_buffer_rsrc_t b, int at, f32x4 v) {
+    __builtin_amdgcn_raw_buffer_store_b128(__builtin_bit_cast(u32x4, v), b, at, 0, kAgentScope);
 }
-__device__ inline f32x4 load_agent4(const float *p) {
-    const uint64_t *q = reinterpret_cast<const uint64_t *>(p);
-    const float2 lo = __builtin_bit_cast(float2, __hip_atomic_load(q, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT));
-    const float2 hi = __builtin_bit_cast(float2, __hip_atomic_load(q + 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT));
-    return f32x4{lo.x, lo.y, hi.x, hi.y};
+__device__ inline void store_agent2(__amdgpu_buffer_rsrc_t b, int at, float2 v) {
+    __builtin_amdgcn_raw_buffer_store_b64(__builtin_bit_cast(u32x2, v), b, at, 0, kAgentScope);
+}
+__device__ inline f32x4 load_agent4(__amdgpu_buffer_rsrc_t b, int at) {
+    return __builtin_bit_cast(f32x4, __builtin_amdgcn_raw_buffer_load_b128(b, at, 0, kAgentScope));
+}
+__device__ inline float2 load_agent2(__amdgpu_buffer_rsrc_t b, int at) {
+    return __builtin_bit_cast(float2, __builtin_amdgcn_raw_buffer_load_b64(b, at, 0, kAgentScope));
 }
 // Counts a workgroup in whose stores of this kind are done; true in the one that is the n-th (which may then read the
 // others').  Called by every thread of the workgroup; `flag` is in LDS.  The n-th brings the count back to zero in the same
 // atomic operation: no count in between can be lost.
 __device__ inline bool arrive_last(uint32_t *count, int n, int32_t *flag) {
-    CA_WAIT_VMCNT(0);                              // this wavefront's stores have been acknowledged
+    asm volatile("s_waitcnt vmcnt(0)" : : : "memory");    // this wavefront's stores have been acknowledged
     __syncthreads();
     if (threadIdx.x == 0) *flag = atomicInc(count, (unsigned)(n - 1)) == (unsigned)(n - 1);
     __syncthreads();

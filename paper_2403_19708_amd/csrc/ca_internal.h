@@ -149,8 +149,7 @@ struct AttnArgs {
     int32_t max_positions;
     int32_t n_items;
     const RowsItem *rows_items;  // launch_attn_rows
-    const int32_t *wg_first;     // launch_attn_rows, four wavefronts: workgroup w takes items [wg_first[w], wg_first[w + 1]);
-                                 // eight: workgroup w takes item w
+    const int32_t *wg_first;     // launch_attn_rows with runs
     uint32_t *arrived;           // launch_attn_rows: shares of each merge that are there already; zero between calls
     int32_t n_wgs;
     int32_t n_combine;
@@ -181,9 +180,10 @@ hipError_t launch_attn_decode(const AttnArgs &args, int max_rows, hipStream_t st
 // few rows: every item has at most kAttnRowsMax stacked rows starting at row 0 (tile_rows 16 or 32); the context is streamed
 // once through LDS rings of single wavefronts; merges its shares itself
 constexpr int kAttnRowsMax = 32;
-hipError_t launch_attn_rows(const AttnArgs &args, int wavefronts, hipStream_t stream);
+// runs: workgroup w of four wavefronts takes items [wg_first[w], wg_first[w + 1]), else, of four or eight, item w
+hipError_t launch_attn_rows(const AttnArgs &args, int wavefronts, bool runs, hipStream_t stream);
 constexpr int kAttnMaxParts = 1024;           // shares of split row tiles per batch (sizes the partial-result buffer)
 constexpr int kAttnMaxPartsPerTile = 16;
-constexpr int kAttnMinPartKeys = 256;         // a share is at least this many keys
+constexpr int kAttnMinPartKeys = 256;         // a share of the tile kernels, or of a run, is at least this many keys
 
 }  // namespace ca

@@ -107,7 +107,8 @@ struct ca_ctx {
     int32_t max_unit_rows = 0;   // most stacked query rows of any (conversation, kv head) of the plan
     // plan of the few-rows kernel (launch_attn_rows): its workgroups' item ranges, and one counter per merge for each of the
     // two attention entry points, which may run at once (zero between calls, and set to zero with every plan)
-    int32_t n_wgs = 0, wg_wavefronts = 0;
+    int32_t n_wgs = 0, wg_wavefronts = 4;
+    bool rows_runs = false;
     size_t off_wg_first = 0, off_rows_items = 0;
     uint32_t *arrived = nullptr, *static_arrived = nullptr;
     int32_t n_split_parts = 0;   // shares of split row tiles of the plan (slots of the partial-result buffer in use)
@@ -161,6 +162,7 @@ ca_status fail(ca_ctx *ctx, ca_status st, const char *fmt, ...) {
 // Workgroups of a few-rows plan that splits keys: two of four wavefronts per compute unit when there is that much to
 // stream, else at most one of eight (kAttnMaxParts / 2 bounds them: a workgroup's run of pages has two shares at most).
 constexpr int kRowsMaxWorkgroups = 512;
+constexpr int kRowsCutPages = 20;
 constexpr size_t kMetaAlign = 64;            // alignment of the arrays of the metadata image
 // Workgroups of a kernel that moves between the pool and pinned host memory (32 KB in flight each), measured on MI355X with
 // 16 conversations of a grouped-query layer (169 MB to load, 18 MB to save): the rate alone, the rate beside the attention of
@@ -1031,9 +1033,14 @@ static bool rows_plan(const ca_ctx *ctx) {
 
 // Work list of the few-rows kernel.  Cuts inside a (conversation, kv head) unit lie on multiples of 64 keys.
 // Much to stream (eight pages per wavefront and more): the pages of all units, laid end to end, are cut into one run per
-// workgroup of four wavefronts; a cut leaves at least kAttnMinPartKeys on either side (a share costs a merge), so runs are
-// equal up to 256 keys.  Less: every unit of at least 512 keys is cut into shares of 16 pages, two per wavefront of a
-// workgroup of eight (both in flight from the start), more where that would be more shares than compute units.
+// workgroup; a cut leaves at least kAttnMinPartKeys on either side (a share costs a merge), so runs are equal up to 256 keys.
+// Less: a workgroup has one share, and the time is a chain: a wavefront takes 0.9 us a page (heads of 128), and the workgroup that
+// merges reads all shares of its unit, about 45 KB/us, some 2 us at least.  Units of kRowsCutPages pages and more are cut into
+// shares of about the square root of their pages, or what an equal spread over the compute units gives where that is more.
+// (us a decode step with shares of 8, 12, 16, 24 and 32 pages: 40 layers of 250 pages, 8 kv heads 765, 707, 675, 726, 757; 80 layers of
+// 174 pages 1332, 1268, 1316, 1359, 1501; 20 layers of 500 pages, 2 kv heads 387, 355, 343, 364, 382; of 1876 pages, 24, 32 and
+// 48 a share 470, 469, 495; 40 layers of 16 conversations of 13 to 26 pages 629 with all of at least 16 cut,
+// 655 with none.)
 static void plan_rows(ca_ctx *ctx, size_t &up) {
     const ca_config &c = ctx->cfg;
     const int B = ctx->n_seqs, Hkv = c.n_kv_heads, G = c.n_q_heads / Hkv;
@@ -1048,9 +1055,9 @@ static void plan_rows(ca_ctx *ctx, size_t &up) {
     const bool split = ctx->partial != nullptr;
     const bool runs = total >= (int64_t)2 * ctx->n_cus * 32;
     const int wgs = !runs ? 0 : split ? std::min(kRowsMaxWorkgroups, 2 * ctx->n_cus) : n_units;
-    const int share = (int)std::max<int64_t>(kMin, (total / ctx->n_cus + kCut - 1) / kCut * kCut);   // pages, where there are no runs
-    const int cuts = !split ? 0 : runs ? wgs : (int)(total / share);      // at most
-    ctx->wg_wavefronts = runs ? 4 : 8;
+    const int even = (int)std::max<int64_t>(kCut, (total / ctx->n_cus + kCut - 1) / kCut * kCut);        // pages, where there are no runs
+    const int cuts = !split ? 0 : runs ? wgs : (int)(total / even);      // at most
+    ctx->rows_runs = runs;
     ctx->off_wg_first = put((size_t)(wgs + 1) * 4);
     ctx->off_items = put((size_t)(n_units + cuts) * sizeof(WorkItem));
     ctx->off_rows_items = put((size_t)(n_units + cuts) * sizeof(RowsItem));
@@ -1064,6 +1071,7 @@ static void plan_rows(ca_ctx *ctx, size_t &up) {
         const int keys = ctx->n_keep[i] + ctx->new_len[i], rows = ctx->new_len[i] * G;
         const int pages = (keys + kPageSize - 1) / kPageSize;
         const int32_t *table = (const int32_t *)(ctx->h_meta + ctx->off_table) + (size_t)i * ctx->max_pages;
+        const int share = std::max(even, (int)(std::sqrt((double)pages) / kCut + 0.5) * kCut);
         for (int g = 0; g < Hkv; ++g, done += pages) {
             const int first_item = n_items;
             for (int at = 0; at < pages;) {
@@ -1079,7 +1087,7 @@ static void plan_rows(ca_ctx *ctx, size_t &up) {
                         else if (keys / kPageSize - cut < kMin) cut = pages;
                     }
                     next_wg = end <= pages;
-                } else if (pages >= 2 * kMin) {
+                } else if (pages >= kRowsCutPages) {
                     cut = std::min(pages, at + share);
                 }
                 if (cut > at) {
@@ -1105,6 +1113,9 @@ static void plan_rows(ca_ctx *ctx, size_t &up) {
     }
     while (w < wgs) wg_first[++w] = n_items;
     ctx->n_wgs = runs ? wgs : n_items;
+    // Whole units that leave compute units over: eight wavefronts take half the steps (a turn of 256 + 32 tokens, 4 heads of 64:
+    // 29.0 us, 30.5 with four).  Where a workgroup's loads are the longer part they are no gain (shares of 16 pages: 1558 us, 1330).
+    ctx->wg_wavefronts = !runs && n_merges == 0 && n_items < ctx->n_cus ? 8 : 4;
     ctx->n_items = n_items;
     ctx->n_combine = n_merges;
     ctx->n_split_parts = n_parts;
@@ -2177,7 +2188,7 @@ static ca_status attn_impl(ca_ctx *ctx, int32_t layer, const void *q, const void
     if (c.attn_variant == 1) {
         CA_HIP(ctx, launch_attn_ref(a, stream));
     } else if (ctx->n_wgs > 0) {
-        CA_HIP(ctx, launch_attn_rows(a, ctx->wg_wavefronts, stream));
+        CA_HIP(ctx, launch_attn_rows(a, ctx->wg_wavefronts, ctx->rows_runs, stream));
     } else if (decode) {
         CA_HIP(ctx, launch_attn_decode(a, ctx->max_unit_rows, stream));
     } else if (direct && ctx->pipelined) {

@@ -61,6 +61,18 @@ def test_units_cut_into_many_runs(shape):
     assert np.array_equal(bits[0], bits[1]) and np.array_equal(bits[0], bits[2])
 
 
+@pytest.mark.parametrize("pages, shares", [(3, 0), (19, 0), (20, 5), (21, 6), (250, 16), (272, 17), (600, 25), (1100, 35)])
+@pytest.mark.parametrize("shape", [(8, 1, 128, 0, 1), (16, 2, 64, 1, 4)], ids=["one-block", "two-blocks"])
+def test_shares_of_one_conversation(shape, pages, shares):
+    """Units below and above the least that is cut, shares that end in the middle of a wavefront's turn, and merges of one batch of
+    eight shares, two, and more than the two in flight at once."""
+    Hq, Hkv, D, style, new = shape
+    case = Case([16 * pages - new - 5], [new], [0], Hq, Hkv, D, seed=66 + pages, style=style, window=32768)
+    items, bits = run_case(case, calls=2)
+    assert (items[:, 6] >= 0).sum() == shares * Hkv
+    assert np.array_equal(bits[0], bits[1])
+
+
 @pytest.mark.parametrize("split", [0, 1], ids=["split", "whole"])
 @pytest.mark.parametrize("shape", [(64, 16, 64, 0, 1), (64, 8, 64, 1, 3), (64, 8, 128, 0, 1), (64, 8, 128, 1, 1), (32, 4, 128, 0, 4), (24, 8, 128, 1, 6)],
                          ids=lambda s: "hq%d-hkv%d-d%d-style%d-new%d" % s)
