@@ -63,7 +63,7 @@ constexpr int kMaxPagesLds = 2048;   // page ids kept in LDS at a time: a window
 // PGW = page ids kept in LDS at a time, OCC = wavefronts per SIMD the register budget is cut for.
 template <int D, int STYLE, int NW, int BN, int NS = 4, int PGW = kMaxPagesLds, int OCC = 2>
 __global__ __launch_bounds__(64 * NW, OCC) void attn_dma_kernel(AttnArgs a) {
-    static_assert(NS >= 4, "the in-place rotary pass needs a tile landed one iteration early");
+    static_assert(NS == 4, "the in-place rotary pass needs a tile landed one iteration early");
     constexpr int NTHREADS = 64 * NW;
     constexpr int MB = BN / 32;              // 32-key blocks of S^T per tile
     constexpr int KS2 = BN / 16;             // 16-key steps of the second product per tile
@@ -259,30 +259,19 @@ __global__ __launch_bounds__(64 * NW, OCC) void attn_dma_kernel(AttnArgs a) {
     const bf16x2 ones2 = {(__bf16)1.0f, (__bf16)1.0f};
 
     // ---- prologue ---------------------------------------------------------------------------------------
+    // the queries are asked for before the page ids arrive, and rotated behind the loads of the first two tiles
+    QueryRows<D, STYLE> rows;
+    if (wave_live) rows.fetch(a, q0, g, G, n, item.row0 + __builtin_amdgcn_readfirstlane(wave) * 32, row_last);
     __syncthreads();                     // page ids are in LDS
     issue(t_begin);
-    if (NS > 2 && t_begin + 1 < n_tiles) issue(t_begin + 1);
-    if (NS > 3 && t_begin + 2 < n_tiles) issue(t_begin + 2);
-    // The query row is fetched behind the tile loads, so its latency and theirs overlap.  These loads are younger than
-    // the tile loads and complete after them: the counted wait below can only become stricter by them.
-    {
-        const uint16_t *qrow = a.q + ((int64_t)(q0 + j) * a.n_q_heads + head) * D;
-#pragma unroll
-        for (int ks = 0; ks < KSTEPS / 2; ++ks) {
-            const int piece = 2 * ks + half;
-            uint4 x = *reinterpret_cast<const uint4 *>(qrow + 8 * piece);
-            uint4 y = *reinterpret_cast<const uint4 *>(qrow + HALF + 8 * piece);
-            float2 cs[8];
-            load_cs<D, STYLE>(a.rope, qpos, piece, cs);
-            uint32_t *px = reinterpret_cast<uint32_t *>(&x), *py = reinterpret_cast<uint32_t *>(&y);
-#pragma unroll
-            for (int w = 0; w < 4; ++w) rotate_dword<STYLE>(px[w], py[w], cs, w, cscale);
-            Qf[ks] = __builtin_bit_cast(bf16x8, x);
-            Qf[ks + KSTEPS / 2] = __builtin_bit_cast(bf16x8, y);
-        }
-    }
-    if (NS > 3 && t_begin + 2 < n_tiles) { CA_WAIT_VMCNT(NI); } else { CA_WAIT_VMCNT(0); }   // the first two tiles have landed
+    if (t_begin + 1 < n_tiles) issue(t_begin + 1);
+    // they pass through the stages of the third and fourth tile
+    static_assert(QueryRows<D, STYLE>::kQueryBytes * (NW / 2) <= STAGE, "half the wavefronts' queries in a stage");
+    if (wave_live)
+        rows.finish(ring + (t_begin + 2 + wave / (NW / 2)) % NS * STAGE + wave % (NW / 2) * QueryRows<D, STYLE>::kQueryBytes, cscale, Qf);
+    CA_WAIT_VMCNT(0);                    // the first two tiles have landed
     __syncthreads();
+    if (t_begin + 2 < n_tiles) issue(t_begin + 2);
     rot_read(ring + (t_begin % NS) * STAGE);
 #pragma unroll
     for (int w = 0; w < 4; ++w) rot_part(ring + (t_begin % NS) * STAGE, w);

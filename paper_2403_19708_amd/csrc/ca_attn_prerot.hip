@@ -197,36 +197,27 @@ __global__ __launch_bounds__(64 * NW, OCC) void attn_prerot_kernel(AttnArgs a) {
     const s16x4 ones = {0x3f80, 0x3f80, 0x3f80, 0x3f80};
 
     // ---- prologue ---------------------------------------------------------------------------------------
+    // the queries are asked for before the page ids arrive, and rotated behind the loads of the first tiles
+    QueryRows<D, STYLE> rows;
+    if (wave_live) rows.fetch(a, q0, g, G, n, item.row0 + wave * 32, row_last);
     __syncthreads();                     // page ids are in LDS
-    // (in this order: what may stay in flight when the walk begins goes out last)
 #pragma unroll
     for (int k = 0; k < KA - 1; ++k)
         if (t_begin + k < n_tiles) issue(t_begin + k, std::false_type{});
 #pragma unroll
     for (int k = 0; k < VA - 1; ++k)
         if (t_begin + k < n_tiles) issue(t_begin + k, std::true_type{});
+    // they pass through the third and fourth stage of either ring
+    constexpr int QPT = NW / 4;          // wavefronts per stage
+    static_assert(QueryRows<D, STYLE>::kQueryBytes * QPT <= TILE && KA == 3 && VA <= 3, "the queries fit the stages without loads");
+    if (wave_live)
+        rows.finish((wave / QPT < 2 ? stage_k(t_begin + 2 + wave / QPT) : stage_v(t_begin + wave / QPT)) + wave % QPT * QueryRows<D, STYLE>::kQueryBytes,
+                    cscale, Qf);
+    CA_WAIT_VMCNT(0);
+    __syncthreads();
+    // what may stay in flight when the walk begins
     if (t_begin + KA - 1 < n_tiles) issue(t_begin + KA - 1, std::false_type{});
     if (t_begin + VA - 1 < n_tiles) issue(t_begin + VA - 1, std::true_type{});
-    // The query row is fetched behind the tile loads, so its latency and theirs overlap.  These loads are younger than
-    // the tile loads and complete after them: the counted wait below can only become stricter by them.
-    {
-        const uint16_t *qrow = a.q + ((int64_t)(q0 + j) * a.n_q_heads + head) * D;
-#pragma unroll
-        for (int ks = 0; ks < KSTEPS / 2; ++ks) {
-            const int piece = 2 * ks + half;
-            uint4 x = *reinterpret_cast<const uint4 *>(qrow + 8 * piece);
-            uint4 y = *reinterpret_cast<const uint4 *>(qrow + HALF + 8 * piece);
-            float2 cs[8];
-            load_cs<D, STYLE>(a.rope, qpos, piece, cs);
-            uint32_t *px = reinterpret_cast<uint32_t *>(&x), *py = reinterpret_cast<uint32_t *>(&y);
-#pragma unroll
-            for (int w = 0; w < 4; ++w) rotate_dword<STYLE>(px[w], py[w], cs, w, cscale);
-            Qf[ks] = __builtin_bit_cast(bf16x8, x);
-            Qf[ks + KSTEPS / 2] = __builtin_bit_cast(bf16x8, y);
-        }
-    }
-    if (t_begin + KA - 1 < n_tiles) { CA_WAIT_VMCNT(NI); } else { CA_WAIT_VMCNT(0); }
-    __syncthreads();
     // first product of a tile: the keys are read KD steps ahead
     constexpr int KD = 2;
     bf16x8 kf[KD][MB];

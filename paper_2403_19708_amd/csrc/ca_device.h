@@ -131,6 +131,63 @@ __device__ inline void rotate_dword(uint32_t &pa, uint32_t &pb, const float2 (&c
     }
 }
 
+// The 32 stacked query rows row_first .. of a wavefront, rotated, scaled by `f` and rounded, as B operand of S^T = K Q^T (lane ->
+// row lane % 32, k-step ks -> piece 2 ks + lane / 32).  A lane that fetches its own row touches 32 cache lines in every
+// instruction, each line in four instructions, for the queries and again for the rotary table, and the first level cache does not hold
+// the lines of eight wavefronts that long: 10.6 us from the start of a workgroup of 256 rows to its first tile (32 heads, one
+// row per position).  Here D / 4 lanes fetch a row and its table row side by side, two rotary pairs each, and the rotated row goes
+// through LDS to the lanes that want it.  `fetch` only asks for the data; `finish` needs stage(): kQueryBytes of LDS that nobody else uses.
+template <int D, int STYLE>
+struct QueryRows {
+    static constexpr int kStride = 2 * D + 16;             // bytes of a row in LDS: 16-byte reads of 32 rows are free of bank conflicts
+    static constexpr int kQueryBytes = 32 * kStride;
+    static constexpr int LPR = D / 4;                      // lanes per row
+    static constexpr int RPS = 64 / LPR;                   // rows per step
+    static constexpr int STEPS = 32 / RPS;
+    float4 cs[STEPS];                                      // (cos, sin) of pairs 2 c and 2 c + 1, c = lane % LPR
+    uint32_t x[STEPS], y[STEPS];
+
+    __device__ inline void fetch(const AttnArgs &a, int q0, int g, int G, int n, int row_first, int row_last) {
+        const int lane = threadIdx.x & 63, c = lane % LPR;
+        const int j0 = row_first / G, r0 = j0 * G;               // (wave-uniform)
+        const float per_g = 1.0f / (float)G;
+#pragma unroll
+        for (int i = 0; i < STEPS; ++i) {
+            const int r = min(row_first + i * RPS + lane / LPR, row_last);
+            const int j = j0 + (int)(((float)(r - r0) + 0.5f) * per_g);      // r / G (the operand is below G + 32)
+            const uint16_t *row = a.q + ((int64_t)(q0 + j) * a.n_q_heads + g * G + (r - j * G)) * D;
+            cs[i] = *reinterpret_cast<const float4 *>(a.rope + (int64_t)(n + j) * (D / 2) + 2 * c);
+            if (STYLE == 0) {
+                x[i] = *reinterpret_cast<const uint32_t *>(row + 2 * c);
+                y[i] = *reinterpret_cast<const uint32_t *>(row + D / 2 + 2 * c);
+            } else {
+                const uint2 v = *reinterpret_cast<const uint2 *>(row + 4 * c);
+                x[i] = v.x;
+                y[i] = v.y;
+            }
+        }
+    }
+    __device__ inline void finish(uint8_t *stage, float f, bf16x8 (&Qf)[D / 16]) {
+        const int lane = threadIdx.x & 63, c = lane % LPR;
+#pragma unroll
+        for (int i = 0; i < STEPS; ++i) {
+            const float2 first = make_float2(cs[i].x, cs[i].y), second = make_float2(cs[i].z, cs[i].w);
+            const float2 both[8] = {first, second, first, second, second, second, second, second};
+            rotate_dword<STYLE>(x[i], y[i], both, 0, f);         // (STYLE 0: pairs both[0], both[1]; 1: both[0], both[4])
+            uint8_t *at = stage + (i * RPS + lane / LPR) * kStride;
+            if (STYLE == 0) {
+                *reinterpret_cast<uint32_t *>(at + 4 * c) = x[i];
+                *reinterpret_cast<uint32_t *>(at + D + 4 * c) = y[i];
+            } else {
+                *reinterpret_cast<uint2 *>(at + 8 * c) = make_uint2(x[i], y[i]);
+            }
+        }
+#pragma unroll
+        for (int ks = 0; ks < D / 16; ++ks)
+            Qf[ks] = *reinterpret_cast<const bf16x8 *>(stage + lane % 32 * kStride + 16 * (2 * ks + lane / 32));
+    }
+};
+
 // four head dimensions d.. of stacked row `row` of a (conversation with first new token q0, kv head g), normalised
 template <int D>
 __device__ inline void store_out_row4(const AttnArgs &a, int q0, int g, int G, int row, int d, f32x4 o, float inv) {

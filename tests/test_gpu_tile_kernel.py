@@ -43,6 +43,21 @@ def test_tile_edges(shape, rows, prerotate):
         check_tight(got[c], case.oracle_out(0, c), int(case.n_keep[c]), c)
 
 
+@pytest.mark.parametrize("prerotate", [1, 2], ids=["rotary", "rotated"])
+@pytest.mark.parametrize("rows", [128, 256])
+@pytest.mark.parametrize("shape", SHAPES, ids=lambda s: "d%d-style%d" % s)
+@pytest.mark.parametrize("G", [1, 3, 5, 40])
+def test_rows_of_odd_groups(G, shape, rows, prerotate):
+    """The 32 query rows of a wavefront start and end inside a token's group of heads, or lie in one or two of them"""
+    D, style = shape
+    new = [300 // G + 1, 7, 1]
+    case = Case([70, 0, 130], new, [0, 0, 0], G, 1, D, seed=80 + D + style, style=style, window=1024)
+    got = outputs(case, attn_tile_rows=rows, attn_prerotate=prerotate, attn_split=1)
+    for c in range(case.B):
+        check_contract(got[c], case.oracle_out(0, c), c)
+        check_tight(got[c], case.oracle_out(0, c), int(case.n_keep[c]), c)
+
+
 @pytest.mark.parametrize("steps", [[1.0, 40.0], [40.0, 1.0], [1.0, 4.0, 16.0, 64.0, 1.0]], ids=["jump", "fall", "stairs"])
 @pytest.mark.parametrize("prerotate", [1, 2], ids=["rotary", "rotated"])
 @pytest.mark.parametrize("rows", [128, 256])
