@@ -434,20 +434,9 @@ __global__ __launch_bounds__(64 * NW, OCC) void attn_dma_kernel(AttnArgs a) {
         }
         return;
     }
-    if (row_valid) {
-        const float inv = 1.f / l_all;
-        uint16_t *orow = a.out + ((int64_t)(q0 + j) * a.n_q_heads + head) * D;
-#pragma unroll
-        for (int db = 0; db < DBLKS; ++db)
-#pragma unroll
-            for (int i4 = 0; i4 < 4; ++i4) {
-                const int d = 32 * db + i4 * 8 + half * 4;
-                uint2 o;
-                o.x = pack_bf16(O[db][4 * i4] * inv, O[db][4 * i4 + 1] * inv);
-                o.y = pack_bf16(O[db][4 * i4 + 2] * inv, O[db][4 * i4 + 3] * inv);
-                *reinterpret_cast<uint2 *>(orow + d) = o;
-            }
-    }
+    // (every wavefront is through with the ring)
+    if (wave_live)
+        store_rows<D>(a, q0, g, G, item.row0 + __builtin_amdgcn_readfirstlane(wave) * 32, row_last, ring + wave * QueryRows<D, STYLE>::kQueryBytes, O, 1.f / l_all);
 }
 
 // Merges the shares of row tiles whose keys were split (Section 2.1's softmax over the union of the key

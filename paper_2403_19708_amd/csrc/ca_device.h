@@ -188,6 +188,31 @@ struct QueryRows {
     }
 };
 
+// The 32 stacked rows of a wavefront, normalised and rounded, from the C layout of O^T (lane -> row lane % 32, dims 32 db + 8 i +
+// 4 (lane / 32) .. + 3 in registers 4 i .. of block db) to `out`.  A lane that stores its own row writes 16 bytes of 32 lines in every
+// instruction; through LDS (`stage`: kQueryBytes that nobody else uses) an instruction writes whole lines.
+template <int D>
+__device__ inline void store_rows(const AttnArgs &a, int q0, int g, int G, int row_first, int row_last, uint8_t *stage, const f32x16 (&O)[D / 32], float inv) {
+    constexpr int kStride = QueryRows<D, 0>::kStride, LPR = D / 8, RPS = 64 / LPR;      // lanes per row, rows per instruction
+    const int lane = threadIdx.x & 63;
+#pragma unroll
+    for (int db = 0; db < D / 32; ++db)
+#pragma unroll
+        for (int i = 0; i < 4; ++i) {
+            const uint2 o = make_uint2(pack_bf16(O[db][4 * i] * inv, O[db][4 * i + 1] * inv), pack_bf16(O[db][4 * i + 2] * inv, O[db][4 * i + 3] * inv));
+            *reinterpret_cast<uint2 *>(stage + lane % 32 * kStride + 2 * (32 * db + 8 * i + 4 * (lane / 32))) = o;
+        }
+    const int j0 = row_first / G, r0 = j0 * G;                   // (wave-uniform)
+    const float per_g = 1.0f / (float)G;
+#pragma unroll
+    for (int i = 0; i < 32 / RPS; ++i) {
+        const int at = i * RPS + lane / LPR, r = row_first + at;
+        const uint4 o = *reinterpret_cast<const uint4 *>(stage + at * kStride + 16 * (lane % LPR));
+        const int j = j0 + (int)(((float)(r - r0) + 0.5f) * per_g);          // r / G (the operand is below G + 32)
+        if (r <= row_last) *reinterpret_cast<uint4 *>(a.out + ((int64_t)(q0 + j) * a.n_q_heads + g * G + (r - j * G)) * D + 8 * (lane % LPR)) = o;
+    }
+}
+
 // four head dimensions d.. of stacked row `row` of a (conversation with first new token q0, kv head g), normalised
 template <int D>
 __device__ inline void store_out_row4(const AttnArgs &a, int q0, int g, int G, int row, int d, f32x4 o, float inv) {
