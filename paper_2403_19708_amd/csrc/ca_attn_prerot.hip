@@ -487,39 +487,48 @@ __global__ __launch_bounds__(64 * NW, OCC) void attn_prerot_kernel(AttnArgs a) {
 // Rotates the keys of the whole batch context once (Section 3.4: the rebased positional encoding, applied
 // when the cache is used): dense page dp of the scratch copy = pool page rot_src_page[dp] with token slot s
 // rotated at position rot_pos0[dp] + s, in fp32 from the table, rounded to bf16 -- the same values the fused
-// path forms tile by tile (there with the rotation advanced by recurrence).  one workgroup per (dense page, kv head);
-// a thread owns one (token, pair of 16-byte pieces).  Slots past the end of a context hold whatever the pool
-// holds; nobody reads them.
-template <int D, int STYLE>
+// path forms tile by tile (there with the rotation advanced by recurrence).  Slots past the end of a context hold whatever
+// the pool holds; nobody reads them.  Bound by HBM (one read, one write).  A workgroup has a dense page and HEADS kv heads, a thread one
+// (token, pair of 16-byte pieces) of each: the table row is fetched once for all of them and their loads are all in flight.
+// With a workgroup to a head and a table row each, 64 conversations of 1024-4096 + 64-512 tokens, 8 kv heads (350 MB of keys) took
+// 157-170 us, now 129-143; loads that pass the cache by are 5 us of that, eight heads to a workgroup are as fast alone and slower
+// beside loads.
+template <int D, int STYLE, int HEADS>
 __global__ __launch_bounds__(D) void rotate_keys_kernel(AttnArgs a) {
     constexpr int HALF = D / 2;
     constexpr int PAIRS = D / 16;                       // piece pairs per row
     static_assert(kPageSize * PAIRS == D, "one thread per (token of the page, piece pair)");
-    // workgroup i runs on die i % 8: the heads of a page go to one die, one after the other, because they
-    // read the same 16 rows of the rotary table (its L2 then serves seven of the eight reads)
-    const int die = blockIdx.x % 8, k = blockIdx.x / 8;
-    const int dp = (k / a.n_kv_heads) * 8 + die, g = k % a.n_kv_heads;
-    if (dp >= a.n_dense_pages) return;
+    const int slices = a.n_kv_heads / HEADS;
+    const int dp = blockIdx.x / slices, g0 = blockIdx.x % slices * HEADS;
     const int key = threadIdx.x / PAIRS, pr = threadIdx.x % PAIRS;
-    if (key >= kPageSize) return;
     const int pos = min(a.rot_pos0[dp] + key, a.max_positions - 1);
-    const int64_t src = (((int64_t)a.rot_src_page[dp] * a.n_kv_heads + g) * kPageSize + key) * D;
-    const int64_t dst = (((int64_t)dp * a.n_kv_heads + g) * kPageSize + key) * D;
-    uint4 x = *reinterpret_cast<const uint4 *>(a.k_pool + src + 8 * pr);
-    uint4 y = *reinterpret_cast<const uint4 *>(a.k_pool + src + HALF + 8 * pr);
+    const uint16_t *src = a.k_pool + (((int64_t)a.rot_src_page[dp] * a.n_kv_heads + g0) * kPageSize + key) * D + 8 * pr;
+    uint16_t *dst = a.k_rot + (((int64_t)dp * a.n_kv_heads + g0) * kPageSize + key) * D + 8 * pr;
+    uint4 x[HEADS], y[HEADS];
+#pragma unroll
+    for (int g = 0; g < HEADS; ++g) {
+        x[g] = __builtin_bit_cast(uint4, __builtin_nontemporal_load(reinterpret_cast<const u32x4 *>(src + g * kPageSize * D)));
+        y[g] = __builtin_bit_cast(uint4, __builtin_nontemporal_load(reinterpret_cast<const u32x4 *>(src + g * kPageSize * D + HALF)));
+    }
     float2 cs[8];
     load_cs<D, STYLE>(a.rope, pos, pr, cs);
-    uint32_t *px = reinterpret_cast<uint32_t *>(&x), *py = reinterpret_cast<uint32_t *>(&y);
 #pragma unroll
-    for (int w = 0; w < 4; ++w) rotate_dword<STYLE>(px[w], py[w], cs, w);
-    *reinterpret_cast<uint4 *>(a.k_rot + dst + 8 * pr) = x;
-    *reinterpret_cast<uint4 *>(a.k_rot + dst + HALF + 8 * pr) = y;
+    for (int g = 0; g < HEADS; ++g) {
+        uint32_t *px = reinterpret_cast<uint32_t *>(&x[g]), *py = reinterpret_cast<uint32_t *>(&y[g]);
+#pragma unroll
+        for (int w = 0; w < 4; ++w) rotate_dword<STYLE>(px[w], py[w], cs, w);
+        *reinterpret_cast<uint4 *>(dst + g * kPageSize * D) = x[g];
+        *reinterpret_cast<uint4 *>(dst + g * kPageSize * D + HALF) = y[g];
+    }
 }
 
 template <int D, int STYLE>
 void launch_all(const AttnArgs &a, hipStream_t stream) {
-    const dim3 rgrid((uint32_t)((a.n_dense_pages + 7) / 8) * 8u * (uint32_t)a.n_kv_heads), grid(a.n_items);
-    hipLaunchKernelGGL((rotate_keys_kernel<D, STYLE>), rgrid, dim3(D), 0, stream, a);
+    const int heads = a.n_kv_heads % 4 == 0 ? 4 : a.n_kv_heads % 2 == 0 ? 2 : 1;
+    const dim3 rgrid((uint32_t)a.n_dense_pages * (uint32_t)(a.n_kv_heads / heads)), grid(a.n_items);
+    if (heads == 4) hipLaunchKernelGGL((rotate_keys_kernel<D, STYLE, 4>), rgrid, dim3(D), 0, stream, a);
+    else if (heads == 2) hipLaunchKernelGGL((rotate_keys_kernel<D, STYLE, 2>), rgrid, dim3(D), 0, stream, a);
+    else hipLaunchKernelGGL((rotate_keys_kernel<D, STYLE, 1>), rgrid, dim3(D), 0, stream, a);
     if (a.tile_rows == 256) hipLaunchKernelGGL((attn_prerot_kernel<D, STYLE, 8, 64, 2>), grid, dim3(512), 0, stream, a);
     else hipLaunchKernelGGL((attn_prerot_kernel<D, STYLE, 4, 32, D == 64 ? 3 : 2>), grid, dim3(256), 0, stream, a);
 }
