@@ -25,7 +25,7 @@
 //   * An item may own only a share [key_begin, key_end) of the keys its rows see (the host splits long
 //     row tiles over several workgroups when a batch would otherwise leave compute units idle).  Such an
 //     item leaves unnormalised sums, reference maxima and denominators in a scratch buffer and
-//     combine_kernel merges the shares of a row tile.
+//     combine_tiles_kernel merges the shares of a row tile.
 //   * Since the LDS side of such a load is fixed (lane l -> byte l*16 of a 1 KiB chunk), the layout
 //     is chosen on the global side: a chunk holds KPC = 1024/(2D) keys, piece-major
 //     (slot = piece*KPC + key_in_chunk), chunks padded by KPC*16 bytes.  With it the A-operand reads
@@ -415,20 +415,19 @@ __global__ __launch_bounds__(64 * NW, OCC) void attn_dma_kernel(AttnArgs a) {
     const float l_all = l_run + __shfl_xor(l_run, 32);
     if (item.part >= 0) {
         // keys split over several workgroups: leave the unnormalised sums, the reference maximum and the
-        // denominator of this share in the scratch buffer; combine_kernel merges the shares
+        // denominator of this share in the scratch buffer; combine_tiles_kernel merges the shares
         if (row_valid) {
             const int rt = r - item.row0;                       // row inside the tile
             float *base = a.partial + (int64_t)item.part * a.tile_rows * (D + 2);
-            float *prow = base + (int64_t)rt * D;
 #pragma unroll
             for (int db = 0; db < DBLKS; ++db)
 #pragma unroll
                 for (int i4 = 0; i4 < 4; ++i4) {
-                    const int d = 32 * db + i4 * 8 + half * 4;
-                    *reinterpret_cast<float4 *>(prow + d) = make_float4(O[db][4 * i4], O[db][4 * i4 + 1], O[db][4 * i4 + 2], O[db][4 * i4 + 3]);
+                    const int d4 = 8 * db + 2 * i4 + half;
+                    reinterpret_cast<float4 *>(base)[d4 * a.tile_rows + rt] = make_float4(O[db][4 * i4], O[db][4 * i4 + 1], O[db][4 * i4 + 2], O[db][4 * i4 + 3]);
                 }
             if (half == 0) {
-                base[(int64_t)a.tile_rows * D + rt] = m_run / cscale;      // combine_kernel takes it in score units
+                base[(int64_t)a.tile_rows * D + rt] = m_run / cscale;      // in score units
                 base[(int64_t)a.tile_rows * (D + 1) + rt] = l_all;
             }
         }
@@ -485,6 +484,71 @@ __global__ __launch_bounds__(256) void combine_kernel(AttnArgs a) {
     *reinterpret_cast<uint2 *>(a.out + ((int64_t)(a.cu_q[ci.seq] + j) * a.n_q_heads + head) * D + d) = ob;
 }
 
+// The same for the tile kernels, whose shares lie as they leave the matrix cores, [D/4][tile_rows][4] sums: lanes of either kernel
+// that hold a row next to each other write and read next to each other.  blockIdx.y = 32 rows of the tile; a thread has D/32
+// groups of four dimensions of one row, four shares of them in flight, and the merged rows leave through LDS in whole lines.
+// (80 tiles of 256 rows in three shares each, 32 MB: 12 us with shares and outputs row by row, 9 us so.)
+template <int D>
+__global__ __launch_bounds__(256) void combine_tiles_kernel(AttnArgs a) {
+    constexpr int N = D / 32, U = 4, kStride = 2 * D + 16;
+    __shared__ __attribute__((aligned(16))) uint8_t stage[32 * kStride];
+    const CombineItem ci = a.combine[blockIdx.x];
+    const int row0 = blockIdx.y * 32, rows = min(32, ci.n_rows - row0);
+    if (rows <= 0) return;
+    const int lr = threadIdx.x % 32, q = threadIdx.x / 32;
+    const int rt = row0 + min(lr, rows - 1);
+    const int G = a.n_q_heads / a.n_kv_heads;
+    const float cscale = a.softmax_scale * 1.4426950408889634f;
+    const int64_t part_stride = (int64_t)a.tile_rows * (D + 2);
+    const float *first = a.partial + ci.first_part * part_stride;
+    float w[kAttnMaxPartsPerTile], lsum = 0.f;
+    float M = -INFINITY;
+#pragma unroll
+    for (int s = 0; s < kAttnMaxPartsPerTile; ++s) {
+        w[s] = s < ci.n_parts ? first[s * part_stride + (int64_t)a.tile_rows * D + rt] : -INFINITY;
+        M = fmaxf(M, w[s]);
+    }
+#pragma unroll
+    for (int s = 0; s < kAttnMaxPartsPerTile; ++s) {
+        w[s] = w[s] == -INFINITY ? 0.f : __builtin_amdgcn_exp2f((w[s] - M) * cscale);
+        if (s < ci.n_parts) lsum += w[s] * first[s * part_stride + (int64_t)a.tile_rows * (D + 1) + rt];
+    }
+    float4 acc[N];
+#pragma unroll
+    for (int k = 0; k < N; ++k) acc[k] = make_float4(0.f, 0.f, 0.f, 0.f);
+#pragma unroll
+    for (int s0 = 0; s0 < kAttnMaxPartsPerTile; s0 += U) {
+        if (s0 >= ci.n_parts) break;
+        float4 o[U][N];
+#pragma unroll
+        for (int u = 0; u < U; ++u) {
+            if (s0 + u >= ci.n_parts) break;
+#pragma unroll
+            for (int k = 0; k < N; ++k)
+                o[u][k] = reinterpret_cast<const float4 *>(first + (s0 + u) * part_stride)[(q + 8 * k) * a.tile_rows + rt];
+        }
+#pragma unroll
+        for (int u = 0; u < U; ++u) {
+            if (s0 + u >= ci.n_parts) break;
+#pragma unroll
+            for (int k = 0; k < N; ++k) {
+                const float f = w[s0 + u];
+                acc[k].x += f * o[u][k].x; acc[k].y += f * o[u][k].y; acc[k].z += f * o[u][k].z; acc[k].w += f * o[u][k].w;
+            }
+        }
+    }
+    const float inv = 1.f / lsum;
+#pragma unroll
+    for (int k = 0; k < N; ++k)
+        *reinterpret_cast<uint2 *>(stage + lr * kStride + 8 * (q + 8 * k)) = make_uint2(pack_bf16(acc[k].x * inv, acc[k].y * inv), pack_bf16(acc[k].z * inv, acc[k].w * inv));
+    __syncthreads();
+    for (int i = threadIdx.x; i < rows * (D / 8); i += 256) {
+        const int at = i / (D / 8), piece = i % (D / 8), r = ci.row0 + row0 + at, j = r / G;
+        *reinterpret_cast<uint4 *>(a.out + ((int64_t)(a.cu_q[ci.seq] + j) * a.n_q_heads + ci.kv_head * G + (r - j * G)) * D + 8 * piece) =
+            *reinterpret_cast<const uint4 *>(stage + at * kStride + 16 * piece);
+    }
+}
+
 template <int NW, int BN>
 hipError_t launch_shape(const AttnArgs &a, hipStream_t stream) {
     dim3 grid(a.n_items), block(64 * NW);
@@ -511,7 +575,16 @@ hipError_t launch_attn_dma(const AttnArgs &a, hipStream_t stream) {
     else if (a.tile_rows == 128) e = launch_shape<4, 32>(a, stream);
     else return hipErrorInvalidValue;
     if (e != hipSuccess || a.n_combine <= 0) return e;
-    return launch_attn_combine(a, stream);
+    return launch_combine_tiles(a, stream);
+}
+
+hipError_t launch_combine_tiles(const AttnArgs &a, hipStream_t stream) {
+    if (a.n_combine <= 0) return hipSuccess;
+    if (a.partial == nullptr || a.combine == nullptr || (a.head_dim != 128 && a.head_dim != 64)) return hipErrorInvalidValue;
+    const dim3 grid(a.n_combine, (a.tile_rows + 31) / 32);
+    if (a.head_dim == 128) hipLaunchKernelGGL(combine_tiles_kernel<128>, grid, dim3(256), 0, stream, a);
+    else hipLaunchKernelGGL(combine_tiles_kernel<64>, grid, dim3(256), 0, stream, a);
+    return hipGetLastError();
 }
 
 hipError_t launch_attn_combine(const AttnArgs &a, hipStream_t stream) {

@@ -460,20 +460,19 @@ __global__ __launch_bounds__(64 * NW, OCC) void attn_prerot_kernel(AttnArgs a) {
     const float l_all = row_sum[0] + __shfl_xor(row_sum[0], 32);
     if (item.part >= 0) {
         // keys split over several workgroups: leave the unnormalised sums, the reference maximum and the
-        // denominator of this share in the scratch buffer; combine_kernel merges the shares
+        // denominator of this share in the scratch buffer; combine_tiles_kernel merges the shares
         if (row_valid) {
             const int rt = r - item.row0;                       // row inside the tile
             float *base = a.partial + (int64_t)item.part * a.tile_rows * (D + 2);
-            float *prow = base + (int64_t)rt * D;
 #pragma unroll
             for (int db = 0; db < DBLKS; ++db)
 #pragma unroll
                 for (int i4 = 0; i4 < 4; ++i4) {
-                    const int d = 32 * db + i4 * 8 + half * 4;
-                    *reinterpret_cast<float4 *>(prow + d) = make_float4(O[db][4 * i4], O[db][4 * i4 + 1], O[db][4 * i4 + 2], O[db][4 * i4 + 3]);
+                    const int d4 = 8 * db + 2 * i4 + half;
+                    reinterpret_cast<float4 *>(base)[d4 * a.tile_rows + rt] = make_float4(O[db][4 * i4], O[db][4 * i4 + 1], O[db][4 * i4 + 2], O[db][4 * i4 + 3]);
                 }
             if (half == 0) {
-                base[(int64_t)a.tile_rows * D + rt] = ref / cscale;      // combine_kernel takes it in score units
+                base[(int64_t)a.tile_rows * D + rt] = ref / cscale;      // in score units
                 base[(int64_t)a.tile_rows * (D + 1) + rt] = l_all;
             }
         }
@@ -547,7 +546,7 @@ hipError_t launch_attn_prerot(const AttnArgs &a, hipStream_t stream) {
     else return hipErrorInvalidValue;
     const hipError_t e = hipGetLastError();
     if (e != hipSuccess || a.n_combine <= 0) return e;
-    return launch_attn_combine(a, stream);
+    return launch_combine_tiles(a, stream);
 }
 
 }  // namespace ca

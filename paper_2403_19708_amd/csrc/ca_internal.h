@@ -134,8 +134,8 @@ struct AttnArgs {
     const int32_t *q_seq;    // [total_q] its conversation
     const WorkItem *items;
     const CombineItem *combine;   // row tiles to merge after the walk (n_combine of them)
-    float *partial;          // shares of split row tiles: per part [tile_rows][head_dim] sums, [tile_rows] maxima,
-                             // [tile_rows] denominators (fp32)
+    float *partial;          // shares of split row tiles: per part the sums ([head_dim/4][tile_rows][4] from the tile kernels,
+                             // [tile_rows][head_dim] from the others), [tile_rows] maxima, [tile_rows] denominators (fp32)
     const float2 *rope;      // [max_positions][head_dim/2] (cos, sin)
     // keys rotated once per batch and layer instead of in every row tile (launch_attn_prerot, launch_attn_pp):
     uint16_t *k_rot;             // scratch copy of the keys, dense pages [n_dense_pages][n_kv_heads][16][head_dim]
@@ -171,7 +171,8 @@ hipError_t launch_attn_prerot(const AttnArgs &args, hipStream_t stream);
 // head_dim 128, 256-row tiles, keys rotated and values transposed once per layer into scratch copies; inside every
 // wavefront the matrix instructions of one key tile are pipelined with the softmax of the previous one
 hipError_t launch_attn_pp(const AttnArgs &args, hipStream_t stream);
-// merges the shares of split row tiles (args.combine) into args.out; used by every kernel that writes shares
+// merges the shares of split row tiles (args.combine) into args.out: those of the tile kernels, and those laid out row by row
+hipError_t launch_combine_tiles(const AttnArgs &args, hipStream_t stream);
 hipError_t launch_attn_combine(const AttnArgs &args, hipStream_t stream);
 // decode steps: every item has at most kAttnDecodeMaxRows stacked rows starting at row 0; streams K/V through
 // registers instead of matrix-core tiles

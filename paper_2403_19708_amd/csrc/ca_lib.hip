@@ -1379,7 +1379,7 @@ ca_status ca_rope_rebase(ca_ctx *ctx, const ca_batch *b, void *stream_) {
 
         // Few, long items leave compute units idle at the end (or, for a small batch, from the start): split
         // the keys of the longest items over several workgroups until a longest-first schedule of the die's
-        // items over its compute units is within 12 % of the ideal.  Shares are merged by combine_kernel.
+        // items over its compute units is within 12 % of the ideal.  Shares are merged by combine_tiles_kernel.
         // Up to four rounds per die; a round halves every item longer than 0.7 of the ideal load of a
         // compute unit (so 16 shares per row tile at most).
         size_t n_live = 0;
