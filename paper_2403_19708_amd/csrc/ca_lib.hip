@@ -25,8 +25,10 @@ using namespace ca;
 // runs on, held until the process ends), so that entry point needs no allocation anywhere.  The name below is a
 // host-side stand-in, not a device address: host code uses the per-device pointer that hipGetSymbolAddress
 // returned (static_scratch_ptr), never the array itself.
-constexpr size_t kStaticScratchBytes = (size_t)32 << 20;
-static __device__ __align__(256) uint8_t scratch[kStaticScratchBytes];
+// Plans cut for their last round only have at most one share to a workgroup place, 256 of 256 rows x 130 floats (32.5 MiB), and
+// always fit; others are held to 32 MiB.
+constexpr size_t kStaticScratchBytes = (size_t)32 << 20, kStaticArrayBytes = (size_t)34 << 20;
+static __device__ __align__(256) uint8_t scratch[kStaticArrayBytes];
 constexpr int kMaxDevices = 64;
 static void *static_scratch_ptr[kMaxDevices] = {nullptr};   // [device ordinal], filled by ca_create with that device current
 
@@ -109,6 +111,7 @@ struct ca_ctx {
     // two attention entry points, which may run at once (zero between calls, and set to zero with every plan)
     int32_t n_wgs = 0, wg_wavefronts = 4;
     bool rows_runs = false;
+    bool last_round_cut = false;   // tile kernels: only items of the last round of workgroups are cut
     size_t off_wg_first = 0, off_rows_items = 0;
     uint32_t *arrived = nullptr, *static_arrived = nullptr;
     int32_t n_split_parts = 0;   // shares of split row tiles of the plan (slots of the partial-result buffer in use)
@@ -1154,21 +1157,26 @@ static bool half_tiles_pay(const ca_ctx *ctx) {
     return rounds >= 1 && cost128 < (1 - cost.margin / rounds) * cost256;
 }
 
+// Cutting the last round only is taken where it is estimated to take at most this share of the better one of the other two plans.
+// Over 1500 drawn batches of 1 to 64 conversations it changes 26 plans, whose attention takes 0.76 to 0.99 of the time, 0.89 on average
+// (one layer of 4 conversations of 1667-1800 tokens with 177-497 new ones, 40 heads: 134 -> 108 us; 8 of 2048 with 64-512, 32 heads,
+// 4 layers with their loads: 893 -> 868).
+constexpr double kLastRoundGain = 0.97;
+
 // A row tile or a share of one, as the planner of the tile kernels handles it
 struct Item { WorkItem w; double cost; int32_t parent; };
 
-// Whether the row tiles of a plan are better left whole than cut into the shares found for them (`bins` workgroups run on a
-// die at a time).  Shares fill compute units that whole items would leave idle, but each is launched, fetches its queries and
-// fills its load pipeline, is written and read back (its valid rows), and the merge is a launch.  Both plans are laid out on
-// the dies in time: us per 64-key tile on a compute unit that other workgroups share and on one of a workgroup's own, and
-// per item, by kernel and shape; 3 us and 1.75 TB/s of shares for the merge, 7 us a launch in either case; `shares` is a factor
-// on the time with shares, where the decisions came out best.  Fitted to 1236 random plans (1 to 64 conversations, no history to
-// 31000 tokens, 2 to 2048 new, seven shapes of heads) timed whole and cut: whole is taken 391 times, for 0.51 to 1.08 of the
-// time with shares, 0.83 on average, and the plan taken is the slower one by more than 3 % in 19.  (One layer of 8 conversations
-// of 2048 tokens with 64-512 new ones, 32 heads: 160 us in 384 shares, 150 whole; of 13 of 2134-2392 with 9-45, 16/8 heads of
-// 64: 38 us in 832 shares, 72 whole.)
-static bool whole_items_pay(const ca_ctx *ctx, const std::vector<std::vector<Item>> &cut, const std::vector<std::vector<Item>> &whole,
-                            const std::vector<int32_t> &parts_of, int bins) {
+// Estimated us of a plan of the tile kernels (`bins` workgroups run on a die at a time), to decide whether its row tiles are left
+// whole, cut into shares, or cut only where the last round of workgroups would leave compute units idle.  Shares fill those
+// units, but each is launched, fetches its queries and fills its load pipeline, is written and read back (its valid rows),
+// and the merge is a launch.  The items are laid out on the dies in time: us per 64-key tile on a compute unit that other
+// workgroups share and on one of a workgroup's own, and per item, by kernel and shape; 3 us and 1.75 TB/s of shares for the
+// merge, 7 us a launch in either case; `shares` is a factor on the time with shares, where the decisions came out best.  Fitted to
+// 1236 random plans (1 to 64 conversations, no history to 31000 tokens, 2 to 2048 new, seven shapes of heads) timed whole and
+// cut: whole is taken 391 times, for 0.51 to 1.08 of the time with shares, 0.83 on average, and the plan taken is the slower one by
+// more than 3 % in 19.  (One layer of 13 conversations of 2134-2392 tokens with 9-45 new ones, 16/8 heads of 64: 38 us in
+// 832 shares, 72 whole.)
+static double plan_time(const ca_ctx *ctx, const std::vector<std::vector<Item>> &plan, const std::vector<int32_t> &parts_of, int bins) {
     struct Times { double tile, tile_alone, item, shares; };
     const bool d64 = ctx->cfg.head_dim == 64, small = ctx->tile_rows == 128;
     const Times t = ctx->prerotate ? (!d64 ? Times{1.65, 1.45, 9.2, 1.05} : small ? Times{1.25, 1.10, 5.5, 1.10} : Times{1.05, 0.95, 4.1, 0.95})
@@ -1176,26 +1184,20 @@ static bool whole_items_pay(const ca_ctx *ctx, const std::vector<std::vector<Ite
                                    : (small ? Times{2.60, 1.95, 3.0, 1.00} : Times{2.10, 1.85, 5.6, 1.00});
     const size_t die_cus = std::max(1, ctx->n_cus / kXcds);
     std::vector<double> heap;
-    const auto span = [&](const std::vector<std::vector<Item>> &dies) {
-        double longest = 0;
-        for (const auto &items : dies) {
-            const double tile = items.size() <= die_cus ? t.tile_alone : t.tile;
-            heap.assign(bins, 0.0);
-            for (const Item &it : items) {
-                const double part = !small && it.w.n_rows <= 128 ? 0.78 : 1.0;      // (four of eight wavefronts have rows)
-                std::pop_heap(heap.begin(), heap.end(), std::greater<double>());
-                heap.back() += t.item + part * tile * ((it.w.key_end + 63) / 64 - it.w.key_begin / 64);
-                longest = std::max(longest, heap.back());
-                std::push_heap(heap.begin(), heap.end(), std::greater<double>());
-            }
-        }
-        return longest + 7.0;
-    };
-    double share_bytes = 0;
-    for (const auto &items : cut)
-        for (const Item &it : items)
+    double longest = 0, share_bytes = 0;
+    for (const auto &items : plan) {
+        const double tile = items.size() <= die_cus ? t.tile_alone : t.tile;
+        heap.assign(bins, 0.0);
+        for (const Item &it : items) {
+            const double part = !small && it.w.n_rows <= 128 ? 0.78 : 1.0;      // (four of eight wavefronts have rows)
+            std::pop_heap(heap.begin(), heap.end(), std::greater<double>());
+            heap.back() += t.item + part * tile * ((it.w.key_end + 63) / 64 - it.w.key_begin / 64);
+            longest = std::max(longest, heap.back());
+            std::push_heap(heap.begin(), heap.end(), std::greater<double>());
             if (parts_of[it.parent] > 1) share_bytes += (double)it.w.n_rows * (ctx->cfg.head_dim + 2) * sizeof(float);
-    return span(whole) < t.shares * (span(cut) + 3.0 + share_bytes / 1.75e6);
+        }
+    }
+    return share_bytes > 0 ? t.shares * (longest + 7.0 + 3.0 + share_bytes / 1.75e6) : longest + 7.0;
 }
 
 ca_status ca_rope_rebase(ca_ctx *ctx, const ca_batch *b, void *stream_) {
@@ -1273,6 +1275,7 @@ ca_status ca_rope_rebase(ca_ctx *ctx, const ca_batch *b, void *stream_) {
 
     // ---- attention work list ------------------------------------------------------------------
     ctx->n_wgs = 0;
+    ctx->last_round_cut = false;
     ctx->max_unit_rows = 0;
     for (int i = 0; i < B; ++i) ctx->max_unit_rows = std::max(ctx->max_unit_rows, b->new_len[i] * (c.n_q_heads / c.n_kv_heads));
     if (rows_plan(ctx)) {
@@ -1497,7 +1500,43 @@ ca_status ca_rope_rebase(ca_ctx *ctx, const ca_batch *b, void *stream_) {
             if (n_split_parts > 0 && !decode_plan) {
                 for (int d = 0; d < kXcds; ++d)
                     if (whole_of[d].empty()) whole_of[d] = per_die[d];          // not cut, or cut in vain
-                if (whole_items_pay(ctx, per_die, whole_of, parts_of, bins)) {
+                // Whole rounds of workgroups stay whole and the items left over for the last round, the shortest ones of the die,
+                // are cut so that they fill it.
+                std::vector<std::vector<Item>> last_of(kXcds);
+                std::vector<int32_t> last_parts(n_parents, 1), one(n_parents, 1);
+                int32_t n_last_parts = 0;
+                // (never more than the static array holds: ca_cached_prefill_attn_static takes the plan whole, and so it takes it cut)
+                const int32_t room = (int32_t)std::min<size_t>(kAttnMaxParts, kStaticArrayBytes / ((size_t)tile * (c.head_dim + 2) * sizeof(float)));
+                for (int d = 0; d < kXcds; ++d) {
+                    const auto &whole = whole_of[d];
+                    auto &v = last_of[d];
+                    const int n = (int)whole.size(), rest = n > bins ? n % bins : 0;
+                    v.assign(whole.begin(), whole.end() - rest);
+                    for (int k = n - rest; k < n; ++k) {
+                        const Item &it = whole[k];
+                        const int len = it.w.key_end - it.w.key_begin, tiles64 = len / 64;
+                        int shares = std::min({bins / rest, kAttnMaxPartsPerTile, len / kAttnMinPartKeys});
+                        if (shares < 2 || n_last_parts + shares > room) shares = 1;
+                        for (int i = 0; i < shares; ++i) {
+                            Item share = it;
+                            share.w.key_begin = it.w.key_begin + tiles64 * i / shares * 64;
+                            if (i + 1 < shares) share.w.key_end = it.w.key_begin + tiles64 * (i + 1) / shares * 64;
+                            share.cost = item_cost(it.w.n_rows, share.w.key_end - share.w.key_begin);
+                            v.push_back(share);
+                        }
+                        last_parts[it.parent] = shares;
+                        if (shares > 1) n_last_parts += shares;
+                    }
+                    std::stable_sort(v.begin(), v.end(), by_cost);
+                }
+                const double us_whole = plan_time(ctx, whole_of, one, bins), us_cut = plan_time(ctx, per_die, parts_of, bins);
+                const double us_last = n_last_parts > 0 ? plan_time(ctx, last_of, last_parts, bins) : INFINITY;
+                if (us_last < kLastRoundGain * std::min(us_whole, us_cut)) {
+                    for (int d = 0; d < kXcds; ++d) per_die[d].swap(last_of[d]);
+                    parts_of = last_parts;
+                    n_split_parts = n_last_parts;
+                    ctx->last_round_cut = true;
+                } else if (us_whole < us_cut) {
                     for (int d = 0; d < kXcds; ++d) per_die[d].swap(whole_of[d]);
                     parts_of.assign(n_parents, 1);
                     n_split_parts = 0;
@@ -2217,7 +2256,7 @@ ca_status ca_cached_prefill_attn_static(ca_ctx *ctx, int32_t layer, const void *
         if (!ctx->static_partial)
             return fail(ctx, CA_ERR_UNSUPPORTED, "ca_cached_prefill_attn_static: no static scratch on device %d", ctx->cfg.device);
         const size_t need = (size_t)ctx->n_split_parts * (size_t)ctx->tile_rows * (size_t)(ctx->cfg.head_dim + 2) * sizeof(float);
-        if (need > kStaticScratchBytes)
+        if (need > (ctx->last_round_cut ? kStaticArrayBytes : kStaticScratchBytes))
             return fail(ctx, CA_ERR_OUT_OF_RANGE, "ca_cached_prefill_attn_static: the plan's %d shares of split row tiles need %zu bytes of "
                         "partial results, the static scratch holds %zu", ctx->n_split_parts, need, kStaticScratchBytes);
     }

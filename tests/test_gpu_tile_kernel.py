@@ -7,7 +7,7 @@ import pytest
 import torch
 
 import oracle
-from harness import Case, GpuRun
+from harness import Case, GpuRun, torch_to_bits
 from test_gpu_parity import check_contract, check_tight
 from synth import bf16_bits_to_f64, f32_to_bf16_bits
 
@@ -179,3 +179,36 @@ def test_tile_rows_of_a_batch(shape, new):
     for c in (0, len(new) - 1):
         check_contract(got[c], case.oracle_out(0, c), c)
         check_tight(got[c], case.oracle_out(0, c), int(case.n_keep[c]), c)
+
+
+@pytest.mark.parametrize("D, heads, batch, new", [(128, 32, 9, 140), (64, 40, 8, 200), (128, 48, 12, 60)], ids=["rows256", "heads64", "rows128"])
+def test_only_the_last_round_is_cut(D, heads, batch, new):
+    """A few more row tiles than workgroups fit the compute units: whole tiles first, the ones left over in shares.  Sampled heads
+    against the oracle; the entry point that allocates nothing takes the plan and gives the same bits."""
+    hist = [1500 + 37 * c for c in range(batch)]
+    case = Case(hist, [new - c for c in range(batch)], [0] * batch, heads, heads, D, seed=90 + D, window=4096)
+    run = GpuRun(case, tier="device")
+    try:
+        run.rebase()
+        run.load(0)
+        run.append(0)
+        items = run.ctx.rebase_read(6).reshape(-1, 8)
+        items = items[items[:, 0] >= 0]
+        shares = items[items[:, 6] >= 0]
+        assert 0 < len(shares) < len(items) and len(items) - len(shares) >= 256
+        assert (shares[:, 4] % 64 == 0).all() and (shares[:, 5] - shares[:, 4] >= 256).all()
+        bits = []
+        for call in (run.ctx.cached_prefill_attn, run.ctx.cached_prefill_attn_static):
+            run.out[0].view(torch.int16).fill_(0x7FC0)
+            call(0, run.q[0], run.k_pool[0], run.v_pool[0], run.out[0], 1.0 / np.sqrt(D))
+            run.finish()
+            bits.append(torch_to_bits(run.out[0]).copy())
+        assert np.array_equal(bits[0], bits[1]) and not np.any(bits[0] == 0x7FC0)
+        cut = {(int(s[0]), int(s[1])) for s in shares}
+        some = sorted(cut)[:: max(1, len(cut) // 4)] + [(0, 0), (batch - 1, heads - 1)]
+        for c, h in some:
+            got, want = run.out_f64(0, c)[:, [h]], case.oracle_out(0, c, heads=[h])
+            check_contract(got, want, c)
+            check_tight(got, want, int(case.n_keep[c]), c)
+    finally:
+        run.close()
