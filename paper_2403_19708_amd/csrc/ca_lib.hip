@@ -1157,11 +1157,11 @@ static bool half_tiles_pay(const ca_ctx *ctx) {
     return rounds >= 1 && cost128 < (1 - cost.margin / rounds) * cost256;
 }
 
-// Cutting the last round only is taken where it is estimated to take at most this share of the better one of the other two plans.
-// Over 1500 drawn batches of 1 to 64 conversations it changes 26 plans, whose attention takes 0.76 to 0.99 of the time, 0.89 on average
-// (one layer of 4 conversations of 1667-1800 tokens with 177-497 new ones, 40 heads: 134 -> 108 us; 8 of 2048 with 64-512, 32 heads,
-// 4 layers with their loads: 893 -> 868).
-constexpr double kLastRoundGain = 0.97;
+// Cutting the last round only is taken where it is estimated to take at most this share of the better one of the other two plans:
+// the estimates are right within a tenth or so, and shares need scratch that whole tiles do not.  Of 3000 drawn batches of 1 to 64
+// conversations it changes the plans of 36, whose attention takes 0.77 to 0.99 of the time, 0.87 on average (one layer of 4
+// conversations of 1667-1800 tokens with 177-497 new ones, 40 heads: 133 -> 106 us).  With 0.97 it would be half as many again.
+constexpr double kLastRoundGain = 0.89;
 
 // A row tile or a share of one, as the planner of the tile kernels handles it
 struct Item { WorkItem w; double cost; int32_t parent; };
