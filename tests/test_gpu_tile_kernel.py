@@ -212,3 +212,29 @@ def test_only_the_last_round_is_cut(D, heads, batch, new):
             check_tight(got, want, int(case.n_keep[c]), c)
     finally:
         run.close()
+
+
+@pytest.mark.parametrize("batch", [4, 12], ids=["three", "four"])
+@pytest.mark.parametrize("style", [0, 1])
+def test_heads_of_64_on_either_side_of_four_workgroups(batch, style):
+    """Fewer than 1024 row tiles of 128 rows, and more: plans of three and of four workgroups to a compute unit.  A context that moves the smaller
+    window of page ids, and sampled heads against the oracle."""
+    case = Case([0] * (batch - 1) + [17000], [512] * (batch - 1) + [40], [0] * batch, 32, 4, 64, seed=95 + style, style=style,
+                window=32768)
+    run = GpuRun(case, tier="device", attn_prerotate=2, attn_tile_rows=128, attn_split=1)
+    try:
+        run.rebase()
+        run.load(0)
+        run.append(0)
+        items = run.ctx.rebase_read(6).reshape(-1, 8)
+        assert (len(items) > 1024) == (batch == 12)
+        run.out[0].view(torch.int16).fill_(0x7FC0)
+        run.attn(0)
+        run.finish()
+        assert not np.any(torch_to_bits(run.out[0]) == 0x7FC0)
+        for c, heads in [(0, [0, 31]), (batch - 1, [5, 16])]:
+            got, want = run.out_f64(0, c)[:, heads], case.oracle_out(0, c, heads=heads)
+            check_contract(got, want, c)
+            check_tight(got, want, int(case.n_keep[c]), c)
+    finally:
+        run.close()
