@@ -131,6 +131,14 @@ __device__ inline void rotate_dword(uint32_t &pa, uint32_t &pb, const float2 (&c
     }
 }
 
+// What lanes of a wavefront wrote to LDS in front of this, its other lanes read behind it.  The hardware keeps the LDS accesses of a
+// wavefront in order; the compiler sees the addresses of one lane only and has to be told (no instruction comes of it).
+__device__ inline void lds_handover() {
+    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+    __builtin_amdgcn_wave_barrier();
+    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+}
+
 // The 32 stacked query rows row_first .. of a wavefront, rotated, scaled by `f` and rounded, as B operand of S^T = K Q^T (lane ->
 // row lane % 32, k-step ks -> piece 2 ks + lane / 32).  A lane that fetches its own row touches 32 cache lines in every
 // instruction, each line in four instructions, for the queries and again for the rotary table, and the first level cache does not hold
@@ -182,6 +190,7 @@ struct QueryRows {
                 *reinterpret_cast<uint2 *>(at + 8 * c) = make_uint2(x[i], y[i]);
             }
         }
+        lds_handover();
 #pragma unroll
         for (int ks = 0; ks < D / 16; ++ks)
             Qf[ks] = *reinterpret_cast<const bf16x8 *>(stage + lane % 32 * kStride + 16 * (2 * ks + lane / 32));
@@ -202,6 +211,7 @@ __device__ inline void store_rows(const AttnArgs &a, int q0, int g, int G, int r
             const uint2 o = make_uint2(pack_bf16(O[db][4 * i] * inv, O[db][4 * i + 1] * inv), pack_bf16(O[db][4 * i + 2] * inv, O[db][4 * i + 3] * inv));
             *reinterpret_cast<uint2 *>(stage + lane % 32 * kStride + 2 * (32 * db + 8 * i + 4 * (lane / 32))) = o;
         }
+    lds_handover();
     const int j0 = row_first / G, r0 = j0 * G;                   // (wave-uniform)
     const float per_g = 1.0f / (float)G;
 #pragma unroll

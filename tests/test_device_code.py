@@ -1,0 +1,47 @@
+"""What the compiler is told about LDS that the lanes of a wavefront hand to each other: read off the intermediate code of the shared device
+helpers, compiled for the GPU here (no GPU needed)."""
+import os
+import re
+import subprocess
+
+import pytest
+
+from paper_2403_19708_amd import build
+
+CSRC = os.path.join(build.HERE, "csrc")
+KERNELS = """
+#include "ca_device.h"
+using namespace ca;
+__global__ void kernel(AttnArgs a, bf16x8 *q, const f32x16 *o) {
+    __shared__ __attribute__((aligned(16))) uint8_t stage[QueryRows<%(D)d, %(style)d>::kQueryBytes];
+#if %(outputs)d
+    f32x16 O[%(D)d / 32];
+    for (int i = 0; i < %(D)d / 32; ++i) O[i] = o[threadIdx.x * 4 + i];
+    store_rows<%(D)d>(a, 0, 0, 3, 0, 31, stage, O, 0.5f);
+#else
+    QueryRows<%(D)d, %(style)d> rows;
+    bf16x8 Q[%(D)d / 16];
+    rows.fetch(a, 0, 0, 3, 0, 0, 31);
+    rows.finish(stage, 0.5f, Q);
+    for (int i = 0; i < %(D)d / 16; ++i) q[threadIdx.x * 8 + i] = Q[i];
+#endif
+}
+"""
+
+
+@pytest.mark.parametrize("D, style, outputs", [(128, 0, 0), (128, 1, 0), (64, 0, 0), (64, 1, 0), (128, 0, 1), (64, 0, 1)])
+def test_rows_handed_on_through_lds_are_read_behind_the_writes(tmp_path, D, style, outputs):
+    """Lanes read what other lanes wrote: without a barrier or fences in between the compiler may move the reads to the front, whatever
+    the hardware's order is."""
+    source = tmp_path / "kernel.hip"
+    source.write_text(KERNELS % dict(D=D, style=style, outputs=outputs))
+    cmd = [build.hipcc()] + [f for f in build.FLAGS if f != "-shared" and not f.startswith("-Wl,")]
+    done = subprocess.run(cmd + ["-I" + CSRC, "--cuda-device-only", "-S", "-emit-llvm", str(source), "-o", "-"], capture_output=True, text=True)
+    assert done.returncode == 0, done.stderr
+    body = re.search(r"define [^\n]*amdgpu_kernel void @[^\n]*kernel.*?\n}", done.stdout, re.S).group(0)
+    kinds = [("store", r"store .*ptr addrspace\(3\)"), ("load", r"load .*ptr addrspace\(3\)"), ("release", r'fence syncscope\("wavefront"\) release'),
+             ("barrier", r"call void @llvm.amdgcn.wave.barrier"), ("acquire", r'fence syncscope\("wavefront"\) acquire')]
+    seen = [kind for line in body.splitlines() for kind, text in kinds if re.search(text, line)]
+    stores, loads = seen.count("store"), seen.count("load")
+    assert stores >= 4 and loads >= 4
+    assert seen == ["store"] * stores + ["release", "barrier", "acquire"] + ["load"] * loads
