@@ -172,6 +172,7 @@ __global__ __launch_bounds__(64 * NWV, 2) void attn_rows_kernel(AttnArgs a) {
         for (int stage = 0; pg <= last_page; pg += NWV, stage = (stage + 1) % NS) {
             // the pages behind this one may stay in flight
             if (pg + (NS - 1) * NWV <= last_page) { CA_WAIT_VMCNT((NS - 1) * LOADS); } else { CA_WAIT_VMCNT(0); }
+            asm volatile("" : : : "memory");       // the reads stay behind the wait (no barrier says so here)
             const uint8_t *st = ring_p + stage * STAGE;
             uint4 k[KK];
             s16x4 v[DB];
