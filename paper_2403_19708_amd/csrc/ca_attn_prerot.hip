@@ -529,10 +529,7 @@ void launch_all(const AttnArgs &a, hipStream_t stream) {
     else if (heads == 2) hipLaunchKernelGGL((rotate_keys_kernel<D, STYLE, 2>), rgrid, dim3(D), 0, stream, a);
     else hipLaunchKernelGGL((rotate_keys_kernel<D, STYLE, 1>), rgrid, dim3(D), 0, stream, a);
     if (a.tile_rows == 256) hipLaunchKernelGGL((attn_prerot_kernel<D, STYLE, 8, 64, 2>), grid, dim3(512), 0, stream, a);
-    // Heads of 64: four workgroups to a compute unit with 128 registers where there are enough for that and more, else three, which spread
-    // a single round better (24 random plans, us of the attention with three and four: 18688 tiles 408, 378; 4604 102, 96; 2236 41, 39;
-    // 1312 39, 38; 820 22.3, 22.0; 816 24.4, 25.5; 340 20.8, 21.6).  Heads of 128 have no registers for more than two.
-    else if (D == 64 && a.n_items > 4 * 256) hipLaunchKernelGGL((attn_prerot_kernel<D, STYLE, 4, 32, D == 64 ? 4 : 2>), grid, dim3(256), 0, stream, a);
+    else if (D == 64 && a.wgs_per_cu == 4) hipLaunchKernelGGL((attn_prerot_kernel<D, STYLE, 4, 32, D == 64 ? 4 : 2>), grid, dim3(256), 0, stream, a);
     else hipLaunchKernelGGL((attn_prerot_kernel<D, STYLE, 4, 32, D == 64 ? 3 : 2>), grid, dim3(256), 0, stream, a);
 }
 

@@ -158,6 +158,7 @@ struct AttnArgs {
     int32_t n_q_heads, n_kv_heads, head_dim;
     int32_t rope_style;
     int32_t tile_rows;       // stacked query rows per workgroup: 128 (4 wavefronts), 256 (8), launch_attn_rows 16 or 32
+    int32_t wgs_per_cu;      // tile kernels: workgroups of the plan's that run on a compute unit at a time
     float softmax_scale;
 };
 

@@ -112,6 +112,7 @@ struct ca_ctx {
     int32_t n_wgs = 0, wg_wavefronts = 4;
     bool rows_runs = false;
     bool last_round_cut = false;   // tile kernels: only items of the last round of workgroups are cut
+    int32_t wgs_per_cu = 0;        // tile kernels: workgroups that run on a compute unit at a time
     size_t off_wg_first = 0, off_rows_items = 0;
     uint32_t *arrived = nullptr, *static_arrived = nullptr;
     int32_t n_split_parts = 0;   // shares of split row tiles of the plan (slots of the partial-result buffer in use)
@@ -1179,7 +1180,7 @@ struct Item { WorkItem w; double cost; int32_t parent; };
 static double plan_time(const ca_ctx *ctx, const std::vector<std::vector<Item>> &plan, const std::vector<int32_t> &parts_of, int bins) {
     struct Times { double tile, tile_alone, item, shares; };
     const bool d64 = ctx->cfg.head_dim == 64, small = ctx->tile_rows == 128;
-    const Times t = ctx->prerotate ? (!d64 ? Times{1.65, 1.45, 9.2, 1.05} : small ? Times{1.25, 1.10, 5.5, 1.10} : Times{1.05, 0.95, 4.1, 0.95})
+    const Times t = ctx->prerotate ? (!d64 ? Times{1.65, 1.45, 9.2, 1.05} : small ? (ctx->wgs_per_cu == 4 ? Times{1.55, 1.10, 6.8, 1.10} : Times{1.25, 1.10, 5.5, 1.10}) : Times{1.05, 0.95, 4.1, 0.95})
                     : d64          ? (small ? Times{1.85, 1.65, 0.5, 1.05} : Times{1.45, 1.30, 2.5, 1.00})
                                    : (small ? Times{2.60, 1.95, 3.0, 1.00} : Times{2.10, 1.85, 5.6, 1.00});
     const size_t die_cus = std::max(1, ctx->n_cus / kXcds);
@@ -1387,11 +1388,22 @@ ca_status ca_rope_rebase(ca_ctx *ctx, const ca_batch *b, void *stream_) {
         // compute unit (so 16 shares per row tile at most).
         size_t n_live = 0;
         for (auto &v : per_die) n_live += v.size();
+        // Workgroups that run on a compute unit at a time: one of eight wavefronts, two of four, and with heads of 64 whose keys are
+        // rotated beforehand, three of four, or four with 128 registers, where the fullest die has more row tiles than that many places:
+        // three spread a single round better (24 random plans left whole, us of the attention with three and four: 18688 tiles 408, 378;
+        // 4604 102, 96; 2236 41, 39; 1312 39, 38; 820 22.3, 22.0; 816 24.4, 25.5; 340 20.8, 21.6).  Decided before anything is cut, so
+        // that the plan is cut for what is launched: 63 random plans of 700 to 1300 tiles that were laid out for three and launched with four
+        // where shares made the items more take 0.90 to 1.035 of that time so, 0.97 on average (1144 tiles whole 273, last
+        // round cut for four 246; 792 cut for three, launched with four 193, with three 187; 944 cut for three 187, 194).
+        size_t fullest = 0;
+        for (auto &v : per_die) fullest = std::max(fullest, v.size());
+        const size_t die_cus = std::max(1, ctx->n_cus / kXcds);
+        ctx->wgs_per_cu = tile != 128 ? 1 : c.head_dim == 128 || !ctx->prerotate ? 2 : fullest > 4 * die_cus ? 4 : 3;
         std::vector<int32_t> parts_of(n_parents, 1);
         int32_t n_split_parts = 0;          // shares that need a slot in the partial-result buffer
         const auto by_cost = [](const Item &x, const Item &y) { return x.cost > y.cost; };
         if (ctx->partial && direct_kernel && n_live < (size_t)(decode_plan ? 1 : 6) * ctx->n_cus) {
-            const int bins = std::max(1, ctx->n_cus / kXcds) * (tile != 128 ? 1 : c.head_dim == 64 && ctx->prerotate ? 3 : 2);
+            const int bins = (int)die_cus * ctx->wgs_per_cu;
             // tiles of 128 rows where there would be 256-row ones: no more shares than the static scratch array holds, so that
             // ca_cached_prefill_attn_static takes the plans it would take with 256-row tiles
             const bool smaller = tile == 128 && most > 128 && c.attn_tile_rows == 0;
@@ -2216,6 +2228,7 @@ static ca_status attn_impl(ca_ctx *ctx, int32_t layer, const void *q, const void
     a.head_dim = c.head_dim;
     a.rope_style = c.rope_style;
     a.tile_rows = ctx->tile_rows;
+    a.wgs_per_cu = ctx->wgs_per_cu;
     a.softmax_scale = softmax_scale;
     int iv = -1;
     if (timed) CA_HIP(ctx, prof_begin(ctx, kProfAttn, stream, &iv));

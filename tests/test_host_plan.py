@@ -98,3 +98,28 @@ def test_the_static_entry_point_takes_plans_with_smaller_tiles(m, batch, heads, 
     check_cover(items, hist, new, heads)
     assert items[:, 3].max() <= 128
     t.attn(static=True)
+
+
+# Heads of 64, keys rotated beforehand: the launch has the workgroups to a compute unit that the plan was laid out for, three, or four
+# where there are more row tiles than that many places.
+@pytest.mark.parametrize("batch, heads, hist_lo, hist_hi, new_lo, new_hi, per_cu, last_round",
+                         [(2, (64, 4, 64), 4366, 5675, 578, 1000, 3, True),        # 792 tiles, 1152 items with the shares
+                          (12, (32, 4, 64), 4167, 5417, 243, 291, 3, True),        # 824, 1496
+                          (8, (64, 4, 64), 4113, 5346, 156, 365, 4, True),         # 1056, 1536
+                          (12, (32, 4, 64), 0, 0, 200, 250, 3, False),
+                          (16, (64, 8, 64), 0, 0, 105, 183, 4, False)])
+@in_model
+def test_the_launch_has_the_workgroups_that_were_planned(m, batch, heads, hist_lo, hist_hi, new_lo, new_hi, per_cu, last_round):
+    hist, new = (np.linspace(lo, hi, batch).round().astype(np.int32) for lo, hi in ((hist_lo, hist_hi), (new_lo, new_hi)))
+    t = Turn(m, hist, new, heads=heads, require_load=0)
+    t.rebase()
+    items = t.ctx.rebase_read(6).reshape(-1, 8)
+    live, die = items[:, 0] >= 0, np.arange(len(items)) % 8
+    check_cover(items[live], hist, new, heads)
+    cut = live & (items[:, 6] >= 0)
+    tiles = sum((int(n) * (heads[0] // heads[1]) + 127) // 128 for n in new) * heads[1]
+    assert (tiles > 1024) == (per_cu == 4)
+    if last_round:                          # whole rounds of workgroups on every die
+        whole = [int((live & ~cut & (die == d)).sum()) for d in range(8)]
+        assert cut.any() and all(w > 0 and w % (32 * per_cu) == 0 for w in whole)
+    assert m.named(m.queued(t.attn), "attn_prerot_kernelILi64ELi0ELi4ELi32ELi%dEE" % per_cu)
