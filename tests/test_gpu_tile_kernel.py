@@ -238,3 +238,42 @@ def test_heads_of_64_on_either_side_of_four_workgroups(batch, style):
             check_tight(got, want, int(case.n_keep[c]), c)
     finally:
         run.close()
+
+
+@pytest.mark.parametrize("heads, batch, hist, new, kw, n_shares, whole",
+                         [((32, 32, 128), 5, (1053, 1053), (291, 320), {}, 256, 256),
+                          ((64, 8, 128), 4, (2426, 2668), (262, 288), {}, 256, 256),
+                          ((64, 8, 128), 4, (2426, 2668), (262, 288), {"attn_schedule": 1}, 256, 256),
+                          ((64, 4, 64), 2, (4366, 5675), (578, 1000), {}, 384, 768),
+                          ((64, 4, 64), 8, (4113, 5346), (156, 365), {}, 512, 1024)],
+                         ids=["rotary", "rotated", "pipelined", "three", "four"])
+def test_last_round_shares_of_every_tile_kernel(heads, batch, hist, new, kw, n_shares, whole):
+    """As above, in the kernels over keys rotated beforehand and with grouped heads; 256 shares of 256 rows are the most there can be, and
+    more than 32 MiB; heads of 64 with three and with four workgroups to a compute unit."""
+    Hq, Hkv, D = heads
+    case = Case(*(list(np.linspace(*lens, batch).round().astype(int)) for lens in (hist, new)), [0] * batch, Hq, Hkv, D, seed=97 + D, window=8192)
+    run = GpuRun(case, tier="device", **kw)
+    try:
+        run.rebase()
+        run.load(0)
+        run.append(0)
+        items = run.ctx.rebase_read(6).reshape(-1, 8)
+        items = items[items[:, 0] >= 0]
+        shares = items[items[:, 6] >= 0]
+        assert len(shares) == n_shares and len(items) - len(shares) == whole
+        assert D == 64 or n_shares * 256 * (D + 2) * 4 > 32 << 20
+        bits = []
+        for call in (run.ctx.cached_prefill_attn, run.ctx.cached_prefill_attn_static):
+            run.out[0].view(torch.int16).fill_(0x7FC0)
+            call(0, run.q[0], run.k_pool[0], run.v_pool[0], run.out[0], 1.0 / np.sqrt(D))
+            run.finish()
+            bits.append(torch_to_bits(run.out[0]).copy())
+        assert np.array_equal(bits[0], bits[1]) and not np.any(bits[0] == 0x7FC0)
+        cut = sorted({(int(s[0]), int(s[1])) for s in shares})
+        for c, g in cut[:: max(1, len(cut) // 4)]:
+            h = g * (Hq // Hkv) + 1 % (Hq // Hkv)
+            got, want = run.out_f64(0, c)[:, [h]], case.oracle_out(0, c, heads=[h])
+            check_contract(got, want, c)
+            check_tight(got, want, int(case.n_keep[c]), c)
+    finally:
+        run.close()
