@@ -7,7 +7,9 @@ import numpy as np
 import pytest
 import torch
 
+import oracle
 from harness import Case, GpuRun, torch_to_bits
+from synth import bf16_bits_to_f64, f32_to_bf16_bits
 from test_gpu_parity import check_contract, check_tight
 
 pytestmark = pytest.mark.gpu
@@ -141,3 +143,47 @@ def test_the_two_entry_points_at_once():
             assert np.array_equal(torch_to_bits(out), want)
     finally:
         run.close()
+
+
+@pytest.mark.parametrize("hist, batch, D, style", [(2777, 1, 128, 0), (6000, 1, 64, 1), (600, 8, 128, 1), (250, 8, 128, 0)], ids=["shares", "long", "batch", "whole"])
+def test_every_new_maximum_of_a_row_has_an_exact_probability(hist, batch, D, style):
+    """In 64 bits over the operands the kernel rounds (rotated keys, rotated and scaled queries, probabilities against the maximum so far
+    of the pages a wavefront has seen), the kernel's output differs by the rounding of the output alone: relative, 2^-8 / sqrt(3) times
+    the root mean square 0.74 of 1 / mantissa, 0.00166.  A tenth is for probabilities that fp32 scores round the other way.
+    Against a maximum that stands still the probabilities would be rounded at other places, by 0.00166 each."""
+    G = 8
+    case = Case([hist + 3 * c for c in range(batch)], [1] * batch, [0] * batch, G, 1, D, seed=69 + D, style=style, window=8192)
+    run = GpuRun(case, tier="device")
+    w = bf16_bits_to_f64
+    diff = total = 0.0
+    try:
+        run.rebase()
+        run.load(0)
+        run.append(0)
+        run.attn(0)
+        run.finish()
+        items = run.ctx.rebase_read(6).reshape(-1, 8)
+        fold = np.float32(1.0 / np.sqrt(D)) * np.float32(1.4426950408889634)
+        for c in range(batch):
+            n = int(case.n_keep[c])
+            K, V = (np.concatenate([w(case.tensor(0, x + "_hist", c)), w(case.tensor(0, x + "_new", c))])[:, 0] for x in "kv")
+            Kr = w(f32_to_bf16_bits(np.array([oracle.rope(K[t], t, style=style) for t in range(n + 1)]).astype(np.float32)))
+            Qr = np.array([oracle.rope(q, n, style=style) for q in w(case.tensor(0, "q", c))[0]])
+            S = w(f32_to_bf16_bits(Qr.astype(np.float32) * fold)) @ Kr.T
+            P = np.zeros_like(S)
+            for begin, end, part in items[items[:, 0] == c][:, 4:7]:
+                waves = 4 if part >= 0 else 8
+                for wave in range(waves):
+                    top = np.full(G, -np.inf)
+                    for at in range(int(begin) + 16 * wave, min(int(end), n + 1), 16 * waves):
+                        s = S[:, at:min(at + 16, int(end), n + 1)]
+                        top = np.maximum(top, s.max(1))
+                        p = w(f32_to_bf16_bits(np.exp2(s - top[:, None]).astype(np.float32)))
+                        P[:, at:at + s.shape[1]] = p * np.exp2(top - S.max(1))[:, None]
+            want = P @ V / P.sum(1, keepdims=True)
+            diff += np.sum((run.out_f64(0, c)[0] - want) ** 2)
+            total += np.sum(want ** 2)
+    finally:
+        run.close()
+    assert (items[:, 6] >= 0).any() == (hist > 300)
+    assert np.sqrt(diff / total) < 1.1 * 0.00166
