@@ -163,9 +163,9 @@ ca_status fail(ca_ctx *ctx, ca_status st, const char *fmt, ...) {
         }                                                                                        \
     } while (0)
 
-// Workgroups of a few-rows plan that splits keys: two of four wavefronts per compute unit when there is that much to
-// stream, else at most one of eight (kAttnMaxParts / 2 bounds them: a workgroup's run of pages has two shares at most).
-constexpr int kRowsMaxWorkgroups = 512;
+// Cuts of a few-rows plan (and its workgroups, where it has runs) are at most this many: two workgroups of four wavefronts per compute
+// unit.  A unit that is cut has at most twice as many shares as cuts, hence kAttnMaxParts / 2.
+constexpr int kRowsMaxWorkgroups = kAttnMaxParts / 2;
 constexpr int kRowsCutPages = 20;
 constexpr size_t kMetaAlign = 64;            // alignment of the arrays of the metadata image
 // Workgroups of a kernel that moves between the pool and pinned host memory (32 KB in flight each), measured on MI355X with
@@ -1045,7 +1045,7 @@ static bool rows_plan(const ca_ctx *ctx) {
 // 174 pages 1332, 1268, 1316, 1359, 1501; 20 layers of 500 pages, 2 kv heads 387, 355, 343, 364, 382; of 1876 pages, 24, 32 and
 // 48 a share 470, 469, 495; 40 layers of 16 conversations of 13 to 26 pages 629 with all of at least 16 cut,
 // 655 with none.)
-static void plan_rows(ca_ctx *ctx, size_t &up) {
+static ca_status plan_rows(ca_ctx *ctx, size_t &up) {
     const ca_config &c = ctx->cfg;
     const int B = ctx->n_seqs, Hkv = c.n_kv_heads, G = c.n_q_heads / Hkv;
     const auto put = [&up](size_t bytes) { const size_t at = up; up = align_up(up + bytes, kMetaAlign); return at; };
@@ -1059,12 +1059,16 @@ static void plan_rows(ca_ctx *ctx, size_t &up) {
     const bool split = ctx->partial != nullptr;
     const bool runs = total >= (int64_t)2 * ctx->n_cus * 32;
     const int wgs = !runs ? 0 : split ? std::min(kRowsMaxWorkgroups, 2 * ctx->n_cus) : n_units;
-    const int even = (int)std::max<int64_t>(kCut, (total / ctx->n_cus + kCut - 1) / kCut * kCut);        // pages, where there are no runs
+    const int spread = std::min(kRowsMaxWorkgroups, ctx->n_cus);
+    const int even = (int)std::max<int64_t>(kCut, (total / spread + kCut - 1) / kCut * kCut);        // pages, where there are no runs
+    // A unit of p pages is cut into shares of at least `even` pages, at most p / even times.
     const int cuts = !split ? 0 : runs ? wgs : (int)(total / even);      // at most
     ctx->rows_runs = runs;
     ctx->off_wg_first = put((size_t)(wgs + 1) * 4);
     ctx->off_items = put((size_t)(n_units + cuts) * sizeof(WorkItem));
     ctx->off_rows_items = put((size_t)(n_units + cuts) * sizeof(RowsItem));
+    if (cuts > kRowsMaxWorkgroups || up > ctx->upload_capacity)
+        return fail(ctx, CA_ERR_OUT_OF_RANGE, "ca_rope_rebase: internal: %d cuts, image of %zu bytes (room for %zu)", cuts, up, ctx->upload_capacity);
     int32_t *wg_first = (int32_t *)(ctx->h_meta + ctx->off_wg_first);
     WorkItem *items = (WorkItem *)(ctx->h_meta + ctx->off_items);
     RowsItem *rows_items = (RowsItem *)(ctx->h_meta + ctx->off_rows_items);
@@ -1123,6 +1127,8 @@ static void plan_rows(ca_ctx *ctx, size_t &up) {
     ctx->n_items = n_items;
     ctx->n_combine = n_merges;
     ctx->n_split_parts = n_parts;
+    if (n_parts > kAttnMaxParts) return fail(ctx, CA_ERR_OUT_OF_RANGE, "ca_rope_rebase: internal: %d shares", n_parts);
+    return CA_OK;
 }
 
 // Whether a plan that has units of more than 128 rows is better served by 128-row tiles, keys rotated in the kernel.  Two
@@ -1280,7 +1286,8 @@ ca_status ca_rope_rebase(ca_ctx *ctx, const ca_batch *b, void *stream_) {
     ctx->max_unit_rows = 0;
     for (int i = 0; i < B; ++i) ctx->max_unit_rows = std::max(ctx->max_unit_rows, b->new_len[i] * (c.n_q_heads / c.n_kv_heads));
     if (rows_plan(ctx)) {
-        plan_rows(ctx, up);
+        st = plan_rows(ctx, up);
+        if (st != CA_OK) return st;
     } else
     // Tiles of stacked query rows, placed die by die.
     // All tiles of one (conversation, kv head) read the same keys/values, so they are given to the

@@ -46,7 +46,7 @@ struct Range {
 
 std::recursive_mutex lock;
 #define MODEL std::lock_guard<std::recursive_mutex> hold(lock)
-int n_devices = 2, launches_until_failure = -1;
+int n_devices = 2, launches_until_failure = -1, n_cus = 256;
 thread_local int current = 0;
 std::map<int, Stream *> default_stream;
 thread_local std::map<int, Stream *> thread_stream;
@@ -124,7 +124,7 @@ hipError_t hipGetDevice(int *d) { *d = current; return hipSuccess; }
 hipError_t hipSetDevice(int d) { if (d < 0 || d >= n_devices) return hipErrorInvalidDevice; current = d; return hipSuccess; }
 hipError_t hipGetLastError() { return hipSuccess; }
 const char *hipGetErrorString(hipError_t) { return "error of the model"; }
-hipError_t hipGetDevicePropertiesR0600(hipDeviceProp_tR0600 *p, int) { std::memset(p, 0, sizeof *p); p->multiProcessorCount = 256; return hipSuccess; }
+hipError_t hipGetDevicePropertiesR0600(hipDeviceProp_tR0600 *p, int) { std::memset(p, 0, sizeof *p); p->multiProcessorCount = n_cus; return hipSuccess; }
 hipError_t hipMalloc(void **p, size_t n) { if (spoils()) return hipErrorStreamCaptureUnsupported; *p = allocate(n, hipMemoryTypeDevice); return *p ? hipSuccess : hipErrorOutOfMemory; }
 hipError_t hipHostMalloc(void **p, size_t n, unsigned) { *p = allocate(n, hipMemoryTypeHost); return *p ? hipSuccess : hipErrorOutOfMemory; }
 hipError_t hipFree(void *p) { MODEL; if (spoils()) return hipErrorStreamCaptureUnsupported; finish([] { std::set<int> all; for (int i = 0; i < (int)ops.size(); ++i) all.insert(i); return all; }()); ranges.erase((uintptr_t)p); return hipSuccess; }
@@ -221,6 +221,7 @@ hipError_t hipLaunchKernel(const void *f, dim3 grid, dim3, void **args, size_t, 
 // kind: 0 device memory, 1 pinned host memory, 2 pinned at another device address, of unknown extent (registered memory)
 void *model_alloc(size_t size, int kind) { return allocate(size, kind ? hipMemoryTypeHost : hipMemoryTypeDevice, kind == 2 ? (ptrdiff_t)1 << 40 : 0, kind != 2); }
 int model_capture(hipStream_t s, int on) { stream_of(s)->capturing = on; return !stream_of(s)->spoilt; }      // 1: the capture is whole
+void model_cus(int n) { n_cus = n; }
 void model_fail_launch(int after) { launches_until_failure = after; }
 int model_ops() { MODEL; return (int)ops.size(); }
 const char *model_what(int op) { MODEL; return ops[op].what.c_str(); }

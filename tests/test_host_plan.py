@@ -123,3 +123,16 @@ def test_the_launch_has_the_workgroups_that_were_planned(m, batch, heads, hist_l
         whole = [int((live & ~cut & (die == d)).sum()) for d in range(8)]
         assert cut.any() and all(w > 0 and w % (32 * per_cu) == 0 for w in whole)
     assert m.named(m.queued(t.attn), "attn_prerot_kernelILi64ELi0ELi4ELi32ELi%dEE" % per_cu)
+
+
+# Few rows: however many compute units there are to spread the shares over, no more cuts than there is room for.
+@pytest.mark.parametrize("cus", [256, 1024])
+@pytest.mark.parametrize("batch, pages", [(2, 1500), (15, 500), (40, 24), (1, 4000)])
+@in_model
+def test_cuts_of_a_few_rows_plan_are_bounded(m, cus, batch, pages):
+    m.lib.model_cus(cus)
+    heads = (64, 8, 128)
+    hist = [16 * pages - 3 - c for c in range(batch)]
+    items = plan(m, hist, [1] * batch, heads)
+    check_cover(items, hist, [1] * batch, heads)
+    assert len(items) <= batch * heads[1] + 512 and (items[:, 6] >= 0).sum() <= 1024
