@@ -158,8 +158,8 @@ struct AttnArgs {
     int32_t n_q_heads, n_kv_heads, head_dim;
     int32_t rope_style;
     int32_t tile_rows;       // stacked query rows per workgroup: 128 (4 wavefronts), 256 (8), launch_attn_rows 16 or 32
-    int32_t wgs_per_cu;      // tile kernels: workgroups of the plan's that run on a compute unit at a time
     float softmax_scale;
+    int32_t wgs_per_cu;      // tile kernels: workgroups that run on a compute unit at a time, as the plan was laid out for
 };
 
 constexpr int kAttnTileRowsMin = 128;   // smallest tile of stacked query rows (4 wavefronts x 32)
