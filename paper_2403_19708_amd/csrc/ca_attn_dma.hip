@@ -67,7 +67,6 @@ __global__ __launch_bounds__(64 * NW, OCC) void attn_dma_kernel(AttnArgs a) {
     constexpr int NTHREADS = 64 * NW;
     constexpr int MB = BN / 32;              // 32-key blocks of S^T per tile
     constexpr int KS2 = BN / 16;             // 16-key steps of the second product per tile
-    constexpr int HALF = D / 2;
     constexpr int KSTEPS = D / 16;           // k-steps of the S^T product
     constexpr int DBLKS = D / 32;            // 32-row blocks of O^T
     constexpr int PPR = D / 8;               // 16-byte pieces per row
@@ -121,7 +120,6 @@ __global__ __launch_bounds__(64 * NW, OCC) void attn_dma_kernel(AttnArgs a) {
     const bool row_valid = r_raw <= row_last;
     const int r = row_valid ? r_raw : row_last;
     const int j = r / G;
-    const int head = g * G + (r - j * G);
     const int qpos = n + j;                                      // keys 0..qpos are visible
     const int wr_first = min(item.row0 + wave * 32, row_last);
     const int wr_last = min(item.row0 + wave * 32 + 31, row_last);
@@ -132,7 +130,7 @@ __global__ __launch_bounds__(64 * NW, OCC) void attn_dma_kernel(AttnArgs a) {
     // The softmax scale and log2(e) are folded into the rotated query before it is rounded to bf16, so the scores
     // come out of the matrix cores in the units of the base-2 exponent.
     const float cscale = a.softmax_scale * 1.4426950408889634f;
-    bf16x8 Qf[KSTEPS];          // loaded and rotated in the prologue, once the first key/value tiles are on their way
+    bf16x8 Qf[KSTEPS];          // asked for before the page ids arrive, rotated in the prologue behind the first loads
 
     // ---- rotary pass: this thread's (key, piece pair) of every K tile ------------------------------
     const bool rot_active = ROT_TASKS >= NTHREADS || tid < ROT_TASKS;
