@@ -1291,7 +1291,7 @@ ca_status ca_rope_rebase(ca_ctx *ctx, const ca_batch *b, void *stream_) {
     } else
     // Tiles of stacked query rows, placed die by die.
     // All tiles of one (conversation, kv head) read the same keys/values, so they are given to the
-    // same die (workgroup i runs on die i % 8) in consecutive launch slots and share its L2.
+    // same die (workgroup i runs on die i % 8), in plans of many rounds one after the other, and share its L2.
     // Units go longest-first to the least loaded die; dies are padded to equal length.
     {
         const int G = c.n_q_heads / c.n_kv_heads;
@@ -1562,10 +1562,23 @@ ca_status ca_rope_rebase(ca_ctx *ctx, const ca_batch *b, void *stream_) {
                 }
             }
         }
-        // Longest first also in plans that are not cut: within a unit the tiles of early rows see few keys, and few rows on a long
-        // context take as long as many (us a pass without and with: 4 layers of 16 first turns of 128-2048 tokens 523, 513; 2 of 60 turns
-        // of 100-4000 + 8-300 tokens, 64/8 heads 1955, 1921; 4 of 40 first turns of 80-137 433, 429).
-        for (auto &v : per_die) std::stable_sort(v.begin(), v.end(), by_cost);
+        // The last items of a die are launched longest first: within a unit the tiles of early rows see few keys, and few rows on a long
+        // context take as long as many.  In front of them the tiles of a unit follow each other and share their keys in the die's
+        // L2 (64 turns of 1024-4096 + 64-512 tokens, 64/8 heads, 4776 tiles: the attention reads 1.51 GB, sorted throughout 2.67).  Four a
+        // compute unit are sorted of tiles of 256 rows, sixteen of 128 rows, whose units have few tiles (of 64-wide heads as
+        // many rounds).  us of one attention call by units, with two, four, six and eight rounds sorted, and all:
+        //   11 of 1402 + 850-1275 tokens, 40 heads      608, 591, 607, 625, 638, 639
+        //   12 of 1000-1050 + 867-2048, 40 heads        811, 807, 827, 837, 858, 872
+        //   47 of 1268 + 200, 64/8 heads                504, 501, 497, 511, 514, 534
+        //   60 first turns of 607-2048, 32 heads        1563, 1554, 1550, 1558, 1555, 1670
+        //   33 first turns of 632-948, 32 heads         445, 440, 439, 444, 436, 427
+        //   45 of 167-250, 40 heads, 128 rows           122, 119, 116, 112, 110, 109
+        //   63 of 3809-3999 + 453-679, 32/4 of 64       1367, 1356, 1386, 1401, 1415, 1436
+        //   11 first turns of 681-2048, 32/8 of 64      129, 124, 123, 123, 123, 123
+        // 40 random plans of this size take 0.92 to 1.03 of the time with all sorted, 0.97 on average.
+        // (Where shares were considered, in plans of few rounds, all items are sorted already.)
+        for (auto &v : per_die)
+            std::stable_sort(v.end() - std::min(v.size(), die_cus * (tile == 128 ? 16 : 4)), v.end(), by_cost);
         // number the shares of split row tiles consecutively and list the tiles for the merge
         ctx->off_combine = put((size_t)n_split_parts * sizeof(CombineItem));    // (a tile has at least two shares)
         CombineItem *combine = (CombineItem *)(ctx->h_meta + ctx->off_combine);

@@ -136,3 +136,28 @@ def test_cuts_of_a_few_rows_plan_are_bounded(m, cus, batch, pages):
     items = plan(m, hist, [1] * batch, heads)
     check_cover(items, hist, [1] * batch, heads)
     assert len(items) <= batch * heads[1] + 512 and (items[:, 6] >= 0).sum() <= 1024
+
+
+# Plans of many rounds of workgroups: the tiles of a unit follow each other on their die, so that its L2 has their keys, up to the die's last items,
+# which are longest first.
+@pytest.mark.parametrize("batch, heads, hist_lo, hist_hi, new_lo, new_hi, last",
+                         [(64, (64, 8, 128), 2500, 2600, 256, 260, 128), (64, (32, 32, 128), 300, 3000, 100, 900, 128),
+                          (40, (32, 4, 64), 500, 4000, 200, 1500, 512), (16, (32, 4, 64), 0, 0, 128, 2048, 512)])
+@in_model
+def test_tiles_of_a_unit_follow_each_other(m, batch, heads, hist_lo, hist_hi, new_lo, new_hi, last):
+    hist, new = (np.linspace(lo, hi, batch).round().astype(np.int32) for lo, hi in ((hist_lo, hist_hi), (new_lo, new_hi)))
+    t = Turn(m, hist, new, heads=heads, require_load=0)
+    t.rebase()
+    all_items = t.ctx.rebase_read(6).reshape(-1, 8)
+    check_cover(all_items[all_items[:, 0] >= 0], hist, new, heads)
+    assert (all_items[:, 6] < 0).all()
+    for die in range(8):
+        items = all_items[die::8]
+        items = items[items[:, 0] >= 0]
+        units = [tuple(u) for u in items[:-last, :2].tolist()]
+        changes = sum(a != b for a, b in zip(units, units[1:]))
+        assert changes == max(len(set(units)) - 1, 0)
+        full = items[-last:]
+        full = full[full[:, 3] == full[:, 3].max()]
+        tiles64 = (full[:, 5] + 63) // 64
+        assert (np.diff(tiles64) <= 0).all()
