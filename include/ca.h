@@ -259,10 +259,12 @@ ca_status ca_cached_prefill_attn(ca_ctx *ctx, int32_t layer, const void *q, cons
  * ends) instead of the context's buffer.  (Keys rotated once per layer go to the context's copy.)
  * The call allocates nothing and records no timing intervals.  A plan whose shares need more than
  * 32 MiB (n_shares * tile_rows * (head_dim + 2) * 4 bytes) is refused with CA_ERR_OUT_OF_RANGE
- * and nothing is launched, unless only its last round of workgroups is cut, which always fits.  Every call on a GPU, from any context, uses that GPU's one array:
- * calls that overlap in time on one GPU race (serialise them on one stream); nothing in the array
- * needs clearing between calls, every share is written before it is read.  (What counts the shares
- * that have arrived is the context's, set to zero with every plan and by every call that ends.)   */
+ * and nothing is launched, unless only its last round of workgroups is cut, which always fits.
+ * Every call on a GPU, from any context, uses that GPU's one array: calls that overlap in time on
+ * one GPU race (serialise them on one stream); which plans have shares is the planner's affair and
+ * no reason to overlap them.  Nothing in the array needs clearing between calls, every share is
+ * written before it is read.  (What counts the shares that have arrived is the context's, set to
+ * zero with every plan and by every call that ends.)                                              */
 ca_status ca_cached_prefill_attn_static(ca_ctx *ctx, int32_t layer, const void *q, const void *k_pool,
                                         const void *v_pool, void *out, float softmax_scale, void *stream);
 

@@ -14,8 +14,9 @@
 //     log2(e) folded into the rotated query, the reference maximum enters as the accumulator and is raised lazily in long runs.
 //   * Keys are rotated in registers between the LDS read and the matrix instruction: a lane's operand pieces of one key
 //     hold both members of every rotary pair.  (cos, sin) advance by a constant rotation from page to page.
-//   * Workgroups of four wavefronts, two to a compute unit (of eight where nothing is cut).  With enough to stream the pages of all (conversation, kv head)
-//     units, laid end to end, are cut into equal runs, one per workgroup: all have the same number of bytes whatever the lengths.
+//   * Workgroups of four wavefronts, two to a compute unit (of eight where nothing is cut and units are few).  With enough to
+//     stream the pages of all (conversation, kv head) units, laid end to end, are cut into equal runs, one per workgroup: all have the
+//     same number of bytes whatever the lengths.
 //     With less (one conversation: 11 MB) the time is a chain of dependent steps and a workgroup has one share, whose
 //     description brings everything the first loads need.  Clock stamps of that chain (2777 tokens, 8 kv heads, 8 rows, 3 pages a
 //     wavefront): description 0.4 us, first loads landed 4.2, walk 7.1, wavefronts merged 7.8, share acknowledged and

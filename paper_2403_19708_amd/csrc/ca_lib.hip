@@ -1040,11 +1040,18 @@ static bool rows_plan(const ca_ctx *ctx) {
 // workgroup; a cut leaves at least kAttnMinPartKeys on either side (a share costs a merge), so runs are equal up to 256 keys.
 // Less: a workgroup has one share, and the time is a chain: a wavefront takes 0.9 us a page (heads of 128), and the workgroup that
 // merges reads all shares of its unit, about 45 KB/us, some 2 us at least.  Units of kRowsCutPages pages and more are cut into
-// shares of about the square root of their pages, or what an equal spread over the compute units gives where that is more.
-// (us a decode step with shares of 8, 12, 16, 24 and 32 pages: 40 layers of 250 pages, 8 kv heads 765, 707, 675, 726, 757; 80 layers of
-// 174 pages 1332, 1268, 1316, 1359, 1501; 20 layers of 500 pages, 2 kv heads 387, 355, 343, 364, 382; of 1876 pages, 24, 32 and
-// 48 a share 470, 469, 495; 40 layers of 16 conversations of 13 to 26 pages 629 with all of at least 16 cut,
-// 655 with none.)
+// shares of about the square root of their pages, which balances the two for 8 rows of 128 (neither heads of 64 nor other
+// numbers of rows are asked about), or what an equal spread over the compute units gives where that is more.  us of one attention
+// call of one conversation with the rule's share (in brackets) and with shares of 8, 12, 16, 24 and 32 pages:
+//                  8 kv heads, 8 rows of 128                    2 kv heads, 4 rows of 128                    4 kv heads, 8 rows of 64
+//    100 pages     11.4 (12)  10.8 11.4 11.5 13.3 15.1          10.6 (12)   9.7 10.5 10.9 12.7 14.3           8.6 (12)   7.7  8.5  9.0 10.2 11.3
+//    174           12.0 (12)  12.7 11.9 12.7 13.5 15.2          10.5 (12)  10.5 10.5 11.6 12.8 14.4           8.7 (12)   8.9  8.7  9.7 10.2 11.3
+//    250           13.0 (16)  14.3 13.6 13.0 14.5 15.3          11.6 (16)  11.1 11.6 11.4 13.3 14.6           9.6 (16)   9.8  9.7  9.5 10.8 11.4
+//    500           16.4 (24)  16.3 16.3 16.3 16.2 16.6          13.9 (24)  14.3 13.6 13.1 14.2 15.2          11.7 (24)  13.9 12.5 11.7 11.8 12.1
+//   1876           27.5 (60)  27.3 27.4 27.4 27.3 27.4          20.5 (44)  21.9 21.9 21.9 19.6 19.6          17.3 (44)  17.8 17.8 17.8 17.8 17.8
+// Where the line of kRowsCutPages lies is not the best for few units (us whole and cut, 8 kv heads): one conversation of 12, 16, 20
+// and 24 pages 9.1, 7.5; 10.7, 7.6; 11.4, 7.6; 12.3, 7.7; 16 conversations 9.2, 9.8; 11.0, 9.8; 11.8, 10.9; 12.9, 10.9; one turn
+// of 32 rows of 128 11.2, 12.4; 12.9, 12.4; 13.8, 12.5; 15.2, 12.6.
 static ca_status plan_rows(ca_ctx *ctx, size_t &up) {
     const ca_config &c = ctx->cfg;
     const int B = ctx->n_seqs, Hkv = c.n_kv_heads, G = c.n_q_heads / Hkv;
@@ -1164,10 +1171,11 @@ static bool half_tiles_pay(const ca_ctx *ctx) {
     return rounds >= 1 && cost128 < (1 - cost.margin / rounds) * cost256;
 }
 
-// Cutting the last round only is taken where it is estimated to take at most this share of the better one of the other two plans:
-// the estimates are right within a tenth or so, and shares need scratch that whole tiles do not.  Of 3000 drawn batches of 1 to 64
-// conversations it changes the plans of 36, whose attention takes 0.77 to 0.99 of the time, 0.87 on average (one layer of 4
-// conversations of 1667-1800 tokens with 177-497 new ones, 40 heads: 133 -> 106 us).  With 0.97 it would be half as many again.
+// Cutting the last round only is taken where it is estimated to take at most this share of the better one of the other two plans.
+// Of 3000 drawn batches of 1 to 64 conversations it changes the plans of 36, whose attention takes 0.77 to 0.99 of the time, 0.87 on
+// average (one layer of 4 conversations of 1667-1800 tokens with 177-497 new ones, 40 heads: 133 -> 106 us).  With 0.97 it would be
+// half as many again, none of 26 measured ones slower, among them 8 conversations of 2048 with 64-512 new ones, 32 heads (4 layers of
+// it 892 -> 868 us); the line lies below that batch because its plan is held to be whole, from a time when there was only whole and cut.
 constexpr double kLastRoundGain = 0.89;
 
 // A row tile or a share of one, as the planner of the tile kernels handles it
@@ -1298,7 +1306,7 @@ ca_status ca_rope_rebase(ca_ctx *ctx, const ca_batch *b, void *stream_) {
         // 256-row tiles (8 wavefronts) halve the K/V re-reads and the rotary work per row when a
         // (conversation, kv head) has more than 128 stacked rows; small turns keep 128-row tiles, and so do mixed batches in which
         // these cost less (half_tiles_pay).  Keys of 64 dimensions
-        // that were rotated beforehand are cheap to read again, and three workgroups of four wavefronts to a compute unit,
+        // that were rotated beforehand are cheap to read again, and three or four workgroups of four wavefronts to a compute unit,
         // none in step with another, beat one of eight: 16 first turns of 128-2048 tokens (32/4 heads) 158 -> 138 us a
         // layer, 8 turns of 1000-3000 + 64-300 tokens 74 -> 62 (with heads of 128: 1750 -> 1975, the other way round).  Where
         // the tiles are fewer than half the compute units, their keys are split many times over, and tiles of half the rows
