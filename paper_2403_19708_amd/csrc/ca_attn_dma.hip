@@ -483,68 +483,65 @@ __global__ __launch_bounds__(256) void combine_kernel(AttnArgs a) {
 }
 
 // The same for the tile kernels, whose shares lie as they leave the matrix cores, [D/4][tile_rows][4] sums: lanes of either kernel
-// that hold a row next to each other write and read next to each other.  blockIdx.y = 32 rows of the tile; a thread has D/32
-// groups of four dimensions of one row, four shares of them in flight, and the merged rows leave through LDS in whole lines.
-// (80 tiles of 256 rows in three shares each, 32 MB: 12 us with shares and outputs row by row, 9 us so.)
+// that hold a row next to each other write and read next to each other.  blockIdx.y = 32 rows of the tile, blockIdx.z = 32
+// dimensions; a thread has four dimensions of one row, and the merged rows leave through LDS in lines of 64 bytes.
+// The shares come from memory (they were written on other dies), so the time is the loads that wait for one another: those of four
+// shares stand without conditions in one block (past the last share: that one again, not counted).  Where each share has a branch
+// of its own the compiler moves its loads there, one after the other: 16 tiles of 256 rows in 16 shares 11.3-12.9 us, now 6.6; 11 of
+// 64 rows in 8 shares 7.6, 4.0; 80 of 256 rows in three shares, 32 MB, 8.6, 7.6 (11.6 with shares and outputs row by row).  With
+// all 16 loads in flight these take 5.7, 4.0 and 12.1, with all D dimensions a thread 7.9, 4.9 and 8.0.
 template <int D>
 __global__ __launch_bounds__(256) void combine_tiles_kernel(AttnArgs a) {
-    constexpr int N = D / 32, U = 4, kStride = 2 * D + 16;
+    constexpr int U = 4, kStride = 64 + 16;
     __shared__ __attribute__((aligned(16))) uint8_t stage[32 * kStride];
     const CombineItem ci = a.combine[blockIdx.x];
     const int row0 = blockIdx.y * 32, rows = min(32, ci.n_rows - row0);
     if (rows <= 0) return;
-    const int lr = threadIdx.x % 32, q = threadIdx.x / 32;
+    const int lr = threadIdx.x % 32, q = threadIdx.x / 32, d4 = blockIdx.z * 8 + q;
     const int rt = row0 + min(lr, rows - 1);
     const int G = a.n_q_heads / a.n_kv_heads;
     const float cscale = a.softmax_scale * 1.4426950408889634f;
     const int64_t part_stride = (int64_t)a.tile_rows * (D + 2);
     const float *first = a.partial + ci.first_part * part_stride;
-    float w[kAttnMaxPartsPerTile], lsum = 0.f;
-    float M = -INFINITY;
-#pragma unroll
-    for (int s = 0; s < kAttnMaxPartsPerTile; ++s) {
-        w[s] = s < ci.n_parts ? first[s * part_stride + (int64_t)a.tile_rows * D + rt] : -INFINITY;
-        M = fmaxf(M, w[s]);
-    }
-#pragma unroll
-    for (int s = 0; s < kAttnMaxPartsPerTile; ++s) {
-        w[s] = w[s] == -INFINITY ? 0.f : __builtin_amdgcn_exp2f((w[s] - M) * cscale);
-        if (s < ci.n_parts) lsum += w[s] * first[s * part_stride + (int64_t)a.tile_rows * (D + 1) + rt];
-    }
-    float4 acc[N];
-#pragma unroll
-    for (int k = 0; k < N; ++k) acc[k] = make_float4(0.f, 0.f, 0.f, 0.f);
+    const auto share = [&](int s) { return first + min(s, ci.n_parts - 1) * part_stride; };
+    float w[kAttnMaxPartsPerTile], l[kAttnMaxPartsPerTile];
+    float M = -INFINITY, lsum = 0.f;
 #pragma unroll
     for (int s0 = 0; s0 < kAttnMaxPartsPerTile; s0 += U) {
         if (s0 >= ci.n_parts) break;
-        float4 o[U][N];
 #pragma unroll
         for (int u = 0; u < U; ++u) {
-            if (s0 + u >= ci.n_parts) break;
-#pragma unroll
-            for (int k = 0; k < N; ++k)
-                o[u][k] = reinterpret_cast<const float4 *>(first + (s0 + u) * part_stride)[(q + 8 * k) * a.tile_rows + rt];
+            w[s0 + u] = share(s0 + u)[(int64_t)a.tile_rows * D + rt];
+            l[s0 + u] = share(s0 + u)[(int64_t)a.tile_rows * (D + 1) + rt];
         }
 #pragma unroll
-        for (int u = 0; u < U; ++u) {
-            if (s0 + u >= ci.n_parts) break;
+        for (int u = 0; u < U; ++u) M = fmaxf(M, w[s0 + u]);
+    }
+    float4 acc = make_float4(0.f, 0.f, 0.f, 0.f);
 #pragma unroll
-            for (int k = 0; k < N; ++k) {
-                const float f = w[s0 + u];
-                acc[k].x += f * o[u][k].x; acc[k].y += f * o[u][k].y; acc[k].z += f * o[u][k].z; acc[k].w += f * o[u][k].w;
-            }
+    for (int s0 = 0; s0 < kAttnMaxPartsPerTile; s0 += U) {
+        if (s0 >= ci.n_parts) break;
+        float4 o[U];
+#pragma unroll
+        for (int u = 0; u < U; ++u) o[u] = reinterpret_cast<const float4 *>(share(s0 + u))[d4 * a.tile_rows + rt];
+#pragma unroll
+        for (int u = 0; u < U; ++u) {
+            const bool on = s0 + u < ci.n_parts;
+            const float f = w[s0 + u] == -INFINITY ? 0.f : __builtin_amdgcn_exp2f((w[s0 + u] - M) * cscale);
+            lsum = on ? fmaf(f, l[s0 + u], lsum) : lsum;
+            acc.x = on ? fmaf(f, o[u].x, acc.x) : acc.x;
+            acc.y = on ? fmaf(f, o[u].y, acc.y) : acc.y;
+            acc.z = on ? fmaf(f, o[u].z, acc.z) : acc.z;
+            acc.w = on ? fmaf(f, o[u].w, acc.w) : acc.w;
         }
     }
     const float inv = 1.f / lsum;
-#pragma unroll
-    for (int k = 0; k < N; ++k)
-        *reinterpret_cast<uint2 *>(stage + lr * kStride + 8 * (q + 8 * k)) = make_uint2(pack_bf16(acc[k].x * inv, acc[k].y * inv), pack_bf16(acc[k].z * inv, acc[k].w * inv));
+    *reinterpret_cast<uint2 *>(stage + lr * kStride + 8 * q) = make_uint2(pack_bf16(acc.x * inv, acc.y * inv), pack_bf16(acc.z * inv, acc.w * inv));
     __syncthreads();
-    for (int i = threadIdx.x; i < rows * (D / 8); i += 256) {
-        const int at = i / (D / 8), piece = i % (D / 8), r = ci.row0 + row0 + at, j = r / G;
-        *reinterpret_cast<uint4 *>(a.out + ((int64_t)(a.cu_q[ci.seq] + j) * a.n_q_heads + ci.kv_head * G + (r - j * G)) * D + 8 * piece) =
+    const int at = threadIdx.x / 4, piece = threadIdx.x % 4, r = ci.row0 + row0 + at, j = r / G;
+    if (at < rows)
+        *reinterpret_cast<uint4 *>(a.out + ((int64_t)(a.cu_q[ci.seq] + j) * a.n_q_heads + ci.kv_head * G + (r - j * G)) * D + 32 * blockIdx.z + 8 * piece) =
             *reinterpret_cast<const uint4 *>(stage + at * kStride + 16 * piece);
-    }
 }
 
 template <int NW, int BN>
@@ -579,7 +576,7 @@ hipError_t launch_attn_dma(const AttnArgs &a, hipStream_t stream) {
 hipError_t launch_combine_tiles(const AttnArgs &a, hipStream_t stream) {
     if (a.n_combine <= 0) return hipSuccess;
     if (a.partial == nullptr || a.combine == nullptr || (a.head_dim != 128 && a.head_dim != 64)) return hipErrorInvalidValue;
-    const dim3 grid(a.n_combine, (a.tile_rows + 31) / 32);
+    const dim3 grid(a.n_combine, (a.tile_rows + 31) / 32, a.head_dim / 32);
     if (a.head_dim == 128) hipLaunchKernelGGL(combine_tiles_kernel<128>, grid, dim3(256), 0, stream, a);
     else hipLaunchKernelGGL(combine_tiles_kernel<64>, grid, dim3(256), 0, stream, a);
     return hipGetLastError();

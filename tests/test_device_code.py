@@ -65,3 +65,13 @@ def test_the_few_rows_kernel_reads_behind_its_waits():
             elif re.search(r"(\bload |ds\.read\.tr).*ptr addrspace\(3\)", line):
                 assert told, line
         assert waits >= 3
+
+
+def test_shares_are_merged_with_their_loads_in_one_block():
+    """Four shares of a row tile are in flight: their loads stand side by side and not behind a branch each, where they would wait for one another."""
+    kernels = re.findall(r"define [^\n]*amdgpu_kernel void @[^\n]*combine_tiles_kernel.*?\n}", intermediate(os.path.join(CSRC, "ca_attn_dma.hip")), re.S)
+    assert len(kernels) == 2
+    for body in kernels:
+        loads = [len(re.findall(r"= load float, ptr addrspace\(1\)", block)) for block in re.split(r"\n\d+:", body)]
+        loads = [n for n in loads if n]
+        assert sorted(loads) == [2 * 4] * 4 + [4 * 4] * 4           # maxima and denominators, then four sums each, of four times four shares

@@ -277,3 +277,25 @@ def test_last_round_shares_of_every_tile_kernel(heads, batch, hist, new, kw, n_s
             check_tight(got, want, int(case.n_keep[c]), c)
     finally:
         run.close()
+
+
+@pytest.mark.parametrize("prerotate", [1, 2], ids=["rotary", "rotated"])
+@pytest.mark.parametrize("D", [64, 128])
+@pytest.mark.parametrize("hist, n_shares", [(1000, 3), (1050, 4), (1850, 5), (2000, 7), (2050, 8), (3650, 9), (4050, 15), (4100, 16)])
+def test_merges_of_three_to_sixteen_shares(hist, n_shares, D, prerotate):
+    """Shares are merged in batches of four; three row tiles, the last one of 24 rows"""
+    case = Case([hist], [7], [0], 40, 1, D, seed=99 + hist, style=hist // 50 % 2, window=8192)
+    run = GpuRun(case, tier="device", attn_prerotate=prerotate, attn_tile_rows=128)
+    try:
+        run.rebase()
+        run.load(0)
+        run.append(0)
+        items = run.ctx.rebase_read(6).reshape(-1, 8)
+        items = items[items[:, 0] >= 0]
+        assert np.unique(items[items[:, 6] >= 0][:, 2], return_counts=True)[1].max() == n_shares
+        run.attn(0)
+        run.finish()
+        check_contract(run.out_f64(0, 0), case.oracle_out(0, 0), 0)
+        check_tight(run.out_f64(0, 0), case.oracle_out(0, 0), hist, 0)
+    finally:
+        run.close()
