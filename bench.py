@@ -822,7 +822,7 @@ def main():
                     frac=attn_live["frac_hbm_peak"], traffic=None)
     roof["avg_launch_us"] = att_us_live
     roof["algorithmic_bytes_per_launch"] = job.attn_bytes
-    roof["launch"] = ("one ca_cached_prefill_attn call inside the timed steps: rotate_keys_kernel + attn_prerot_kernel (+ combine_kernel "
+    roof["launch"] = ("one ca_cached_prefill_attn call inside the timed steps: rotate_keys_kernel + attn_prerot_kernel (+ combine_tiles_kernel "
                       "when keys are split)" if prerot else "one ca_cached_prefill_attn call inside the timed steps")
     sustained = mfma_rate_probe()
     if sustained:

@@ -24,8 +24,8 @@
 //     beyond its cache, and a wavefront alone on its SIMD 0.9 us a page, most of it the rotation: hence few loads (each
 //     query row is fetched and rotated once per workgroup, and a share is read 16 bytes a lane) and few pages a wavefront.
 //     With eight wavefronts of 16 pages a share, each fetching the queries by itself, this took 14.4 us; the
-//     decode step of that conversation over 80 layers 1508 -> 1267 us, of 8 of 700 to 1800 tokens over 20 layers 620 -> 464, of 64 of
-//     200 to 600 tokens 733 -> 589.
+//     decode step of that conversation over 80 layers 1506 -> 1279 us, of 8 of 700 to 1800 tokens over 20 layers 620 -> 469, of 64 of
+//     200 to 600 tokens 730 -> 602.
 //   * A share that is not a whole unit leaves unnormalised sums, maximum and denominator, and the workgroup that finishes a
 //     unit's last share merges them: no second launch (a combine kernel behind a decode step's attention cost 4 us plus the
 //     gap in front of it).  Shares are written through to memory; with release fences instead, each of which writes back a
