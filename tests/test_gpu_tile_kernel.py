@@ -299,3 +299,28 @@ def test_merges_of_three_to_sixteen_shares(hist, n_shares, D, prerotate):
         check_tight(run.out_f64(0, 0), case.oracle_out(0, 0), hist, 0)
     finally:
         run.close()
+
+
+@pytest.mark.parametrize("offset", [1, 4], ids=["2-bytes", "8-bytes"])
+@pytest.mark.parametrize("heads, new, kw", [((8, 8, 128), 150, {}), ((8, 1, 64), 200, {"attn_prerotate": 2}), ((8, 1, 128), 1, {}), ((8, 1, 128), 20, {})],
+                         ids=["rotary", "rotated", "few-rows", "shares"])
+def test_queries_and_outputs_at_any_element(heads, new, kw, offset):
+    """Queries and outputs that are aligned to their elements only; nothing is written beside the outputs, and the bits are those of aligned ones."""
+    case = Case([900, 40], [new, max(1, new // 3)], [0, 0], *heads, seed=120 + new, window=2048)
+    run = GpuRun(case, tier="device", **kw)
+    try:
+        run.rebase()
+        run.load(0)
+        run.append(0)
+        run.attn(0)
+        n = run.q[0].numel()
+        room = [torch.zeros(n + 16, dtype=torch.bfloat16, device=run.dev) for _ in range(2)]
+        q, out = (t[offset:offset + n].view(run.q[0].shape) for t in room)
+        q.copy_(run.q[0])
+        run.ctx.cached_prefill_attn(0, q, run.k_pool[0], run.v_pool[0], out, 1.0 / np.sqrt(heads[2]))
+        run.finish()
+        assert np.array_equal(torch_to_bits(out), torch_to_bits(run.out[0]))
+        assert not room[1][:offset].any() and not room[1][offset + n:].any()
+        check_contract(run.out_f64(0, 0), case.oracle_out(0, 0), 0)
+    finally:
+        run.close()
